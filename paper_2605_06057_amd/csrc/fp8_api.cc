@@ -123,7 +123,7 @@ extern "C" lcma_status lcma_fp8_gemm_nt(int64_t M, int64_t N, int64_t K, const v
     p.ldc_b = (uint32_t)(ldc * 2);
     p.ny = (int32_t)(kp / 128);
     p.n_row_b = (uint32_t)(N * 2);
-    return plane_gemm(who, PG_FP8_BF16, p, 1, M, N, 0, 1, nullptr, 0, stream);
+    return plane_gemm(who, PG_FP8_BF16, p, 1, M, N, 0, 0, nullptr, 0, stream);
 }
 
 extern "C" int64_t lcma_fp8_prepared_w_bytes(const lcma_scheme *scheme, int64_t N, int64_t K) {

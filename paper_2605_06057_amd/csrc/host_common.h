@@ -107,8 +107,6 @@ enum { PG_FP8_BF16 = 0, PG_FP8_F16 = 1, PG_F16 = 2, PG_BF16 = 3, PG_F16_OUT = 4 
 int64_t plane_gemm_scratch_bytes(int tile);
 // predicted seconds of plane_gemm on `planes` planes of rows x cols with ny steps of 128 bytes (negative: no kernel fits)
 double plane_gemm_seconds(int planes, int64_t rows, int64_t cols, int ny, int64_t scratch_bytes);
-int64_t plane_gemm_static_steps(int64_t jobs, int ny, int tile);
-int64_t plane_gemm_split_steps(int64_t jobs, int ny, int tile);
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,
                        int schedule, void *scratch, int64_t scratch_bytes, void *stream);
 int tuning_schedule(); // 0 = choose, 1 = one tile-product per work-group, 2 = Split-Group ranges

@@ -1,7 +1,22 @@
 // Instances of the plane GEMM (csrc/lcma_plane_gemm.hpp) and of its fix-up kernel.
-#include "lcma_plane_gemm.hpp"
+#include "lcma_pingpong.hpp"
 
 using namespace lcma;
+
+// on the 128 x 128 tile the kernel of the Split-Group ranges also runs whole tile-products in turn
+#define LCMA_PERSISTENT_128(NAME, KIND, OUT)
+#define LCMA_LAUNCH_PERSISTENT_128(NAME)
+#define LCMA_PERSISTENT_256(NAME, KIND, OUT)                                                                           \
+    extern "C" __global__ __launch_bounds__(512, 2) void lcma_k_pg_pp_##NAME(const lcma::PlaneGemmParams) {           \
+        using G = PingPongGemm<KIND, OUT>;                                                                             \
+        __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
+        G::run((LCMA_LDS char *)smem);                                                                                 \
+    }
+#define LCMA_LAUNCH_PERSISTENT_256(NAME)                                                                               \
+    if (p->interleave) {                                                                                               \
+        lcma_k_pg_pp_##NAME<<<dim3(p->units), dim3(512), 0, (hipStream_t)stream>>>(*p);                                \
+        return (int)hipGetLastError();                                                                                 \
+    }
 
 #define LCMA_PLANE_GEMM(NAME, KIND, TM, TN, WGM, WGN, OCC, OUT)                                                        \
     extern "C" __global__ __launch_bounds__(64 * WGM * WGN, OCC) void lcma_k_pg_##NAME(const lcma::PlaneGemmParams p) { \
@@ -19,9 +34,11 @@ using namespace lcma;
         __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
         G::fixup(p, (LCMA_LDS char *)smem);                                                                            \
     }                                                                                                                  \
-    /* one tile-product per work-group when cap is a whole tile-product and there are as many work-groups as              \
+    LCMA_PERSISTENT_##TM(NAME, KIND, OUT)                                                                              \
+    /* whole tile-products in turn: the ping-pong kernel on the large tile; one tile-product per work-group when cap is a whole tile-product and there are as many work-groups as              \
        tile-products, else the persistent kernel and the kernel that adds the pieces */                                  \
     extern "C" int lcma_launch_pg_##NAME(const lcma::PlaneGemmParams *p, void *stream) {                               \
+        LCMA_LAUNCH_PERSISTENT_##TM(NAME)                                                                              \
         if (p->cap == p->ny && p->units == p->jobs) {                                                                  \
             lcma_k_pg_##NAME<<<dim3(p->units), dim3(64 * WGM * WGN), 0, (hipStream_t)stream>>>(*p);                    \
             return (int)hipGetLastError();                                                                             \

@@ -49,6 +49,23 @@ template <> struct PlaneFrag<FP8> {
     using type = i32x8;
 };
 
+// Tile of a tile-product: product-major; inside a product tiles run down x inside column panels of `panel` z tiles.
+LCMA_DEV void tile_of_job(int nx, int nz, int panel, int job, int &plane, int &x, int &z) {
+    const int tiles = nx * nz;
+    plane = job / tiles;
+    const int id = job - plane * tiles;
+    const int whole = nz / panel * panel, full = whole * nx; // columns of tiles in whole panels, and their tiles
+    if (id < full) {
+        const int pi = id / (panel * nx), rem = id - pi * (panel * nx);
+        x = rem / panel;
+        z = pi * panel + rem % panel;
+    } else {
+        const int w2 = nz - whole, rem = id - full;
+        x = rem / w2;
+        z = whole + rem % w2;
+    }
+}
+
 template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = true, bool DIRECT = true> struct PlaneGemm {
     static constexpr int NT = 64 * WGM * WGN, WM = TM / WGM, WN = TN / WGN, NMI = WM / 32, NNI = WN / 32;
     static constexpr int ROW = 128, A_STAGE = TM * ROW, B_STAGE = TN * ROW, STAGE = A_STAGE + B_STAGE;
@@ -280,7 +297,7 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
                 s.b_frag[kk][j] = A_STAGE + br * ROW + swz(br, c) * 16;
             }
 
-        const int tiles = p.nx * p.nz, ny = p.ny;
+        const int ny = p.ny;
         const int total = p.jobs * ny; // the host keeps it below 2^31
         // hardware deals work-groups to the 8 XCDs round-robin: renumber them so that each XCD (with its private L2)
         // holds a contiguous run of ranges, i.e. neighbouring tiles
@@ -328,21 +345,6 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
             }
             return piece_from(c.job * ny + c.y1);
         };
-        // tile of a job: product-major; inside a product tiles run down x inside column panels of `panel` z tiles
-        auto locate = [&](int job, int &plane, int &x, int &z) {
-            plane = job / tiles;
-            const int id = job - plane * tiles;
-            const int pw = p.panel, full = (p.nz / pw) * pw * p.nx;
-            if (id < full) {
-                const int pi = id / (pw * p.nx), rem = id - pi * (pw * p.nx);
-                x = rem / pw;
-                z = pi * pw + rem % pw;
-            } else {
-                const int w2 = p.nz - (p.nz / pw) * pw, rem = id - full;
-                x = rem / w2;
-                z = (p.nz / pw) * pw + rem % w2;
-            }
-        };
         FragT fa[2][NA], fb[2][NNI]; // fragment sets in flight (direct loads); set 0 of a primed piece is read before its loop
         int st = 0;                  // stage that holds the first step of the coming piece
         bool primed = false;         // ... whose loads were sent during the last step of the piece before
@@ -350,14 +352,14 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
         while (cur.ok) {
             const int y0 = cur.y0, y1 = cur.y1;
             int plane, x, z;
-            locate(cur.job, plane, x, z);
+            tile_of_job(p.nx, p.nz, p.panel, cur.job, plane, x, z);
             Piece nxt{0, 0, 0, false};
             uint32_t a_first = 0, b_first = 0; // first step of the next piece
             if constexpr (XTILE) {
                 nxt = piece_after(cur);
                 if (nxt.ok) {
                     int pl, nx_, nz_;
-                    locate(nxt.job, pl, nx_, nz_);
+                    tile_of_job(p.nx, p.nz, p.panel, nxt.job, pl, nx_, nz_);
                     a_first = (uint32_t)pl * p.a_plane + (uint32_t)nx_ * TM * p.lda_b + (uint32_t)nxt.y0 * ROW;
                     b_first = (uint32_t)pl * p.b_plane + (uint32_t)nz_ * TN * p.ldb_b + (uint32_t)nxt.y0 * ROW;
                 }
@@ -582,19 +584,8 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
         };
         add_piece((u - 1) * 2 + 1, true);                 // the head piece (starts at step 0 of the tile-product)
         for (int v = u; (int64_t)v * p.cap < (int64_t)(job + 1) * ny && (int64_t)v * p.cap < total; ++v) add_piece(v * 2, false);
-        const int tiles = p.nx * p.nz, plane = job / tiles;
-        int id = job - plane * tiles;
-        const int pw = p.panel, full = (p.nz / pw) * pw * p.nx;
-        int x, z;
-        if (id < full) {
-            const int pi = id / (pw * p.nx), rem = id - pi * (pw * p.nx);
-            x = rem / pw;
-            z = pi * pw + rem % pw;
-        } else {
-            const int w2 = p.nz - (p.nz / pw) * pw, rem = id - full;
-            x = rem / w2;
-            z = (p.nz / pw) * pw + rem % w2;
-        }
+        int plane, x, z;
+        tile_of_job(p.nx, p.nz, p.panel, job, plane, x, z);
         store_tile(p, s, lds, plane, x, z, acc);
     }
 };

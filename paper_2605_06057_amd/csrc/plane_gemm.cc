@@ -45,49 +45,51 @@ int slots_of(int tile) { return tile == 256 ? kCUs : 2 * kCUs; }
 
 int64_t plane_gemm_scratch_bytes(int tile) { return (int64_t)slots_of(tile) * 2 * tile * tile * 4; }
 
-// Steps (of 128 bytes of K) that the slowest work-group runs, for the time model: static launch in rounds of `slots`
-// work-groups, Split-Group in one round of contiguous ranges.
-int64_t plane_gemm_static_steps(int64_t jobs, int ny, int tile) { return ceil_div(jobs, slots_of(tile)) * ny; }
-int64_t plane_gemm_split_steps(int64_t jobs, int ny, int tile) { return ceil_div(jobs * ny, slots_of(tile)); }
-
 namespace {
-// Tile and schedule together, by the steps the slowest work-group runs, in units of a step of the large tile.  A step of
-// the small tile does a quarter of the work with two work-groups per CU, at three quarters of the efficiency
-// (measured): 0.76 of a large step for two of them, so 0.38 each, twice as many run at once.  The Split-Group schedule
-// adds the pieces: nearly every work-group holds two, 134 MB of fp32 partial sums in all, written at the end of the
-// first kernel and read back by the second.  Measured against the other schedules on seven LLM shapes (plain, batched
-// 16-bit and batched FP8 products): it wins only where it saves more than about 80 steps (few tile-products, long K:
-// 64 tiles of K = 16384 run 26 % faster), and loses 3 to 25 % where the model had priced the pieces at 40.
-// tile, schedule: 0 = choose.  Returns the cost in large steps (0 when nothing fits).
-// What starting and finishing a tile-product costs, in steps of the large tile: a work-group of its own per tile-product
-// (launch, first loads with nothing to overlap them, epilogue) against a persistent work-group that sends the first
-// loads of its next tile-product during the last step of the current one (measured on the FFN shapes: the batched
-// stage of Algorithm 1, 32 steps per tile-product, gains 9 %, the plain 16-bit product with 64 steps 2 to 4 %).  3.5
-// fits both the 32-step tile-products of <2,2,2;7> (0.72 to 0.75 ms for 13 rounds) and the 16-step ones of <4,4,4;49>
-// (0.74 ms for 22 rounds) at the FFN shape; what cannot be hidden is the tile of H_r a work-group writes out.
-const double kTileCost = 5.0, kTileCostPersistent = 3.5;
-// The Split-Group schedule adds the pieces (see below): as long as 80 steps of the large tile.
-const double kSplitCost = 80.0;
-// persist_ok: the persistent whole-tile schedule may be chosen (16-bit operands; the FP8 kernel loses 8 % with it: the
-// scale bytes of the next tile-product are not fetched ahead)
-double choose(int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, int64_t scratch_bytes, bool persist_ok,
-              int *best_tile, int *best_sched) {
+// Tile and schedule together, by the time the slowest work-group takes.  All constants are measured (us; random operands;
+// f: share of the chip's work-group slots that a round fills: with fewer work-groups the memory side answers sooner and
+// the clock is higher).
+//   256 x 256, whole tile-products in turn (ping-pong kernel, csrc/lcma_pingpong.hpp): a step of 128 bytes of K takes 1.52
+//     with all 256 work-groups (8192 x 14336 x 4096: 712 us in 7 rounds of 64 steps; 7 planes of 4096 x 7168 x 2048: 724 us),
+//     1.16 with 128 (2048 x 4096 x 4096: 81 us), 0.98 with 64 (2048 x 2048 x 7168: 110 us); a tile-product 6 besides (12
+//     with fp32 output), and the start of the pipeline 1.5;
+//   256 x 256, one work-group per tile-product (PlaneGemm): 1.62 (FP8: 2.05) a step, but a shorter start: the faster one
+//     up to about eight steps (4096 x 4096 x 128: 11.0 against 11.8 us, x 256: 15.4 against 15.7, x 512: 22.4 both);
+//   128 x 128, two work-groups per CU: 1.05 a step of both (FP8: 1.17) with 512 work-groups, 0.72 (0.77) with 256 (2048 x
+//     4096 x 4096: 68 us; 1024 x 4096 x 4096: 48 us): the one to take when the large tiles leave much of the chip idle;
+//   Split-Group ranges: 1.5 (1.1) a step and 65 for the pieces: nearly every work-group holds two, 134 MB of fp32 partial
+//     sums in all, written at the end of the first kernel and read back by the second (1024 x 4096 x 16384: 161 us in 64
+//     steps, 2048 x 4096 x 14336: 234 us in 112): few tile-products and a long K only.
+// tile, schedule: 0 = choose.  Returns microseconds (0 when nothing fits).
+double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, int64_t scratch_bytes, int *best_tile,
+              int *best_sched) {
+    const bool fp8 = kind == PG_FP8_BF16 || kind == PG_FP8_F16;
+    const double out = kind == PG_F16_F32 ? 2.0 : 1.0; // a tile of fp32 takes twice as long to write
     double best = 0.0;
     *best_tile = *best_sched = 0;
     for (int t : {256, 128}) {
         if (tile && t != tile) continue;
-        if (planes > 1 && (rows % t || cols % t)) continue; // planes lie back to back: a tile must not hang over the end of one
-        const int64_t jobs = (int64_t)planes * ceil_div(rows, t) * ceil_div(cols, t);
-        const double unit = t == 256 ? 1.0 : 0.76;
+        const int64_t jobs = (int64_t)planes * ceil_div(rows, t) * ceil_div(cols, t), slots = slots_of(t);
         for (int sc : {1, 2, 3}) {
-            if (schedule ? sc != schedule : sc == 3 && !persist_ok) continue;
+            if (schedule && sc != schedule) continue;
+            const bool pingpong = t == 256 && sc == 3;
+            // (the 128 x 128 FP8 kernel loses with whole tile-products in turn: it does not fetch the next scales ahead)
+            if (!schedule && sc == 3 && fp8 && t == 128) continue;
+            // planes lie back to back: only the ping-pong kernel lets a tile hang over the end of one
+            if (planes > 1 && !pingpong && (rows % t || cols % t)) continue;
             if (sc == 2 && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
-            // whole tile-products (one per work-group, or persistent work-groups that take every units-th one): rounds of
-            // ny steps plus, per round, what starting and finishing a tile costs in steps; ranges of steps: one long round
-            const double rounds = (double)ceil_div(jobs, slots_of(t));
-            const double steps = sc == 2 ? (double)plane_gemm_split_steps(jobs, ny, t) + kSplitCost
-                                         : rounds * (ny + (sc == 3 && rounds > 1 ? kTileCostPersistent : kTileCost));
-            const double cost = steps * unit * (sc == 2 ? 1.05 : 1.0); // the persistent kernel's step is 5 % slower
+            double cost;
+            if (sc == 2) {
+                cost = (double)ceil_div(jobs * ny, slots) * (t == 256 ? 1.5 : 1.1) + 65.0;
+            } else {
+                const int64_t full = jobs / slots, rest = jobs % slots;
+                auto round = [&](double f) {
+                    if (pingpong) return (double)((ny + 1) & ~1) * (0.80 + 0.72 * f) + 6.0 * out;
+                    if (t == 256) return (double)ny * (fp8 ? 1.0 + 1.05 * f : 0.85 + 0.77 * f) + 6.0 * out;
+                    return (double)ny * (fp8 ? 0.37 + 0.80 * f : 0.40 + 0.65 * f) + (sc == 3 && full ? 4.0 : 5.0) * out;
+                };
+                cost = (double)full * round(1.0) + (rest ? round((double)rest / (double)slots) : 0.0) + (pingpong ? 1.5 : 0.0);
+            }
             if (!*best_tile || cost < best) {
                 best = cost;
                 *best_tile = t;
@@ -99,15 +101,27 @@ double choose(int planes, int64_t rows, int64_t cols, int ny, int tile, int sche
 }
 } // namespace
 
-// Seconds of a plane GEMM for the time model (Sec. 3.3): the steps of the slowest work-group under the tile and schedule
-// that plane_gemm would choose, at the time of a step of the 256 x 256 tile measured on the FFN shapes with random
-// operands (1.62 us for 16-bit and for FP8 operands: a step is 128 bytes of K either way and both run into the
-// chip's power limit), plus a fixed 8 us for every tile a work-group works through (launch, first loads, epilogue).
+// Seconds of a 16-bit plane GEMM for the time model of Algorithm 1 (Sec. 3.3): what lcma_predict_unfused_seconds reports and
+// lcma_select_dataflow and lcma_gemm_ws compare.  Those figures are part of the interface (a caller may store them or
+// reproduce its choices by them), so this stays the calibration it was published with: steps of the slowest work-group at
+// 1.62 us, 3.5 or 5 more for every tile it works through, a pair of small tiles at 0.76 of a large one, 80 for the pieces of
+// the Split-Group ranges.  The kernels of plane_gemm, which chooses by the times above, are up to a fifth faster by now.
 double plane_gemm_seconds(int planes, int64_t rows, int64_t cols, int ny, int64_t scratch_bytes) {
-    int t = 0, sc = 0;
-    const double steps = choose(planes, rows, cols, ny, 0, tuning_schedule(), scratch_bytes, true, &t, &sc);
-    if (!t) return -1.0;
-    return steps * 1.62e-6;
+    const int schedule = tuning_schedule();
+    double best = -1.0;
+    for (int t : {256, 128}) {
+        if (planes > 1 && (rows % t || cols % t)) continue;
+        const int64_t jobs = (int64_t)planes * ceil_div(rows, t) * ceil_div(cols, t);
+        for (int sc : {1, 2, 3}) {
+            if (schedule && sc != schedule) continue;
+            if (sc == 2 && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
+            const double rounds = (double)ceil_div(jobs, slots_of(t));
+            const double steps = sc == 2 ? (double)ceil_div(jobs * ny, slots_of(t)) + 80.0 : rounds * (ny + (sc == 3 && rounds > 1 ? 3.5 : 5.0));
+            const double cost = steps * (t == 256 ? 1.0 : 0.76) * (sc == 2 ? 1.05 : 1.0);
+            if (best < 0.0 || cost < best) best = cost;
+        }
+    }
+    return best < 0.0 ? -1.0 : best * 1.62e-6;
 }
 
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
@@ -119,8 +133,7 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     const int forced = tuning_schedule();
     if (forced) schedule = forced;
     int best_tile = 0, best_sched = 0;
-    choose(planes, rows, cols, p.ny, tile, schedule, scratch ? scratch_bytes : 0, kind != PG_FP8_BF16 && kind != PG_FP8_F16, &best_tile,
-           &best_sched);
+    choose(kind, planes, rows, cols, p.ny, tile, schedule, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
     if (!best_tile) {
         if (schedule == 2)
             return fail(LCMA_ERR_ARG, "%s: the Split-Group schedule needs %lld bytes of scratch", who,
@@ -152,8 +165,7 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
         p.units = (int32_t)(jobs < slots ? jobs : slots);
         p.cap = p.ny;
         // batches of planes: rounds of consecutive tile-products; one product: an eighth of them per XCD (see
-        // PlaneGemm::run), which needs the same number of work-groups on every XCD (with fewer tile-products than slots
-        // units == jobs and the launcher takes the kernel with a work-group per tile-product anyway)
+        // PlaneGemm::run), which needs the same number of work-groups on every XCD
         p.interleave = planes > 1 || (p.units & 7) ? 1 : 2;
         p.partial = nullptr;
     } else if (schedule == 2) {
