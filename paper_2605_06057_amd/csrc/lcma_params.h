@@ -84,6 +84,20 @@ struct PlaneGemmParams {
                                                             // (never touched when cap is a multiple of ny)
 };
 
+// Argument block of the plain product on few rows (csrc/lcma_few_rows.hpp).
+struct FewRowsParams {
+    const void *A, *W;
+    void *C;
+    uint32_t a_bytes, w_bytes, c_bytes; // byte extents (< 2 GiB each)
+    uint32_t lda_b, ldw_b, ldc_b;       // row pitches in bytes
+    uint32_t n_row_b;                   // N * 2: columns of C at or beyond it are never written
+    int32_t steps;                      // K / 32
+    int32_t row_blocks, block_rows;     // blocks of rows of C, and the rows of a block
+    int32_t slices, slice_steps;        // slices of K (1: C is written directly), steps of a slice
+    int32_t partial_ld;                 // row pitch of the partial products in floats
+    void *partial;                      // slices x (row_blocks * block_rows) x partial_ld fp32 partial products
+};
+
 struct Fp8QuantParams {
     const void *X;             // bf16 source, row-major
     void *Q, *S;               // codes and scale bytes (first plane)

@@ -2,6 +2,7 @@
 // Parallelism), launch.
 #include "host_common.h"
 
+#include <algorithm>
 #include <cstring>
 
 #define LCMA_PG_DECL(NAME) extern "C" int lcma_launch_pg_##NAME(const lcma::PlaneGemmParams *p, void *stream);
@@ -15,6 +16,16 @@ LCMA_PG_DECL(f16_t256_f32)
 LCMA_PG_DECL(f16_t128_f32)
 LCMA_PG_DECL(bf16_t256_bf16)
 LCMA_PG_DECL(bf16_t128_bf16)
+
+extern "C" int lcma_launch_few_rows_sum_f16(const lcma::FewRowsParams *p, int rows, void *stream);
+extern "C" int lcma_launch_few_rows_sum_bf16(const lcma::FewRowsParams *p, int rows, void *stream);
+#define LCMA_FR_DECL(NAME) extern "C" int lcma_launch_few_rows_##NAME(const lcma::FewRowsParams *p, int n, void *stream);
+LCMA_FR_DECL(f16_16)
+LCMA_FR_DECL(f16_32)
+LCMA_FR_DECL(f16_64)
+LCMA_FR_DECL(bf16_16)
+LCMA_FR_DECL(bf16_32)
+LCMA_FR_DECL(bf16_64)
 
 namespace lcma {
 
@@ -55,11 +66,13 @@ namespace {
 //     with fp32 output), and the start of the pipeline 1.5;
 //   256 x 256, one work-group per tile-product (PlaneGemm): 1.62 (FP8: 2.05) a step, but a shorter start: the faster one
 //     up to about eight steps (4096 x 4096 x 128: 11.0 against 11.8 us, x 256: 15.4 against 15.7, x 512: 22.4 both);
-//   128 x 128, two work-groups per CU: 1.05 a step of both (FP8: 1.17) with 512 work-groups, 0.72 (0.77) with 256 (2048 x
-//     4096 x 4096: 68 us; 1024 x 4096 x 4096: 48 us): the one to take when the large tiles leave much of the chip idle;
-//   Split-Group ranges: 1.5 (1.1) a step and 65 for the pieces: nearly every work-group holds two, 134 MB of fp32 partial
-//     sums in all, written at the end of the first kernel and read back by the second (1024 x 4096 x 16384: 161 us in 64
-//     steps, 2048 x 4096 x 14336: 234 us in 112): few tile-products and a long K only.
+//   128 x 128, two work-groups per CU: 1.06 a step of both (FP8: 1.16) with 512 work-groups, 0.72 to 0.9 with 256, 0.62
+//     with a few (2048 x 4096 x 4096: 68 us; 1024 x 4096 x 4096: 48 us; x 16384: 232 us; 64 x 4096 x 4096: 41 us): the one to take when the large
+//     tiles leave much of the chip idle;
+//   Split-Group ranges: 1.75 (0.95; FP8 2.0 and 1.1) a step, 6 (3) a tile-product and 65 (40) for the pieces: nearly every
+//     work-group holds two, 134 (67) MB of fp32 partial sums in all, written at the end of the first kernel and read back by
+//     the second (1024 x 4096 x 16384: 161 us against 232 with 128 x 128 tiles; 512 x 4096 x 14336: 95 against 221): few
+//     tile-products and a long K only (2463 x 8344 x 6528: 334 against 248 with the ping-pong kernel).
 // tile, schedule: 0 = choose.  Returns microseconds (0 when nothing fits).
 double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, int64_t scratch_bytes, int *best_tile,
               int *best_sched) {
@@ -80,13 +93,15 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             if (sc == 2 && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
             double cost;
             if (sc == 2) {
-                cost = (double)ceil_div(jobs * ny, slots) * (t == 256 ? 1.5 : 1.1) + 65.0;
+                cost = (double)ceil_div(jobs * ny, slots) * (t == 256 ? fp8 ? 2.0 : 1.75 : fp8 ? 1.1 : 0.95) +
+                       (t == 256 ? 6.0 : 3.0) * out * (double)jobs / (double)slots + (t == 256 ? 65.0 : 40.0);
             } else {
                 const int64_t full = jobs / slots, rest = jobs % slots;
                 auto round = [&](double f) {
                     if (pingpong) return (double)((ny + 1) & ~1) * (0.80 + 0.72 * f) + 6.0 * out;
                     if (t == 256) return (double)ny * (fp8 ? 1.0 + 1.05 * f : 0.85 + 0.77 * f) + 6.0 * out;
-                    return (double)ny * (fp8 ? 0.37 + 0.80 * f : 0.40 + 0.65 * f) + (sc == 3 && full ? 4.0 : 5.0) * out;
+                    const double alone = 0.62 + 0.5 * (f < 0.5 ? f : 0.5); // one work-group per CU up to f = 0.5
+                    return (double)ny * (alone + (f > 0.5 ? 0.5 * (f - 0.5) : 0.0)) + (sc == 3 && full ? 2.5 : 3.0) * out;
                 };
                 cost = (double)full * round(1.0) + (rest ? round((double)rest / (double)slots) : 0.0) + (pingpong ? 1.5 : 0.0);
             }
@@ -182,6 +197,39 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     return LCMA_OK;
 }
 
+namespace {
+// Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): tile and slices of K with the smallest time.  A work-group
+// pulls in 36 bytes/ns (measured on all three tiles), about 256 run at a time; 2.0 (2.2, 4.4) us besides for the launch and
+// the sum over the waves, 3.7 for the kernel that adds the slices (both sides measured: see lcma_few_rows.hpp).
+struct FewRowsPlan {
+    int tile;
+    int64_t row_blocks, col_blocks, slices, slice_steps;
+    double us;
+};
+FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, int64_t scratch_bytes) {
+    FewRowsPlan best{};
+    for (int tile : {16, 32, 64}) {
+        const int64_t rb = ceil_div(M, tile), cb = ceil_div(N, tile), steps = K / 32, batch = tile == 64 ? 16 : 32;
+        if (rb * cb > 4 * kCUs) continue; // (far from where it pays)
+        int64_t slices = tile == 64 ? kCUs / (rb * cb) : 1;
+        if (slices < 1) slices = 1;
+        int64_t slice_steps = ceil_div(ceil_div(steps, slices), batch) * batch; // whole batches of all eight waves
+        slices = ceil_div(steps, slice_steps);
+        const int64_t scratch = slices > 1 ? slices * rb * tile * cb * tile * 4 : 0;
+        if (scratch > scratch_bytes) { // (then in one piece)
+            slices = 1;
+            slice_steps = steps;
+        }
+        double us = (double)ceil_div(rb * cb * slices, kCUs) * (double)(slice_steps * 64 * 2 * tile) / 36e3;
+        // rows of A that do not fit an XCD's L2 come from beyond it for every block of columns (270 x 5488 x 12864: 178 us)
+        if (M * K * 2 > (3 << 20)) us = std::max(us, (double)(cb * M + N) * (double)K * 2.0 / 4.2e6);
+        us += (tile == 16 ? 2.0 : tile == 32 ? 2.2 : 4.4) + (slices > 1 ? 3.7 : 0.0);
+        if (!best.tile || us < best.us) best = FewRowsPlan{tile, rb, cb, slices, slice_steps, us};
+    }
+    return best;
+}
+} // namespace
+
 } // namespace lcma
 
 using namespace lcma;
@@ -221,5 +269,41 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
     p.ny = (int32_t)(K / 64);
     p.n_row_b = (uint32_t)(N * 2);
     if (workspace && ((uintptr_t)workspace & 255)) return fail(LCMA_ERR_ARG, "%s: the workspace must be 256-byte aligned", who);
-    return plane_gemm(who, dtype == LCMA_BF16 ? PG_BF16 : PG_F16_OUT, p, 1, M, N, 0, 0, workspace, workspace ? workspace_bytes : 0, stream);
+    const int kind = dtype == LCMA_BF16 ? PG_BF16 : PG_F16_OUT;
+    const int64_t scratch = workspace ? workspace_bytes : 0;
+    if (!tuning_schedule()) { // (a forced schedule is one of the plane GEMM's)
+        const FewRowsPlan f = few_rows_plan(M, N, K, scratch);
+        int t = 0, sc = 0;
+        if (f.tile && f.us < choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc)) {
+            FewRowsParams q;
+            std::memset(&q, 0, sizeof q);
+            q.A = A;
+            q.W = W;
+            q.C = C;
+            q.a_bytes = p.a_bytes;
+            q.w_bytes = p.b_bytes;
+            q.c_bytes = p.c_bytes;
+            q.lda_b = p.lda_b;
+            q.ldw_b = p.ldb_b;
+            q.ldc_b = p.ldc_b;
+            q.n_row_b = p.n_row_b;
+            q.steps = (int32_t)(K / 32);
+            q.row_blocks = (int32_t)f.row_blocks;
+            q.block_rows = f.tile;
+            q.slices = (int32_t)f.slices;
+            q.slice_steps = (int32_t)f.slice_steps;
+            q.partial_ld = (int32_t)(f.col_blocks * f.tile);
+            q.partial = workspace;
+            const bool bf = dtype == LCMA_BF16;
+            const auto launch = f.tile == 16   ? (bf ? lcma_launch_few_rows_bf16_16 : lcma_launch_few_rows_f16_16)
+                                : f.tile == 32 ? (bf ? lcma_launch_few_rows_bf16_32 : lcma_launch_few_rows_f16_32)
+                                               : (bf ? lcma_launch_few_rows_bf16_64 : lcma_launch_few_rows_f16_64);
+            // (the column blocks and slices of a block of rows in eights, one per XCD)
+            int err = launch(&q, (int)(ceil_div(f.col_blocks * f.slices, 8) * 8 * f.row_blocks), stream);
+            if (!err && f.slices > 1) err = (bf ? lcma_launch_few_rows_sum_bf16 : lcma_launch_few_rows_sum_f16)(&q, (int)M, stream);
+            if (err) return fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err);
+            return LCMA_OK;
+        }
+    }
+    return plane_gemm(who, kind, p, 1, M, N, 0, 0, workspace, scratch, stream);
 }

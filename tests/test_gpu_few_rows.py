@@ -1,0 +1,43 @@
+"""lcma_gemm_nt_ws on few rows or a small C (csrc/lcma_few_rows.hpp): tiles of 16, 32 and 64, K in one piece and in slices (the
+last one shorter), rows and columns past the end of C, with the workspace and without.  Integer inputs are exact in any order
+of the sums; float inputs against the fp64 product within the rounding of C plus that of fp32 sums over K."""
+import numpy as np
+import pytest
+
+import lcma_inputs as inp
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+# by the library's time model: tiles of 16 up to (100, 520, 4160), of 32 (300, 520, 1024), of 64 the rest, with 4, 2, 14 (of 448
+# steps of 32, the last slice shorter), 2 and 1 slices
+SHAPES = [(1, 8, 64), (17, 72, 192), (33, 1000, 576), (100, 520, 4160), (300, 520, 1024), (64, 4096, 4096), (65, 4088, 4160),
+          (129, 200, 14400), (250, 2000, 2112), (100, 8200, 512)]
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_few_rows(dt, shape):
+    import torch
+    import gpu_util as G
+    from paper_2605_06057_amd import binding as B
+    M, N, K = shape
+    Ai, Wi = inp.integers(81, 1, (M, K + 8), -2, 2), inp.integers(81, 2, (N, K), -2, 2)
+    dev = lambda x: G.to_device(inp.store(x, dt), dt)
+    ws = torch.full((B.lcma_split_group_scratch_bytes(),), 255, dtype=torch.uint8, device="cuda")  # NaN wherever it is read unwritten
+    want = inp.store(Ai[:, :K].astype(np.float64) @ Wi.T.astype(np.float64), dt)
+    a, w = dev(Ai)[:, :K], dev(Wi)
+    for space in (ws, None):
+        c = G.empty_like_c(M + 3, N + 8, dt, fill=float("nan"))
+        print(f"few rows {dt} {M}x{N}x{K} workspace {space is not None}", flush=True)
+        B.lcma_gemm_nt_ws(a, w, c[:M, :N], space)
+        torch.cuda.synchronize()
+        assert np.array_equal(G.to_host_stored(c[:M, :N], dt).view(np.uint8), want.view(np.uint8))
+        assert torch.isnan(c[M:]).all().item() and torch.isnan(c[:, N:]).all().item(), "wrote outside C"
+    rng = np.random.default_rng(M + N + K)
+    Af, Wf = inp.store(rng.standard_normal((M, K)), dt), inp.store(rng.standard_normal((N, K)) * 0.05, dt)
+    c = G.empty_like_c(M, N, dt, fill=float("nan"))
+    B.lcma_gemm_nt_ws(G.to_device(Af, dt), G.to_device(Wf, dt), c, ws)
+    ref = oracle.gemm(inp.widen(Af, dt), np.ascontiguousarray(inp.widen(Wf, dt).T))
+    # the one rounding of C (at most half a unit of its 8 or 11 bits on every element) and fp32 sums of K terms
+    assert oracle.rel_frobenius(G.to_host_f64(c, dt), ref) <= 2.0 ** (-9 if dt == "bf16" else -12) + 1e-5
