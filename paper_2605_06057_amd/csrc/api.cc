@@ -47,6 +47,33 @@ const Variant *pick_variant(int scheme_id, int dtype, int64_t M, int64_t N, int6
     return best;
 }
 
+// The direct kernel (csrc/lcma_direct.hpp) to run in place of the staged variant `v` that pick_variant chose, or `v` itself.
+// The direct kernels are bound by the lines a CU can ask for: about 256 work-groups of eight waves run at a time, and one takes
+// 14.5 ns per element of K/k on the 16 x 16 tile and 41 ns on the 32 x 32 one (K = 1500 to 3000), 1 us besides, 3 us for
+// the launch.  Staged against direct, <2,2,2;7> fp32: 256^3 20.3 against 8.3 us, 512^3 35.6 / 8.3, 1024^3 66.5 / 26.1,
+// 857 x 1048 x 808 55.9 / 23.2; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
+// K x N kernels for any form of B, so that both layouts make the same choice and give the same bits, and prepared operands
+// (whose planes carry the same roundings) the same precision.
+static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K) {
+    const Variant *staged = pick_variant(v->scheme_id, v->dtype, M, N, K, 0, 0), *best = v;
+    if (!staged) return v;
+    double best_us = 0.9 * 1e6 * predict_variant(*staged, M, N, K);
+    for (int i = 0; i < kVariantCount; ++i) {
+        const Variant &d = kVariants[i];
+        if (!d.direct || d.scheme_id != v->scheme_id || d.dtype != v->dtype || d.b_nk != v->b_nk || d.prepared != v->prepared ||
+            !fits(d, M, N, K))
+            continue;
+        const int64_t bm = round_up(M, (int64_t)d.m * d.TM) / d.m, bn = round_up(N, (int64_t)d.n * d.TN) / d.n;
+        const int64_t bk = round_up(K, (int64_t)d.k * d.TK) / d.k, groups = (bm / d.TM) * (bn / d.TN);
+        const double us = 3.0 + (double)((groups + 255) / 256) * ((d.TM == 16 ? 0.0145 : 0.041) * (double)bk + 1.0);
+        if (us < best_us) {
+            best = &d;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
 static const Variant *find_variant(const char *name) {
     for (int i = 0; i < kVariantCount; ++i)
         if (!std::strcmp(kVariants[i].name, name)) return &kVariants[i];
@@ -128,7 +155,9 @@ static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const 
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: N = %lld and K = %lld must be multiples of %d (16 bytes of elements)",
                     (long long)N, (long long)K, 16 / es);
     // blocks are cut from the matrices padded to whole tiles; the extents stay the true ones
-    const int64_t Mp = round_up(M, (int64_t)v.m * v.TM), Np = round_up(N, (int64_t)v.n * v.TN),
+    // (the planes of lcma_prepare_b hold whole 64 rows, whatever the tile)
+    const int64_t tn = v.prepared && v.TN < 64 ? 64 : v.TN;
+    const int64_t Mp = round_up(M, (int64_t)v.m * v.TM), Np = round_up(N, (int64_t)v.n * tn),
                   Kp = round_up(K, (int64_t)v.k * v.TK);
     const int64_t bm = Mp / v.m, bn = Np / v.n, bk = Kp / v.k;
     const int64_t a_bytes = ((M - 1) * lda + K) * es,
@@ -211,7 +240,10 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
     if (M == 0 || N == 0) return LCMA_OK;
     const Variant *v = forced_variant(); // ablation override
     if (v && (v->scheme_id != id || v->dtype != (int)dtype || v->prepared || v->b_nk != b_nk)) v = nullptr;
-    if (!v) v = pick_variant(id, dtype, M, N, K, 0, b_nk);
+    if (!v) {
+        v = pick_variant(id, dtype, M, N, K, 0, b_nk);
+        if (v) v = pick_direct(v, M, N, K);
+    }
     if (!v) {
         bool any = false;
         for (int i = 0; i < kVariantCount; ++i)
@@ -374,7 +406,10 @@ extern "C" lcma_status lcma_gemm_prepared(int64_t M, int64_t N, int64_t K, const
     if (M == 0 || N == 0) return LCMA_OK;
     const Variant *v = forced_variant(); // ablation override
     if (v && (v->scheme_id != id || v->dtype != (int)dtype || !v->prepared)) v = nullptr;
-    if (!v) v = pick_variant(id, dtype, M, N, K, 1);
+    if (!v) {
+        v = pick_variant(id, dtype, M, N, K, 1);
+        if (v) v = pick_direct(v, M, N, K);
+    }
     if (!v) {
         bool any = false;
         for (int i = 0; i < kVariantCount; ++i)

@@ -47,6 +47,7 @@ struct Variant {
     int b_nk;           // 1: takes B as the N x K weight matrix W (W[n][k] = B[k][n])
     int left_planes;    // 1: takes the output of the stand-alone Combine-A kernel instead of A (stage kernel)
     int batch;          // 1: batched plain GEMM over planes (stage kernel of the unfused dataflow)
+    int direct;         // > 0: direct kernel for small products: that many waves split K (csrc/lcma_direct.hpp)
     int (*launch)(const Params *p, int grid, void *stream); // returns a hipError_t
 };
 extern const Variant kVariants[];

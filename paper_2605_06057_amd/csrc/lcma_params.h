@@ -74,6 +74,7 @@ struct PlaneGemmParams {
     int32_t nx, nz, ny;                                     // tiles along M and N; steps of 128 bytes along K
     int32_t panel;                                          // width (in z tiles) of a column panel of the tile order
     uint32_t n_row_b;                                       // N * 2: columns of C at or beyond it are never written
+    uint32_t tail_b;                                        // bytes of a row of the operands in the last step (a multiple of 16, 128 = whole)
     int32_t jobs;                                           // tile-products: planes * nx * nz
     int32_t units;                                          // persistent work-groups launched
     int32_t interleave;                                     // persistent kernel: 0 = work-group u owns the steps [u * cap, (u + 1) * cap);

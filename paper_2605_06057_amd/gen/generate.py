@@ -150,9 +150,12 @@ class Variant:
     tb: int = 0               # 1: B is given as the N x K weight matrix (k-contiguous rows)
     pa: int = 0               # 1 (with pb, staged loop): the left operands come ready-made from planes too
     batch: int = 0            # 1 (plain, tb): the grid covers R products on planes (Algorithm 1's batched GEMM)
+    ks: int = 0               # > 0: direct kernel (csrc/lcma_direct.hpp): ks waves split K, fragments come straight from memory
     name: str = field(default="")
 
     def finish(self):
+        if not self.name and self.ks:
+            self.name = f"{self.scheme}_{self.dtype}_d{self.TM}x{self.TN}k{self.ks}" + ("b" if self.pb else "") + ("t" if self.tb else "")
         if not self.name:
             self.name = (f"{self.scheme}_{self.dtype}_t{self.TM}x{self.TN}x{self.TK}_c{self.chunk}"
                          + (f"x{len(self.comp)}" if self.comp else "") + (f"w{self.wgm}x{self.wgn}" if (self.wgm, self.wgn) != (2, 2) else "") + ("f" if self.fc else "") + ("i" if self.pipe == 2 else "") + ("s3" if self.stages == 3 else "") + ("a" if self.pa else "") + ("b" if self.pb else "") + ("d" if self.dl else "") + ("t" if self.tb else "") + ("g" if self.batch else "") + (f"o{self.occ}" if self.occ > 1 else ""))
@@ -182,6 +185,9 @@ def chunks_of(s: Scheme, v: Variant) -> list[list[int]]:
 def plan(s: Scheme, v: Variant):
     """On-chip resource planning: (accumulator registers per lane, LDS bytes, peak live C tiles)."""
     es = 4 if v.dtype == "f32" else 2
+    if v.ks:  # every product's accumulators; the partial tiles of C of all waves, rows padded by 16 bytes
+        assert v.dtype == "f32" and v.chunk >= s.R
+        return s.R * v.TM * v.TN // 64, v.ks * s.m * s.n * v.TM * (v.TN + 4) * 4, 0, s.R, 0, 0
     tile_regs = (v.TM // v.wgm // 32) * (v.TN // v.wgn // 32) * 16
     chunks = chunks_of(s, v)
     nslot = max(len(c) for c in chunks)
@@ -295,10 +301,11 @@ def emit_kernel(s: Scheme, v: Variant) -> str:
     w(f"// GENERATED by gen/generate.py - do not edit.  Scheme {s.name} <{s.m},{s.k},{s.n};{s.R}>, dtype {v.dtype},")
     w(f"// tile {v.TM}x{v.TN}x{v.TK}, {len(chunks)} chunk(s) of up to {nslot} products; planned accumulator registers")
     w(f"// per lane {regs}, LDS {lds} bytes, peak live C tiles {live_c}.")
-    w('#include "lcma_device.hpp"')
+    w('#include "lcma_direct.hpp"' if v.ks else '#include "lcma_device.hpp"')
     w("namespace {")
     w("using namespace lcma;")
-    w(f"using T = Tile<{in_t}, {ct_t}, {v.TM}, {v.TN}, {v.TK}, {v.wgm}, {v.wgn}, {nsa}, {nsb}, {v.pipe}, {v.fc}, {v.stages}, {v.pb}, {v.dl}, {v.tb}, {v.pa}, {v.batch}>;")
+    if not v.ks:
+        w(f"using T = Tile<{in_t}, {ct_t}, {v.TM}, {v.TN}, {v.TK}, {v.wgm}, {v.wgn}, {nsa}, {nsb}, {v.pipe}, {v.fc}, {v.stages}, {v.pb}, {v.dl}, {v.tb}, {v.pa}, {v.batch}>;")
     for ci, ch in enumerate(chunks):
         a_blocks = sorted({(i, l) for r in ch for i in range(s.m) for l in range(s.k) if s.U[r, i, l]})
         b_blocks = sorted({(l, j) for r in ch for l in range(s.k) for j in range(s.n) if s.V[r, l, j]})
@@ -339,6 +346,8 @@ def emit_kernel(s: Scheme, v: Variant) -> str:
                                           for r in ch], len(b_blocks), wide)
         w("};")
     w("")
+    if v.ks:
+        return "\n".join(L + emit_direct_tail(s, v)) + "\n"
     w("} // namespace")
     w("")
     w("// the kernel carries the variant's name so that profiles tell the variants apart")
@@ -389,6 +398,39 @@ def emit_kernel(s: Scheme, v: Variant) -> str:
     return "\n".join(L) + "\n"
 
 
+def emit_direct_tail(s: Scheme, v: Variant) -> list[str]:
+    """The rest of a direct kernel's source behind its Chunk0: Eq. 6 on one wave's accumulators, kernel and launcher."""
+    L = []
+    w = L.append
+    w("struct Blocks {  // blocks of C: the signed sums of Eq. 6")
+    w(f"    static constexpr int NC = {s.m * s.n};")
+    w(f"    static LCMA_DEV constexpr int c_i(int o) {{ return o / {s.n}; }}")
+    w(f"    static LCMA_DEV constexpr int c_j(int o) {{ return o % {s.n}; }}")
+    w("    template <int MI, int NI> static LCMA_DEV f32x4 comb(const f32x4 (&h)[Chunk0::NP][MI][NI], int o, int mi, int ni) {")
+    w("        switch (o) {")
+    for i in range(s.m):
+        for j in range(s.n):
+            terms = [(int(s.W[r, i, j]), f"h[{r}][mi][ni]") for r in range(s.R) if s.W[r, i, j]]
+            w(f"        case {i * s.n + j}: return {signed_sum(terms)};")
+    w("        default: return h[0][mi][ni];")
+    w("        }")
+    w("    }")
+    w("};")
+    w(f"using D = Direct<{v.TM // 16}, {v.TN // 16}, {v.ks}, {'true' if v.tb else 'false'}, {'true' if v.pb else 'false'}, Chunk0, Blocks>;")
+    w("} // namespace")
+    w("")
+    w(f'extern "C" __global__ __launch_bounds__({64 * v.ks}, {max(1, v.ks // 4)}) void lcma_k_{v.name}(const lcma::Params p) {{')
+    w("    __shared__ __attribute__((aligned(16))) char smem[D::LDS_BYTES];")
+    w("    D::run(p, (LCMA_LDS char *)smem);")
+    w("}")
+    w("")
+    w(f'extern "C" int lcma_launch_{v.name}(const lcma::Params *p, int grid, void *stream) {{')
+    w(f"    lcma_k_{v.name}<<<dim3(grid), dim3({64 * v.ks}), 0, (hipStream_t)stream>>>(*p);")
+    w("    return (int)hipGetLastError();")
+    w("}")
+    return L
+
+
 def emit_registry(schemes: dict[str, Scheme], variants: list[Variant]) -> str:
     L = ["// GENERATED by gen/generate.py - do not edit.", '#include "host_common.h"', ""]
     for v in variants:
@@ -398,7 +440,7 @@ def emit_registry(schemes: dict[str, Scheme], variants: list[Variant]) -> str:
         s = schemes[v.scheme]
         hash_expr = "0" if s.name == "plain" else f"0x{scheme_hash(s):016x}ull"
         L.append(f'    {{"{v.name}", {SCHEME_IDS[v.scheme]}, {DTYPE_IDS[v.dtype]}, {s.m}, {s.k}, {s.n}, {s.R}, '
-                 f"{hash_expr}, {v.TM}, {v.TN}, {v.TK}, {min(v.chunk, s.R)}, {v.rank}, {v.eff}, {v.occ}, {s.R + len(v.comp)}, {v.pb}, {v.tb}, {v.pa}, {v.batch}, lcma_launch_{v.name}}},")
+                 f"{hash_expr}, {v.TM}, {v.TN}, {v.TK}, {min(v.chunk, s.R)}, {v.rank}, {v.eff}, {v.occ}, {s.R + len(v.comp)}, {v.pb}, {v.tb}, {v.pa}, {v.batch}, {v.ks}, lcma_launch_{v.name}}},")
     L += ["};", f"const int kVariantCount = {len(variants)};"]
     preps = prep_kernels(variants)
     L.append("const PrepKernel kPrepKernels[] = {")
@@ -798,6 +840,10 @@ def manifest(schemes: dict[str, Scheme] | None = None) -> list[Variant]:
               Variant("laderman", dt, 128 if dt != "f32" else 64, 64, tk, chunk=1, pa=1, pb=1, rank=95)]
         if dt != "f16":
             V += [Variant("strassen2", dt, 64, 64, tk, chunk=7, pa=1, pb=1, rank=95)]
+    # Small fp32 products (chosen by run-time size, see pick_direct in csrc/api.cc; rank 96: outside the published time model)
+    for name in ("strassen", "winograd"):
+        if name in schemes:
+            V += [Variant(name, "f32", t, t, 16, chunk=7, ks=8, tb=tb, pb=pb, rank=96) for t in (16, 32) for tb, pb in ((0, 0), (1, 0), (0, 1))]
     # Every kernel that lcma_gemm can pick for the paper's schemes also exists for B given as the N x K
     # weight matrix ("t"): its B tiles are staged like A's, with 16-byte loads and no transposition.
     from dataclasses import replace
