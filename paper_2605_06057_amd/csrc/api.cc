@@ -1,6 +1,7 @@
 // C ABI entry points: argument checks, variant choice, kernel launch.
 #include "host_common.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -135,8 +136,9 @@ lcma_status empty_product(int64_t M, int64_t N, void *C, int64_t ldc, int dtype,
 
 // B and ldb describe the K x N matrix; for a variant that takes the weight layout, the N x K matrix W;
 // for a prepared-B variant, the planes written by lcma_prepare_b (ldb is then ignored).
+// plain_us > 0: the plain product may run on the ping-pong kernels instead if they take less than that.
 static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
-                       int64_t ldb, void *C, int64_t ldc, void *stream, float alpha = 1.f, float beta = 0.f) {
+                       int64_t ldb, void *C, int64_t ldc, void *stream, float alpha = 1.f, float beta = 0.f, double plain_us = 0.0) {
     const int es = dtype_size(v.dtype);
     if (v.left_planes || v.batch)
         return fail(LCMA_ERR_ARG, "lcma_gemm: %s is a stage kernel of lcma_gemm_unfused and takes no matrices", v.name);
@@ -173,6 +175,11 @@ static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const 
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: a matrix spans 2 GiB or more");
     if (overlap(C, c_bytes, A, a_bytes) || overlap(C, c_bytes, B, b_bytes))
         return fail(LCMA_ERR_ARG, "lcma_gemm: C overlaps A or B");
+    if (plain_us > 0.0) {
+        int err = 0;
+        if (plain_product(!v.b_nk, M, N, K, A, lda, B, ldb, C, ldc, v.dtype, plain_us, stream, &err))
+            return err ? fail(LCMA_ERR_HIP, "lcma_gemm: launch failed with HIP error %d", err) : LCMA_OK;
+    }
     Params p;
     p.A = A;
     p.B = B;
@@ -240,8 +247,15 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
     if (M == 0 || N == 0) return LCMA_OK;
     const Variant *v = forced_variant(); // ablation override
     if (v && (v->scheme_id != id || v->dtype != (int)dtype || v->prepared || v->b_nk != b_nk)) v = nullptr;
+    double plain_us = 0.0;
     if (!v) {
         v = pick_variant(id, dtype, M, N, K, 0, b_nk);
+        // the plain 16-bit product without scaling: the ping-pong kernels where they are faster (the same bits)
+        // (the published prediction knows no latency: a step takes at least 0.27 us, 0.14 for N x K weights, and 0.36 and 0.22 with
+        // a hundred work-groups: 215 x 208 x 1976 19.7 and 11.7 us, 704 x 704 x 8000 97.6 and 63.2)
+        if (v && id == LCMA_PLAIN && dtype != LCMA_F32 && alpha == 1.f && beta == 0.f && K > 0)
+            plain_us = std::max(1e6 * predict_variant(*v, M, N, K),
+                                2.5 + ((M + 63) / 64 * ((N + 63) / 64) < 100 ? (b_nk ? 0.14 : 0.27) : (b_nk ? 0.22 : 0.36)) * (double)K / v->TK);
         if (v) v = pick_direct(v, M, N, K);
     }
     if (!v) {
@@ -255,7 +269,7 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: no kernel of scheme id %d takes N = %lld (whole 16-byte vectors) and K = %lld (whole tiles)",
                     id, (long long)N, (long long)K);
     }
-    return run(*v, M, N, K, A, lda, B, ldb, C, ldc, stream, alpha, beta);
+    return run(*v, M, N, K, A, lda, B, ldb, C, ldc, stream, alpha, beta, plain_us);
 }
 
 extern "C" lcma_status lcma_gemm_ex(float alpha, float beta, int b_layout, int64_t M, int64_t N, int64_t K, const void *A,

@@ -27,7 +27,41 @@
 
 namespace lcma {
 
-template <class KIND, class OUT> struct PingPongGemm {
+// Fragments of 32 columns of a K x N tile in LDS (64 rows of 256 bytes) for the four 32x32x16 instructions of a step: eight k of a
+// column are two transposing reads of four.  Sixteen lanes of such a read give the addresses of four rows (k) x 16 columns,
+// four lanes to a row, and get a column each; column_base says where.  One block of instructions that waits for its own
+// results: the compiler's form of the read carries no alias information and would wait for every load in flight.
+// Measured: the K x N kernels run within 1 to 4 % of the N x K ones.
+template <class FragT> LCMA_DEV void read_columns(const LCMA_LDS char *tile, uint32_t base, FragT (&f)[4]) {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 r[4][2];
+    const uint32_t at = (uint32_t)(uintptr_t)tile + base;
+    asm volatile("ds_read_b64_tr_b16 %0, %8\n"
+                 "ds_read_b64_tr_b16 %1, %8 offset:1024\n"
+                 "ds_read_b64_tr_b16 %2, %8 offset:4096\n"
+                 "ds_read_b64_tr_b16 %3, %8 offset:5120\n"
+                 "ds_read_b64_tr_b16 %4, %8 offset:8192\n"
+                 "ds_read_b64_tr_b16 %5, %8 offset:9216\n"
+                 "ds_read_b64_tr_b16 %6, %8 offset:12288\n"
+                 "ds_read_b64_tr_b16 %7, %8 offset:13312\n"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[2][0]), "=&v"(r[2][1]), "=&v"(r[3][0]), "=&v"(r[3][1])
+                 : "v"(at)
+                 : "memory");
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[k] = __builtin_bit_cast(FragT, u32x4{r[k][0][0], r[k][0][1], r[k][1][0], r[k][1][1]});
+}
+// Byte of this lane's part of the first read for the 32 columns from 32 `block` on (block: 0 .. 3).  16-byte chunk c of row k sits at
+// position c ^ 4 (k % 4): the four rows of a read are 64 bytes apart in the banks.  Lane group lane / 16: columns 16 (group % 2), k 8
+// (group / 2).
+LCMA_DEV uint32_t column_base(int lane, int block) {
+    const int i = lane & 15, g = lane >> 4, k = i >> 2;
+    return (uint32_t)(((g >> 1) * 8 + k) * 256 + ((block * 4 + (g & 1) * 2 + ((i & 3) >> 1)) ^ (k << 2)) * 16 + (i & 1) * 8);
+}
+
+// KN: the right operand is the K x N matrix B, not the rows of W (16-bit types).  Half h of its tile is 64 rows (k) of 128 columns,
+// 128 h and on, and wave column wn holds columns 32 wn .. of both halves; fragments are read with the transposing LDS read.
+template <class KIND, class OUT, bool KN = false> struct PingPongGemm {
     static constexpr int TM = 256, TN = 256, NT = 512, WM = 128, WN = 64, NMI = 4, NNI = 2, ROW = 128;
     static constexpr bool SCALED = std::is_same_v<KIND, FP8>;
     // fragments of a step per tile row: FP8 two of 32 bytes, 16-bit four of 16 bytes
@@ -39,6 +73,8 @@ template <class KIND, class OUT> struct PingPongGemm {
     static constexpr int LDS_BYTES = 8 * HALF + 8 * STRIP + SCALES;
     static_assert(LDS_BYTES <= 160 * 1024, "LDS budget of one CU");
     using FragT = typename PlaneFrag<KIND>::type;
+    static_assert(!(KN && SCALED), "FP8 operands are k-contiguous");
+    static constexpr int NI_COLS = KN ? 128 : 32; // columns from a wave's first 32 to its second
 
     // as in PlaneGemm: 16-byte chunk c of a row sits at position swz(row, c)
     static LCMA_DEV constexpr int swz(int row, int c) { return c ^ ((row >> 1) & 7); }
@@ -46,6 +82,7 @@ template <class KIND, class OUT> struct PingPongGemm {
     struct State {
         __amdgpu_buffer_rsrc_t ra, rb, rs; // rs: the scale bytes this wave loads (first group: of A, second: of B)
         uint32_t a_voff, b_voff;                         // of this thread's chunk in the first 64 rows of half 0
+        uint32_t a_tail, b_tail;                         // the same in the last step: past the extents for chunks past K
         uint32_t a_rows, b_rows, a_half, b_half;         // byte step to the other 64 rows of a half, and to half 1
         uint32_t a_frag[4], b_frag[4];
         int wave_chunk, w, wm, wn, l32, lh;
@@ -90,9 +127,12 @@ template <class KIND, class OUT> struct PingPongGemm {
 #pragma unroll
             for (int i = 0; i < 2; ++i) f[i][k] = fragment(half + i * 32 * ROW, s.a_frag, k);
     }
+    // (KN: what was read before has landed as well when the function returns)
     static LCMA_DEV void read_b(const State &s, const LCMA_LDS char *half, FragT (&f)[NK]) {
+        if constexpr (KN) read_columns(half, s.b_frag[0], f);
+        else
 #pragma unroll
-        for (int k = 0; k < NK; ++k) f[k] = fragment(half, s.b_frag, k);
+            for (int k = 0; k < NK; ++k) f[k] = fragment(half, s.b_frag, k);
     }
     // a quadrant: two accumulators, ascending k (the lowest byte of a scale register is the one that counts)
     static LCMA_DEV void multiply(const FragT (&a)[2][NK], const FragT (&b)[NK], f32x16 &c0, f32x16 &c1, int sa0, int sa1, int sb) {
@@ -145,11 +185,20 @@ template <class KIND, class OUT> struct PingPongGemm {
         {
             const int row = tid >> 3, c = swz(row, tid & 7) * 16;
             s.a_voff = (uint32_t)row * p->lda_b + c;
-            s.b_voff = (uint32_t)((row >> 5) * 64 + (row & 31)) * p->ldb_b + c;
             s.a_rows = 128 * p->lda_b;
-            s.b_rows = 128 * p->ldb_b;
             s.a_half = 64 * p->lda_b;
-            s.b_half = 32 * p->ldb_b;
+            s.a_tail = (uint32_t)c < p->tail_b ? s.a_voff : p->a_bytes;
+            if constexpr (KN) { // load q of a thread fills row (k) q * 32 + tid / 16, position tid % 16; rows past K lie past the extent
+                const int k = tid >> 4;
+                s.b_tail = s.b_voff = (uint32_t)k * p->ldb_b + ((tid & 15) ^ ((k & 3) << 2)) * 16;
+                s.b_rows = 32 * p->ldb_b;
+                s.b_half = 256;
+            } else {
+                s.b_voff = (uint32_t)((row >> 5) * 64 + (row & 31)) * p->ldb_b + c;
+                s.b_tail = (uint32_t)c < p->tail_b ? s.b_voff : p->b_bytes;
+                s.b_rows = 128 * p->ldb_b;
+                s.b_half = 32 * p->ldb_b;
+            }
         }
         const int ar = s.wm * 64 + s.l32, br = s.wn * 32 + s.l32;
 #pragma unroll
@@ -158,6 +207,8 @@ template <class KIND, class OUT> struct PingPongGemm {
             s.a_frag[k] = ar * ROW + swz(ar, c) * 16;
             s.b_frag[k] = br * ROW + swz(br, c) * 16;
         }
+        if constexpr (KN) s.b_frag[0] = column_base(tid & 63, s.wn);
+        const uint32_t b_step = KN ? 64 * p->ldb_b : ROW; // byte step of B from one step to the next
         // an odd number of steps is rounded up by one whose operands are past the extents, i.e. zero
         const int ny = p->ny, n2 = (ny + 1) & ~1;
         // the tile-products of this work-group, dealt as in PlaneGemm::run
@@ -186,7 +237,7 @@ template <class KIND, class OUT> struct PingPongGemm {
                 int plane, x, z;
                 tile_of_job(q->nx, q->nz, q->panel, j, plane, x, z);
                 a = (uint32_t)plane * q->a_plane + (uint32_t)(x * TM) * q->lda_b;
-                b = (uint32_t)plane * q->b_plane + (uint32_t)(z * TN) * q->ldb_b;
+                b = (uint32_t)plane * q->b_plane + (uint32_t)(z * TN) * (KN ? 2 : q->ldb_b);
                 if constexpr (SCALED)
                     sc = s.wm ? (uint32_t)plane * q->sb_plane + (uint32_t)(z * TN) * q->lsb_b
                               : (uint32_t)plane * q->sa_plane + (uint32_t)(x * TM) * q->lsa_b;
@@ -211,38 +262,43 @@ template <class KIND, class OUT> struct PingPongGemm {
         origin(job, a_cur, b_cur, s_cur);
         FragT fa0[2][NK], fa1[2][NK], fb0[NK], fb1[NK];
         f32x16 acc[NMI][NNI];
-        auto load_step = [&](LCMA_LDS char *A0, LCMA_LDS char *A1, LCMA_LDS char *B0, LCMA_LDS char *B1, uint32_t a, uint32_t b) {
-            load_half(s, s.rb, B0, s.b_voff, b, s.b_rows);
-            load_half(s, s.ra, A0, s.a_voff, a, s.a_rows);
-            load_half(s, s.ra, A1, s.a_voff, a + s.a_half, s.a_rows);
-            load_half(s, s.rb, B1, s.b_voff, b + s.b_half, s.b_rows);
+        auto load_step = [&](LCMA_LDS char *A0, LCMA_LDS char *A1, LCMA_LDS char *B0, LCMA_LDS char *B1, uint32_t a, uint32_t b, bool last) {
+            const uint32_t av = last ? s.a_tail : s.a_voff, bv = last ? s.b_tail : s.b_voff;
+            load_half(s, s.rb, B0, bv, b, s.b_rows);
+            load_half(s, s.ra, A0, av, a, s.a_rows);
+            load_half(s, s.ra, A1, av, a + s.a_half, s.a_rows);
+            load_half(s, s.rb, B1, bv, b + s.b_half, s.b_rows);
         };
         load_scales(s_cur, 0);
-        load_step(A00, A10, B00, B10, a_cur, b_cur);
-        load_step(A01, A11, B01, B11, ny > 1 ? a_cur + ROW : a_none, ny > 1 ? b_cur + ROW : b_none);
+        load_step(A00, A10, B00, B10, a_cur, b_cur, ny == 1);
+        load_step(A01, A11, B01, B11, ny > 1 ? a_cur + ROW : a_none, ny > 1 ? b_cur + b_step : b_none, ny == 2);
         memory_slot_end();
         read_b(s, B00, fb0);
         if (s.wm) slot_end(); // the second group runs one slot behind the first
         // One step out of stage (A0, A1, B0, B1); nextB0: half 0 of B of the next step; a, b: the operands two steps on, which go
-        // into this stage.  The slot of the last multiplication is ended by the caller.
-        auto step = [&](LCMA_LDS char *A0, LCMA_LDS char *A1, LCMA_LDS char *B0, LCMA_LDS char *B1, LCMA_LDS char *nextB0, uint32_t a, uint32_t b) {
+        // into this stage (last: they are those of a last step).  The slot of the last multiplication is ended by the caller.
+        auto step = [&](LCMA_LDS char *A0, LCMA_LDS char *A1, LCMA_LDS char *B0, LCMA_LDS char *B1, LCMA_LDS char *nextB0, uint32_t a, uint32_t b,
+                        bool last) {
+            const uint32_t av = last ? s.a_tail : s.a_voff, bv = last ? s.b_tail : s.b_voff;
             read_a(s, A0, fa0);
-            load_half(s, s.rb, B0, s.b_voff, b, s.b_rows);
+            load_half(s, s.rb, B0, bv, b, s.b_rows);
             memory_slot_end();
             multiply(fa0, fb0, acc[0][0], acc[1][0], (int)sa[0], (int)sa[1], (int)sb[0]);
             slot_end();
             read_a(s, A1, fa1);
-            load_half(s, s.ra, A0, s.a_voff, a, s.a_rows);
+            load_half(s, s.ra, A0, av, a, s.a_rows);
             memory_slot_end();
             multiply(fa1, fb0, acc[2][0], acc[3][0], (int)sa[2], (int)sa[3], (int)sb[0]);
             slot_end();
-            read_b(s, B1, fb1);
-            load_half(s, s.ra, A1, s.a_voff, a + s.a_half, s.a_rows);
+            if constexpr (!KN) read_b(s, B1, fb1); // (KN: behind the loads, it waits for its results)
+            load_half(s, s.ra, A1, av, a + s.a_half, s.a_rows);
+            if constexpr (KN) read_b(s, B1, fb1);
             memory_slot_end();
             multiply(fa1, fb1, acc[2][1], acc[3][1], (int)sa[2], (int)sa[3], (int)sb[1]);
             slot_end();
-            read_b(s, nextB0, fb0);
-            load_half(s, s.rb, B1, s.b_voff, b + s.b_half, s.b_rows);
+            if constexpr (!KN) read_b(s, nextB0, fb0);
+            load_half(s, s.rb, B1, bv, b + s.b_half, s.b_rows);
+            if constexpr (KN) read_b(s, nextB0, fb0);
             memory_slot_end();
             multiply(fa0, fb1, acc[0][1], acc[1][1], (int)sa[0], (int)sa[1], (int)sb[1]);
         };
@@ -267,9 +323,9 @@ template <class KIND, class OUT> struct PingPongGemm {
                     }
                 }
                 const bool in = y + 2 < n2, pad = y + 3 == ny;
-                const uint32_t a2 = in ? a_cur + (uint32_t)(y + 2) * ROW : a_nxt, b2 = in ? b_cur + (uint32_t)(y + 2) * ROW : b_nxt;
+                const uint32_t a2 = in ? a_cur + (uint32_t)(y + 2) * ROW : a_nxt, b2 = in ? b_cur + (uint32_t)(y + 2) * b_step : b_nxt;
                 const bool none = in ? pad : ny == 1;
-                step(A00, A10, B00, B10, B01, a2, b2);
+                step(A00, A10, B00, B10, B01, a2, b2, (in ? y + 3 : 1) == ny);
                 slot_end();
                 if constexpr (SCALED) {
                     // (past the last step the scale bytes are nobody's: 1 for the zeros of a rounded-up step)
@@ -279,7 +335,7 @@ template <class KIND, class OUT> struct PingPongGemm {
 #pragma unroll
                     for (int ni = 0; ni < NNI; ++ni) sb[ni] = past ? 127u : sb[ni] >> 8;
                 }
-                step(A01, A11, B01, B11, B00, none ? a_none : a2 + ROW, none ? b_none : b2 + ROW);
+                step(A01, A11, B01, B11, B00, none ? a_none : a2 + ROW, none ? b_none : b2 + b_step, (in ? y + 4 : 2) == ny);
                 if constexpr (SCALED) {
 #pragma unroll
                     for (int mi = 0; mi < NMI; ++mi) sa[mi] >>= 8;
@@ -340,7 +396,8 @@ template <class KIND, class OUT> struct PingPongGemm {
                 for (int it = 0; it < NIT; ++it) {
                     const int idx = it * 64 + lane, row = idx / CPRW, ch = idx % CPRW;
                     const u32x4 v = *(LCMA_LDS u32x4 *)(strip + row * PITCH + ch * 16);
-                    const uint32_t colb = (uint32_t)(s.wn * WN) * OES + ch * 16; // byte column inside the tile
+                    // byte column inside the tile (2 OES chunks of 16 bytes are 32 columns)
+                    const uint32_t colb = (uint32_t)(s.wn * (KN ? 32 : WN) + ch / (2 * OES) * NI_COLS) * OES + ch % (2 * OES) * 16;
                     const uint32_t off = ((uint32_t)z * TN * OES + colb < p->n_row_b)
                                              ? c_base + (uint32_t)(s.wm * WM + mi * 32 + h * SR + row) * p->ldc_b + colb
                                              : extent;

@@ -1,5 +1,5 @@
 // Instances of the plane GEMM (csrc/lcma_plane_gemm.hpp) and of its fix-up kernel.
-#include "lcma_pingpong.hpp"
+#include "lcma_pingpong_narrow.hpp"
 
 using namespace lcma;
 
@@ -63,3 +63,32 @@ LCMA_PLANE_GEMM(bf16_t256_bf16, BF16, 256, 256, 2, 4, 1, BF16)
 LCMA_PLANE_GEMM(bf16_t128_bf16, BF16, 128, 128, 2, 2, 2, BF16)
 
 
+
+// The ping-pong kernels of the plain product (csrc/plane_gemm.cc, plain_product): K x N operand on the 256 x 256 tile, either
+// operand on the 256 x 128 tile.
+#define LCMA_PINGPONG_KN(NAME, KIND)                                                                                   \
+    extern "C" __global__ __launch_bounds__(512, 2) void lcma_k_pp_kn_##NAME(const lcma::PlaneGemmParams) {            \
+        using G = PingPongGemm<KIND, KIND, true>;                                                                      \
+        __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
+        G::run((LCMA_LDS char *)smem);                                                                                 \
+    }                                                                                                                  \
+    extern "C" int lcma_launch_pp_kn_##NAME(const lcma::PlaneGemmParams *p, void *stream) {                            \
+        lcma_k_pp_kn_##NAME<<<dim3(p->units), dim3(512), 0, (hipStream_t)stream>>>(*p);                                \
+        return (int)hipGetLastError();                                                                                 \
+    }
+#define LCMA_PINGPONG_NARROW(NAME, KIND, KN)                                                                           \
+    extern "C" __global__ __launch_bounds__(512, 2) void lcma_k_ppn_##NAME(const lcma::PlaneGemmParams p) {            \
+        using G = PingPongNarrow<KIND, KIND, KN>;                                                                      \
+        __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
+        G::run(p, (LCMA_LDS char *)smem);                                                                              \
+    }                                                                                                                  \
+    extern "C" int lcma_launch_ppn_##NAME(const lcma::PlaneGemmParams *p, void *stream) {                              \
+        lcma_k_ppn_##NAME<<<dim3(p->jobs), dim3(512), 0, (hipStream_t)stream>>>(*p);                                   \
+        return (int)hipGetLastError();                                                                                 \
+    }
+LCMA_PINGPONG_KN(bf16, BF16)
+LCMA_PINGPONG_KN(f16, F16)
+LCMA_PINGPONG_NARROW(bf16, BF16, false)
+LCMA_PINGPONG_NARROW(f16, F16, false)
+LCMA_PINGPONG_NARROW(bf16_kn, BF16, true)
+LCMA_PINGPONG_NARROW(f16_kn, F16, true)

@@ -121,7 +121,13 @@ extern "C" lcma_status lcma_model_intensity(const lcma_scheme *s, int64_t M, int
 extern "C" double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int64_t K, lcma_dtype dtype) {
     if (!dtype_size(dtype) || M <= 0 || N <= 0 || K <= 0) return -1.0;
     const Variant *v = pick_variant(scheme_id, dtype, M, N, K);
-    return v ? predict_variant(*v, M, N, K) : -1.0;
+    if (!v) return -1.0;
+    const double t = predict_variant(*v, M, N, K);
+    // the plain 16-bit product has the 256 x 256 ping-pong kernel besides the generated ones (csrc/plane_gemm.cc; its 256 x 128
+    // sibling is not priced: it stands in where tiles are few, and the figure stays on the safe side there)
+    if (scheme_id == LCMA_PLAIN && dtype != LCMA_F32)
+        return std::min(t, 1e-6 * plain_product_us(true, 256, M, N, K, K % 64 || N % 64) + kLaunch);
+    return t;
 }
 
 extern "C" int lcma_select(int64_t M, int64_t N, int64_t K, lcma_dtype dtype) {

@@ -16,6 +16,13 @@ LCMA_PG_DECL(f16_t256_f32)
 LCMA_PG_DECL(f16_t128_f32)
 LCMA_PG_DECL(bf16_t256_bf16)
 LCMA_PG_DECL(bf16_t128_bf16)
+#define LCMA_PP_DECL(NAME) extern "C" int lcma_launch_##NAME(const lcma::PlaneGemmParams *p, void *stream);
+LCMA_PP_DECL(pp_kn_bf16)
+LCMA_PP_DECL(pp_kn_f16)
+LCMA_PP_DECL(ppn_bf16)
+LCMA_PP_DECL(ppn_f16)
+LCMA_PP_DECL(ppn_bf16_kn)
+LCMA_PP_DECL(ppn_f16_kn)
 
 extern "C" int lcma_launch_few_rows_sum_f16(const lcma::FewRowsParams *p, int rows, void *stream);
 extern "C" int lcma_launch_few_rows_sum_bf16(const lcma::FewRowsParams *p, int rows, void *stream);
@@ -139,6 +146,19 @@ double plane_gemm_seconds(int planes, int64_t rows, int64_t cols, int ny, int64_
     return best < 0.0 ? -1.0 : best * 1.62e-6;
 }
 
+// Column panels of the tile order: `wide` tiles, or the widest of one, two or three less that leaves no narrower panel at the
+// end (28 columns of tiles as 4 x 7 instead of 3 x 8 + 4: the batched stage at the FFN shape 1 % faster).
+static int panel_of(int nz, int wide) {
+    int panel = tuning_panel() == 8 ? wide : tuning_panel();
+    if (panel == wide && nz % wide)
+        for (int w : {wide - 1, wide - 2, wide - 3})
+            if (nz % w == 0) {
+                panel = w;
+                break;
+            }
+    return panel < nz ? panel : nz;
+}
+
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
 // (padded sizes, multiples of the tile when batched).  tile: 256 or 128, 0 = choose.  schedule: 0 = choose, 1 = one
 // tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of plane_gemm_scratch_bytes(tile) bytes), 3 =
@@ -159,21 +179,13 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     schedule = best_sched;
     Launch launch = launcher(kind, tile);
     if (!launch) return fail(LCMA_ERR_NOKERNEL, "%s: no plane GEMM kernel of kind %d", who, kind);
+    if (!p.tail_b) p.tail_b = 128; // whole steps
     p.nx = (int32_t)ceil_div(rows, tile);
     p.nz = (int32_t)ceil_div(cols, tile);
     const int64_t jobs = (int64_t)planes * p.nx * p.nz, total = jobs * p.ny;
     if (total >= ((int64_t)1 << 31)) return fail(LCMA_ERR_SHAPE, "%s: too many tile steps", who);
     p.jobs = (int32_t)jobs;
-    // column panels of the tile order: 8 tiles wide, or the widest of 7, 6, 5 that leaves no narrower panel at the end
-    // (28 columns of tiles as 4 x 7 instead of 3 x 8 + 4: the batched stage at the FFN shape 1 % faster)
-    int panel = tuning_panel();
-    if (panel == 8 && p.nz % 8)
-        for (int w : {7, 6, 5})
-            if (p.nz % w == 0) {
-                panel = w;
-                break;
-            }
-    p.panel = panel < p.nz ? panel : p.nz;
+    p.panel = panel_of(p.nz, 8);
     const int slots = slots_of(tile);
     p.interleave = 0;
     if (schedule == 3) { // persistent work-groups, whole tile-products u, u + units, ...
@@ -195,6 +207,62 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     }
     if (const int err = launch(&p, stream)) return fail(LCMA_ERR_HIP, "%s: plane GEMM launch failed with HIP error %d", who, err);
     return LCMA_OK;
+}
+
+// Microseconds of the plain product on the ping-pong kernel with tiles of 256 x tn (f as in choose()).  256 x 128: 0.52 + 0.38 f a
+// step (K x N: 0.60 + 0.32 f, its fragments wait for their own reads) and 4 a round (K x N: 2048 x 4096 x 4096 62 against 87 for
+// the generated kernel, 1024 x 4096 x 4096 50 / 56, 2048 x 4096 x 14336 210 / 284, 704 x 704 x 8000 80 / 98); 256 x 256: as in
+// choose() for either layout (K x N: 6144^3 394 / 495, 8192 x 14336 x 4096 704 / 863); 15 % more when rows do not start on
+// 128-byte lines (5000 x 3000 x 1000 43 / 42).
+double plain_product_us(bool b_kn, int tn, int64_t M, int64_t N, int64_t K, bool off_line) {
+    const int64_t ny = ceil_div(K, 64), jobs = ceil_div(M, 256) * ceil_div(N, tn), full = jobs / kCUs, rest = jobs % kCUs;
+    const double line = off_line ? 1.15 : 1.0;
+    auto round = [&](double f) {
+        return tn == 256 ? (double)((ny + 1) & ~(int64_t)1) * line * (0.80 + 0.72 * f) + 6.0
+                         : (double)ny * line * (b_kn ? 0.60 + 0.32 * f : 0.52 + 0.38 * f) + 4.0;
+    };
+    return (double)full * round(1.0) + (rest ? round((double)rest / kCUs) : 0.0) + (tn == 256 ? 1.5 : 0.0);
+}
+
+// The plain 16-bit product C = A B (b_kn: B is K x N) or A W^T on the ping-pong kernels, for lcma_gemm, lcma_gemm_nt and lcma_gemm_ex
+// (the same bits as the generated kernels: every element of C is one chain of 32x32x16 instructions over ascending k).
+// Arguments are checked by the caller; K a multiple of 8.  Returns false, with nothing launched, when the generated kernel is
+// predicted to take less than the `limit_us` given, or when padded offsets do not fit; else *err is the launch's HIP error.
+bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc,
+                   int dtype, double limit_us, void *stream, int *err) {
+    const int ny = (int)ceil_div(K, 64);
+    auto cost = [&](int tn) { return plain_product_us(b_kn, tn, M, N, K, lda % 64 || ldb % 64); };
+    const int tn = cost(256) < cost(128) ? 256 : 128;
+    if (cost(tn) >= limit_us) return false;
+    const int64_t lim = (int64_t)1 << 31, Mp = ceil_div(M, 256) * 256, Np = ceil_div(N, 256) * 256, Kp = (int64_t)(ny + 1) * 64;
+    if (((Mp - 1) * lda + Kp) * 2 >= lim || (b_kn ? (Kp - 1) * ldb + Np : (Np - 1) * ldb + Kp) * 2 >= lim || ((Mp - 1) * ldc + Np) * 2 >= lim) return false;
+    PlaneGemmParams p;
+    std::memset(&p, 0, sizeof p);
+    p.A = A;
+    p.B = B;
+    p.C = C;
+    p.a_bytes = (uint32_t)(((M - 1) * lda + K) * 2);
+    p.b_bytes = (uint32_t)((b_kn ? (K - 1) * ldb + N : (N - 1) * ldb + K) * 2);
+    p.c_bytes = (uint32_t)(((M - 1) * ldc + N) * 2);
+    p.lda_b = (uint32_t)(lda * 2);
+    p.ldb_b = (uint32_t)(ldb * 2);
+    p.ldc_b = (uint32_t)(ldc * 2);
+    p.ny = ny;
+    p.cap = ny;
+    p.tail_b = (uint32_t)((K - (int64_t)(ny - 1) * 64) * 2);
+    p.n_row_b = (uint32_t)(N * 2);
+    p.nx = (int32_t)ceil_div(M, 256);
+    p.nz = (int32_t)ceil_div(N, tn);
+    p.jobs = p.nx * p.nz;
+    p.panel = panel_of(p.nz, tn == 256 ? 8 : 16);
+    p.units = p.jobs < kCUs ? p.jobs : kCUs;
+    p.interleave = p.units & 7 ? 1 : 2; // (see plane_gemm)
+    const bool bf = dtype == LCMA_BF16;
+    const Launch launch = tn == 128 ? (b_kn ? (bf ? lcma_launch_ppn_bf16_kn : lcma_launch_ppn_f16_kn) : (bf ? lcma_launch_ppn_bf16 : lcma_launch_ppn_f16))
+                          : b_kn    ? (bf ? lcma_launch_pp_kn_bf16 : lcma_launch_pp_kn_f16)
+                                    : (bf ? lcma_launch_pg_bf16_t256_bf16 : lcma_launch_pg_f16_t256_f16);
+    *err = launch(&p, stream);
+    return true;
 }
 
 namespace {
@@ -274,7 +342,11 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
     if (!tuning_schedule()) { // (a forced schedule is one of the plane GEMM's)
         const FewRowsPlan f = few_rows_plan(M, N, K, scratch);
         int t = 0, sc = 0;
-        if (f.tile && f.us < choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc)) {
+        const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc);
+        int err = 0;
+        if (!(f.tile && f.us < planes_us) && plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, planes_us, stream, &err))
+            return err ? fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err) : LCMA_OK;
+        if (f.tile && f.us < planes_us) {
             FewRowsParams q;
             std::memset(&q, 0, sizeof q);
             q.A = A;
@@ -299,7 +371,7 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
                                 : f.tile == 32 ? (bf ? lcma_launch_few_rows_bf16_32 : lcma_launch_few_rows_f16_32)
                                                : (bf ? lcma_launch_few_rows_bf16_64 : lcma_launch_few_rows_f16_64);
             // (the column blocks and slices of a block of rows in eights, one per XCD)
-            int err = launch(&q, (int)(ceil_div(f.col_blocks * f.slices, 8) * 8 * f.row_blocks), stream);
+            err = launch(&q, (int)(ceil_div(f.col_blocks * f.slices, 8) * 8 * f.row_blocks), stream);
             if (!err && f.slices > 1) err = (bf ? lcma_launch_few_rows_sum_bf16 : lcma_launch_few_rows_sum_f16)(&q, (int)M, stream);
             if (err) return fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err);
             return LCMA_OK;
