@@ -376,9 +376,10 @@ lcma_status prepare_b_planes(bool transposed, int64_t N, int64_t K, const void *
         p.b_brow = (uint32_t)(bn * ldb * es); // from block row j of W to j + 1
         p.b_bcol = (uint32_t)(bk * es);       // from block column l of W to l + 1
         p.n_row_b = (uint32_t)(K * es);       // row length of W
-        gx = (int)(bn / 16);
-        gy = (int)((bk * es + 255) / 256);
-        if (gx > 65535) return fail(LCMA_ERR_SHAPE, "%s: N is too large", who); // (the rows are the y dimension of the grid)
+        if (bn / 16 > 65535) return fail(LCMA_ERR_SHAPE, "%s: N is too large", who); // (the rows are the y dimension of the grid)
+        p.lane_shift = lane_shift_of(bk * es / 16, bn);
+        gx = row_groups(bn, p.lane_shift);
+        gy = vector_groups(bk * es / 16, p.lane_shift);
         err = (own ? stage->launch_comb_bt : pk->launch_t)(&p, gx, gy, stream);
     } else {
         p.b_brow = (uint32_t)(bk * ldb * es);

@@ -95,6 +95,21 @@ lcma_status prepare_b_planes(bool transposed, int64_t N, int64_t K, const void *
 
 int dtype_size(int dtype); // bytes, or 0
 
+// The kernels that stream whole matrices (Combine A, Combine B of N x K weights, Combine H, the FP8 quantisations) give 16 bytes of
+// a row to a thread; a work-group of 256 covers 2^s vectors of 256 / 2^s rows.  A whole wave along a row (s = 6, 1 KB in one
+// piece) where the rows are a whole number of them or nearly so, else half or a quarter: Combine H at the FFN shape 120.7
+// us with a quarter wave (5.35 TB/s), 112 with a whole one, 101 with streamed loads besides (6.40 TB/s, a device copy 6.3).
+inline int lane_shift_of(int64_t vectors, int64_t rows) {
+    for (int s : {6, 5}) {
+        const int64_t lanes = (int64_t)1 << s, idle = (vectors + lanes - 1) / lanes * lanes - vectors;
+        if (idle * 4 <= vectors && ((rows << s) + 255) / 256 <= 65535) return s; // (the rows are the y dimension of the grid)
+    }
+    return 4;
+}
+// work-groups along the rows and along a row
+inline int row_groups(int64_t rows, int s) { return (int)(((rows << s) + 255) / 256); }
+inline int vector_groups(int64_t vectors, int s) { return (int)((vectors + (1 << s) - 1) >> s); }
+
 // Measurement aids set by lcma_set_tuning (initial values: the LCMA_* environment variables, read once).
 const Variant *forced_variant();
 const Variant *forced_unfused_variant();

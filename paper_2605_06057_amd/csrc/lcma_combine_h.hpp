@@ -19,6 +19,10 @@
 
 namespace lcma {
 
+// Cache policy of the loads of the planes: 16-bit planes are read streamed as well (8192 x 14336, <2,2,2;7>: 109 -> 100 us with a
+// whole wave along a row; <4,4,4;49> 164 -> 155), fp32 planes are not (25 planes of 2048 x 2048: 114 -> 153 us).
+template <int ES> constexpr int kPlaneLoad = ES == 2 ? kStreamed : 0;
+
 // CH (generated): NP planes, NC = m*n outputs with c_i(o), c_j(o); comb(in, o) = Eq. 6 for output o on floats.
 // HT: element type of the planes; IN: storage type of C (same element size).
 template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombHParams &p) {
@@ -26,18 +30,19 @@ template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombH
     static_assert(HT::ES == ES || (HT::ES == 4 && ES == 2), "planes in the element size of C, or fp32 planes for 16-bit C");
     const auto rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.H), 0, (int)p.h_bytes, 0x00020000);
     const auto rc = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)p.c_bytes, 0x00020000);
-    // 256 threads: 16 rows x 16 vectors (256 bytes of a row of C); work-groups that start together cover consecutive pieces
+    // 256 threads: 2^lane_shift vectors of 256 / 2^lane_shift rows; work-groups that start together cover consecutive pieces
     // of the same rows (4 to 24 % faster than consecutive rows of the same piece)
-    const uint32_t row = blockIdx.y * 16 + threadIdx.x / 16;
-    const uint32_t colb = (blockIdx.x * 16 + threadIdx.x % 16) * 16; // byte column inside a block of C
-    if (colb * HV >= p.h_ld_b) return;
+    const uint32_t sh = (uint32_t)p.lane_shift;
+    const uint32_t row = blockIdx.y * (256 >> sh) + (threadIdx.x >> sh);
+    const uint32_t colb = ((blockIdx.x << sh) + (threadIdx.x & ((1u << sh) - 1))) * 16; // byte column inside a block of C
+    if (colb * HV >= p.h_ld_b || row * p.h_ld_b >= p.h_plane_b) return;
     // the planes stay in registers as loaded and are widened where a sum uses them (see forget_derived)
     u32x4 h[HV][CH::NP];
 #pragma unroll
     for (int r = 0; r < CH::NP; ++r)
 #pragma unroll
         for (int q = 0; q < HV; ++q)
-            h[q][r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + colb * HV + q * 16), (int)(r * p.h_plane_b), 0);
+            h[q][r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + colb * HV + q * 16), (int)(r * p.h_plane_b), kPlaneLoad<HT::ES>);
     constexpr int HPV = 16 / HT::ES; // elements of a plane per 16-byte vector
     for_each_const<CH::NC>([&](auto oc_) {
         constexpr int o = decltype(oc_)::value;

@@ -46,6 +46,7 @@ struct PrepParams {
     uint32_t bt_plane_b;        // plane stride in bytes = (N/n) * (K/k) * ES
     int32_t bk, bn;             // K/k, padded N/n
     uint32_t n_row_b;           // N * element size of B: columns at or beyond it are read as 0
+    int32_t lane_shift = 4;     // k-contiguous input: 2^lane_shift neighbouring threads along a row (host_common.h, lane_shift_of)
 };
 
 // Argument block of the stand-alone Combine-H kernels (stage 4 of Algorithm 1).
@@ -58,6 +59,7 @@ struct CombHParams {
     uint32_t ldc_b;            // leading dimension of C in bytes
     uint32_t c_brow, c_bcol;   // byte step from block C_{i,j} to C_{i+1,j} / C_{i,j+1}
     uint32_t n_row_b;          // N * element size: columns at or beyond it are never written
+    int32_t lane_shift;        // 2^lane_shift neighbouring threads along a row
 };
 
 // Argument blocks of the FP8 kernels (E4M3 codes, one E8M0 scale byte per 1 x 128 block along K).
@@ -109,6 +111,7 @@ struct Fp8QuantParams {
     uint32_t q_plane, s_plane; // byte step between planes
     uint32_t k_row_b;          // K * 2: columns of X at or beyond it read as zero
     int32_t rows;              // rows of a plane (padded); rows past the extent of X read as zero
+    int32_t lane_shift;        // 2^lane_shift neighbouring threads along a row
 };
 
 } // namespace lcma

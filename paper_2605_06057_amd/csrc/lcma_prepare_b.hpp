@@ -179,11 +179,13 @@ template <class IN, class CT, class CH> LCMA_DEV void prepare_bt_tile(const Prep
     static_assert(CT::ES == ES, "the output keeps the element size");
     const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.B), 0, (int)p.b_bytes, 0x00020000);
     const auto rt = __builtin_amdgcn_make_buffer_rsrc(p.Bt, 0, (int)p.bt_bytes, 0x00020000);
-    // 256 threads: 16 rows (n) x 16 vectors (k) of every block; work-groups that start together cover consecutive
-    // pieces of the same rows (whole rows of the planes are written at a time: 19 % faster at 4096^3 than row-major order)
-    const int rn = blockIdx.y * 16 + (int)threadIdx.x / 16;
-    const uint32_t kb = (uint32_t)(blockIdx.x * 16 + (int)threadIdx.x % 16) * 16; // byte column inside a block
-    if (kb >= p.bt_ld_b) return; // past the padded K/k (whole work-group columns only when K/k < 256 B)
+    // 256 threads: 2^lane_shift vectors (k) of 256 / 2^lane_shift rows (n) of every block; work-groups that start together cover
+    // consecutive pieces of the same rows (whole rows of the planes are written at a time: 19 % faster at 4096^3 than row-major
+    // order)
+    const int tid = (int)threadIdx.x, sh = p.lane_shift;
+    const int rn = (int)blockIdx.y * (256 >> sh) + (tid >> sh);
+    const uint32_t kb = ((blockIdx.x << sh) + (uint32_t)(tid & ((1 << sh) - 1))) * 16; // byte column inside a block
+    if (kb >= p.bt_ld_b || rn >= p.bn) return; // past the padded K/k or N/n
     u32x4 in[CH::NB];
 #pragma unroll
     for (int t = 0; t < CH::NB; ++t) {

@@ -269,8 +269,9 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
         p.bk = (int32_t)g.bk;
         p.bn = (int32_t)g.bm;
         p.n_row_b = (uint32_t)(K * es);
-        const int64_t gy = (g.bk * es + 255) / 256;
-        if (const int err = sk->launch_comb_a(&p, (int)(g.bm / 16), (int)gy, stream))
+        // (with <4,4,4;49>'s 49 planes a quarter wave along a row is the faster form: 42.7 against 47.1 us for 8192 x 4096)
+        p.lane_shift = R > 32 ? 4 : lane_shift_of(g.bk * es / 16, g.bm);
+        if (const int err = sk->launch_comb_a(&p, row_groups(g.bm, p.lane_shift), vector_groups(g.bk * es / 16, p.lane_shift), stream))
             return fail(LCMA_ERR_HIP, "%s: Combine-A launch failed with HIP error %d", who, err);
     }
     // stage 2: Combine B (Eq. 4), unless the planes of an earlier call are still valid (static weights)
@@ -346,8 +347,9 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
         h.c_brow = (uint32_t)(g.bm * ldc * es);
         h.c_bcol = (uint32_t)(g.bn * es);
         h.n_row_b = (uint32_t)(N * es);
-        const int64_t gy = (g.bn * es + 255) / 256;
-        if (const int err = (h_es != es ? sk->launch_comb_h32 : sk->launch_comb_h)(&h, (int)(g.bm / 16), (int)gy, stream))
+        h.lane_shift = lane_shift_of(g.bn * es / 16, g.bm);
+        if (const int err = (h_es != es ? sk->launch_comb_h32 : sk->launch_comb_h)(&h, row_groups(g.bm, h.lane_shift),
+                                                                                   vector_groups(g.bn * es / 16, h.lane_shift), stream))
             return fail(LCMA_ERR_HIP, "%s: Combine-H launch failed with HIP error %d", who, err);
     } else {
         // stages 3 and 4 in one kernel: group by group, W applied to the fp32 accumulators
