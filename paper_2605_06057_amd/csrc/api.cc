@@ -55,10 +55,14 @@ const Variant *pick_variant(int scheme_id, int dtype, int64_t M, int64_t N, int6
 // 857 x 1048 x 808 55.9 / 23.2; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
 // K x N kernels for any form of B, so that both layouts make the same choice and give the same bits, and prepared operands
 // (whose planes carry the same roundings) the same precision.
+// The 16-bit ones (csrc/lcma_direct16.hpp): 16 x 64 tiles, 4.0 us a step of 64 for the four waves (2.8 to 3.5 for K x N, 4.8 for N x K)
+// and 2.5 a round; the staged kernel takes 0.90 us (fp16 0.72) a step of 32 however few its work-groups are.
 static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K) {
     const Variant *staged = pick_variant(v->scheme_id, v->dtype, M, N, K, 0, 0), *best = v;
     if (!staged) return v;
     double best_us = 0.9 * 1e6 * predict_variant(*staged, M, N, K);
+    // (16 bit: the published prediction knows no latency; a step of 32 takes this long however few work-groups there are)
+    if (v->dtype != LCMA_F32) best_us = std::max(best_us, 3.0 + (v->dtype == LCMA_BF16 ? 0.90 : 0.72) * (double)round_up(K, 32 * staged->k) / (32.0 * staged->k));
     for (int i = 0; i < kVariantCount; ++i) {
         const Variant &d = kVariants[i];
         if (!d.direct || d.scheme_id != v->scheme_id || d.dtype != v->dtype || d.b_nk != v->b_nk || d.prepared != v->prepared ||
@@ -66,7 +70,8 @@ static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_
             continue;
         const int64_t bm = round_up(M, (int64_t)d.m * d.TM) / d.m, bn = round_up(N, (int64_t)d.n * d.TN) / d.n;
         const int64_t bk = round_up(K, (int64_t)d.k * d.TK) / d.k, groups = (bm / d.TM) * (bn / d.TN);
-        const double us = 3.0 + (double)((groups + 255) / 256) * ((d.TM == 16 ? 0.0145 : 0.041) * (double)bk + 1.0);
+        const double rounds = (double)((groups + 255) / 256), steps = (double)((bk / d.TK + d.direct - 1) / d.direct);
+        const double us = 3.0 + (v->dtype == LCMA_F32 ? rounds * ((d.TM == 16 ? 0.0145 : 0.041) * (double)bk + 1.0) : rounds * (4.0 * steps + 2.5));
         if (us < best_us) {
             best = &d;
             best_us = us;

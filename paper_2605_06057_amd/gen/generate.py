@@ -186,7 +186,7 @@ def plan(s: Scheme, v: Variant):
     """On-chip resource planning: (accumulator registers per lane, LDS bytes, peak live C tiles)."""
     es = 4 if v.dtype == "f32" else 2
     if v.ks:  # every product's accumulators; the partial tiles of C of all waves, rows padded by 16 bytes
-        assert v.dtype == "f32" and v.chunk >= s.R
+        assert v.chunk >= s.R and (v.dtype == "f32" or (v.TM, v.TN, v.pb) == (16, 64, 0))
         return s.R * v.TM * v.TN // 64, v.ks * s.m * s.n * v.TM * (v.TN + 4) * 4, 0, s.R, 0, 0
     tile_regs = (v.TM // v.wgm // 32) * (v.TN // v.wgn // 32) * 16
     chunks = chunks_of(s, v)
@@ -301,7 +301,7 @@ def emit_kernel(s: Scheme, v: Variant) -> str:
     w(f"// GENERATED by gen/generate.py - do not edit.  Scheme {s.name} <{s.m},{s.k},{s.n};{s.R}>, dtype {v.dtype},")
     w(f"// tile {v.TM}x{v.TN}x{v.TK}, {len(chunks)} chunk(s) of up to {nslot} products; planned accumulator registers")
     w(f"// per lane {regs}, LDS {lds} bytes, peak live C tiles {live_c}.")
-    w('#include "lcma_direct.hpp"' if v.ks else '#include "lcma_device.hpp"')
+    w(f'#include "lcma_direct{"" if v.dtype == "f32" else "16"}.hpp"' if v.ks else '#include "lcma_device.hpp"')
     w("namespace {")
     w("using namespace lcma;")
     if not v.ks:
@@ -416,7 +416,10 @@ def emit_direct_tail(s: Scheme, v: Variant) -> list[str]:
     w("        }")
     w("    }")
     w("};")
-    w(f"using D = Direct<{v.TM // 16}, {v.TN // 16}, {v.ks}, {'true' if v.tb else 'false'}, {'true' if v.pb else 'false'}, Chunk0, Blocks>;")
+    if v.dtype != "f32":
+        w(f"using D = Direct16<{CPP_TYPES[v.dtype][0]}, {v.ks}, {'true' if v.tb else 'false'}, Chunk0, Blocks>;")
+    else:
+        w(f"using D = Direct<{v.TM // 16}, {v.TN // 16}, {v.ks}, {'true' if v.tb else 'false'}, {'true' if v.pb else 'false'}, Chunk0, Blocks>;")
     w("} // namespace")
     w("")
     w(f'extern "C" __global__ __launch_bounds__({64 * v.ks}, {max(1, v.ks // 4)}) void lcma_k_{v.name}(const lcma::Params p) {{')
@@ -844,6 +847,7 @@ def manifest(schemes: dict[str, Scheme] | None = None) -> list[Variant]:
     for name in ("strassen", "winograd"):
         if name in schemes:
             V += [Variant(name, "f32", t, t, 16, chunk=7, ks=8, tb=tb, pb=pb, rank=96) for t in (16, 32) for tb, pb in ((0, 0), (1, 0), (0, 1))]
+    V += [Variant("strassen", dt, 16, 64, 64, chunk=7, ks=4, tb=tb, rank=96) for dt in ("bf16", "f16") for tb in (0, 1)]
     # Every kernel that lcma_gemm can pick for the paper's schemes also exists for B given as the N x K
     # weight matrix ("t"): its B tiles are staged like A's, with 16-byte loads and no transposition.
     from dataclasses import replace

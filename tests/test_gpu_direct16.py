@@ -1,0 +1,42 @@
+"""The direct kernels for 16-bit products with few tiles (csrc/lcma_direct16.hpp): the same bits for both layouts of B, at one
+element, a step that ends inside a lane's 32 bytes of K, fewer steps than waves, one more than a round of waves, edges of the
+16 x 64 tile, and where lcma_gemm chooses them; alpha and beta applied once.  (Exactness on integers, ragged edges and guard
+rows: every variant, tests/test_gpu_parity.py.)"""
+import pytest
+
+import lcma_inputs as inp
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(1, 8, 8), (33, 136, 72), (64, 264, 520), (239, 376, 2056), (130, 1000, 648)], ids=lambda s: "x".join(map(str, s)))
+def test_layouts_and_scaling(shape, dtype):
+    import torch
+    import gpu_util as G
+    from paper_2605_06057_amd import binding as B
+    M, N, K = shape
+    s = B.lcma_scheme_load("builtin:strassen")
+    As, Bs = inp.matrices("uniform", "uniform", M, N, K, dtype, 23)
+    a, b = G.to_device(As, dtype), G.to_device(Bs, dtype)
+    w = b.t().contiguous()
+    c, ct, d, e = (G.empty_like_c(M, N, dtype, fill=float("nan")) for _ in range(4))
+    name = f"strassen_{dtype}_d16x64k4"
+    print(f"{name} {M}x{N}x{K}", flush=True)
+    B.lcma_gemm_variant(name, a, b, c)
+    B.lcma_gemm_variant(name + "t", a, w, ct, True)
+    B.lcma_gemm(a, b, d, s)
+    B.lcma_gemm_nt(a, w, e, s)
+    torch.cuda.synchronize()
+    ref = oracle.gemm(inp.widen(As, dtype), inp.widen(Bs, dtype))
+    assert oracle.rel_frobenius(G.to_host_f64(c, dtype), ref) <= 2e-2   # the bound of the 16-bit products
+    assert torch.equal(c, ct) and torch.equal(d, e)
+    old = (torch.arange(M * N, device="cuda", dtype=torch.float32).view(M, N) / (M * N)).to(c.dtype)
+    y = old.clone()
+    B.lcma_gemm_ex(0.5, -2.0, a, b, y, s, b_nk=False)
+    torch.cuda.synchronize()
+    # C = d rounded once (half an ulp of d, u = 2^-9 or 2^-12 of its magnitude, halved by alpha), then the sum rounded once
+    u = 2.0 ** (-9 if dtype == "bf16" else -12)
+    want = 0.5 * d.double() - 2.0 * old.double()
+    assert ((y.double() - want).abs() <= 2 * u * (d.double().abs() + want.abs()) + 1e-7).all().item()
