@@ -273,7 +273,10 @@ template <class KIND, class OUT, bool KN = false> struct PingPongGemm {
         load_step(A00, A10, B00, B10, a_cur, b_cur, ny == 1);
         load_step(A01, A11, B01, B11, ny > 1 ? a_cur + ROW : a_none, ny > 1 ? b_cur + b_step : b_none, ny == 2);
         memory_slot_end();
+        // A slot of its own, for all waves: the first load of the first step, sent by group 0, goes to the place that both groups read
+        // here.  (In the steps the slot of either group that reads half 0 of B has ended when its place is loaded anew.)
         read_b(s, B00, fb0);
+        memory_slot_end();
         if (s.wm) slot_end(); // the second group runs one slot behind the first
         // One step out of stage (A0, A1, B0, B1); nextB0: half 0 of B of the next step; a, b: the operands two steps on, which go
         // into this stage (last: they are those of a last step).  The slot of the last multiplication is ended by the caller.
