@@ -48,6 +48,25 @@ const Variant *pick_variant(int scheme_id, int dtype, int64_t M, int64_t N, int6
     return best;
 }
 
+// The matrices padded to whole tiles of a kernel: blocks are cut from these, the extents stay the true ones.
+struct Padded {
+    int64_t M, N, K;
+};
+static Padded padded(const Variant &v, int64_t M, int64_t N, int64_t K) {
+    const int64_t tn = v.prepared && v.TN < 64 ? 64 : v.TN; // (the planes of lcma_prepare_b hold whole 64 rows, whatever the tile)
+    return {round_up(M, (int64_t)v.m * v.TM), round_up(N, (int64_t)v.n * tn), round_up(K, (int64_t)v.k * v.TK)};
+}
+// Offsets of padded rows and columns are formed in 32 bits before the range check drops them: every padded matrix spans less than
+// 2 GiB (prepared B: all planes together).
+static bool spans_fit(const Variant &v, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
+    const int64_t lim = (int64_t)1 << 31, es = dtype_size(v.dtype);
+    const Padded q = padded(v, M, N, K);
+    if (v.prepared) ldb = N;
+    const int64_t b_span = v.b_nk ? (q.N - 1) * ldb + q.K : (q.K - 1) * ldb + q.N;
+    return ((q.M - 1) * lda + q.K) * es < lim && b_span * es < lim && ((q.M - 1) * ldc + q.N) * es < lim &&
+           (!v.prepared || v.products * (q.N / v.n) * (q.K / v.k) * es < lim);
+}
+
 // The direct kernel (csrc/lcma_direct.hpp) to run in place of the staged variant `v` that pick_variant chose, or `v` itself.
 // The direct kernels are bound by the lines a CU can ask for: about 256 work-groups of eight waves run at a time, and one takes
 // 14.5 ns per element of K/k on the 16 x 16 tile and 41 ns on the 32 x 32 one (K = 1500 to 3000), 1 us besides, 3 us for
@@ -57,7 +76,8 @@ const Variant *pick_variant(int scheme_id, int dtype, int64_t M, int64_t N, int6
 // (whose planes carry the same roundings) the same precision.
 // The 16-bit ones (csrc/lcma_direct16.hpp): 16 x 64 tiles, 4.0 us a step of 64 for the four waves (2.8 to 3.5 for K x N, 4.8 for N x K)
 // and 2.5 a round; the staged kernel takes 0.90 us (fp16 0.72) a step of 32 however few its work-groups are.
-static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K) {
+// A direct kernel pads K further than the staged one in 16 bit: where its spans do not fit, the staged one runs.
+static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const Variant *staged = pick_variant(v->scheme_id, v->dtype, M, N, K, 0, 0), *best = v;
     if (!staged) return v;
     double best_us = 0.9 * 1e6 * predict_variant(*staged, M, N, K);
@@ -66,8 +86,10 @@ static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_
     for (int i = 0; i < kVariantCount; ++i) {
         const Variant &d = kVariants[i];
         if (!d.direct || d.scheme_id != v->scheme_id || d.dtype != v->dtype || d.b_nk != v->b_nk || d.prepared != v->prepared ||
-            !fits(d, M, N, K))
+            !fits(d, M, N, K) || !spans_fit(d, M, N, K, lda, ldb, ldc))
             continue;
+        const Padded q = padded(d, M, N, K); // (either layout of a dense B, for the same choice)
+        if (std::max((q.K - 1) * N + q.N, (q.N - 1) * K + q.K) * dtype_size(d.dtype) >= (int64_t)1 << 31) continue;
         const int64_t bm = round_up(M, (int64_t)d.m * d.TM) / d.m, bn = round_up(N, (int64_t)d.n * d.TN) / d.n;
         const int64_t bk = round_up(K, (int64_t)d.k * d.TK) / d.k, groups = (bm / d.TM) * (bn / d.TN);
         const double rounds = (double)((groups + 255) / 256), steps = (double)((bk / d.TK + d.direct - 1) / d.direct);
@@ -161,22 +183,14 @@ static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const 
     if (!fits(v, M, N, K))
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: N = %lld and K = %lld must be multiples of %d (16 bytes of elements)",
                     (long long)N, (long long)K, 16 / es);
-    // blocks are cut from the matrices padded to whole tiles; the extents stay the true ones
-    // (the planes of lcma_prepare_b hold whole 64 rows, whatever the tile)
-    const int64_t tn = v.prepared && v.TN < 64 ? 64 : v.TN;
-    const int64_t Mp = round_up(M, (int64_t)v.m * v.TM), Np = round_up(N, (int64_t)v.n * tn),
-                  Kp = round_up(K, (int64_t)v.k * v.TK);
-    const int64_t bm = Mp / v.m, bn = Np / v.n, bk = Kp / v.k;
+    const Padded q = padded(v, M, N, K);
+    const int64_t bm = q.M / v.m, bn = q.N / v.n, bk = q.K / v.k;
     const int64_t a_bytes = ((M - 1) * lda + K) * es,
                   b_bytes = v.prepared ? (int64_t)v.products * bn * bk * es
                             : v.b_nk   ? ((N - 1) * ldb + K) * es
                                        : ((K - 1) * ldb + N) * es,
                   c_bytes = ((M - 1) * ldc + N) * es;
-    const int64_t lim = (int64_t)1 << 31;
-    // offsets of padded rows and columns are formed in 32 bits before the range check drops them
-    const int64_t b_span = v.b_nk ? (Np - 1) * ldb + Kp : (Kp - 1) * ldb + Np;
-    if (((Mp - 1) * lda + Kp) * es >= lim || b_span * es >= lim || ((Mp - 1) * ldc + Np) * es >= lim ||
-        b_bytes >= lim)
+    if (!spans_fit(v, M, N, K, lda, ldb, ldc))
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: a matrix spans 2 GiB or more");
     if (overlap(C, c_bytes, A, a_bytes) || overlap(C, c_bytes, B, b_bytes))
         return fail(LCMA_ERR_ARG, "lcma_gemm: C overlaps A or B");
@@ -223,7 +237,7 @@ static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const 
         p.k_tail_b = (uint32_t)(whole * es);
     }
     const int64_t grid = (int64_t)p.nx * p.nz;
-    if (grid >= lim) return fail(LCMA_ERR_SHAPE, "lcma_gemm: too many tiles");
+    if (grid >= (int64_t)1 << 31) return fail(LCMA_ERR_SHAPE, "lcma_gemm: too many tiles");
     const int panel = tuning_panel();
     p.panel = panel < p.nz ? panel : p.nz;
     const int err = v.launch(&p, (int)grid, stream);
@@ -261,7 +275,7 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
         if (v && id == LCMA_PLAIN && dtype != LCMA_F32 && alpha == 1.f && beta == 0.f && K > 0)
             plain_us = std::max(1e6 * predict_variant(*v, M, N, K),
                                 2.5 + ((M + 63) / 64 * ((N + 63) / 64) < 100 ? (b_nk ? 0.14 : 0.27) : (b_nk ? 0.22 : 0.36)) * (double)K / v->TK);
-        if (v) v = pick_direct(v, M, N, K);
+        if (v) v = pick_direct(v, M, N, K, lda, ldb, ldc);
     }
     if (!v) {
         bool any = false;
@@ -428,7 +442,7 @@ extern "C" lcma_status lcma_gemm_prepared(int64_t M, int64_t N, int64_t K, const
     if (v && (v->scheme_id != id || v->dtype != (int)dtype || !v->prepared)) v = nullptr;
     if (!v) {
         v = pick_variant(id, dtype, M, N, K, 1);
-        if (v) v = pick_direct(v, M, N, K);
+        if (v) v = pick_direct(v, M, N, K, lda, N, ldc);
     }
     if (!v) {
         bool any = false;
