@@ -74,8 +74,10 @@ static bool spans_fit(const Variant &v, int64_t M, int64_t N, int64_t K, int64_t
 // 857 x 1048 x 808 55.9 / 23.2; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
 // K x N kernels for any form of B, so that both layouts make the same choice and give the same bits, and prepared operands
 // (whose planes carry the same roundings) the same precision.
-// The 16-bit ones (csrc/lcma_direct16.hpp): 16 x 64 tiles, 4.0 us a step of 64 for the four waves (2.8 to 3.5 for K x N, 4.8 for N x K)
-// and 2.5 a round; the staged kernel takes 0.90 us (fp16 0.72) a step of 32 however few its work-groups are.
+// The 16-bit ones (csrc/lcma_direct16.hpp): 16 x 64 tiles, 4.0 us a step of 64 for the four waves (measured 2.6 to 4.2 for K x N, 2.9 to
+// 4.6 for N x K) and 2.5 a round; the staged kernel takes 0.90 us (fp16 0.72; N x K 0.72, 0.55) a step of 32 however few its
+// work-groups are.  Both types and layouts at 360 shapes, M 16 to 2048, K 64 to 9024: where this chooses the direct kernel it
+// is nowhere the slower one, least of all with N x K fp16 (1024^3 15.9 against 15.6, most others a tenth or more).
 // A direct kernel pads K further than the staged one in 16 bit: where its spans do not fit, the staged one runs.
 static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const Variant *staged = pick_variant(v->scheme_id, v->dtype, M, N, K, 0, 0), *best = v;

@@ -9,11 +9,13 @@
 // Tile and step: a lane's 16 elements of a row are the two halves of one 32-byte piece, so that both fragments of a step take whole
 // 128-byte lines of A (and of W); 64 columns are a whole line of B.  Which k meets which lane is the same for both layouts of
 // B, so both give the same bits.
-// What bounds it: a load instruction takes a CU about 26 clocks wherever the line comes from (48 bytes/ns), 2.8 to 3.5 us for a step of
-// four waves (W: 4.8).  Measured (bf16, us, staged 64 x 64 x 32 against this, K x N): 239 x 2176 x 9024 133 / 55, 473 x 344 x 2696
-// 44 / 21.6, 64 x 4096 x 4096 64 / 30, 256 x 2048 x 14336 208 / 82, 1024^3 20.5 / 13.3; with more than a round of 256 work-groups
-// the larger tiles win: 1000 x 1544 x 2056 36.8 / 40, 1536^3 28 / 44.  Two or four waves side by side along M, one step apart in
-// time, so that they ask for the same lines of B together: 156 and 304 at 239 x 2176 x 9024 (fewer waves along K, no line saved).
+// What bounds it: a load instruction takes a CU about 26 clocks wherever the line comes from (48 bytes/ns), 2.6 to 4.2 us for a step of
+// four waves, N x K 2.9 to 4.6 (16 bytes per lane of 16 rows: see SWAP).  Measured (us, staged 64 x 64 x 32 against this; three sets
+// of operands in turn, launches from a graph), K x N bf16, N x K bf16, N x K fp16: 239 x 2176 x 9024 133 / 63, 108 / 75, 85 / 66;
+// 473 x 344 x 2696 45 / 27, 41 / 28, 41 / 25; 64 x 4096 x 4096 65 / 33, 53 / 36, 41 / 33; 1024^3 21.1 / 15.4, 18.2 / 15.1, 15.9 /
+// 15.6.  With more than a round of 256 work-groups the larger tiles win: 1000 x 1544 x 2056 37 / 44, 33 / 46, 33 / 41.  Two or four
+// waves side by side along M, one step apart in time, so that they ask for the same lines of B together: 156 and 304 at 239 x 2176
+// x 9024 (fewer waves along K, no line saved).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -36,6 +38,15 @@ template <class IN, int KS, bool TB, class CH, class CHH> struct Direct16 {
     };
 
     static LCMA_DEV void run(const Params &p, LCMA_LDS char *lds) {
+        if (TB && p.ldb_b % 128 == 0) body<true>(p, lds);
+        else body<false>(p, lds);
+    }
+
+    // SWAP (rows of W that all start at the same place of a line): neighbouring lanes would ask for the same 16 bytes of two lines,
+    // which the L1 cache serves one after the other.  So the odd rows read the second half of their 32 bytes first, and the
+    // halves change places in registers (fp16, without / with: 101 x 456 x 1024 16.5 / 12.5 us, 57 x 3488 x 7168 69 / 54; rows
+    // that start anywhere else 25 / 26, where the exchange would only cost).
+    template <bool SWAP> static LCMA_DEV void body(const Params &p, LCMA_LDS char *lds) {
         const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         // an eighth of the tiles to every XCD (work-groups go to the eight in turn), cut along the longer side of C, so that the
         // longer operand is read by one XCD only
@@ -76,9 +87,11 @@ template <class IN, int KS, bool TB, class CH, class CHH> struct Direct16 {
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-                        for (int u = 0; u < 2; ++u)
-                            m.b[u][t][ni] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)(off + q * 32 + u * 16 < p.k_row_b ? b_row[ni] : p.b_bytes),
-                                                                                  (int)((uint32_t)CH::b_j(t) * p.b_bcol + off + u * 16), 0);
+                        for (int u = 0; u < 2; ++u) {
+                            const uint32_t at = off + (SWAP ? 0 : u * 16), half = !SWAP ? 0 : r & 1 ? 16 - u * 16 : u * 16;
+                            m.b[u][t][ni] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)(at + q * 32 + half < p.k_row_b ? b_row[ni] + half : p.b_bytes),
+                                                                                  (int)((uint32_t)CH::b_j(t) * p.b_bcol + at), 0);
+                        }
                 } else {
                     const uint32_t off = (uint32_t)CH::b_l(t) * p.b_brow + (uint32_t)y * 64 * p.ldb_b;
 #pragma unroll
@@ -108,7 +121,7 @@ template <class IN, int KS, bool TB, class CH, class CHH> struct Direct16 {
                     for (int t = 0; t < CH::NB; ++t) {
                         u32x4 raw;
                         if constexpr (TB) {
-                            raw = m.b[u][t][ni];
+                            raw = SWAP && r & 1 ? m.b[1 - u][t][ni] : m.b[u][t][ni];
                         } else {
 #pragma unroll
                             for (int e = 0; e < 4; ++e) // the low or high halves of two rows
