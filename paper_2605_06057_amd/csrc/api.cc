@@ -69,9 +69,11 @@ static bool spans_fit(const Variant &v, int64_t M, int64_t N, int64_t K, int64_t
 
 // The direct kernel (csrc/lcma_direct.hpp) to run in place of the staged variant `v` that pick_variant chose, or `v` itself.
 // The direct kernels are bound by the lines a CU can ask for: about 256 work-groups of eight waves run at a time, and one takes
-// 14.5 ns per element of K/k on the 16 x 16 tile and 41 ns on the 32 x 32 one (K = 1500 to 3000), 1 us besides, 3 us for
-// the launch.  Staged against direct, <2,2,2;7> fp32: 256^3 20.3 against 8.3 us, 512^3 35.6 / 8.3, 1024^3 66.5 / 26.1,
-// 857 x 1048 x 808 55.9 / 23.2; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
+// 14.5 ns per element of K/k on the 16 x 16 tile and 41 ns on the 32 x 32 one (K = 1500 to 3000), 0.8 and 2.5 us besides, 3 us
+// for the launch (with 1 us on either tile 848 x 1388 x 192 went to the larger one: 17.5 to 18.1 us against 17.4 staged and 12.6 to
+// 13.7 on the smaller).  Prepared operands have columns of whole 64 rows: 1614 x 572 x 128 is 260 work-groups, not 234, 13.7 us
+// against 12.9 staged and 9.0 on the smaller tile.  Staged against direct, <2,2,2;7> fp32: 256^3 20.4 against 4.5 us, 512^3 35.6 / 7.5, 1024^3 66.6 / 27.3,
+// 857 x 1048 x 808 55.4 / 23.9; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
 // K x N kernels for any form of B, so that both layouts make the same choice and give the same bits, and prepared operands
 // (whose planes carry the same roundings) the same precision.
 // The 16-bit ones (csrc/lcma_direct16.hpp): 16 x 64 tiles, 4.0 us a step of 64 for the four waves (measured 2.6 to 4.2 for K x N, 2.9 to
@@ -92,10 +94,9 @@ static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_
             continue;
         const Padded q = padded(d, M, N, K); // (either layout of a dense B, for the same choice)
         if (std::max((q.K - 1) * N + q.N, (q.N - 1) * K + q.K) * dtype_size(d.dtype) >= (int64_t)1 << 31) continue;
-        const int64_t bm = round_up(M, (int64_t)d.m * d.TM) / d.m, bn = round_up(N, (int64_t)d.n * d.TN) / d.n;
-        const int64_t bk = round_up(K, (int64_t)d.k * d.TK) / d.k, groups = (bm / d.TM) * (bn / d.TN);
+        const int64_t bk = q.K / d.k, groups = (q.M / d.m / d.TM) * (q.N / d.n / d.TN);
         const double rounds = (double)((groups + 255) / 256), steps = (double)((bk / d.TK + d.direct - 1) / d.direct);
-        const double us = 3.0 + (v->dtype == LCMA_F32 ? rounds * ((d.TM == 16 ? 0.0145 : 0.041) * (double)bk + 1.0) : rounds * (4.0 * steps + 2.5));
+        const double us = 3.0 + (v->dtype == LCMA_F32 ? rounds * (d.TM == 16 ? 0.0145 * (double)bk + 0.8 : 0.041 * (double)bk + 2.5) : rounds * (4.0 * steps + 2.5));
         if (us < best_us) {
             best = &d;
             best_us = us;

@@ -19,3 +19,14 @@ def test_a_direct_kernel_refuses_nothing(dtype, nk):
     assert D.gemm(M, N, K - (1 << 22), dtype, "strassen", nk)[1][0].startswith(f"strassen_{dtype}_d16x64k4")  # (its usual kernel)
     status, ran = D.gemm(M, N, K + 64, dtype, "strassen", nk)   # what was too large stays so
     assert (status, ran) == (5, [])
+
+
+# A round of 256 work-groups of the 32 x 32 tile and a few more, and a short K: the smaller tile is the faster one, the larger one slower
+# than the staged kernel (measured, csrc/api.cc); prepared operands have N padded to whole 64 columns of every block.
+@pytest.mark.parametrize("scheme", ["strassen", "winograd"])
+def test_small_fp32_products_take_the_smaller_tile(scheme):
+    M, N, K = 848, 1388, 192
+    for ran in (D.gemm(M, N, K, "f32", scheme), D.gemm(M, N, K, "f32", scheme, True), D.gemm_prepared(M, N, K, "f32", scheme)):
+        assert ran[0] == 0 and ran[1][0].startswith(f"{scheme}_f32_d16x16k8"), ran
+    assert D.gemm_prepared(1614, 572, 128, "f32", scheme) == (0, [f"{scheme}_f32_d16x16k8b"])
+    assert D.gemm(1614, 572, 128, "f32", scheme) == (0, [f"{scheme}_f32_d32x32k8"])   # (234 work-groups: one round)
