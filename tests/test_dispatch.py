@@ -30,3 +30,14 @@ def test_small_fp32_products_take_the_smaller_tile(scheme):
         assert ran[0] == 0 and ran[1][0].startswith(f"{scheme}_f32_d16x16k8"), ran
     assert D.gemm_prepared(1614, 572, 128, "f32", scheme) == (0, [f"{scheme}_f32_d16x16k8b"])
     assert D.gemm(1614, 572, 128, "f32", scheme) == (0, [f"{scheme}_f32_d32x32k8"])   # (234 work-groups: one round)
+
+
+def test_nt_ws_leaves_a_small_workspace_alone():
+    """include/lcma.h: with fewer bytes than lcma_split_group_scratch_bytes() the product is never split between work-groups."""
+    whole = D.lib().lcma_split_group_scratch_bytes()
+    for M, N, K in ((64, 4096, 4096), (129, 200, 14400), (512, 4096, 14336)):
+        split, none = D.gemm_nt_ws(M, N, K, "bf16", whole), D.gemm_nt_ws(M, N, K, "bf16", 0)
+        assert split[0] == 0 and split != none
+        for few in (4 << 20, whole // 2, whole - 256):
+            assert D.gemm_nt_ws(M, N, K, "bf16", few) == none
+        assert none[0] == 0 and len(none[1]) == 1 and ("slices=1" in none[1][0] or "few_rows" not in none[1][0]), none
