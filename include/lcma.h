@@ -295,7 +295,9 @@ lcma_status lcma_gemm_unfused_static(int level, int64_t M, int64_t N, int64_t K,
  * (lcma_gemm_unfused level 1) for a built-in scheme id, stage by stage (Combine A, Combine B unless
  * combine_b_offline, the batched GEMM, Combine H; negative when the scheme has no stage kernels), and the
  * choice with the smallest predicted time among plain, the fused kernels and Algorithm 1 of the paper's
- * schemes.  dataflow: 0 = lcma_gemm (fused; scheme_id LCMA_PLAIN means the plain GEMM), 1 = lcma_gemm_unfused
+ * schemes.  The forms are compared at the times their kernels take by now, which lcma_predict_unfused_seconds (published with
+ * an earlier GEMM stage) states up to a fifth too long; `seconds` is what lcma_predict_seconds or lcma_predict_unfused_seconds
+ * says of the choice.  dataflow: 0 = lcma_gemm (fused; scheme_id LCMA_PLAIN means the plain GEMM), 1 = lcma_gemm_unfused
  * level 1.  Pure host arithmetic. */
 typedef struct { int scheme_id; int dataflow; double seconds; } lcma_choice;
 double lcma_predict_unfused_seconds(int scheme_id, int64_t M, int64_t N, int64_t K, lcma_dtype dtype,
@@ -366,7 +368,8 @@ lcma_status lcma_model_stages(const lcma_scheme *s, int64_t M, int64_t N, int64_
 lcma_status lcma_model_intensity(const lcma_scheme *s, int64_t M, int64_t N, int64_t K,
                                  double *eq8, double *eq9, double *eq10);
 /* The model lcma_select uses for THIS library's fused kernels: predicted seconds of the
- * preferred variant of built-in `scheme_id` (LCMA_PLAIN..LCMA_LADERMAN) on MI355X, or a
+ * preferred variant of built-in `scheme_id` (LCMA_PLAIN..LCMA_LADERMAN) on MI355X (the plain 16-bit product:
+ * or of the kernel on 256 x 256 tiles that lcma_gemm takes besides the variants, if that is faster), or a
  * negative value when no variant fits the shape. */
 double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int64_t K, lcma_dtype dtype);
 

@@ -123,8 +123,10 @@ enum { PG_FP8_BF16 = 0, PG_FP8_F16 = 1, PG_F16 = 2, PG_BF16 = 3, PG_F16_OUT = 4 
 int64_t plane_gemm_scratch_bytes(int tile);
 // predicted seconds of plane_gemm on `planes` planes of rows x cols with ny steps of 128 bytes (negative: no kernel fits)
 double plane_gemm_seconds(int planes, int64_t rows, int64_t cols, int ny, int64_t scratch_bytes);
+double batched_plane_gemm_seconds(bool fp32_out, int planes, int64_t rows, int64_t cols, int ny);
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,
                        int schedule, void *scratch, int64_t scratch_bytes, void *stream);
+double plain_seconds(int64_t M, int64_t N, int64_t K, int dtype); // csrc/model.cc
 double plain_product_us(bool b_kn, int tn, int64_t M, int64_t N, int64_t K, bool off_line);
 bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc,
                    int dtype, double limit_us, void *stream, int *err);

@@ -123,11 +123,18 @@ extern "C" double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int6
     const Variant *v = pick_variant(scheme_id, dtype, M, N, K);
     if (!v) return -1.0;
     const double t = predict_variant(*v, M, N, K);
-    // the plain 16-bit product has the 256 x 256 ping-pong kernel besides the generated ones (csrc/plane_gemm.cc; its 256 x 128
-    // sibling is not priced: it stands in where tiles are few, and the figure stays on the safe side there)
+    // the plain 16-bit product has the 256 x 256 ping-pong kernel besides the generated ones (csrc/plane_gemm.cc)
     if (scheme_id == LCMA_PLAIN && dtype != LCMA_F32)
         return std::min(t, 1e-6 * plain_product_us(true, 256, M, N, K, K % 64 || N % 64) + kLaunch);
     return t;
+}
+
+// The plain product as lcma_select_dataflow prices it: with the 256 x 128 ping-pong kernel too, which stands in where tiles are few
+// (2048 x 4096 x 4096 62 us; the published prediction, without it, 86).
+double lcma::plain_seconds(int64_t M, int64_t N, int64_t K, int dtype) {
+    const double t = lcma_predict_seconds(LCMA_PLAIN, M, N, K, (lcma_dtype)dtype);
+    if (t <= 0.0 || dtype == LCMA_F32) return t;
+    return std::min(t, 1e-6 * plain_product_us(true, 128, M, N, K, K % 64 || N % 64) + kLaunch);
 }
 
 extern "C" int lcma_select(int64_t M, int64_t N, int64_t K, lcma_dtype dtype) {

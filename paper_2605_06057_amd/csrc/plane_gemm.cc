@@ -123,11 +123,17 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
 }
 } // namespace
 
-// Seconds of a 16-bit plane GEMM for the time model of Algorithm 1 (Sec. 3.3): what lcma_predict_unfused_seconds reports and
-// lcma_select_dataflow and lcma_gemm_ws compare.  Those figures are part of the interface (a caller may store them or
-// reproduce its choices by them), so this stays the calibration it was published with: steps of the slowest work-group at
-// 1.62 us, 3.5 or 5 more for every tile it works through, a pair of small tiles at 0.76 of a large one, 80 for the pieces of
-// the Split-Group ranges.  The kernels of plane_gemm, which chooses by the times above, are up to a fifth faster by now.
+// Seconds of the batched stage of Algorithm 1 in 16 bit as plane_gemm runs it by now (fp32_out: products kept in fp32), for
+// lcma_select_dataflow: measured 54.6 us at 53 predicted (7 planes, 2048 x 4096 x 4096), 318 / 315 (6144^3), 695 / 695 (FFN).
+double batched_plane_gemm_seconds(bool fp32_out, int planes, int64_t rows, int64_t cols, int ny) {
+    int t = 0, sc = 0;
+    const double us = choose(fp32_out ? PG_F16_F32 : PG_F16, planes, rows, cols, ny, 0, tuning_schedule(), 0, &t, &sc);
+    return t ? 1e-6 * us : -1.0;
+}
+
+// The same as lcma_predict_unfused_seconds was published with, and as lcma_gemm_ws, whose contract names that function, compares it:
+// steps of the slowest work-group at 1.62 us, 3.5 or 5 more for every tile it works through, a pair of small tiles at 0.76 of a
+// large one, 80 for the pieces of the Split-Group ranges, whole tiles only.  The kernels are up to a fifth faster by now.
 double plane_gemm_seconds(int planes, int64_t rows, int64_t cols, int ny, int64_t scratch_bytes) {
     const int schedule = tuning_schedule();
     double best = -1.0;
@@ -160,7 +166,8 @@ static int panel_of(int nz, int wide) {
 }
 
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
-// (padded sizes, multiples of the tile when batched).  tile: 256 or 128, 0 = choose.  schedule: 0 = choose, 1 = one
+// (padded sizes; when batched the ping-pong kernel alone takes
+// planes that are no whole tiles).  tile: 256 or 128, 0 = choose.  schedule: 0 = choose, 1 = one
 // tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of plane_gemm_scratch_bytes(tile) bytes), 3 =
 // persistent work-groups that each take every units-th whole tile-product.
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,

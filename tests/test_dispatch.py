@@ -41,3 +41,15 @@ def test_nt_ws_leaves_a_small_workspace_alone():
         for few in (4 << 20, whole // 2, whole - 256):
             assert D.gemm_nt_ws(M, N, K, "bf16", few) == none
         assert none[0] == 0 and len(none[1]) == 1 and ("slices=1" in none[1][0] or "few_rows" not in none[1][0]), none
+
+
+# Measured (us; weights combined before): plain 62.4, 206, 403, 703, 6606; Algorithm 1 with <2,2,2;7> 71.7, 265, 393, 819, 6270, with <4,4,4;49>
+# 86, 304, 427, 854, 6009
+@pytest.mark.parametrize("shape,want", [((2048, 4096, 4096), (0, 0)), ((8192, 4096, 4096), (0, 0)), ((6144, 6144, 6144), (1, 1)),
+                                        ((8192, 14336, 4096), (0, 0)), ((16384, 16384, 16384), (2, 1))], ids=str)
+def test_select_dataflow_prices_all_forms_by_the_present_kernels(shape, want):
+    from paper_2605_06057_amd import binding as B
+    c = B.lcma_select_dataflow(*shape, B.LCMA_BF16, True)
+    assert (c["scheme_id"], c["dataflow"]) == want
+    published = B.lcma_predict_unfused_seconds if want[1] else lambda i, M, N, K, dt, _: B.lcma_predict_seconds(i, M, N, K, dt)
+    assert c["seconds"] == published(want[0], *shape, B.LCMA_BF16, True)
