@@ -166,8 +166,8 @@ static int panel_of(int nz, int wide) {
 }
 
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
-// (padded sizes; when batched the ping-pong kernel alone takes
-// planes that are no whole tiles).  tile: 256 or 128, 0 = choose.  schedule: 0 = choose, 1 = one
+// (padded sizes; when batched only the ping-pong kernel takes planes that are no whole tiles).  tile: 256 or 128, 0 = choose.
+// schedule: 0 = choose, 1 = one
 // tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of plane_gemm_scratch_bytes(tile) bytes), 3 =
 // persistent work-groups that each take every units-th whole tile-product.
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,

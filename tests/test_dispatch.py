@@ -53,3 +53,46 @@ def test_select_dataflow_prices_all_forms_by_the_present_kernels(shape, want):
     assert (c["scheme_id"], c["dataflow"]) == want
     published = B.lcma_predict_unfused_seconds if want[1] else lambda i, M, N, K, dt, _: B.lcma_predict_seconds(i, M, N, K, dt)
     assert c["seconds"] == published(want[0], *shape, B.LCMA_BF16, True)
+
+
+# ------------------------------------------------------------------ the GPU tests of these kernels reach them
+def gemm_on_lines(M, N, K, dtype, nk):
+    import test_gpu_plain_pingpong as T
+    return D.call("lcma_gemm_nt" if nk else "lcma_gemm", M, N, K, D.A, T.pitch(K), D.B, T.pitch(K if nk else N), D.C, N + 8,
+                  ctypes.c_int(D.DTYPES[dtype]), ctypes.c_void_p(None), ctypes.c_void_p(None))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_shapes_of_the_plain_ping_pong_tests(dtype):
+    import test_gpu_plain_pingpong as T
+    for shape in T.SHAPES:
+        names = ((f"ppn_{dtype}_kn", f"ppn_{dtype}") if shape in T.NARROW else (f"pp_kn_{dtype}", f"pg_{dtype}_t256_{dtype}"))
+        for nk in (False, True):
+            status, ran = gemm_on_lines(*shape, dtype, nk)
+            assert status == 0 and len(ran) == 1 and ran[0].split()[0] == names[nk], (shape, nk, ran)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_shapes_of_the_few_rows_tests(dtype):
+    import test_gpu_few_rows as T
+    whole = D.lib().lcma_split_group_scratch_bytes()
+    for (M, N, K), plans in T.PLANS.items():
+        for (tile, slices), space in zip(plans, (whole, 0)):
+            for lda in (K, K + 8):
+                status, ran = D.gemm_nt_ws(M, N, K, dtype, space, lda)
+                assert status == 0 and len(ran) == 1 + (slices > 1), ran
+                assert ran[0].startswith(f"few_rows_{dtype}_{tile} ") and f" slices={slices} " in ran[0], ran
+
+
+def test_shapes_of_the_direct_tests():
+    import test_gpu_direct as F
+    import test_gpu_direct16 as H
+    for scheme in ("strassen", "winograd"):
+        for shape in F.SHAPES[1:]:
+            tile = "d32x32k8" if shape == (857, 1048, 808) else "d16x16k8"
+            for nk in (False, True):
+                assert D.gemm(*shape, "f32", scheme, nk) == (0, [f"{scheme}_f32_{tile}" + "t" * nk])
+    for dtype in ("bf16", "f16"):
+        for shape in H.CHOSEN:
+            for nk in (False, True):
+                assert D.gemm(*shape, dtype, "strassen", nk) == (0, [f"strassen_{dtype}_d16x64k4" + "t" * nk])

@@ -11,8 +11,12 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
+# tiles of 16, and of 32 (857 x 1048 x 808): test_dispatch.py; 3 x 4 x 4 stays with the staged kernel
+SHAPES = [(3, 4, 4), (3, 4, 16), (33, 36, 20), (256, 256, 256), (130, 516, 1000), (700, 712, 404), (857, 1048, 808)]
+
+
 @pytest.mark.parametrize("scheme", ["strassen", "winograd"])
-@pytest.mark.parametrize("shape", [(3, 4, 4), (33, 36, 20), (256, 256, 256), (130, 516, 1000), (700, 712, 404)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_layouts_and_scaling(scheme, shape):
     import torch
     import gpu_util as G

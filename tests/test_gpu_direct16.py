@@ -1,6 +1,6 @@
 """The direct kernels for 16-bit products with few tiles (csrc/lcma_direct16.hpp): the same bits for both layouts of B, at one
 element, a step that ends inside a lane's 32 bytes of K, fewer steps than waves, one more than a round of waves, edges of the
-16 x 64 tile, and where lcma_gemm chooses them; alpha and beta applied once.  (Exactness on integers, ragged edges and guard
+16 x 64 tile, and where lcma_gemm chooses them (CHOSEN); alpha and beta applied once, at every shape.  (Exactness on integers, ragged edges and guard
 rows: every variant, tests/test_gpu_parity.py.)"""
 import pytest
 
@@ -10,8 +10,11 @@ import oracle
 pytestmark = pytest.mark.gpu
 
 
+CHOSEN = [(40, 72, 840), (64, 264, 840), (239, 376, 2056), (130, 1000, 1480)]   # by the library's rule, both types and layouts: test_dispatch.py
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("shape", [(1, 8, 8), (33, 136, 72), (64, 264, 520), (239, 376, 2056), (130, 1000, 648)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", [(1, 8, 8), (33, 136, 72), (64, 264, 520), (130, 1000, 648)] + CHOSEN, ids=lambda s: "x".join(map(str, s)))
 def test_layouts_and_scaling(shape, dtype):
     import torch
     import gpu_util as G
@@ -32,14 +35,22 @@ def test_layouts_and_scaling(shape, dtype):
     ref = oracle.gemm(inp.widen(As, dtype), inp.widen(Bs, dtype))
     assert oracle.rel_frobenius(G.to_host_f64(c, dtype), ref) <= 2e-2   # the bound of the 16-bit products
     assert torch.equal(c, ct) and torch.equal(d, e)
+    if shape in CHOSEN:
+        assert torch.equal(c, d)
     old = (torch.arange(M * N, device="cuda", dtype=torch.float32).view(M, N) / (M * N)).to(c.dtype)
-    y = old.clone()
-    B.lcma_gemm_ex(0.5, -2.0, a, b, y, s, b_nk=False)
+    y, z = old.clone(), old.clone()
+    for right, out, variant, nk in ((b, y, name, False), (w, z, name + "t", True)):
+        B.lcma_set_tuning("variant", variant)
+        try:
+            B.lcma_gemm_ex(0.5, -2.0, a, right, out, s, b_nk=nk)
+        finally:
+            B.lcma_set_tuning("variant", "")
     torch.cuda.synchronize()
-    # C = d rounded once (half an ulp of d, u = 2^-9 or 2^-12 of its magnitude, halved by alpha), then the sum rounded once
+    assert torch.equal(y, z)
+    # c rounded once (half an ulp of c, u = 2^-9 or 2^-12 of its magnitude, halved by alpha), then the sum rounded once
     u = 2.0 ** (-9 if dtype == "bf16" else -12)
-    want = 0.5 * d.double() - 2.0 * old.double()
-    assert ((y.double() - want).abs() <= 2 * u * (d.double().abs() + want.abs()) + 1e-7).all().item()
+    want = 0.5 * c.double() - 2.0 * old.double()
+    assert ((y.double() - want).abs() <= 2 * u * (c.double().abs() + want.abs()) + 1e-7).all().item()
 
 
 # K of a step and less, of a step that ends inside a lane's 32 bytes, and more steps than waves

@@ -1,6 +1,6 @@
 """The plain 16-bit product on the ping-pong kernels (csrc/lcma_pingpong.hpp, lcma_pingpong_narrow.hpp) where lcma_gemm, lcma_gemm_nt
 and lcma_gemm_nt_ws choose them: K that ends inside a step of 64 (what lies behind a row of A or W is NaN and must not be
-read as part of it), K of one to three steps beyond whole pairs, ragged M and N, both tiles.  lcma_gemm's results are those of
+read as part of it), K of less than one step to many, ragged M and N, both tiles and both layouts of B.  lcma_gemm's results are those of
 the generated kernels bit for bit, which is what the float inputs are compared with."""
 import numpy as np
 import pytest
@@ -9,8 +9,19 @@ import lcma_inputs as inp
 
 pytestmark = pytest.mark.gpu
 
-# 256 x 128 tiles: few tiles and a long K; 256 x 256: many
-SHAPES = [(520, 1160, 4104), (2000, 4088, 4224), (1300, 2100 // 8 * 8, 6200), (4352, 4608, 1032), (4100, 8200, 1080), (6144, 6144, 648)]
+# What the library takes for rows that start on lines (test_dispatch.py holds it to that, both types and layouts).  256 x 128 tiles:
+# one to four steps of K, the last one of 8, 16, ... elements, 33 and 65 tiles, more tiles than work-groups run at a time, a long K
+NARROW = [(4100, 1032, 8), (250, 8200, 64), (250, 8200, 128), (520, 8200, 136), (250, 8200, 192), (520, 8200, 264), (4100, 4104, 776),
+          (2040, 2056, 4104)]
+# 256 x 256: six, seven and eight steps, 56, 64 and 8 elements in the last; 132 tiles (dealt in rounds), 561 (two and three to a
+# work-group, an eighth to every XCD), a long K
+WIDE = [(1000, 8200, 376), (1000, 8200, 448), (1000, 8200, 456), (4100, 8200, 1080), (4100, 2056, 4104)]
+SHAPES = NARROW + WIDE
+
+
+def pitch(n):
+    """Row pitch: at least one unused column, rows on 128-byte lines."""
+    return n // 64 * 64 + 64
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
@@ -24,7 +35,7 @@ def test_same_bits_as_the_generated_kernels(dt, shape):
     gen.manual_seed(M + N + K)
     td = {"bf16": torch.bfloat16, "f16": torch.float16}[dt]
     nan = lambda r, c: torch.full((r, c), float("nan"), device="cuda", dtype=td)
-    a, b, w = nan(M, K + 24), nan(K, N + 8), nan(N, K + 24)
+    a, b, w = nan(M, pitch(K)), nan(K, pitch(N)), nan(N, pitch(K))
     a[:, :K] = torch.randn((M, K), device="cuda", generator=gen)
     b[:, :N] = torch.randn((K, N), device="cuda", generator=gen) * 0.05
     w[:, :K] = b[:, :N].t()
@@ -32,7 +43,7 @@ def test_same_bits_as_the_generated_kernels(dt, shape):
     want = G.empty_like_c(M, N, dt, fill=float("nan"))
     B.lcma_gemm_variant(f"plain_{dt}_t128x128x64_c1o2", a, b, want)
     for name, call in (("lcma_gemm", lambda c: B.lcma_gemm(a, b, c)), ("lcma_gemm_nt", lambda c: B.lcma_gemm_nt(a, w, c)),
-                       ("lcma_gemm_ex", lambda c: B.lcma_gemm_ex(1.0, 0.0, a, b, c))):
+                       ("lcma_gemm_ex", lambda c: B.lcma_gemm_ex(1.0, 0.0, a, b, c)), ("lcma_gemm_ex N x K", lambda c: B.lcma_gemm_ex(1.0, 0.0, a, w, c, None, True))):
         c = G.empty_like_c(M + 3, N + 8, dt, fill=float("nan"))
         print(f"plain {name} {dt} {M}x{N}x{K}", flush=True)
         call(c[:M, :N])
