@@ -7,7 +7,7 @@
 // fragments come from memory straight into registers, a batch of U steps ahead of the matrix instructions (16x16x32: 16 rows
 // of W and 16 of A per fragment, 16 bytes per lane).  At the end the eight partial tiles are added in LDS in ascending wave
 // order, in fp32, and rounded once.
-// What bounds it is what ONE CU can pull in, about 40 bytes/ns whatever the source: so the bytes per work-group decide, a
+// What bounds it is what ONE CU can pull in, 33 to 42 bytes/ns whatever the source (few_rows_plan takes 36): so the bytes per work-group decide, a
 // large tile of C reads least in all, and when large tiles alone would not fill the chip K is cut into slices for
 // work-groups of their own, whose fp32 partial products a second kernel adds in ascending order (3.7 us for its launch).
 // Measured (bf16, us, against the 128 x 128 plane GEMM): 64 x 4096 x 4096 14.3 (four slices; one 31.2) against 41.4; 64 x 4096

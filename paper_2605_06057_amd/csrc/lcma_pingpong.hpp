@@ -19,8 +19,9 @@
 // Measured, one run, against PlaneGemm's persistent schedule (random operands; in brackets all-zero operands, where the
 // chip's power limit does not hide the difference): 8192 x 4096 x 14336 bf16 1182 -> 1393 TFLOP/s (1400 -> 2024);
 // 8192 x 14336 x 4096 1212 -> 1382 (1735 -> 2134); 7 planes of 4096 x 7168 x 2048 fp16 1025 -> 1185 (1329 -> 1756); 25
-// planes of 2048^3 with fp32 output 847 -> 1002 (1050 -> 1363).  Random operands are then bound by power (the matrix pipe
-// alone sustains about 1570 on such values): leaving out the stores of C altogether gains 1.5 to 3.5 % more.
+// planes of 2048^3 with fp32 output 847 -> 1002 (1050 -> 1363).  On random operands the matrix pipe alone sustains 1490 to 1570:
+// the plain product is at 0.89 of that (pipe 82 % busy), a batch of planes at 0.79 (72 %: a last round that is not full, tiles of 32
+// steps); leaving out the stores of C altogether gains 1.5 to 3.5 % more.
 // Measured and not kept: a larger count for the waits while the stores of the tile before are in flight (nothing).
 #pragma once
 #include "lcma_plane_gemm.hpp"

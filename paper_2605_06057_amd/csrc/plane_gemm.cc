@@ -167,9 +167,8 @@ static int panel_of(int nz, int wide) {
 
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
 // (padded sizes; when batched only the ping-pong kernel takes planes that are no whole tiles).  tile: 256 or 128, 0 = choose.
-// schedule: 0 = choose, 1 = one
-// tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of plane_gemm_scratch_bytes(tile) bytes), 3 =
-// persistent work-groups that each take every units-th whole tile-product.
+// schedule: 0 = choose, 1 = one tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of
+// plane_gemm_scratch_bytes(tile) bytes), 3 = persistent work-groups that each take every units-th whole tile-product.
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,
                        int schedule, void *scratch, int64_t scratch_bytes, void *stream) {
     const int forced = tuning_schedule();
@@ -274,7 +273,7 @@ bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, in
 
 namespace {
 // Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): tile and slices of K with the smallest time.  A work-group
-// pulls in 36 bytes/ns (measured on all three tiles), about 256 run at a time; 2.0 (2.2, 4.4) us besides for the launch and
+// pulls in 36 bytes/ns (33 to 42 measured, on all three tiles), about 256 run at a time; 2.0 (2.2, 4.4) us besides for the launch and
 // the sum over the waves, 3.7 for the kernel that adds the slices (both sides measured: see lcma_few_rows.hpp).
 struct FewRowsPlan {
     int tile;
