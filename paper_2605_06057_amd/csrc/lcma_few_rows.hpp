@@ -12,7 +12,9 @@
 // work-groups of their own, whose fp32 partial products a second kernel adds in ascending order (3.7 us for its launch).
 // Measured (bf16, us, against the 128 x 128 plane GEMM): 64 x 4096 x 4096 14.3 (four slices; one 31.2) against 41.4; 64 x 4096
 // x 14336 36.1 against 199 (117 MB of weights: 3.3 TB/s); 64 x 14336 x 4096 35.9 (one slice) against 61.4; 128 x 4096 x 4096
-// 21.5 against 42.1; 64 x 1024 x 1024 3.9 (tiles of 16) against 10.1; 256 x 1024 x 1024 5.8 (tiles of 32) against 10.1.
+// 21.5 against 42.1; 64 x 1024 x 1024 3.9 (tiles of 16) against 10.1; 256 x 1024 x 1024 5.8 (tiles of 32) against 10.1.  Few columns
+// (fp16): 4266 x 128 x 4288 33 against 48, 4095 x 192 x 2176 19.6 against 24 (97 and 37 with the blocks of columns dealt to the XCDs
+// one by one, which leaves most XCDs without work where there are fewer than eight).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -46,10 +48,14 @@ template <class KIND, int MT, int NT, int U> struct FewRows {
         const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.A), 0, (int)p.a_bytes, 0x00020000);
         const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.W), 0, (int)p.w_bytes, 0x00020000);
-        // the row blocks of one column block and slice follow each other on the same XCD (work-groups go to the eight XCDs in turn)
-        const int in = blockIdx.x % (8 * p.row_blocks), mb = in / 8;
-        const int job = blockIdx.x / (8 * p.row_blocks) * 8 + in % 8, slice = job % p.slices, cb = job / p.slices;
-        if (cb * COLS * 2 >= (int)p.n_row_b) return;
+        // an eighth of the work-groups to every XCD (they go to the eight in turn), cut along the longer side of C and, first, along K: an
+        // XCD reads its part of the longer operand alone and few slices of the other one
+        const int col_blocks = p.partial_ld / COLS, jobs = col_blocks * p.slices, groups = jobs * p.row_blocks; // (groups: the grid)
+        const int share = (groups + 7) / 8, left = groups % 8, xcd = blockIdx.x % 8;
+        const int id = (left && xcd > left ? left * share + (xcd - left) * (share - 1) : xcd * share) + blockIdx.x / 8;
+        const bool tall = p.row_blocks * ROWS > p.partial_ld;
+        const int inner = tall ? jobs : p.row_blocks, hi = id / inner, lo = id - hi * inner;
+        const int mb = tall ? hi : lo, job = tall ? lo : hi, slice = job / col_blocks, cb = job - slice * col_blocks;
         const int first = slice * p.slice_steps, end = first + p.slice_steps < p.steps ? first + p.slice_steps : p.steps;
         // rows past M or N lie past the extents and read as zero
         uint32_t a_off[MT], b_off[NT];

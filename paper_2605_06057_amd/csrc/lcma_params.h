@@ -97,7 +97,7 @@ struct FewRowsParams {
     int32_t steps;                      // K / 32
     int32_t row_blocks, block_rows;     // blocks of rows of C, and the rows of a block
     int32_t slices, slice_steps;        // slices of K (1: C is written directly), steps of a slice
-    int32_t partial_ld;                 // row pitch of the partial products in floats
+    int32_t partial_ld;                 // columns of C in whole blocks: the row pitch of the partial products in floats
     void *partial;                      // slices x (row_blocks * block_rows) x partial_ld fp32 partial products
 };
 

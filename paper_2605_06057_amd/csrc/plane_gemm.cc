@@ -377,8 +377,7 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
             const auto launch = f.tile == 16   ? (bf ? lcma_launch_few_rows_bf16_16 : lcma_launch_few_rows_f16_16)
                                 : f.tile == 32 ? (bf ? lcma_launch_few_rows_bf16_32 : lcma_launch_few_rows_f16_32)
                                                : (bf ? lcma_launch_few_rows_bf16_64 : lcma_launch_few_rows_f16_64);
-            // (the column blocks and slices of a block of rows in eights, one per XCD)
-            err = launch(&q, (int)(ceil_div(f.col_blocks * f.slices, 8) * 8 * f.row_blocks), stream);
+            err = launch(&q, (int)(f.row_blocks * f.col_blocks * f.slices), stream);
             if (!err && f.slices > 1) err = (bf ? lcma_launch_few_rows_sum_bf16 : lcma_launch_few_rows_sum_f16)(&q, (int)M, stream);
             if (err) return fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err);
             return LCMA_OK;

@@ -46,3 +46,34 @@ def test_few_rows(dt, shape):
     # square, ulp / sqrt(12) against 1.5 in the middle of a binade, is 2^-9.4 (2^-12.4).  So half of it where there are many values.
     u = 2.0 ** (-8 if dt == "bf16" else -11)
     assert oracle.rel_frobenius(G.to_host_f64(c, dt), ref) <= (u if M * N < 1000 else u / 2) + 1e-5
+
+
+# Many rows and few columns: fewer blocks of columns (and slices of K) than XCDs.  Measured, this kernel / the plane GEMM, us: 34 / 48 (97 on two XCDs), 7.2 / 7.4 (17.6)
+@pytest.mark.parametrize("shape", [(4266, 128, 4288), (5369, 192, 512)], ids=lambda s: "x".join(map(str, s)))
+def test_few_columns_are_no_slower_than_one_tile_per_work_group(shape):
+    import torch
+    from paper_2605_06057_amd import binding as B
+    M, N, K = shape
+    a, w = torch.randn((M, K), device="cuda").half(), torch.randn((N, K), device="cuda").half()
+    c = torch.empty((M, N), device="cuda", dtype=torch.float16)
+    ws = torch.empty((B.lcma_split_group_scratch_bytes(),), dtype=torch.uint8, device="cuda")
+    graphs = []
+    for schedule in ("static", ""):
+        B.lcma_set_tuning("schedule", schedule)
+        B.lcma_gemm_nt_ws(a, w, c, ws)
+        torch.cuda.synchronize()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            for _ in range(20):
+                B.lcma_gemm_nt_ws(a, w, c, ws)
+    best = [float("inf")] * 2
+    for _ in range(7):
+        for i, g in enumerate(graphs):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            g.replay()
+            e1.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], e0.elapsed_time(e1) / 20 * 1e3)
+    print(f"{M}x{N}x{K}: static {best[0]:.1f} us, chosen {best[1]:.1f}", flush=True)
+    assert best[1] <= 1.15 * best[0], best
