@@ -243,8 +243,8 @@ int64_t lcma_unfused_workspace_bytes(int64_t M, int64_t N, int64_t K, lcma_dtype
  * then differ from the other schedule in the last bit (the partial sums are cut elsewhere). */
 int64_t lcma_split_group_scratch_bytes(void);
 /* Plain GEMM C = A x W^T for weights stored N x K (as lcma_gemm_nt with scheme == NULL; BF16 and F16) on the kernel of the
- * batched stage, with a workspace (device, 256-byte aligned, lcma_split_group_scratch_bytes() bytes, overwritten; NULL or
- * fewer bytes: never split) that lets it hand the steps of all tiles out in Split-Group ranges: the split-K form of a plain
+ * batched stage, with a workspace (device, 256-byte aligned, lcma_split_group_scratch_bytes() bytes, overwritten; half of
+ * them serve its 128 x 128 tiles alone; NULL or fewer bytes: never split) that lets it hand the steps of all tiles out in Split-Group ranges: the split-K form of a plain
  * GEMM, chosen when the tiles alone would leave much of the chip idle (few tiles, long K).  Few rows or a small C run on a
  * kernel of their own, whose waves split K inside a work-group; with the whole workspace K is split between work-groups as well
  * (fp32 partial products, added in ascending order).  K not a multiple of 64 and F32

@@ -344,10 +344,10 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
     p.n_row_b = (uint32_t)(N * 2);
     if (workspace && ((uintptr_t)workspace & 255)) return fail(LCMA_ERR_ARG, "%s: the workspace must be 256-byte aligned", who);
     const int kind = dtype == LCMA_BF16 ? PG_BF16 : PG_F16_OUT;
-    // a workspace of fewer bytes than lcma_split_group_scratch_bytes() is not touched (a forced schedule uses what it gets)
-    const int64_t scratch = workspace && (workspace_bytes >= plane_gemm_scratch_bytes(256) || tuning_schedule()) ? workspace_bytes : 0;
+    const int64_t scratch = workspace ? workspace_bytes : 0;
     if (!tuning_schedule()) { // (a forced schedule is one of the plane GEMM's)
-        const FewRowsPlan f = few_rows_plan(M, N, K, scratch);
+        // (slices only with the bytes that the interface names: half of them serve the ranges on 128 x 128 tiles, fewer are left alone)
+        const FewRowsPlan f = few_rows_plan(M, N, K, scratch >= plane_gemm_scratch_bytes(256) ? scratch : 0);
         int t = 0, sc = 0;
         const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc);
         int err = 0;

@@ -33,14 +33,19 @@ def test_small_fp32_products_take_the_smaller_tile(scheme):
 
 
 def test_nt_ws_leaves_a_small_workspace_alone():
-    """include/lcma.h: with fewer bytes than lcma_split_group_scratch_bytes() the product is never split between work-groups."""
+    """include/lcma.h: half of lcma_split_group_scratch_bytes() serves the ranges on 128 x 128 tiles alone, fewer bytes nothing."""
     whole = D.lib().lcma_split_group_scratch_bytes()
     for M, N, K in ((64, 4096, 4096), (129, 200, 14400), (512, 4096, 14336)):
         split, none = D.gemm_nt_ws(M, N, K, "bf16", whole), D.gemm_nt_ws(M, N, K, "bf16", 0)
         assert split[0] == 0 and split != none
-        for few in (4 << 20, whole // 2, whole - 256):
+        for few in (4 << 20, whole // 2 - 256):
             assert D.gemm_nt_ws(M, N, K, "bf16", few) == none
+        for half in (whole // 2, whole - 256):
+            ran = D.gemm_nt_ws(M, N, K, "bf16", half)[1]
+            assert len(ran) == 1 and ("slices=1" in ran[0] or "few_rows" not in ran[0]), ran
         assert none[0] == 0 and len(none[1]) == 1 and ("slices=1" in none[1][0] or "few_rows" not in none[1][0]), none
+    # 38 tiles of 104 steps in ranges of eight (33 us)
+    assert D.gemm_nt_ws(2372, 256, 6656, "bf16", whole // 2)[1][0].startswith("pg_bf16_t128_bf16 jobs=38 units=494 ")
 
 
 # Measured (us; weights combined before): plain 62.4, 206, 403, 703, 6606; Algorithm 1 with <2,2,2;7> 71.7, 265, 393, 819, 6270, with <4,4,4;49>
