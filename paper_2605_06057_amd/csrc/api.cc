@@ -273,10 +273,14 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
     if (!v) {
         v = pick_variant(id, dtype, M, N, K, 0, b_nk);
         // the plain 16-bit product without scaling: the ping-pong kernels where they are faster (the same bits)
-        // (the published prediction knows no latency: a step takes at least 0.27 us, 0.14 for N x K weights, and 0.36 and 0.22 with
-        // a hundred work-groups: 215 x 208 x 1976 19.7 and 11.7 us, 704 x 704 x 8000 97.6 and 63.2)
+        // What the generated kernel takes: the published prediction counts a launch, 4 us, of which the kernel itself takes 2, and beyond
+        // that K x N kernels take 0.9 to 1.2 of it, N x K kernels 0.75 to 1.0 (128 x 128 tiles) and from 0.92 on (the others).  It knows
+        // no latency: a step takes at least 0.27 us, 0.14 for N x K weights, and 0.36 and 0.22 with a hundred work-groups: 215 x 208 x
+        // 1976 19.7 and 11.7 us, 704 x 704 x 8000 97.6 and 63.2.  At 1800 products, 8 to 8192 rows, K 64 to 10000, both types and
+        // layouts, rows on lines and off, no choice is slower than the generated kernel by more than 2.5 % (with the prediction as it
+        // is 45 were, 839 x 1400 x 192 by half; 5913 x 472 x 8776, K x N, 175 against 145).
         if (v && id == LCMA_PLAIN && dtype != LCMA_F32 && alpha == 1.f && beta == 0.f && K > 0)
-            plain_us = std::max(1e6 * predict_variant(*v, M, N, K),
+            plain_us = std::max(2.0 + (!b_nk ? 0.95 : v->TM == 128 ? 0.75 : 0.92) * (1e6 * predict_variant(*v, M, N, K) - 4.0),
                                 2.5 + ((M + 63) / 64 * ((N + 63) / 64) < 100 ? (b_nk ? 0.14 : 0.27) : (b_nk ? 0.22 : 0.36)) * (double)K / v->TK);
         if (v) v = pick_direct(v, M, N, K, lda, ldb, ldc);
     }

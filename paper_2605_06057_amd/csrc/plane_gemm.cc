@@ -219,10 +219,10 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
 // step (K x N: 0.60 + 0.32 f, its fragments wait for their own reads) and 4 a round (K x N: 2048 x 4096 x 4096 62 against 87 for
 // the generated kernel, 1024 x 4096 x 4096 50 / 56, 2048 x 4096 x 14336 210 / 284, 704 x 704 x 8000 80 / 98); 256 x 256: as in
 // choose() for either layout (K x N: 6144^3 394 / 495, 8192 x 14336 x 4096 704 / 863); 15 % more when rows do not start on
-// 128-byte lines (5000 x 3000 x 1000 43 / 42).
+// 128-byte lines (5000 x 3000 x 1000 43 / 42), 30 % with N x K weights on the 256 x 128 tile (1178 x 2592 x 9952 130 / 104).
 double plain_product_us(bool b_kn, int tn, int64_t M, int64_t N, int64_t K, bool off_line) {
     const int64_t ny = ceil_div(K, 64), jobs = ceil_div(M, 256) * ceil_div(N, tn), full = jobs / kCUs, rest = jobs % kCUs;
-    const double line = off_line ? 1.15 : 1.0;
+    const double line = !off_line ? 1.0 : tn == 128 && !b_kn ? 1.3 : 1.15;
     auto round = [&](double f) {
         return tn == 256 ? (double)((ny + 1) & ~(int64_t)1) * line * (0.80 + 0.72 * f) + 6.0
                          : (double)ny * line * (b_kn ? 0.60 + 0.32 * f : 0.52 + 0.38 * f) + 4.0;

@@ -21,7 +21,7 @@ extern "C" const char *dispatch_log() { return g_log.c_str(); }
 static int note(const char *name, const std::string &args = "") { g_log += std::string(name) + args + "\\n"; return 0; }
 static std::string num(const char *k, long long v) { return std::string(" ") + k + "=" + std::to_string(v); }
 static std::string args(const lcma::PlaneGemmParams *p) {
-    return num("jobs", p->jobs) + num("units", p->units) + num("ny", p->ny) + num("tail", p->tail_b) + num("panel", p->panel);
+    return num("jobs", p->jobs) + num("units", p->units) + num("ny", p->ny) + num("tail", p->tail_b) + num("panel", p->panel) + num("dealt", p->interleave);
 }
 static std::string args(const lcma::FewRowsParams *p) {
     return num("tile", p->block_rows) + num("steps", p->steps) + num("slices", p->slices) + num("slice_steps", p->slice_steps);

@@ -60,6 +60,18 @@ def test_select_dataflow_prices_all_forms_by_the_present_kernels(shape, want):
     assert c["seconds"] == published(want[0], *shape, B.LCMA_BF16, True)
 
 
+# Measured, us, generated kernel / 256 x 128 ping-pong kernel: 4.5 / 6.9, 3.5 / 5.7, 6.5 / 9.0, 10.4 / 12.6; the last with rows that do not start on
+# lines, 104 / 130 (256 x 256: 168)
+@pytest.mark.parametrize("shape,ld", [((839, 1400, 192), 0), ((136, 5488, 64), 0), ((2210, 512, 512), 0), ((942, 1160, 832), 0), ((1178, 2592, 9952), 8)], ids=str)
+def test_plain_products_that_the_generated_kernel_does_faster(shape, ld):
+    for dtype in ("bf16", "f16"):
+        status, ran = D.gemm(*shape, dtype, None, True, ld)
+        assert status == 0 and ran[0].startswith(f"plain_{dtype}_t"), ran
+        for tall in ((5913, 472, 8776), (7153, 328, 8192)):   # (K x N: 145 / 175, 105 / 121)
+            status, ran = D.gemm(*tall, dtype)
+            assert status == 0 and ran[0].startswith(f"plain_{dtype}_t"), ran
+
+
 # ------------------------------------------------------------------ the GPU tests of these kernels reach them
 def gemm_on_lines(M, N, K, dtype, nk):
     import test_gpu_plain_pingpong as T
@@ -74,7 +86,8 @@ def test_shapes_of_the_plain_ping_pong_tests(dtype):
         names = ((f"ppn_{dtype}_kn", f"ppn_{dtype}") if shape in T.NARROW else (f"pp_kn_{dtype}", f"pg_{dtype}_t256_{dtype}"))
         for nk in (False, True):
             status, ran = gemm_on_lines(*shape, dtype, nk)
-            assert status == 0 and len(ran) == 1 and ran[0].split()[0] == names[nk], (shape, nk, ran)
+            assert status == 0 and len(ran) == 1, ran
+            assert (ran[0].split()[0] == names[nk]) != (nk and shape in T.KN_ONLY), (shape, nk, ran)
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])

@@ -1,6 +1,6 @@
 """The plain 16-bit product on the ping-pong kernels (csrc/lcma_pingpong.hpp, lcma_pingpong_narrow.hpp) where lcma_gemm, lcma_gemm_nt
 and lcma_gemm_nt_ws choose them: K that ends inside a step of 64 (what lies behind a row of A or W is NaN and must not be
-read as part of it), K of less than one step to many, ragged M and N, both tiles and both layouts of B.  lcma_gemm's results are those of
+read as part of it), ragged M and N, both tiles and both layouts of B.  lcma_gemm's results are those of
 the generated kernels bit for bit, which is what the float inputs are compared with."""
 import numpy as np
 import pytest
@@ -9,13 +9,15 @@ import lcma_inputs as inp
 
 pytestmark = pytest.mark.gpu
 
-# What the library takes for rows that start on lines (test_dispatch.py holds it to that, both types and layouts).  256 x 128 tiles:
-# one to four steps of K, the last one of 8, 16, ... elements, 33 and 65 tiles, more tiles than work-groups run at a time, a long K
-NARROW = [(4100, 1032, 8), (250, 8200, 64), (250, 8200, 128), (520, 8200, 136), (250, 8200, 192), (520, 8200, 264), (4100, 4104, 776),
+# What the library takes for rows that start on lines (test_dispatch.py holds it to that, both types).  256 x 128 tiles: 8 to 65 steps of K,
+# 8 elements or a whole step in the last, 32 to 660 tiles (256 work-groups run at a time)
+NARROW = [(1000, 4104, 456), (520, 8200, 648), (1000, 4104, 960), (1000, 4104, 1032), (1000, 4104, 1096), (5000, 4104, 1032), (520, 8200, 4104),
           (2040, 2056, 4104)]
-# 256 x 256: six, seven and eight steps, 56, 64 and 8 elements in the last; 132 tiles (dealt in rounds), 561 (two and three to a
-# work-group, an eighth to every XCD), a long K
-WIDE = [(1000, 8200, 376), (1000, 8200, 448), (1000, 8200, 456), (4100, 8200, 1080), (4100, 2056, 4104)]
+# 256 x 256: 10 to 65 steps, 56, 8 and 64 elements in the last; 132 tiles (dealt in rounds), 561 (two and three to a work-group, an
+# eighth to every XCD), a long K
+WIDE = [(1000, 8200, 632), (1000, 8200, 832), (1000, 8200, 840), (4100, 8200, 1144), (4100, 2056, 4104)]
+# (N x K weights stay with the generated kernel here)
+KN_ONLY = [(1000, 4104, 456), (520, 8200, 648)]
 SHAPES = NARROW + WIDE
 
 
