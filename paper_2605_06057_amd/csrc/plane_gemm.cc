@@ -76,10 +76,11 @@ namespace {
 //   128 x 128, two work-groups per CU: 1.06 a step of both (FP8: 1.16) with 512 work-groups, 0.72 to 0.9 with 256, 0.62
 //     with a few (2048 x 4096 x 4096: 68 us; 1024 x 4096 x 4096: 48 us; x 16384: 232 us; 64 x 4096 x 4096: 41 us): the one to take when the large
 //     tiles leave much of the chip idle;
-//   Split-Group ranges: 1.75 (0.95; FP8 2.0 and 1.1) a step, 6 (3) a tile-product and 65 (40) for the pieces: nearly every
-//     work-group holds two, 134 (67) MB of fp32 partial sums in all, written at the end of the first kernel and read back by
-//     the second (1024 x 4096 x 16384: 161 us against 232 with 128 x 128 tiles; 512 x 4096 x 14336: 95 against 221): few
-//     tile-products and a long K only (2463 x 8344 x 6528: 334 against 248 with the ping-pong kernel).
+//   Split-Group ranges: 1.75 (1.6; FP8 2.0 and 1.1) a step, 6 (3) a tile-product and 65 (20, and 0.45 for every piece of a tile; FP8 40)
+//     for the pieces: nearly every work-group holds two, 134 (67) MB of fp32 partial sums in all, written at the end of the first
+//     kernel and read back by the second (1024 x 4096 x 16384: 161 us against 232 with 128 x 128 tiles; 512 x 4096 x 14336: 95 against 221): few
+//     tile-products and a long K only (2463 x 8344 x 6528: 334 against 248 with the ping-pong kernel; neighbouring tiles of the 128 x
+//     128 form start at different k and share little in L2: 857 x 3720 x 7040 112 against 91 with a work-group per tile).
 // tile, schedule: 0 = choose.  Returns microseconds (0 when nothing fits).
 double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, int64_t scratch_bytes, int *best_tile,
               int *best_sched) {
@@ -100,8 +101,8 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             if (sc == 2 && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
             double cost;
             if (sc == 2) {
-                cost = (double)ceil_div(jobs * ny, slots) * (t == 256 ? fp8 ? 2.0 : 1.75 : fp8 ? 1.1 : 0.95) +
-                       (t == 256 ? 6.0 : 3.0) * out * (double)jobs / (double)slots + (t == 256 ? 65.0 : 40.0);
+                const double cap = (double)ceil_div(jobs * ny, slots), pieces = t == 256 ? 65.0 : fp8 ? 40.0 : 20.0 + 0.45 * (double)ny / cap;
+                cost = cap * (t == 256 ? fp8 ? 2.0 : 1.75 : fp8 ? 1.1 : 1.6) + (t == 256 ? 6.0 : 3.0) * out * (double)jobs / (double)slots + pieces;
             } else {
                 const int64_t full = jobs / slots, rest = jobs % slots;
                 auto round = [&](double f) {
@@ -292,7 +293,7 @@ FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, int64_t scratch_bytes
         const int64_t scratch = slices > 1 ? slices * rb * tile * cb * tile * 4 : 0;
         if (scratch > scratch_bytes) { // (then in one piece)
             slices = 1;
-            slice_steps = steps;
+            slice_steps = ceil_div(steps, batch) * batch;
         }
         double us = (double)ceil_div(rb * cb * slices, kCUs) * (double)(slice_steps * 64 * 2 * tile) / 36e3;
         // rows of A that do not fit an XCD's L2 come from beyond it for every block of columns (270 x 5488 x 12864: 178 us)
@@ -351,7 +352,8 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
         int t = 0, sc = 0;
         const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc);
         int err = 0;
-        if (!(f.tile && f.us < planes_us) && plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, planes_us, stream, &err))
+        // (1.5 us on the safe side: 840 x 5592 x 768 15.7 against 14.4, 4358 x 256 x 640 10.4 against 9.2)
+        if (!(f.tile && f.us < planes_us) && plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, planes_us - 1.5, stream, &err))
             return err ? fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err) : LCMA_OK;
         if (f.tile && f.us < planes_us) {
             FewRowsParams q;

@@ -72,6 +72,22 @@ def test_plain_products_that_the_generated_kernel_does_faster(shape, ld):
             assert status == 0 and ran[0].startswith(f"plain_{dtype}_t"), ran
 
 
+# Measured, us, a work-group per 128 x 128 tile / what was taken: 91 / 112 (ranges of steps; 256 x 128 ping-pong 86), 143 / 189 (ping-pong 117),
+# 14.4 / 15.7 and 9.2 / 10.4 (256 x 128 ping-pong)
+def test_nt_ws_between_the_plane_gemm_and_its_kin():
+    whole = D.lib().lcma_split_group_scratch_bytes()
+    for shape, pad in (((857, 3720, 7040), 8), ((559, 7184, 9856), 0)):
+        ran = D.gemm_nt_ws(*shape, "f16", whole, shape[2] + pad)[1]
+        jobs, units = (int(ran[0].split(k + "=")[1].split()[0]) for k in ("jobs", "units"))
+        assert len(ran) == 1 and units == min(jobs, 256 if "t128" not in ran[0] else 512), ran   # no ranges
+    for shape, pad in (((840, 5592, 768), 64), ((4358, 256, 640), 64)):
+        assert D.gemm_nt_ws(*shape, "bf16", whole, shape[2] + pad)[1][0].startswith("pg_bf16_t128_bf16 ")
+    # without a workspace the eight waves of a few-rows kernel run whole batches of 16 steps: 20 cost what 32 do (7.8 / 8.9)
+    assert D.gemm_nt_ws(109, 2432, 640, "f16", 0)[1][0].startswith("pg_f16_t128_f16 ")
+    ran = D.gemm_nt_ws(512, 4096, 14336, "bf16", whole)[1]   # 128 tiles of 224 steps: ranges, 95 us against 221
+    assert ran[0].startswith("pg_bf16_t128_bf16 jobs=128 units=512 "), ran
+
+
 # ------------------------------------------------------------------ the GPU tests of these kernels reach them
 def gemm_on_lines(M, N, K, dtype, nk):
     import test_gpu_plain_pingpong as T
