@@ -87,8 +87,7 @@ extern "C" lcma_status lcma_fp8_quantize(int64_t rows, int64_t K, const void *X,
     p.lds_b = (uint32_t)ls;
     p.k_row_b = (uint32_t)(K * 2);
     p.rows = (int32_t)rows;
-    p.lane_shift = 4; // (a quarter wave along a row: 15.9 us for 8192 x 4096, a whole one 16.7)
-    if (const int err = lcma_launch_fp8_quantize_rows(&p, row_groups(rows, p.lane_shift), vector_groups(kp / 8, p.lane_shift), stream))
+    if (const int err = lcma_launch_fp8_quantize_rows(&p, (int)((rows + 15) / 16), (int)(kp / 128), stream))
         return fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err);
     return LCMA_OK;
 }

@@ -111,7 +111,7 @@ struct Fp8QuantParams {
     uint32_t q_plane, s_plane; // byte step between planes
     uint32_t k_row_b;          // K * 2: columns of X at or beyond it read as zero
     int32_t rows;              // rows of a plane (padded); rows past the extent of X read as zero
-    int32_t lane_shift;        // 2^lane_shift neighbouring threads along a row
+    int32_t lane_shift;        // combine kernels: 2^lane_shift neighbouring threads along a row
 };
 
 } // namespace lcma
