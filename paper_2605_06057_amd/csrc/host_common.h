@@ -95,7 +95,7 @@ lcma_status prepare_b_planes(bool transposed, int64_t N, int64_t K, const void *
 
 int dtype_size(int dtype); // bytes, or 0
 
-// The kernels that stream whole matrices (Combine A, Combine B of N x K weights, Combine H, the FP8 quantisations) give 16 bytes of
+// The kernels that stream whole matrices (Combine A, Combine B of N x K weights, Combine H, the combinations in FP8) give 16 bytes of
 // a row to a thread; a work-group of 256 covers 2^s vectors of 256 / 2^s rows.  A whole wave along a row (s = 6, 1 KB in one
 // piece) where the rows are a whole number of them or nearly so, else half or a quarter: Combine H at the FFN shape 120.7
 // us with a quarter wave (5.35 TB/s), 112 with a whole one, 101 with streamed loads besides (6.40 TB/s, a device copy 6.3).
@@ -105,6 +105,14 @@ inline int lane_shift_of(int64_t vectors, int64_t rows) {
         if (idle * 4 <= vectors && ((rows << s) + 255) / 256 <= 65535) return s; // (the rows are the y dimension of the grid)
     }
     return 4;
+}
+// Combine H: many 16-bit planes that the caches hold, up to 24 MB all together, are read with the ordinary policy and a quarter wave along
+// a row: <4,4,4;49> on planes of 128 x 1024 (12.8 MB) 7.9 against 10.5 us.  Not so seven planes: behind the GEMM stage, whose stores pass
+// the caches by, the other form is level or faster (2048 x 4096 x 4096 as a whole 72.4 us against 72.9).
+inline void combine_h_access(CombHParams &p, int planes, int64_t rows, int64_t cols, int64_t plane_es, int64_t c_es) {
+    const bool small = plane_es == 2 && planes > 16 && planes * rows * cols * plane_es <= 24000000;
+    p.lane_shift = small ? 4 : lane_shift_of(cols * c_es / 16, rows);
+    p.streamed = !small;
 }
 // work-groups along the rows and along a row
 inline int row_groups(int64_t rows, int s) { return (int)(((rows << s) + 255) / 256); }

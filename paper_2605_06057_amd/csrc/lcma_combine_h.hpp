@@ -19,9 +19,9 @@
 
 namespace lcma {
 
-// Cache policy of the loads of the planes: 16-bit planes are read streamed as well (8192 x 14336, <2,2,2;7>: 109 -> 100 us with a
-// whole wave along a row; <4,4,4;49> 164 -> 155), fp32 planes are not (25 planes of 2048 x 2048: 114 -> 153 us).
-template <int ES> constexpr int kPlaneLoad = ES == 2 ? kStreamed : 0;
+// Cache policy of the loads of the planes: 16-bit planes that the caches do not hold are read streamed as well (8192 x 14336, <2,2,2;7>: 109
+// -> 100 us with a whole wave along a row; <4,4,4;49> 164 -> 155), many small ones are not (combine_h_access, host_common.h: <4,4,4;49>
+// 358 x 3840 x 832 as a whole 55 us, streamed 59), fp32 planes are not (25 planes of 2048 x 2048: 114 -> 153 us).
 
 // CH (generated): NP planes, NC = m*n outputs with c_i(o), c_j(o); comb(in, o) = Eq. 6 for output o on floats.
 // HT: element type of the planes; IN: storage type of C (same element size).
@@ -38,11 +38,15 @@ template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombH
     if (colb * HV >= p.h_ld_b || row * p.h_ld_b >= p.h_plane_b) return;
     // the planes stay in registers as loaded and are widened where a sum uses them (see forget_derived)
     u32x4 h[HV][CH::NP];
+    auto load = [&](auto policy) {
 #pragma unroll
-    for (int r = 0; r < CH::NP; ++r)
+        for (int r = 0; r < CH::NP; ++r)
 #pragma unroll
-        for (int q = 0; q < HV; ++q)
-            h[q][r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + colb * HV + q * 16), (int)(r * p.h_plane_b), kPlaneLoad<HT::ES>);
+            for (int q = 0; q < HV; ++q)
+                h[q][r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + colb * HV + q * 16), (int)(r * p.h_plane_b), decltype(policy)::value);
+    };
+    if (HT::ES == 2 && (CH::NP <= 16 || p.streamed)) load(std::integral_constant<int, kStreamed>{});
+    else load(std::integral_constant<int, 0>{});
     constexpr int HPV = 16 / HT::ES; // elements of a plane per 16-byte vector
     for_each_const<CH::NC>([&](auto oc_) {
         constexpr int o = decltype(oc_)::value;

@@ -27,7 +27,7 @@ namespace lcma {
 // the first to leave the L2 and the Infinity Cache, instead of displacing the planes At_r / Bt_r that the work-groups of
 // the batched GEMM read again and again.  Measured on the whole of Algorithm 1, bf16: +4 % at 8192 x 14336 x 4096, +6 %
 // at 4096^3.  Loads are NOT given the policy: on the inputs A and B it makes Combine A / Combine B 15 % (large shape)
-// to 90 % (4096^3) slower, on fp32 planes H_r a third; fp16 planes are read with it (kPlaneLoad, lcma_combine_h.hpp).
+// to 90 % (4096^3) slower, on fp32 planes H_r a third; large fp16 planes are read with it (lcma_combine_h.hpp).
 constexpr int kStreamed = 2;
 
 

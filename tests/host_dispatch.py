@@ -26,6 +26,7 @@ static std::string args(const lcma::PlaneGemmParams *p) {
 static std::string args(const lcma::FewRowsParams *p) {
     return num("tile", p->block_rows) + num("steps", p->steps) + num("slices", p->slices) + num("slice_steps", p->slice_steps);
 }
+static std::string args(const lcma::CombHParams *p) { return num("lanes", 1 << p->lane_shift) + num("streamed", p->streamed); }
 """
 
 _lib = None
@@ -52,7 +53,8 @@ def lib():
     with open(stub, "w") as f:
         f.write(STUBS)
         for n in names:
-            kind = "FewRowsParams" if "few_rows" in n else "PlaneGemmParams" if n.startswith(("lcma_launch_pg_", "lcma_launch_pp")) else None
+            kind = ("FewRowsParams" if "few_rows" in n else "PlaneGemmParams" if n.startswith(("lcma_launch_pg_", "lcma_launch_pp")) else
+                    "CombHParams" if "_comb_h" in n else None)
             f.write(f'extern "C" int {n}(const lcma::{kind} *p) {{ return note("{n[12:]}", args(p)); }}\n' if kind else
                     f'extern "C" int {n}() {{ return note("{n[12:]}"); }}\n')
     so = os.path.join(out, "dispatch.so")

@@ -88,6 +88,17 @@ def test_nt_ws_between_the_plane_gemm_and_its_kin():
     assert ran[0].startswith("pg_bf16_t128_bf16 jobs=128 units=512 "), ran
 
 
+# Combine H, lanes along a row and cache policy: many small fp16 planes 7.9 us with 16 lanes, 10.5 with 64 and streamed loads (<4,4,4;49>, planes
+# of 128 x 1024)
+@pytest.mark.parametrize("scheme,shape,lanes", [("strassen2", (358, 3840, 832), 16), ("laderman", (1340, 744, 2464), 16), ("strassen", (2048, 4096, 4096), 64),
+                                                ("strassen", (8192, 14336, 4096), 64)], ids=str)
+def test_combine_h_access(scheme, shape, lanes):
+    M, N, K = shape
+    status, ran = D.call("lcma_gemm_unfused", ctypes.c_int(1), M, N, K, D.A, K, D.B, N, D.C, N, ctypes.c_int(D.DTYPES["bf16"]), D.Scheme(scheme), D.WORK,
+                         1 << 40, ctypes.c_int(0), ctypes.c_void_p(None))
+    assert status == 0 and ran[-1] == f"comb_h_{scheme}_bf16 lanes={lanes} streamed={int(lanes == 64)}"
+
+
 # ------------------------------------------------------------------ the GPU tests of these kernels reach them
 def gemm_on_lines(M, N, K, dtype, nk):
     import test_gpu_plain_pingpong as T
