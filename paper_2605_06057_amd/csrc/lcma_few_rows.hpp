@@ -2,19 +2,19 @@
 //
 // With M of a few dozen the product is bound by reading W once (N K 2 bytes), not by the matrix pipe, and tiles of 128 x 128
 // leave most of the chip idle: 64 x 4096 x 4096 is 32 of them, each walking all of K in 64 dependent steps.  Here a
-// work-group owns a tile of 64 x 64 (32 x 32, 16 x 16) of C and its eight waves split K between them, two neighbouring steps
-// of 32 elements (a 128-byte line of every row) to a wave in turn.  Nothing is shared between waves, so nothing is staged:
-// fragments come from memory straight into registers, a batch of U steps ahead of the matrix instructions (16x16x32: 16 rows
-// of W and 16 of A per fragment, 16 bytes per lane).  At the end the eight partial tiles are added in LDS in ascending wave
-// order, in fp32, and rounded once.
-// What bounds it is what ONE CU can pull in, 33 to 42 bytes/ns whatever the source (few_rows_plan takes 36): so the bytes per work-group decide, a
-// large tile of C reads least in all, and when large tiles alone would not fill the chip K is cut into slices for
-// work-groups of their own, whose fp32 partial products a second kernel adds in ascending order (3.7 us for its launch).
-// Measured (bf16, us, against the 128 x 128 plane GEMM): 64 x 4096 x 4096 14.3 (four slices; one 31.2) against 41.4; 64 x 4096
-// x 14336 36.1 against 199 (117 MB of weights: 3.3 TB/s); 64 x 14336 x 4096 35.9 (one slice) against 61.4; 128 x 4096 x 4096
-// 21.5 against 42.1; 64 x 1024 x 1024 3.9 (tiles of 16) against 10.1; 256 x 1024 x 1024 5.8 (tiles of 32) against 10.1.  Few columns
-// (fp16): 4266 x 128 x 4288 33 against 48, 4095 x 192 x 2176 19.6 against 24 (97 and 37 with the blocks of columns dealt to the XCDs
-// one by one, which leaves most XCDs without work where there are fewer than eight).
+// work-group owns a tile of 64 x 64 (32 x 32, 16 x 16) of C and its waves split K between them, a line (64 k, 128 bytes of
+// every row) to a wave in turn.  Nothing is shared between waves, so there is no barrier in the loop: each wave has stages of its own in
+// LDS, sends the loads of its next lines straight into them, waits for a line by count and reads its fragments.  At the end the
+// partial tiles are added in LDS in ascending wave order, in fp32, and rounded once.
+// What bounds it is what ONE CU can take in.  A load whose neighbouring lanes ask for one row after the other, as the fragments of the matrix
+// instructions want them, takes a CU 64 clocks (38 bytes/ns, measured, 16 rows x 64 bytes and 32 x 32 alike); with eight lanes to the
+// 128 bytes of a row it takes 16 (140 to 150 from the L2, 100 with all CUs at it).  So lines travel whole into LDS and the fragments are read there.
+// The bytes per work-group decide next: a large tile of C reads least in all, and when large tiles alone would not fill the chip
+// K is cut into slices for work-groups of their own, whose fp32 partial products a second kernel adds in ascending order (3 us).
+// Measured (bf16, us, fragments from memory straight into registers / this): 64 x 4096 x 4096 in four slices 14.9 / 13.1, in one piece
+// 17.3 / 9.3; 64 x 4096 x 14336 39 / 31 (117 MB of weights: 3.8 TB/s); 64 x 14336 x 4096 39 / 29; 128 x 4096 x 4096 21.8 / 14.3;
+// 256 x 1024 x 1024 5.8 / 4.2; 65 x 4088 x 4160 23.6 / 14.0.  Few columns (fp16): 4266 x 128 x 4288 31, 4095 x 192 x 2176 19.6 (97 and 37
+// with the blocks of columns dealt to the XCDs one by one, which leaves most XCDs without work where there are fewer than eight).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -35,92 +35,140 @@ template <> struct Mma16<BF16> {
     static LCMA_DEV f32x4 run(frag a, frag b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 
-// MT, NT: 16-row fragments of A and of W per wave; U: steps of a batch.
-template <class KIND, int MT, int NT, int U> struct FewRows {
-    static constexpr int WK = 8, ROWS = 16 * MT, COLS = 16 * NT; // waves, all along K; the tile of C
-    static constexpr int PITCH = COLS + 4; // (floats; 4: the four row groups of a write meet different banks)
-    static constexpr int LDS_BYTES = WK * ROWS * PITCH * 4;
-    static_assert(LDS_BYTES <= 160 * 1024 && U % 2 == 0, "LDS budget of one CU; whole lines per batch");
+// s_waitcnt for all but the N youngest vector memory instructions; nothing moves across it
+template <int N> LCMA_DEV void wait_loads() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 0x0F70);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// T: rows and columns of the tile of C; WK waves, all along K; S lines of 64 k of a wave in flight.
+template <class KIND, int T, int WK, int S> struct FewRows {
+    static constexpr int F = T == 16 ? 16 : 32, NF = T / F, KF = 64 / (512 / F); // 16x16x32 or 32x32x16 instructions; fragments of a line along K
+    static constexpr int LOADS = T / 8, HALF = T * 128, STAGE = 2 * HALF;         // direct loads of 1 KB and bytes of a line of either operand
+    static constexpr int PITCH = T + 4;                                           // (floats; 4: the row groups of a write meet different banks)
+    static constexpr int SUMS = WK * T * PITCH * 4, STAGES = WK * S * STAGE, LDS_BYTES = SUMS > STAGES ? SUMS : STAGES;
+    static_assert(LDS_BYTES <= 160 * 1024 && (S == 2 || S == 4) && 2 * LOADS * S <= 63, "LDS budget of one CU; counter of loads");
     using Frag = typename Mma16<KIND>::frag;
+    using Acc = std::conditional_t<F == 16, f32x4, f32x16>;
 
     static LCMA_DEV void run(const FewRowsParams &p, LCMA_LDS char *lds) {
-        const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+        LCMA_LDS char *mine = lds + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (S * STAGE);
+        body(p, lds, mine, mine + STAGE, mine + (S == 4 ? 2 * STAGE : 0), mine + (S == 4 ? 3 * STAGE : 0));
+    }
+    // s0 .. s3: the stages of the wave.  restrict: the loads in flight towards one do not touch what is read from another (the
+    // compiler would otherwise wait for all of them in front of every read)
+    static LCMA_DEV void body(const FewRowsParams &p, LCMA_LDS char *lds, LCMA_LDS char *__restrict__ s0, LCMA_LDS char *__restrict__ s1,
+                              LCMA_LDS char *__restrict__ s2, LCMA_LDS char *__restrict__ s3) {
+        const int lane = threadIdx.x & 63, fr = lane & (F - 1), fk = lane / F;
         const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.A), 0, (int)p.a_bytes, 0x00020000);
         const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.W), 0, (int)p.w_bytes, 0x00020000);
         // an eighth of the work-groups to every XCD (they go to the eight in turn), cut along the longer side of C and, first, along K: an
         // XCD reads its part of the longer operand alone and few slices of the other one
-        const int col_blocks = p.partial_ld / COLS, jobs = col_blocks * p.slices, groups = jobs * p.row_blocks; // (groups: the grid)
+        const int col_blocks = p.partial_ld / T, jobs = col_blocks * p.slices, groups = jobs * p.row_blocks; // (groups: the grid)
         const int share = (groups + 7) / 8, left = groups % 8, xcd = blockIdx.x % 8;
         const int id = (left && xcd > left ? left * share + (xcd - left) * (share - 1) : xcd * share) + blockIdx.x / 8;
-        const bool tall = p.row_blocks * ROWS > p.partial_ld;
+        const bool tall = p.row_blocks * T > p.partial_ld;
         const int inner = tall ? jobs : p.row_blocks, hi = id / inner, lo = id - hi * inner;
         const int mb = tall ? hi : lo, job = tall ? lo : hi, slice = job / col_blocks, cb = job - slice * col_blocks;
-        const int first = slice * p.slice_steps, end = first + p.slice_steps < p.steps ? first + p.slice_steps : p.steps;
-        // rows past M or N lie past the extents and read as zero
-        uint32_t a_off[MT], b_off[NT];
+        const int lines = p.steps / 2, per = p.slice_steps / 2, first = slice * per, end = first + per < lines ? first + per : lines;
+        // A load brings 8 rows of 128 bytes, lanes 8 i to 8 i + 7 one row.  Rows past M or N lie past the extents and read as zero; 16-byte
+        // chunk c of row i sits at position c ^ (i / 2 % 8), so that 16 rows at one chunk column meet all banks once.
+        uint32_t av[2], bv[2]; // even and odd loads of a line
 #pragma unroll
-        for (int i = 0; i < MT; ++i) a_off[i] = (uint32_t)(mb * ROWS + i * 16 + r) * p.lda_b + q * 16;
-#pragma unroll
-        for (int j = 0; j < NT; ++j) b_off[j] = (uint32_t)(cb * COLS + j * 16 + r) * p.ldw_b + q * 16;
-        f32x4 acc[MT][NT];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        struct Batch {
-            u32x4 a[U][MT], b[U][NT];
-        };
-        auto load = [&](Batch &x, int at) { // a step past the end reads from the end of the extents: zeros
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int step = at + (u >> 1) * (2 * WK) + 2 * wk + (u & 1); // (two steps are a 128-byte line of a row)
-                const uint32_t ka = step < end ? (uint32_t)step * 64 : p.a_bytes, kb = step < end ? (uint32_t)step * 64 : p.w_bytes;
-#pragma unroll
-                for (int j = 0; j < NT; ++j) x.b[u][j] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)b_off[j], (int)kb, 0);
-#pragma unroll
-                for (int i = 0; i < MT; ++i) x.a[u][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_off[i], (int)ka, 0);
-            }
-        };
-        auto multiply = [&](const Batch &x) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        acc[i][j] = Mma16<KIND>::run(__builtin_bit_cast(Frag, x.a[u][i]), __builtin_bit_cast(Frag, x.b[u][j]), acc[i][j]);
-        };
-        Batch even, odd;
-        load(even, first);
-        for (int s = first;;) { // (uniform: all waves run the same number of batches)
-            load(odd, s + U * WK);
-            multiply(even);
-            if ((s += U * WK) >= end) break;
-            load(even, s + U * WK);
-            multiply(odd);
-            if ((s += U * WK) >= end) break;
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t c = ((lane & 7) ^ (lane >> 4) ^ (4 * i)) * 16;
+            av[i] = (uint32_t)(mb * T + (lane >> 3)) * p.lda_b + c;
+            bv[i] = (uint32_t)(cb * T + (lane >> 3)) * p.ldw_b + c;
         }
-        LCMA_LDS float *mine = (LCMA_LDS float *)lds + wk * (ROWS * PITCH);
+        auto load = [&](LCMA_LDS char *st, int line) { // a line past the end is read from the end of the extents: zeros
+            const uint32_t ka = line < end ? (uint32_t)line * 128 : p.a_bytes, kb = line < end ? (uint32_t)line * 128 : p.w_bytes;
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+            for (int i = 0; i < LOADS; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LCMA_LDS void *)(st + i * 1024), 16, (int)av[i & 1], (int)(ka + i * 8 * p.lda_b), 0, 0);
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
+            for (int i = 0; i < LOADS; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (LCMA_LDS void *)(st + HALF + i * 1024), 16, (int)bv[i & 1], (int)(kb + i * 8 * p.ldw_b), 0, 0);
+        };
+        uint32_t frag[KF]; // of this lane's 16 bytes in either operand's rows
 #pragma unroll
-                for (int v = 0; v < 4; ++v) mine[(i * 16 + q * 4 + v) * PITCH + j * 16 + r] = acc[i][j][v];
+        for (int k = 0; k < KF; ++k) frag[k] = fr * 128 + ((k * (64 / F) + fk) ^ (fr >> 1 & 7)) * 16;
+        Acc acc[NF][NF];
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+#pragma unroll
+                for (int v = 0; v < F * F / 64; ++v) acc[i][j][v] = 0.f;
+        auto step = [&](LCMA_LDS char *st, int line) {
+            Frag a[KF][NF], b[KF][NF];
+            wait_loads<2 * LOADS *(S - 1)>();
+#pragma unroll
+            for (int k = 0; k < KF; ++k)
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    a[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + frag[k] + i * F * 128));
+                    b[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + HALF + frag[k] + i * F * 128));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): what was read has left LDS, so its place may be loaded anew
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            load(st, line + S * WK);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < KF; ++k)
+#pragma unroll
+                for (int i = 0; i < NF; ++i)
+#pragma unroll
+                    for (int j = 0; j < NF; ++j) {
+                        if constexpr (F == 16) acc[i][j] = Mma16<KIND>::run(a[k][i], b[k][j], acc[i][j]);
+                        else Mma<KIND>::run(a[k][i], b[k][j], acc[i][j]);
+                    }
+        };
+        int line = first + wk;
+        load(s0, line);
+        load(s1, line + WK);
+        if constexpr (S == 4) {
+            load(s2, line + 2 * WK);
+            load(s3, line + 3 * WK);
+        }
+        while (line < end) {
+            step(s0, line);
+            if ((line += WK) >= end) break;
+            step(s1, line);
+            if constexpr (S == 4) {
+                if ((line += WK) >= end) break;
+                step(s2, line);
+                if ((line += WK) >= end) break;
+                step(s3, line);
+            }
+            line += WK;
+        }
+        wait_loads<0>();
+        __syncthreads(); // no load is in flight and every wave has read its last line: the partial tiles take the place of the stages
+        LCMA_LDS float *mine = (LCMA_LDS float *)lds + wk * (T * PITCH);
+#pragma unroll
+        for (int i = 0; i < NF; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+#pragma unroll
+                for (int v = 0; v < F * F / 64; ++v) mine[(i * F + (v >> 2) * 8 + fk * 4 + (v & 3)) * PITCH + j * F + fr] = acc[i][j][v];
         __syncthreads();
         const auto rc = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)p.c_bytes, 0x00020000);
-        for (int t = threadIdx.x; t < ROWS * COLS / 4; t += 512) { // four neighbouring columns
-            const int row = t / (COLS / 4), col = t % (COLS / 4) * 4;
+        for (int t = threadIdx.x; t < T * T / 4; t += 64 * WK) { // four neighbouring columns
+            const int row = t / (T / 4), col = t % (T / 4) * 4;
             const LCMA_LDS float *at = (const LCMA_LDS float *)lds + row * PITCH + col;
             f32x4 sum = *(const LCMA_LDS f32x4 *)at;
 #pragma unroll
-            for (int k = 1; k < WK; ++k) sum += *(const LCMA_LDS f32x4 *)(at + k * ROWS * PITCH);
-            const int m = mb * ROWS + row;
+            for (int k = 1; k < WK; ++k) sum += *(const LCMA_LDS f32x4 *)(at + k * T * PITCH);
+            const int m = mb * T + row;
             if (p.slices > 1) { // (the second kernel adds the slices)
-                *(f32x4 *)((float *)p.partial + ((int64_t)slice * p.row_blocks * ROWS + m) * p.partial_ld + cb * COLS + col) = sum;
+                *(f32x4 *)((float *)p.partial + ((int64_t)slice * p.row_blocks * T + m) * p.partial_ld + cb * T + col) = sum;
             } else {
-                const uint32_t colb = (uint32_t)(cb * COLS + col) * 2;
+                const uint32_t colb = (uint32_t)(cb * T + col) * 2;
                 const uint32_t off = colb < p.n_row_b ? (uint32_t)m * p.ldc_b + colb : p.c_bytes; // rows past M: past the extent
                 const u32x2 v = {Round<KIND>::run(sum[0]) | (Round<KIND>::run(sum[1]) << 16), Round<KIND>::run(sum[2]) | (Round<KIND>::run(sum[3]) << 16)};
                 __builtin_amdgcn_raw_buffer_store_b64(v, rc, (int)off, 0, 0);
