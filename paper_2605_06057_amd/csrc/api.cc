@@ -76,17 +76,18 @@ static bool spans_fit(const Variant &v, int64_t M, int64_t N, int64_t K, int64_t
 // 857 x 1048 x 808 55.4 / 23.9; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
 // K x N kernels for any form of B, so that both layouts make the same choice and give the same bits, and prepared operands
 // (whose planes carry the same roundings) the same precision.
-// The 16-bit ones (csrc/lcma_direct16.hpp): 16 x 64 tiles, 4.0 us a step of 64 for the four waves (measured 2.6 to 4.2 for K x N, 2.9 to
-// 4.6 for N x K) and 2.5 a round; the staged kernel takes 0.90 us (fp16 0.72; N x K 0.72, 0.55) a step of 32 however few its
-// work-groups are.  Both types and layouts at 360 shapes, M 16 to 2048, K 64 to 9024: where this chooses the direct kernel it
-// is nowhere the slower one, least of all with N x K fp16 (1024^3 15.9 against 15.6, most others a tenth or more).
+// The 16-bit ones (csrc/lcma_direct16.hpp), tiles of 16 x 64 and 32 x 64: a step of 64 k takes 0.68 and 0.83 us (fp16 0.62, 0.70) with few
+// work-groups and 0.82 and 0.98 (0.75, 0.92) with 256, a round 2.9 and 3.8 besides; the staged kernel 5.4 and 0.90 us (fp16 0.72; N x K
+// 0.73, 0.56) a step of 32 however few its work-groups are.  The N x K time is the one compared with, so that neither layout loses
+// by the common choice: on 70 shapes, M 16 to 4096, K 64 to 14336, both types and layouts, no choice of a direct kernel is slower than the
+// staged one (1991 x 1120 x 12592 fp16 stays with it: 142 and 145 against 150 and 165), and none misses the best by more than 6 %.
 // A direct kernel pads K further than the staged one in 16 bit: where its spans do not fit, the staged one runs.
 static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const Variant *staged = pick_variant(v->scheme_id, v->dtype, M, N, K, 0, 0), *best = v;
     if (!staged) return v;
     double best_us = 0.9 * 1e6 * predict_variant(*staged, M, N, K);
     // (16 bit: the published prediction knows no latency; a step of 32 takes this long however few work-groups there are)
-    if (v->dtype != LCMA_F32) best_us = std::max(best_us, 3.0 + (v->dtype == LCMA_BF16 ? 0.90 : 0.72) * (double)round_up(K, 32 * staged->k) / (32.0 * staged->k));
+    if (v->dtype != LCMA_F32) best_us = std::max(best_us, 5.4 + (v->dtype == LCMA_BF16 ? 0.73 : 0.56) * (double)round_up(K, 32 * staged->k) / (32.0 * staged->k));
     for (int i = 0; i < kVariantCount; ++i) {
         const Variant &d = kVariants[i];
         if (!d.direct || d.scheme_id != v->scheme_id || d.dtype != v->dtype || d.b_nk != v->b_nk || d.prepared != v->prepared ||
@@ -95,8 +96,17 @@ static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_
         const Padded q = padded(d, M, N, K); // (either layout of a dense B, for the same choice)
         if (std::max((q.K - 1) * N + q.N, (q.N - 1) * K + q.K) * dtype_size(d.dtype) >= (int64_t)1 << 31) continue;
         const int64_t bk = q.K / d.k, groups = (q.M / d.m / d.TM) * (q.N / d.n / d.TN);
-        const double rounds = (double)((groups + 255) / 256), steps = (double)((bk / d.TK + d.direct - 1) / d.direct);
-        const double us = 3.0 + (v->dtype == LCMA_F32 ? rounds * (d.TM == 16 ? 0.0145 * (double)bk + 0.8 : 0.041 * (double)bk + 2.5) : rounds * (4.0 * steps + 2.5));
+        const double rounds = (double)((groups + 255) / 256);
+        double us;
+        if (v->dtype == LCMA_F32) {
+            us = 3.0 + rounds * (d.TM == 16 ? 0.0145 * (double)bk + 0.8 : 0.041 * (double)bk + 2.5);
+        } else {
+            const bool bf = v->dtype == LCMA_BF16;
+            const double few = d.TM == 16 ? (bf ? 0.68 : 0.62) : bf ? 0.83 : 0.70, all = d.TM == 16 ? (bf ? 0.82 : 0.75) : bf ? 0.98 : 0.92;
+            const double last = (double)(groups % 256) / 256.0; // (a whole last round: no partial one)
+            const double step = (double)(groups / 256) * all + (last > 0.0 ? few + (all - few) * last : 0.0);
+            us = 1.2 + rounds * (d.TM == 16 ? 2.9 : 3.8) + step * (double)(bk / d.TK);
+        }
         if (us < best_us) {
             best = &d;
             best_us = us;

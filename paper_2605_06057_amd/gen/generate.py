@@ -186,7 +186,7 @@ def plan(s: Scheme, v: Variant):
     """On-chip resource planning: (accumulator registers per lane, LDS bytes, peak live C tiles)."""
     es = 4 if v.dtype == "f32" else 2
     if v.ks:  # every product's accumulators; the partial tiles of C of all waves, rows padded by 16 bytes
-        assert v.chunk >= s.R and (v.dtype == "f32" or (v.TM, v.TN, v.pb) == (16, 64, 0))
+        assert v.chunk >= s.R and (v.dtype == "f32" or (v.TM in (16, 32) and (v.TN, v.pb, v.ks) == (64, 0, 4)))
         return s.R * v.TM * v.TN // 64, v.ks * s.m * s.n * v.TM * (v.TN + 4) * 4, 0, s.R, 0, 0
     tile_regs = (v.TM // v.wgm // 32) * (v.TN // v.wgn // 32) * 16
     chunks = chunks_of(s, v)
@@ -406,7 +406,7 @@ def emit_direct_tail(s: Scheme, v: Variant) -> list[str]:
     w(f"    static constexpr int NC = {s.m * s.n};")
     w(f"    static LCMA_DEV constexpr int c_i(int o) {{ return o / {s.n}; }}")
     w(f"    static LCMA_DEV constexpr int c_j(int o) {{ return o % {s.n}; }}")
-    w("    template <int MI, int NI> static LCMA_DEV f32x4 comb(const f32x4 (&h)[Chunk0::NP][MI][NI], int o, int mi, int ni) {")
+    w("    template <class Acc, int MI, int NI> static LCMA_DEV Acc comb(const Acc (&h)[Chunk0::NP][MI][NI], int o, int mi, int ni) {")
     w("        switch (o) {")
     for i in range(s.m):
         for j in range(s.n):
@@ -417,18 +417,19 @@ def emit_direct_tail(s: Scheme, v: Variant) -> list[str]:
     w("    }")
     w("};")
     if v.dtype != "f32":
-        w(f"using D = Direct16<{CPP_TYPES[v.dtype][0]}, {v.ks}, {'true' if v.tb else 'false'}, Chunk0, Blocks>;")
+        w(f"using D = Direct16<{CPP_TYPES[v.dtype][0]}, {v.TM}, {'true' if v.tb else 'false'}, Chunk0, Blocks>;")
     else:
         w(f"using D = Direct<{v.TM // 16}, {v.TN // 16}, {v.ks}, {'true' if v.tb else 'false'}, {'true' if v.pb else 'false'}, Chunk0, Blocks>;")
     w("} // namespace")
     w("")
-    w(f'extern "C" __global__ __launch_bounds__({64 * v.ks}, {max(1, v.ks // 4)}) void lcma_k_{v.name}(const lcma::Params p) {{')
+    threads = 64 * v.ks if v.dtype == "f32" else 512  # 16 bit: two waves along the columns besides
+    w(f'extern "C" __global__ __launch_bounds__({threads}, {threads // 256}) void lcma_k_{v.name}(const lcma::Params p) {{')
     w("    __shared__ __attribute__((aligned(16))) char smem[D::LDS_BYTES];")
     w("    D::run(p, (LCMA_LDS char *)smem);")
     w("}")
     w("")
     w(f'extern "C" int lcma_launch_{v.name}(const lcma::Params *p, int grid, void *stream) {{')
-    w(f"    lcma_k_{v.name}<<<dim3(grid), dim3({64 * v.ks}), 0, (hipStream_t)stream>>>(*p);")
+    w(f"    lcma_k_{v.name}<<<dim3(grid), dim3({threads}), 0, (hipStream_t)stream>>>(*p);")
     w("    return (int)hipGetLastError();")
     w("}")
     return L
@@ -847,7 +848,7 @@ def manifest(schemes: dict[str, Scheme] | None = None) -> list[Variant]:
     for name in ("strassen", "winograd"):
         if name in schemes:
             V += [Variant(name, "f32", t, t, 16, chunk=7, ks=8, tb=tb, pb=pb, rank=96) for t in (16, 32) for tb, pb in ((0, 0), (1, 0), (0, 1))]
-    V += [Variant("strassen", dt, 16, 64, 64, chunk=7, ks=4, tb=tb, rank=96) for dt in ("bf16", "f16") for tb in (0, 1)]
+    V += [Variant("strassen", dt, t, 64, 64, chunk=7, ks=4, tb=tb, rank=96) for t in (16, 32) for dt in ("bf16", "f16") for tb in (0, 1)]
     # Every kernel that lcma_gemm can pick for the paper's schemes also exists for B given as the N x K
     # weight matrix ("t"): its B tiles are staged like A's, with 16-byte loads and no transposition.
     from dataclasses import replace
