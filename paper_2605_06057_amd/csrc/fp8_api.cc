@@ -256,7 +256,7 @@ extern "C" lcma_status lcma_fp8_gemm_lcma(int64_t M, int64_t N, int64_t K, const
     h.c_brow = (uint32_t)(g.bm * ldc * 2);
     h.c_bcol = (uint32_t)(g.bn * 2);
     h.n_row_b = (uint32_t)(N * 2);
-    combine_h_access(h, R, g.bm, g.bn, 2, 2);
+    combine_h_access(h, R, g.bm, g.bn, 2);
     if (const int err = sk->launch_comb_h(&h, row_groups(g.bm, h.lane_shift), vector_groups(g.bn * 2 / 16, h.lane_shift), stream))
         return fail(LCMA_ERR_HIP, "%s: Combine-H launch failed with HIP error %d", who, err);
     return LCMA_OK;

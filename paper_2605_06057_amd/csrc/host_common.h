@@ -109,9 +109,9 @@ inline int lane_shift_of(int64_t vectors, int64_t rows) {
 // Combine H: many 16-bit planes that the caches hold, up to 24 MB all together, are read with the ordinary policy and a quarter wave along
 // a row: <4,4,4;49> on planes of 128 x 1024 (12.8 MB) 7.9 against 10.5 us.  Not so seven planes: behind the GEMM stage, whose stores pass
 // the caches by, the other form is level or faster (2048 x 4096 x 4096 as a whole 72.4 us against 72.9).
-inline void combine_h_access(CombHParams &p, int planes, int64_t rows, int64_t cols, int64_t plane_es, int64_t c_es) {
+inline void combine_h_access(CombHParams &p, int planes, int64_t rows, int64_t cols, int64_t plane_es) {
     const bool small = plane_es == 2 && planes > 16 && planes * rows * cols * plane_es <= 24000000;
-    p.lane_shift = small ? 4 : lane_shift_of(cols * c_es / 16, rows);
+    p.lane_shift = small ? 4 : lane_shift_of(cols * plane_es / 16, rows);
     p.streamed = !small;
 }
 // work-groups along the rows and along a row

@@ -9,8 +9,9 @@
 // fall outside the extent of C (dropped by the range check), columns past N are sent there.
 //
 // HBM-bound: reads R/(m n) and writes 1 element per element of C.  One thread handles one 16-byte
-// vector position of C in every plane (two 16-byte loads per plane when the planes hold fp32 and C 16-bit
-// elements) and writes the m*n vectors it yields.
+// vector of every plane and writes the m*n vectors it yields, of 8 bytes where the planes hold fp32 and C 16-bit elements.
+// (Two 16-byte loads per plane and 16-byte vectors of C there: each load takes every second 16 bytes of its lines and the 25 planes
+// of <3,3,3;23> fill 200 registers: 115 us for planes of 2048 x 2048, 4.3 TB/s, now 90, 5.5; 8192 x 14336, <2,2,2;7> 178, now 171.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -19,14 +20,14 @@
 
 namespace lcma {
 
-// Cache policy of the loads of the planes: 16-bit planes that the caches do not hold are read streamed as well (8192 x 14336, <2,2,2;7>: 109
-// -> 100 us with a whole wave along a row; <4,4,4;49> 164 -> 155), many small ones are not (combine_h_access, host_common.h: <4,4,4;49>
-// 358 x 3840 x 832 as a whole 55 us, streamed 59), fp32 planes are not (25 planes of 2048 x 2048: 114 -> 153 us).
+// Cache policy of the loads of the planes: they are read streamed where the caches do not hold them (8192 x 14336, <2,2,2;7> fp16 planes: 109
+// -> 100 us with a whole wave along a row; <4,4,4;49> 164 -> 155; 25 fp32 planes of 2048 x 2048 97 -> 90), many small 16-bit ones are
+// not (combine_h_access, host_common.h: <4,4,4;49> 358 x 3840 x 832 as a whole 55 us, streamed 59).
 
 // CH (generated): NP planes, NC = m*n outputs with c_i(o), c_j(o); comb(in, o) = Eq. 6 for output o on floats.
 // HT: element type of the planes; IN: storage type of C (same element size).
 template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombHParams &p) {
-    constexpr int ES = IN::ES, EPT = 16 / ES, HV = HT::ES / ES; // HV: 16-byte vectors of a plane per vector of C
+    constexpr int ES = IN::ES, HV = HT::ES / ES; // HV: vectors of C per 16 bytes of it
     static_assert(HT::ES == ES || (HT::ES == 4 && ES == 2), "planes in the element size of C, or fp32 planes for 16-bit C");
     const auto rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.H), 0, (int)p.h_bytes, 0x00020000);
     const auto rc = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)p.c_bytes, 0x00020000);
@@ -34,53 +35,40 @@ template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombH
     // of the same rows (4 to 24 % faster than consecutive rows of the same piece)
     const uint32_t sh = (uint32_t)p.lane_shift;
     const uint32_t row = blockIdx.y * (256 >> sh) + (threadIdx.x >> sh);
-    const uint32_t colb = ((blockIdx.x << sh) + (threadIdx.x & ((1u << sh) - 1))) * 16; // byte column inside a block of C
-    if (colb * HV >= p.h_ld_b || row * p.h_ld_b >= p.h_plane_b) return;
+    const uint32_t at = ((blockIdx.x << sh) + (threadIdx.x & ((1u << sh) - 1))) * 16, colb = at / HV; // byte column inside a plane, a block of C
+    if (at >= p.h_ld_b || row * p.h_ld_b >= p.h_plane_b) return;
     // the planes stay in registers as loaded and are widened where a sum uses them (see forget_derived)
-    u32x4 h[HV][CH::NP];
+    u32x4 h[CH::NP];
     auto load = [&](auto policy) {
 #pragma unroll
         for (int r = 0; r < CH::NP; ++r)
-#pragma unroll
-            for (int q = 0; q < HV; ++q)
-                h[q][r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + colb * HV + q * 16), (int)(r * p.h_plane_b), decltype(policy)::value);
+            h[r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + at), (int)(r * p.h_plane_b), decltype(policy)::value);
     };
-    if (HT::ES == 2 && (CH::NP <= 16 || p.streamed)) load(std::integral_constant<int, kStreamed>{});
+    if (CH::NP <= 16 || p.streamed) load(std::integral_constant<int, kStreamed>{});
     else load(std::integral_constant<int, 0>{});
-    constexpr int HPV = 16 / HT::ES; // elements of a plane per 16-byte vector
     for_each_const<CH::NC>([&](auto oc_) {
         constexpr int o = decltype(oc_)::value;
         // (only where the widened copies of all planes would not fit beside them and the planes themselves do, <4,4,4;49>
         // with 16-bit planes: two waves per SIMD instead of one; with fewer planes the barrier only delays the first sums)
-        if constexpr (HV * CH::NP * 4 > 128 && HV * CH::NP * 4 <= 224) {
+        if constexpr (HV == 1 && CH::NP * 4 > 128 && CH::NP * 4 <= 224) forget_derived(h);
+        auto sum = [&](int e) {
+            float col[CH::NP];
 #pragma unroll
-            for (int q = 0; q < HV; ++q) forget_derived(h[q]);
-        }
-        u32x4 v;
-        if constexpr (ES == 2) {
+            for (int r = 0; r < CH::NP; ++r) col[r] = Elem<HT>::get(h[r], e);
+            return Round<IN>::run(CH::comb(col, o));
+        };
+        uint32_t v[4 / HV];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float col0[CH::NP], col1[CH::NP];
-#pragma unroll
-                for (int r = 0; r < CH::NP; ++r) {
-                    col0[r] = Elem<HT>::get(h[(2 * e) / HPV][r], (2 * e) % HPV);
-                    col1[r] = Elem<HT>::get(h[(2 * e + 1) / HPV][r], (2 * e + 1) % HPV);
-                }
-                v[e] = Round<IN>::run(CH::comb(col0, o)) | (Round<IN>::run(CH::comb(col1, o)) << 16);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float col[CH::NP];
-#pragma unroll
-                for (int r = 0; r < CH::NP; ++r) col[r] = Elem<HT>::get(h[0][r], e);
-                v[e] = Round<IN>::run(CH::comb(col, o));
-            }
+        for (int e = 0; e < 4 / HV; ++e) {
+            if constexpr (ES == 2) v[e] = sum(2 * e) | (sum(2 * e + 1) << 16);
+            else v[e] = sum(e);
         }
         const uint32_t cb = (uint32_t)CH::c_j(o) * p.c_bcol + colb;
         const uint32_t off = cb < p.n_row_b ? (uint32_t)CH::c_i(o) * p.c_brow + row * p.ldc_b + cb : p.c_bytes;
-        // (16-byte store: the scalar-offset field stays a literal zero, see Ctx::store_c in lcma_device.hpp)
-        __builtin_amdgcn_raw_buffer_store_b128(v, rc, (int)off, 0, kStreamed);
+        // (stores: the scalar-offset field stays a literal zero, see Ctx::store_c in lcma_device.hpp)
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        if constexpr (HV == 1) __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0], v[1], v[2], v[3]}, rc, (int)off, 0, kStreamed);
+        else __builtin_amdgcn_raw_buffer_store_b64(u32x2{v[0], v[1]}, rc, (int)off, 0, kStreamed);
     });
 }
 

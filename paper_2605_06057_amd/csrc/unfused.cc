@@ -363,9 +363,9 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
         h.c_brow = (uint32_t)(g.bm * ldc * es);
         h.c_bcol = (uint32_t)(g.bn * es);
         h.n_row_b = (uint32_t)(N * es);
-        combine_h_access(h, R, g.bm, g.bn, h_es, es);
+        combine_h_access(h, R, g.bm, g.bn, h_es);
         if (const int err = (h_es != es ? sk->launch_comb_h32 : sk->launch_comb_h)(&h, row_groups(g.bm, h.lane_shift),
-                                                                                   vector_groups(g.bn * es / 16, h.lane_shift), stream))
+                                                                                   vector_groups(g.bn * h_es / 16, h.lane_shift), stream))
             return fail(LCMA_ERR_HIP, "%s: Combine-H launch failed with HIP error %d", who, err);
     } else {
         // stages 3 and 4 in one kernel: group by group, W applied to the fp32 accumulators
