@@ -90,6 +90,34 @@ template <int NB> LCMA_DEV void forget_derived(u32x4 (&raw)[NB]) {
 // by this.
 constexpr int kPrepBSegments = 2;
 
+// Combination r of one vector of every block, rounded once, to nearest-even (see CH below).
+template <class IN, class CH, int r> LCMA_DEV u32x4 combination(const u32x4 (&in)[CH::NB]) {
+    constexpr int EPT = 16 / IN::ES;
+    if constexpr (IN::ES == 2) {
+        f16x8 h;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            float col[CH::NB];
+#pragma unroll
+            for (int t = 0; t < CH::NB; ++t) col[t] = Elem<IN>::get(in[t], e);
+            float o = CH::comb(col, r);
+            if (CH::residual(r)) o -= (float)(_Float16)o; // what rounding the sum loses (exact in fp32)
+            h[e] = (_Float16)o;
+        }
+        return __builtin_bit_cast(u32x4, h);
+    } else {
+        f32x4 f;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            float col[CH::NB];
+#pragma unroll
+            for (int t = 0; t < CH::NB; ++t) col[t] = Elem<IN>::get(in[t], e);
+            f[e] = CH::comb(col, r);
+        }
+        return __builtin_bit_cast(u32x4, f);
+    }
+}
+
 // CH (generated): NB raw blocks with b_l(t), b_j(t); NP outputs; comb(in, r) = Eq. 4 for product r on floats;
 // residual(r): plane r holds what rounding that sum to fp16 loses instead of the rounded sum (16-bit types only).
 template <class IN, class CT, class CH> LCMA_DEV void prepare_b_tile(const PrepParams &p) {
@@ -97,18 +125,27 @@ template <class IN, class CT, class CH> LCMA_DEV void prepare_b_tile(const PrepP
     constexpr int KV = kPrepBSegments;
     constexpr int KS = 64 / ES;                     // k rows per 64-byte segment of an output row (32 or 16)
     constexpr int KT = KV * KS;                     // k rows of the tile
-    constexpr int PITCH = KV * 64 + 16;             // LDS row pitch in bytes, 16-byte aligned
+    constexpr int VPR = 64 / EPT;                   // vectors of a row of the tile
+    constexpr int PITCH = KV * 64;                  // LDS row pitch in bytes
+    static_assert(KV == 2 && VPR * KS == 256, "rows of eight 16-byte chunks; a vector of every second row a thread");
     static_assert(CT::ES == ES, "the output keeps the element size");
-    __shared__ __attribute__((aligned(16))) char tile[64 * PITCH];
+    // Up to nine blocks (72 KB of LDS, two work-groups per CU): all of them are transposed, behind one barrier, and the sums are formed
+    // from what is read back; <3,3,3;23> on 6144 x 6144 66 -> 63 us, 744 x 2464 11.3 -> 7.8, <2,2,2;7> 1.00.  More (16 for <4,4,4;49>: 128 KB):
+    // the sums are formed first and the tile of each product is transposed in turn, two barriers a product.
+    constexpr bool BLOCKS = CH::NB <= 9;
+    constexpr int TILE = 64 * PITCH;
+    __shared__ __attribute__((aligned(16))) char tile[(BLOCKS ? CH::NB : 1) * TILE];
     const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.B), 0, (int)p.b_bytes, 0x00020000);
     const auto rt = __builtin_amdgcn_make_buffer_rsrc(p.Bt, 0, (int)p.bt_bytes, 0x00020000);
     const int tid = threadIdx.x;
     // work-groups that start together cover consecutive pieces of the same 64 rows of the planes (23 % faster at
     // 8192 x 14336 x 4096 than the other order, which reads B in whole rows instead)
     const int z0 = blockIdx.y * 64, y0 = blockIdx.x * KT;
-    // a lane takes KV consecutive k rows and consecutive lanes the next ones, so that the transposed LDS writes are
-    // whole dwords at consecutive addresses
-    const int ky = tid % KS, tx = tid / KS; // tx: which vector of EPT columns
+    // A thread takes KV consecutive k rows, so that the transposed LDS writes are whole dwords, and neighbouring lanes run along a row,
+    // whose 128 bytes one load then asks for once (one row after the other, a lane's 16 bytes each: a load takes a CU four times as
+    // long: 72 us with it, 67 without at 4096 x 14336, <2,2,2;7>).  B is read once and streamed: 71 -> 67 us there, 63 -> 58 for <3,3,3;23>
+    // on 6144 x 6144; 2048 x 4096 x 4096 as a whole 94 -> 87.  16-byte chunk c of LDS row n sits at position c ^ n / EPT % 8: the lanes of a write are in eight chunks.
+    const int ky = tid / VPR, tx = tid % VPR; // tx: which vector of EPT columns
     u32x4 in[KV][CH::NB];
 #pragma unroll
     for (int v = 0; v < KV; ++v)
@@ -120,8 +157,41 @@ template <class IN, class CT, class CH> LCMA_DEV void prepare_b_tile(const PrepP
             // of the extent, which returns zero
             const uint32_t off = colb < p.n_row_b && k < p.bk ? (uint32_t)CH::b_l(t) * p.b_brow + (uint32_t)k * p.ldb_b + colb
                                                               : p.b_bytes;
-            in[v][t] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)off, 0, 0);
+            in[v][t] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)off, 0, kStreamed);
         }
+    if constexpr (BLOCKS) {
+        constexpr int D = 16 / (KV * ES); // threads to a chunk
+#pragma unroll
+        for (int t = 0; t < CH::NB; ++t)
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                char *dst = tile + t * TILE + (tx * EPT + e) * PITCH + (ky / D ^ (tx & 7)) * 16 + ky % D * (KV * ES);
+                if constexpr (ES == 2) *(uint32_t *)dst = __builtin_amdgcn_perm(in[1][t][e / 2], in[0][t][e / 2], e & 1 ? 0x07060302u : 0x05040100u);
+                else {
+                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                    *(u32x2 *)dst = u32x2{in[0][t][e], in[1][t][e]};
+                }
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < KV; ++i) { // 4 * KV threads per output row, 16 bytes each
+            const int idx = tid + 256 * i, rn = idx / (4 * KV), rc = idx % (4 * KV);
+            u32x4 raw[CH::NB];
+#pragma unroll
+            for (int t = 0; t < CH::NB; ++t) raw[t] = *(const u32x4 *)(tile + t * TILE + rn * PITCH + (rc ^ (rn / EPT & 7)) * 16);
+            const uint32_t kb = (uint32_t)y0 * ES + rc * 16; // byte column in the row of the plane
+            for_each_const<CH::NP>([&](auto rc_) {
+                constexpr int r = decltype(rc_)::value;
+                forget_derived(raw);
+                const u32x4 v = combination<IN, CH, r>(raw);
+                // a segment past K/k is dropped (stored to the end of the extent)
+                const uint32_t off = kb < (uint32_t)p.bk * ES ? (uint32_t)r * p.bt_plane_b + (uint32_t)(z0 + rn) * p.bt_ld_b + kb : p.bt_bytes;
+                // (16-byte store: the scalar-offset field stays a literal zero, see Ctx::store_c in lcma_device.hpp)
+                __builtin_amdgcn_raw_buffer_store_b128(v, rt, (int)off, 0, 0);
+            });
+        }
+        return;
+    }
     for_each_const<CH::NP>([&](auto rc_) {
         constexpr int r = decltype(rc_)::value;
 #pragma unroll
@@ -139,7 +209,8 @@ template <class IN, class CT, class CH> LCMA_DEV void prepare_b_tile(const PrepP
                     if (CH::residual(r)) o[v] -= (float)(_Float16)o[v]; // what rounding the sum loses (exact in fp32)
                 }
             }
-            char *dst = tile + (tx * EPT + e) * PITCH + KV * ky * ES;
+            constexpr int D = 16 / (KV * ES); // threads to a chunk
+            char *dst = tile + (tx * EPT + e) * PITCH + (ky / D ^ (tx & 7)) * 16 + ky % D * (KV * ES);
             if constexpr (ES == 2) { // one rounding, nearest-even
                 if constexpr (KV == 2) {
                     typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
@@ -158,7 +229,7 @@ template <class IN, class CT, class CH> LCMA_DEV void prepare_b_tile(const PrepP
 #pragma unroll
         for (int i = 0; i < KV; ++i) {
             const int idx = tid + 256 * i, rn = idx / (4 * KV), rc = idx % (4 * KV);
-            const u32x4 v = *(const u32x4 *)(tile + rn * PITCH + rc * 16);
+            const u32x4 v = *(const u32x4 *)(tile + rn * PITCH + (rc ^ (rn / EPT & 7)) * 16);
             const uint32_t kb = (uint32_t)y0 * ES + rc * 16; // byte column in the row of the plane
             // a segment past K/k is dropped (stored to the end of the extent)
             const uint32_t off = kb < (uint32_t)p.bk * ES ? (uint32_t)r * p.bt_plane_b + (uint32_t)(z0 + rn) * p.bt_ld_b + kb : p.bt_bytes;
@@ -198,30 +269,7 @@ template <class IN, class CT, class CH> LCMA_DEV void prepare_bt_tile(const Prep
     for_each_const<CH::NP>([&](auto rc_) {
         constexpr int r = decltype(rc_)::value;
         forget_derived(in);
-        u32x4 v;
-        if constexpr (ES == 2) {
-            f16x8 h;
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                float col[CH::NB];
-#pragma unroll
-                for (int t = 0; t < CH::NB; ++t) col[t] = Elem<IN>::get(in[t], e);
-                float o = CH::comb(col, r);
-                if (CH::residual(r)) o -= (float)(_Float16)o; // what rounding the sum loses (exact in fp32)
-                h[e] = (_Float16)o; // one rounding, nearest-even
-            }
-            v = __builtin_bit_cast(u32x4, h);
-        } else {
-            f32x4 f;
-#pragma unroll
-            for (int e = 0; e < EPT; ++e) {
-                float col[CH::NB];
-#pragma unroll
-                for (int t = 0; t < CH::NB; ++t) col[t] = Elem<IN>::get(in[t], e);
-                f[e] = CH::comb(col, r);
-            }
-            v = __builtin_bit_cast(u32x4, f);
-        }
+        const u32x4 v = combination<IN, CH, r>(in);
         const uint32_t off = (uint32_t)r * p.bt_plane_b + (uint32_t)rn * p.bt_ld_b + kb;
         // (16-byte store: the scalar-offset field stays a literal zero, see Ctx::store_c in lcma_device.hpp)
         __builtin_amdgcn_raw_buffer_store_b128(v, rt, (int)off, 0, 0);
