@@ -9,7 +9,7 @@
 // Fragments brought from memory straight into registers, as this kernel had them before, take a CU 26 to 64 clocks a load; a
 // load with eight lanes to the 128 bytes of a row takes 16.  So raw lines travel straight into LDS, two or three steps ahead
 // behind counted waits, and K x N operands are read from there with transposing reads.
-// What bounds it: vector instructions (bf16: 272 conversions and sums of 4 clocks per SIMD in a step of the larger tile, against
+// What bounds it: vector instructions (bf16: 224 conversions and sums of 4 clocks per SIMD in a step of the larger tile, against
 // 448 clocks of matrix instructions, with which they overlap in part) and the 40 or 48 KB a CU takes in per step, 70 to 80 bytes/ns
 // beside the reads from LDS.  Measured (us, before, on 16 x 64 tiles or staged / this; three sets of operands in turn, launches from a graph),
 // K x N bf16, N x K bf16, K x N fp16, N x K fp16: 239 x 2176 x 9024 61 / 47, 74 / 48, 54 / 38, 65 / 42; 473 x 344 x 2696 26 / 20, 28 / 21, 23 /
@@ -225,38 +225,62 @@ template <class IN, int TM, bool TB, class CH, class CHH> struct Direct16 {
             // stage of a step in front of it, group 1 in the middle of the step before, which is the same barrier.  A stage is
             // read in the first half of a step only, so it may be loaded anew one barrier later.
             constexpr int FIRST = LOADS / 2; // loads of the first slot
+            // bf16: group 0 writes the blocks of A back as fp16, in the place it read them from, and group 1 reads them so one slot later
+            // (both converting: 1000 x 1544 x 2056 22.4 us, so 21.2).  A loop of its own for each group: the branches on the group inside
+            // one loop cost up to a seventh (fp16 239 x 2176 x 9024 on this tile 45 us, so 38).
+            constexpr bool SHARE = !std::is_same_v<IN, F16>;
             auto loads = [&](int from, int to) {
 #pragma unroll
                 for (int i = from; i < to; ++i) load(lds + ahead, i);
                 __builtin_amdgcn_sched_barrier(0);
             };
             for_each_const<CH::NP>([&](auto s) { ca[s] = cb[s] = __builtin_bit_cast(f16x8, u32x4{0, 0, 0, 0}); });
-            if (group) step_begin<LOADS>();
-            for (int y = 0; y < p.ny; ++y) {
-                if (group) step_begin<63>();
-                else step_begin<LOADS>();
-                multiply(ca, cb, 0, 0, 3);
-                aim(y + 2);
-                read_a_b(base + now + a_frag, base + now + b_frag[0], ar, br);
-                loads(0, FIRST);
+            auto steps = [&](auto g) {
+                constexpr bool G = decltype(g)::value;
+                if constexpr (G) step_begin<LOADS>();
+                for (int y = 0; y < p.ny; ++y) {
+                    if constexpr (G) step_begin<63>();
+                    else step_begin<LOADS>();
+                    multiply(ca, cb, 0, 0, 3);
+                    aim(y + 2);
+                    read_a_b(base + now + a_frag, base + now + b_frag[0], ar, br);
+                    loads(0, FIRST);
+                    if constexpr (SHARE && !G) {
+                        LCMA_LDS char *at = lds + now + a_frag;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    multiply(ca, cb, 0, 3 + t, 4 + t);
-                    a[t] = Convert<IN, F16>::run(ar[t]);
-                    b[t] = Convert<IN, F16>::run(br[t]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (t == 0) {
-                        if (group) step_begin<FIRST>();
-                        else step_begin<63>();
+                        for (int t = 0; t < 4; ++t) {
+                            multiply(ca, cb, 0, 3 + t, 4 + t);
+                            a[t] = Convert<IN, F16>::run(ar[t]);
+                            *(LCMA_LDS f16x8 *)(at + t * A_BLOCK) = a[t];
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        step_begin<63>();
                         loads(FIRST, LOADS);
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) b[t] = Convert<IN, F16>::run(br[t]);
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            multiply(ca, cb, 0, 3 + t, 4 + t);
+                            a[t] = SHARE ? __builtin_bit_cast(f16x8, ar[t]) : Convert<IN, F16>::run(ar[t]);
+                            b[t] = Convert<IN, F16>::run(br[t]);
+                            __builtin_amdgcn_sched_barrier(0);
+                            if (t == (SHARE ? 1 : 0)) {
+                                if constexpr (G) step_begin<FIRST>();
+                                else step_begin<63>();
+                                loads(FIRST, LOADS);
+                            }
+                        }
                     }
+                    CH::comb_a(a, ca);
+                    CH::comb_b(b, cb);
+                    now = after(now);
+                    ahead = after(ahead);
                 }
-                CH::comb_a(a, ca);
-                CH::comb_b(b, cb);
-                now = after(now);
-                ahead = after(ahead);
-            }
-            if (!group) step_begin<63>();
+                if constexpr (!G) step_begin<63>();
+            };
+            if (group) steps(std::true_type{});
+            else steps(std::false_type{});
             multiply(ca, cb, 0, 0, CH::NP);
         } else {
             // A step takes a group two slots, the other group takes the next step one slot later.  A stage is read in one slot, and in
