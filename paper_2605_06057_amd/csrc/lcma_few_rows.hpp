@@ -54,17 +54,8 @@ template <class KIND, int T, int WK, int S> struct FewRows {
     using Acc = std::conditional_t<F == 16, f32x4, f32x16>;
 
     static LCMA_DEV void run(const FewRowsParams &p, LCMA_LDS char *lds) {
-        LCMA_LDS char *mine = lds + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * (S * STAGE);
-        body(p, lds, mine, mine + STAGE, mine + (S == 4 ? 2 * STAGE : 0), mine + (S == 4 ? 3 * STAGE : 0));
-    }
-    // s0 .. s3: the stages of the wave.  restrict: the loads in flight towards one do not touch what is read from another (the
-    // compiler would otherwise wait for all of them in front of every read)
-    static LCMA_DEV void body(const FewRowsParams &p, LCMA_LDS char *lds, LCMA_LDS char *__restrict__ s0, LCMA_LDS char *__restrict__ s1,
-                              LCMA_LDS char *__restrict__ s2, LCMA_LDS char *__restrict__ s3) {
         const int lane = threadIdx.x & 63, fr = lane & (F - 1), fk = lane / F;
         const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.A), 0, (int)p.a_bytes, 0x00020000);
-        const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.W), 0, (int)p.w_bytes, 0x00020000);
         // an eighth of the work-groups to every XCD (they go to the eight in turn), cut along the longer side of C and, first, along K: an
         // XCD reads its part of the longer operand alone and few slices of the other one
         const int col_blocks = p.partial_ld / T, jobs = col_blocks * p.slices, groups = jobs * p.row_blocks; // (groups: the grid)
@@ -74,27 +65,6 @@ template <class KIND, int T, int WK, int S> struct FewRows {
         const int inner = tall ? jobs : p.row_blocks, hi = id / inner, lo = id - hi * inner;
         const int mb = tall ? hi : lo, job = tall ? lo : hi, slice = job / col_blocks, cb = job - slice * col_blocks;
         const int lines = p.steps / 2, per = p.slice_steps / 2, first = slice * per, end = first + per < lines ? first + per : lines;
-        // A load brings 8 rows of 128 bytes, lanes 8 i to 8 i + 7 one row.  Rows past M or N lie past the extents and read as zero; 16-byte
-        // chunk c of row i sits at position c ^ (i / 2 % 8), so that 16 rows at one chunk column meet all banks once.
-        uint32_t av[2], bv[2]; // even and odd loads of a line
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t c = ((lane & 7) ^ (lane >> 4) ^ (4 * i)) * 16;
-            av[i] = (uint32_t)(mb * T + (lane >> 3)) * p.lda_b + c;
-            bv[i] = (uint32_t)(cb * T + (lane >> 3)) * p.ldw_b + c;
-        }
-        auto load = [&](LCMA_LDS char *st, int line) { // a line past the end is read from the end of the extents: zeros
-            const uint32_t ka = line < end ? (uint32_t)line * 128 : p.a_bytes, kb = line < end ? (uint32_t)line * 128 : p.w_bytes;
-#pragma unroll
-            for (int i = 0; i < LOADS; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LCMA_LDS void *)(st + i * 1024), 16, (int)av[i & 1], (int)(ka + i * 8 * p.lda_b), 0, 0);
-#pragma unroll
-            for (int i = 0; i < LOADS; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (LCMA_LDS void *)(st + HALF + i * 1024), 16, (int)bv[i & 1], (int)(kb + i * 8 * p.ldw_b), 0, 0);
-        };
-        uint32_t frag[KF]; // of this lane's 16 bytes in either operand's rows
-#pragma unroll
-        for (int k = 0; k < KF; ++k) frag[k] = fr * 128 + ((k * (64 / F) + fk) ^ (fr >> 1 & 7)) * 16;
         Acc acc[NF][NF];
 #pragma unroll
         for (int i = 0; i < NF; ++i)
@@ -102,52 +72,8 @@ template <class KIND, int T, int WK, int S> struct FewRows {
             for (int j = 0; j < NF; ++j)
 #pragma unroll
                 for (int v = 0; v < F * F / 64; ++v) acc[i][j][v] = 0.f;
-        auto step = [&](LCMA_LDS char *st, int line) {
-            Frag a[KF][NF], b[KF][NF];
-            wait_loads<2 * LOADS *(S - 1)>();
-#pragma unroll
-            for (int k = 0; k < KF; ++k)
-#pragma unroll
-                for (int i = 0; i < NF; ++i) {
-                    a[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + frag[k] + i * F * 128));
-                    b[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + HALF + frag[k] + i * F * 128));
-                }
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): what was read has left LDS, so its place may be loaded anew
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            load(st, line + S * WK);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int k = 0; k < KF; ++k)
-#pragma unroll
-                for (int i = 0; i < NF; ++i)
-#pragma unroll
-                    for (int j = 0; j < NF; ++j) {
-                        if constexpr (F == 16) acc[i][j] = Mma16<KIND>::run(a[k][i], b[k][j], acc[i][j]);
-                        else Mma<KIND>::run(a[k][i], b[k][j], acc[i][j]);
-                    }
-        };
-        int line = first + wk;
-        load(s0, line);
-        load(s1, line + WK);
-        if constexpr (S == 4) {
-            load(s2, line + 2 * WK);
-            load(s3, line + 3 * WK);
-        }
-        while (line < end) {
-            step(s0, line);
-            if ((line += WK) >= end) break;
-            step(s1, line);
-            if constexpr (S == 4) {
-                if ((line += WK) >= end) break;
-                step(s2, line);
-                if ((line += WK) >= end) break;
-                step(s3, line);
-            }
-            line += WK;
-        }
-        wait_loads<0>();
+        LCMA_LDS char *st = lds + wk * (S * STAGE);
+        lines_of_wave(p, mb, cb, first + wk, end, acc, st, st + STAGE, st + (S == 4 ? 2 * STAGE : 0), st + (S == 4 ? 3 * STAGE : 0));
         __syncthreads(); // no load is in flight and every wave has read its last line: the partial tiles take the place of the stages
         LCMA_LDS float *mine = (LCMA_LDS float *)lds + wk * (T * PITCH);
 #pragma unroll
@@ -174,6 +100,81 @@ template <class KIND, int T, int WK, int S> struct FewRows {
                 __builtin_amdgcn_raw_buffer_store_b64(v, rc, (int)off, 0, 0);
             }
         }
+    }
+    // Lines `line`, line + WK, ... below `end` of tile (mb, cb).  s0 .. s3: the stages of the wave.  restrict: the loads in flight towards
+    // one do not touch what is read from another (the compiler would otherwise wait for all of them in front of every read).  It holds
+    // in here only: the partial tiles, which take the place of the stages, are written where it has ended.
+    static LCMA_DEV void lines_of_wave(const FewRowsParams &p, int mb, int cb, int line, int end, Acc (&acc)[NF][NF], LCMA_LDS char *__restrict__ s0,
+                                       LCMA_LDS char *__restrict__ s1, LCMA_LDS char *__restrict__ s2, LCMA_LDS char *__restrict__ s3) {
+        const int lane = threadIdx.x & 63, fr = lane & (F - 1), fk = lane / F;
+        const auto ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.A), 0, (int)p.a_bytes, 0x00020000);
+        const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.W), 0, (int)p.w_bytes, 0x00020000);
+        // A load brings 8 rows of 128 bytes, lanes 8 i to 8 i + 7 one row.  Rows past M or N lie past the extents and read as zero; 16-byte
+        // chunk c of row i sits at position c ^ (i / 2 % 8), so that 16 rows at one chunk column meet all banks once.
+        uint32_t av[2], bv[2]; // even and odd loads of a line
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t c = ((lane & 7) ^ (lane >> 4) ^ (4 * i)) * 16;
+            av[i] = (uint32_t)(mb * T + (lane >> 3)) * p.lda_b + c;
+            bv[i] = (uint32_t)(cb * T + (lane >> 3)) * p.ldw_b + c;
+        }
+        auto load = [&](LCMA_LDS char *st, int line) { // a line past the end is read from the end of the extents: zeros
+            const uint32_t ka = line < end ? (uint32_t)line * 128 : p.a_bytes, kb = line < end ? (uint32_t)line * 128 : p.w_bytes;
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LCMA_LDS void *)(st + i * 1024), 16, (int)av[i & 1], (int)(ka + i * 8 * p.lda_b), 0, 0);
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (LCMA_LDS void *)(st + HALF + i * 1024), 16, (int)bv[i & 1], (int)(kb + i * 8 * p.ldw_b), 0, 0);
+        };
+        uint32_t frag[KF]; // of this lane's 16 bytes in either operand's rows
+#pragma unroll
+        for (int k = 0; k < KF; ++k) frag[k] = fr * 128 + ((k * (64 / F) + fk) ^ (fr >> 1 & 7)) * 16;
+        auto step = [&](LCMA_LDS char *st, int line) {
+            Frag a[KF][NF], b[KF][NF];
+            wait_loads<2 * LOADS *(S - 1)>();
+#pragma unroll
+            for (int k = 0; k < KF; ++k)
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    a[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + frag[k] + i * F * 128));
+                    b[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + HALF + frag[k] + i * F * 128));
+                }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): what was read has left LDS, so its place may be loaded anew
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            load(st, line + S * WK);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < KF; ++k)
+#pragma unroll
+                for (int i = 0; i < NF; ++i)
+#pragma unroll
+                    for (int j = 0; j < NF; ++j) {
+                        if constexpr (F == 16) acc[i][j] = Mma16<KIND>::run(a[k][i], b[k][j], acc[i][j]);
+                        else Mma<KIND>::run(a[k][i], b[k][j], acc[i][j]);
+                    }
+        };
+        load(s0, line);
+        load(s1, line + WK);
+        if constexpr (S == 4) {
+            load(s2, line + 2 * WK);
+            load(s3, line + 3 * WK);
+        }
+        while (line < end) {
+            step(s0, line);
+            if ((line += WK) >= end) break;
+            step(s1, line);
+            if constexpr (S == 4) {
+                if ((line += WK) >= end) break;
+                step(s2, line);
+                if ((line += WK) >= end) break;
+                step(s3, line);
+            }
+            line += WK;
+        }
+        wait_loads<0>();
     }
 };
 

@@ -1,0 +1,29 @@
+"""Where the tile of C takes the place of the stages in LDS, its writes and reads lie outside the promise that the loop over K makes to the
+compiler, namely that nothing else reaches the stages (restrict); under it the compiler may move them in front of the last reads
+of a stage.  From the alias scopes of the compiler's own output."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2605_06057_amd import build
+
+
+def kernels(source, name, tmp_path):
+    """{name: LLVM IR} of the kernels of a source that match `name`."""
+    out = str(tmp_path / "out.ll")
+    subprocess.run([build.HIPCC] + build.COMMON + build.DEVICE_FLAGS + ["--cuda-device-only", "-S", "-emit-llvm", source, "-o", out], check=True, capture_output=True)
+    return {m.group(1): m.group(0) for m in re.finditer(rf"^define [^\n]*@lcma_k_({name})\(.*?^}}", open(out).read(), re.M | re.S)}
+
+
+@pytest.mark.skipif(not (os.path.exists(build.HIPCC) or shutil.which(build.HIPCC)), reason="needs hipcc")
+def test_partial_tiles_of_the_few_rows_kernels(tmp_path):
+    found = kernels(os.path.join(build.CSRC, "lcma_few_rows.hip"), r"few_rows_b?f16_\d+", tmp_path)
+    assert sorted(found) == sorted(f"few_rows_{t}_{n}" for t in ("bf16", "f16") for n in (16, 32, 64))
+    for name, body in found.items():
+        sums = re.findall(r"^.*(?:store float .*|load <4 x float>, )ptr addrspace\(3\).*$", body, re.M)
+        assert sum("store" in line for line in sums) >= 4 and any("load" in line for line in sums), name
+        assert "!noalias" in body, f"{name}: the loop has lost its promise"
+        assert not [line for line in sums if "!noalias" in line or "!alias.scope" in line], name
