@@ -100,6 +100,7 @@ struct FewRowsParams {
     int32_t slices, slice_steps;        // slices of K (1: C is written directly), steps of a slice
     int32_t partial_ld;                 // columns of C in whole blocks: the row pitch of the partial products in floats
     void *partial;                      // slices x (row_blocks * block_rows) x partial_ld fp32 partial products
+    int32_t deep;                       // blocks of 16 rows: eight waves with four lines in flight each instead of four with two
 };
 
 struct Fp8QuantParams {

@@ -375,6 +375,10 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
             q.slice_steps = (int32_t)f.slice_steps;
             q.partial_ld = (int32_t)(f.col_blocks * f.tile);
             q.partial = workspace;
+            // Tiles of 16: eight waves with four lines in flight each (128 KB of LDS, one work-group per CU) only where each CU has one
+            // work-group and a long way to go: 1 x 4096 x 14336 22.5 us, 25.6 with four waves and two lines (32 KB), but 1 x 4096 x 4096 7.9 / 7.4,
+            // 1 x 1000 x 2048 4.3 / 3.7, and with more work-groups than CUs 1 x 14336 x 1024 12.1 / 7.6, 16 x 8192 x 512 6.0 / 3.9.
+            q.deep = f.row_blocks * f.col_blocks <= kCUs && K > 8192;
             const bool bf = dtype == LCMA_BF16;
             const auto launch = f.tile == 16   ? (bf ? lcma_launch_few_rows_bf16_16 : lcma_launch_few_rows_f16_16)
                                 : f.tile == 32 ? (bf ? lcma_launch_few_rows_bf16_32 : lcma_launch_few_rows_f16_32)

@@ -24,7 +24,7 @@ static std::string args(const lcma::PlaneGemmParams *p) {
     return num("jobs", p->jobs) + num("units", p->units) + num("ny", p->ny) + num("tail", p->tail_b) + num("panel", p->panel) + num("dealt", p->interleave);
 }
 static std::string args(const lcma::FewRowsParams *p) {
-    return num("tile", p->block_rows) + num("steps", p->steps) + num("slices", p->slices) + num("slice_steps", p->slice_steps);
+    return num("tile", p->block_rows) + num("steps", p->steps) + num("slices", p->slices) + num("slice_steps", p->slice_steps) + num("deep", p->deep);
 }
 static std::string args(const lcma::CombHParams *p) { return num("lanes", 1 << p->lane_shift) + num("streamed", p->streamed); }
 """

@@ -88,6 +88,14 @@ def test_nt_ws_between_the_plane_gemm_and_its_kin():
     assert ran[0].startswith("pg_bf16_t128_bf16 jobs=128 units=512 "), ran
 
 
+# Measured, us, four waves with two lines in flight each / eight with four (one work-group per CU): 3.9 / 6.0, 7.6 / 12.1, 26.0 / 30.4, 3.7 / 4.3, 25.6 / 22.5
+@pytest.mark.parametrize("shape,deep", [((16, 8192, 512), 0), ((1, 14336, 1024), 0), ((16, 14336, 4096), 0), ((1, 1000, 2048), 0), ((1, 4096, 14336), 1)], ids=str)
+def test_few_rows_wait_with_as_many_work_groups_as_fit(shape, deep):
+    for space in (0, D.lib().lcma_split_group_scratch_bytes()):
+        ran = D.gemm_nt_ws(*shape, "bf16", space)[1]
+        assert ran[0].startswith("few_rows_bf16_16 ") and ran[0].endswith(f" deep={deep}"), ran
+
+
 # Combine H, lanes along a row and cache policy: many small fp16 planes 7.9 us with 16 lanes, 10.5 with 64 and streamed loads (<4,4,4;49>, planes
 # of 128 x 1024)
 @pytest.mark.parametrize("scheme,shape,lanes", [("strassen2", (358, 3840, 832), 16), ("laderman", (1340, 744, 2464), 16), ("strassen", (2048, 4096, 4096), 64),
