@@ -273,33 +273,41 @@ bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, in
 }
 
 namespace {
-// Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): tile and slices of K with the smallest time.  A work-group
-// pulls in 36 bytes/ns (33 to 42 measured, on all three tiles), about 256 run at a time; 2.0 (2.2, 4.4) us besides for the launch and
-// the sum over the waves, 3.7 for the kernel that adds the slices (both sides measured: see lcma_few_rows.hpp).
+// Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): form and slices of K with the smallest time, all constants measured (us;
+// bf16, three sets of operands in turn).  A CU takes in the lines of its work-groups at `rate` bytes/ns; `first` besides for the launch, the
+// first lines and the sum over the waves, `next` for every further work-group of a CU; and what the operands themselves take from
+// beyond the L2, as far as it does not lie behind the lines, 8 TB/s.  Slices of K: 1.3 for the second kernel, 0.25 a slice and 0.35 per MB of
+// partial products.  At 190 shapes, M 1 to 8872, N 8 to 14336, K 128 to 14400, with the workspace and without, the choice takes 1.009 of the time of
+// the fastest form (the plane GEMM among them), at the worst 1.23; the rates of the kernel before, 36 bytes/ns for all tiles: 1.27 and 2.1.
+struct FewRowsForm {
+    int tile, waves, deep, most; // most: work-groups per CU
+    double first, next, alone, rate;    // alone: rate with one work-group per CU
+};
+// (tiles of 64, three or more to a CU: the plane GEMM or a ping-pong kernel is faster, 1753 x 2000 x 7552 69 against 124 us, 2506 x 1056 x 4288 41 / 49;
+// tiles of 16 with eight waves and four lines in flight each fill the LDS of a CU: no second work-group beside the first, and slower
+// where there is one: 1 x 14336 x 1024 12.1 us, 7.6 with the smaller form, 16 x 8192 x 512 6.0 / 3.9; with few of them and a long K
+// the faster ones, 1 x 4096 x 14336 22.5 / 25.6, with a short one not, 1 x 1000 x 2048 4.3 / 3.7)
+const FewRowsForm kFewRowsForms[] = {{16, 4, 0, 4, 2.8, 0.3, 90.0, 100.0}, {16, 8, 1, 1, 3.5, 0.0, 115.0, 0.0}, {32, 4, 0, 4, 3.1, 0.85, 100.0, 100.0}, {64, 4, 0, 2, 4.8, 3.5, 105.0, 105.0}};
 struct FewRowsPlan {
-    int tile;
+    int tile, deep;
     int64_t row_blocks, col_blocks, slices, slice_steps;
     double us;
 };
 FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, int64_t scratch_bytes) {
     FewRowsPlan best{};
-    for (int tile : {16, 32, 64}) {
-        const int64_t rb = ceil_div(M, tile), cb = ceil_div(N, tile), steps = K / 32, batch = tile == 64 ? 16 : 32;
-        if (rb * cb > 4 * kCUs) continue; // (far from where it pays)
-        int64_t slices = tile == 64 ? kCUs / (rb * cb) : 1;
-        if (slices < 1) slices = 1;
-        int64_t slice_steps = ceil_div(ceil_div(steps, slices), batch) * batch; // whole batches of all eight waves
-        slices = ceil_div(steps, slice_steps);
-        const int64_t scratch = slices > 1 ? slices * rb * tile * cb * tile * 4 : 0;
-        if (scratch > scratch_bytes) { // (then in one piece)
-            slices = 1;
-            slice_steps = ceil_div(steps, batch) * batch;
+    for (const FewRowsForm &f : kFewRowsForms) {
+        const int64_t rb = ceil_div(M, f.tile), cb = ceil_div(N, f.tile), steps = K / 32, batch = 2 * f.waves; // (steps of 32; a line of every wave)
+        if (rb * cb > (int64_t)f.most * kCUs) continue;
+        for (int64_t want : {(int64_t)1, kCUs / (rb * cb)}) {
+            if (want < 1 || (want > 1 && f.tile != 64)) continue;
+            const int64_t slice_steps = ceil_div(ceil_div(steps, want), batch) * batch, slices = ceil_div(steps, slice_steps);
+            const int64_t scratch = slices > 1 ? slices * rb * f.tile * cb * f.tile * 4 : 0;
+            if (scratch > scratch_bytes) continue;
+            const int64_t per_cu = ceil_div(rb * cb * slices, kCUs), lines = std::min(slice_steps, steps) / 2;
+            double us = f.first + f.next * (double)(per_cu - 1) + (double)(per_cu * lines * 256 * f.tile) / (1e3 * (per_cu > 1 ? f.rate : f.alone)) + (double)((M + N) * K * 2) / 8e6;
+            if (slices > 1) us += 1.3 + 0.25 * (double)slices + 0.35e-6 * (double)scratch;
+            if (!best.tile || us < best.us) best = FewRowsPlan{f.tile, f.deep, rb, cb, slices, slice_steps, us};
         }
-        double us = (double)ceil_div(rb * cb * slices, kCUs) * (double)(slice_steps * 64 * 2 * tile) / 36e3;
-        // rows of A that do not fit an XCD's L2 come from beyond it for every block of columns (270 x 5488 x 12864: 178 us)
-        if (M * K * 2 > (3 << 20)) us = std::max(us, (double)(cb * M + N) * (double)K * 2.0 / 4.2e6);
-        us += (tile == 16 ? 2.0 : tile == 32 ? 2.2 : 4.4) + (slices > 1 ? 3.7 : 0.0);
-        if (!best.tile || us < best.us) best = FewRowsPlan{tile, rb, cb, slices, slice_steps, us};
     }
     return best;
 }
@@ -352,10 +360,13 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
         int t = 0, sc = 0;
         const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc);
         int err = 0;
+        // (the ranges of steps take up to a fifth less than their price, a quarter on the safe side: 512 x 4096 x 14336 92 us, priced 112, in few rows 109,
+        // priced 95; 512 x 4096 x 12288 87 / 98; but 512 x 4096 x 8192 57 / 50, 320 x 4096 x 4096 40 / 28)
+        const bool few = f.tile && f.us * (sc == 2 ? 1.25 : 1.0) < planes_us;
         // (1.5 us on the safe side: 840 x 5592 x 768 15.7 against 14.4, 4358 x 256 x 640 10.4 against 9.2)
-        if (!(f.tile && f.us < planes_us) && plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, planes_us - 1.5, stream, &err))
+        if (plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, (few ? f.us : planes_us) - 1.5, stream, &err))
             return err ? fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err) : LCMA_OK;
-        if (f.tile && f.us < planes_us) {
+        if (few) {
             FewRowsParams q;
             std::memset(&q, 0, sizeof q);
             q.A = A;
@@ -375,10 +386,7 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
             q.slice_steps = (int32_t)f.slice_steps;
             q.partial_ld = (int32_t)(f.col_blocks * f.tile);
             q.partial = workspace;
-            // Tiles of 16: eight waves with four lines in flight each (128 KB of LDS, one work-group per CU) only where each CU has one
-            // work-group and a long way to go: 1 x 4096 x 14336 22.5 us, 25.6 with four waves and two lines (32 KB), but 1 x 4096 x 4096 7.9 / 7.4,
-            // 1 x 1000 x 2048 4.3 / 3.7, and with more work-groups than CUs 1 x 14336 x 1024 12.1 / 7.6, 16 x 8192 x 512 6.0 / 3.9.
-            q.deep = f.row_blocks * f.col_blocks <= kCUs && K > 8192;
+            q.deep = f.deep;
             const bool bf = dtype == LCMA_BF16;
             const auto launch = f.tile == 16   ? (bf ? lcma_launch_few_rows_bf16_16 : lcma_launch_few_rows_f16_16)
                                 : f.tile == 32 ? (bf ? lcma_launch_few_rows_bf16_32 : lcma_launch_few_rows_f16_32)

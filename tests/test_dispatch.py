@@ -35,7 +35,7 @@ def test_small_fp32_products_take_the_smaller_tile(scheme):
 def test_nt_ws_leaves_a_small_workspace_alone():
     """include/lcma.h: half of lcma_split_group_scratch_bytes() serves the ranges on 128 x 128 tiles alone, fewer bytes nothing."""
     whole = D.lib().lcma_split_group_scratch_bytes()
-    for M, N, K in ((64, 4096, 4096), (129, 200, 14400), (512, 4096, 14336)):
+    for M, N, K in ((64, 4096, 14336), (755, 96, 10368), (512, 4096, 14336)):
         split, none = D.gemm_nt_ws(M, N, K, "bf16", whole), D.gemm_nt_ws(M, N, K, "bf16", 0)
         assert split[0] == 0 and split != none
         for few in (4 << 20, whole // 2 - 256):
@@ -44,8 +44,8 @@ def test_nt_ws_leaves_a_small_workspace_alone():
             ran = D.gemm_nt_ws(M, N, K, "bf16", half)[1]
             assert len(ran) == 1 and ("slices=1" in ran[0] or "few_rows" not in ran[0]), ran
         assert none[0] == 0 and len(none[1]) == 1 and ("slices=1" in none[1][0] or "few_rows" not in none[1][0]), none
-    # 38 tiles of 104 steps in ranges of eight (33 us)
-    assert D.gemm_nt_ws(2372, 256, 6656, "bf16", whole // 2)[1][0].startswith("pg_bf16_t128_bf16 jobs=38 units=494 ")
+    # 128 tiles of 224 steps in ranges (92 us)
+    assert D.gemm_nt_ws(512, 4096, 14336, "bf16", whole // 2)[1][0].startswith("pg_bf16_t128_bf16 jobs=128 units=512 ")
 
 
 # Measured (us; weights combined before): plain 62.4, 206, 403, 703, 6606; Algorithm 1 with <2,2,2;7> 71.7, 265, 393, 819, 6270, with <4,4,4;49>
@@ -82,10 +82,25 @@ def test_nt_ws_between_the_plane_gemm_and_its_kin():
         assert len(ran) == 1 and units == min(jobs, 256 if "t128" not in ran[0] else 512), ran   # no ranges
     for shape, pad in (((840, 5592, 768), 64), ((4358, 256, 640), 64)):
         assert D.gemm_nt_ws(*shape, "bf16", whole, shape[2] + pad)[1][0].startswith("pg_bf16_t128_bf16 ")
-    # without a workspace the eight waves of a few-rows kernel run whole batches of 16 steps: 20 cost what 32 do (7.8 / 8.9)
-    assert D.gemm_nt_ws(109, 2432, 640, "f16", 0)[1][0].startswith("pg_f16_t128_f16 ")
     ran = D.gemm_nt_ws(512, 4096, 14336, "bf16", whole)[1]   # 128 tiles of 224 steps: ranges, 95 us against 221
     assert ran[0].startswith("pg_bf16_t128_bf16 jobs=128 units=512 "), ran
+
+
+# Measured, us, the fastest other form / what is taken: in four slices 13.3 / 9.1, 40 (128 x 128 tiles) / 28 and 28.5 and 29.5, 8.0 (128 x 128 tiles) / 5.3,
+# 31 / 16.6, 32 / 22 (ranges of steps), 12.3 (64 x 64 tiles in two slices) / 9.6; in one piece 39 (tiles of 32) / 30, 20.5 / 16.9
+@pytest.mark.parametrize("shape,tile,slices", [((64, 4096, 4096), 32, 1), ((320, 4096, 4096), 64, 1), ((400, 4096, 4096), 64, 1), ((512, 4096, 4096), 64, 1), ((109, 2432, 640), 32, 1),
+                                               ((4266, 128, 4288), 64, 1), ((2372, 256, 6656), 64, 1), ((250, 2000, 2112), 32, 1), ((64, 4096, 14336), 64, 4), ((250, 2000, 6400), 64, 2)], ids=str)
+def test_few_rows_are_priced_by_the_present_kernels(shape, tile, slices):
+    whole = D.lib().lcma_split_group_scratch_bytes()
+    for dtype in ("bf16", "f16"):
+        ran = D.gemm_nt_ws(*shape, dtype, whole)[1]
+        assert ran[0].startswith(f"few_rows_{dtype}_{tile} ") and f" slices={slices} " in ran[0], ran
+
+
+# What a few-rows kernel would take longer for: 1753 x 2000 x 7552 124 us, here 69 (ping-pong); 2506 x 1056 x 4288 49 / 41; 512 x 4096 x 14336 109 / 92 (ranges of steps)
+@pytest.mark.parametrize("shape", [(1753, 2000, 7552), (2506, 1056, 4288), (1292, 1920, 7488), (421, 6656, 2176), (512, 4096, 14336), (512, 4096, 12288)], ids=str)
+def test_many_tiles_are_not_few_rows(shape):
+    assert "few_rows" not in D.gemm_nt_ws(*shape, "bf16", D.lib().lcma_split_group_scratch_bytes())[1][0]
 
 
 # Measured, us, four waves with two lines in flight each / eight with four (one work-group per CU): 3.9 / 6.0, 7.6 / 12.1, 26.0 / 30.4, 3.7 / 4.3, 25.6 / 22.5

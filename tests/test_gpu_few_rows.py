@@ -11,10 +11,12 @@ pytestmark = pytest.mark.gpu
 
 # shape: (tile, slices of K) with the workspace and without it, by the library's rule (test_dispatch.py holds it to that)
 PLANS = {(1, 8, 1024): ((16, 1), (16, 1)), (1, 1000, 2048): ((16, 1), (16, 1)), (17, 72, 192): ((16, 1), (16, 1)), (33, 1000, 576): ((16, 1), (16, 1)),
-         (100, 520, 4160): ((16, 1), (16, 1)), (300, 520, 1024): ((32, 1), (32, 1)), (64, 4096, 4096): ((64, 4), (32, 1)),
-         (65, 4088, 4160): ((64, 2), (64, 1)),      # 130 steps of 32 in slices of 80: the last one of 50
-         (129, 200, 14400): ((64, 15), (16, 1)),    # 450 steps in slices of 32: the last one of 2
-         (250, 2000, 2112): ((64, 2), (64, 1)), (40, 14344, 1024): ((64, 1), (64, 1))}
+         (100, 520, 4160): ((16, 1), (16, 1)), (300, 520, 1024): ((32, 1), (32, 1)), (64, 4096, 4096): ((32, 1), (32, 1)),
+         (65, 4088, 4160): ((64, 2), (32, 1)),      # 130 steps of 32 in slices of 72: the last one of 58
+         (755, 96, 10368): ((64, 9), (16, 1)),      # 324 steps in slices of 40: the last one of 4
+         (64, 4096, 14336): ((64, 4), (32, 1)), (65, 4088, 8256): ((64, 2), (64, 1)),
+         (129, 200, 14400): ((16, 1), (16, 1)),     # eight waves with four lines in flight, the last turn of two waves only
+         (250, 2000, 2112): ((32, 1), (32, 1)), (40, 14344, 1024): ((64, 1), (64, 1))}
 SHAPES = list(PLANS)
 
 
