@@ -20,14 +20,16 @@
 
 namespace lcma {
 
-// Cache policy of the loads of the planes: they are read streamed where the caches do not hold them (8192 x 14336, <2,2,2;7> fp16 planes: 109
-// -> 100 us with a whole wave along a row; <4,4,4;49> 164 -> 155; 25 fp32 planes of 2048 x 2048 97 -> 90), many small 16-bit ones are
-// not (combine_h_access, host_common.h: <4,4,4;49> 358 x 3840 x 832 as a whole 55 us, streamed 59).
+// Cache policy of the loads of the planes: for 16-bit C they are read streamed (8192 x 14336, <2,2,2;7> fp16 planes: 109 -> 100 us with a whole
+// wave along a row; <4,4,4;49> 164 -> 155; 25 fp32 planes of 2048 x 2048 97 -> 90), except many small ones that the caches hold
+// (combine_h_access, host_common.h: <4,4,4;49> 358 x 3840 x 832 as a whole 55 us, streamed 59).  For fp32 C they are not
+// (<3,3,3;23> 384^3, weights combined before, 18.4 us, streamed 18.8; 768^3 28.2 / 28.7; <4,4,4;49> 512^3 22.7 / 23.2; from 1000^3 on level).  Many small fp32
+// planes of 16-bit C: level (<3,3,3;23> fp16 1340 x 744 x 2464 25.3 / 25.3, 600 x 4096 x 1024 36.0 / 34.9, 768^3 15.4 / 16.4), streamed like the large ones.
 
 // CH (generated): NP planes, NC = m*n outputs with c_i(o), c_j(o); comb(in, o) = Eq. 6 for output o on floats.
-// HT: element type of the planes; IN: storage type of C (same element size).
+// HT: element type of the planes; IN: storage type of C (of the same or of half the size).
 template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombHParams &p) {
-    constexpr int ES = IN::ES, HV = HT::ES / ES; // HV: vectors of C per 16 bytes of it
+    constexpr int ES = IN::ES, HV = HT::ES / ES; // 16 bytes of a plane become 16 / HV bytes of C
     static_assert(HT::ES == ES || (HT::ES == 4 && ES == 2), "planes in the element size of C, or fp32 planes for 16-bit C");
     const auto rh = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.H), 0, (int)p.h_bytes, 0x00020000);
     const auto rc = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)p.c_bytes, 0x00020000);
@@ -44,7 +46,7 @@ template <class IN, class HT, class CH> LCMA_DEV void combine_h_tile(const CombH
         for (int r = 0; r < CH::NP; ++r)
             h[r] = __builtin_amdgcn_raw_buffer_load_b128(rh, (int)(row * p.h_ld_b + at), (int)(r * p.h_plane_b), decltype(policy)::value);
     };
-    if (CH::NP <= 16 || p.streamed) load(std::integral_constant<int, kStreamed>{});
+    if (ES == 2 && (CH::NP <= 16 || p.streamed)) load(std::integral_constant<int, kStreamed>{});
     else load(std::integral_constant<int, 0>{});
     for_each_const<CH::NC>([&](auto oc_) {
         constexpr int o = decltype(oc_)::value;

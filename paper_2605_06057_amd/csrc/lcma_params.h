@@ -60,7 +60,7 @@ struct CombHParams {
     uint32_t c_brow, c_bcol;   // byte step from block C_{i,j} to C_{i+1,j} / C_{i,j+1}
     uint32_t n_row_b;          // N * element size: columns at or beyond it are never written
     int32_t lane_shift;        // 2^lane_shift neighbouring threads along a row
-    int32_t streamed;          // more than 16 planes: read with the streamed cache policy (fewer always are)
+    int32_t streamed;          // more than 16 planes of 16-bit C: read with the streamed cache policy (fewer always are; those of fp32 C never)
 };
 
 // Argument blocks of the FP8 kernels (E4M3 codes, one E8M0 scale byte per 1 x 128 block along K).
