@@ -193,7 +193,7 @@ def lcma_scheme_coeffs(s: Scheme):
 
 
 # What small products wait for is this file: 256^3 took 8.4 us a call, 3.7 of them here, where its kernel takes 4.5.  So the stream's handle
-# comes from torch's getter by device number (0.12 us; torch.cuda.current_stream() builds two objects, 1.9), the strides of a tensor are
+# comes from torch's getter by device number (0.12 us; torch.cuda.current_stream(), for a torch without it, builds two objects, 1.9), the strides of a tensor are
 # asked for once, and what does not change from call to call is looked up once a process: 1.15 us here, 5.8 a call (4.3 in C).
 _dtypes: dict = {}
 _raw_stream = None
@@ -211,7 +211,7 @@ def _stream_of(t) -> int:
     global _raw_stream
     if _raw_stream is None:
         import torch
-        _raw_stream = torch._C._cuda_getCurrentRawStream
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
     device = t.get_device()
     if device < 0:
         raise ValueError(f"expected a tensor on the GPU, got one on {t.device}")
