@@ -150,7 +150,7 @@ class Variant:
     tb: int = 0               # 1: B is given as the N x K weight matrix (k-contiguous rows)
     pa: int = 0               # 1 (with pb, staged loop): the left operands come ready-made from planes too
     batch: int = 0            # 1 (plain, tb): the grid covers R products on planes (Algorithm 1's batched GEMM)
-    ks: int = 0               # > 0: direct kernel (csrc/lcma_direct.hpp): ks waves split K, fragments come straight from memory
+    ks: int = 0               # > 0: direct kernel: ks waves split K (csrc/lcma_direct.hpp; 16 bit: csrc/lcma_direct16.hpp, four and two along the columns)
     name: str = field(default="")
 
     def finish(self):
@@ -185,9 +185,12 @@ def chunks_of(s: Scheme, v: Variant) -> list[list[int]]:
 def plan(s: Scheme, v: Variant):
     """On-chip resource planning: (accumulator registers per lane, LDS bytes, peak live C tiles)."""
     es = 4 if v.dtype == "f32" else 2
-    if v.ks:  # every product's accumulators; the partial tiles of C of all waves, rows padded by 16 bytes
+    if v.ks:  # every product's accumulators; the partial tiles of C of all waves along K, rows padded by 16 bytes
         assert v.chunk >= s.R and (v.dtype == "f32" or (v.TM in (16, 32) and (v.TN, v.pb, v.ks) == (64, 0, 4)))
-        return s.R * v.TM * v.TN // 64, v.ks * s.m * s.n * v.TM * (v.TN + 4) * 4, 0, s.R, 0, 0
+        regs, lds = s.R * v.TM * v.TN // 64, v.ks * s.m * s.n * v.TM * (v.TN + 4) * 4
+        if v.dtype != "f32":  # two waves share the columns; raw blocks in three or four stages of LDS, whose place the partial tiles take (Direct16)
+            regs, lds = regs // 2, max(lds, (3 if v.TM == 32 else 4) * (s.m * s.k * v.TM + s.k * s.n * v.TN) * v.TK * es)
+        return regs, lds, 0, s.R, 0, 0
     tile_regs = (v.TM // v.wgm // 32) * (v.TN // v.wgn // 32) * 16
     chunks = chunks_of(s, v)
     nslot = max(len(c) for c in chunks)
