@@ -76,11 +76,12 @@ static bool spans_fit(const Variant &v, int64_t M, int64_t N, int64_t K, int64_t
 // 857 x 1048 x 808 55.4 / 23.9; from about 1500^3 (96 both) the staged kernel is ahead.  The time of `v` comes from the
 // K x N kernels for any form of B, so that both layouts make the same choice and give the same bits, and prepared operands
 // (whose planes carry the same roundings) the same precision.
-// The 16-bit ones (csrc/lcma_direct16.hpp), tiles of 16 x 64 and 32 x 64: a step of 64 k takes 0.68 and 0.83 us (fp16 0.62, 0.70) with few
-// work-groups and 0.82 and 0.98 (0.75, 0.92) with 256, a round 2.9 and 3.8 besides; the staged kernel 5.4 and 0.90 us (fp16 0.72; N x K
+// The 16-bit ones (csrc/lcma_direct16.hpp), tiles of 16 x 64 and 32 x 64: a step of 64 k takes 0.68 and 0.79 us (fp16 0.62, 0.66) with few
+// work-groups and 0.82 and 0.95 (0.75, 0.88) with 256, a round 2.9 and 3.8 besides; the staged kernel 5.4 and 0.90 us (fp16 0.72; N x K
 // 0.73, 0.56) a step of 32 however few its work-groups are.  The N x K time is the one compared with, so that neither layout loses
-// by the common choice: on 70 shapes, M 16 to 4096, K 64 to 14336, both types and layouts, no choice of a direct kernel is slower than the
-// staged one (1991 x 1120 x 12592 fp16 stays with it: 142 and 145 against 150 and 165), and none misses the best by more than 6 %.
+// by the common choice: on 110 shapes, M 16 to 4096, K 64 to 14336, both types and layouts, the choices take 1.001 of the time of the fastest
+// kernels; five of 440 miss it by more than 3 %, four that stay with the staged kernel (1991 x 1120 x 12592 K x N: 182 against 164 us, fp16
+// 170 against 153, but N x K 146 and 153 against 170 and 165) and 213 x 392 x 1800 N x K fp16 (14.2 against 12.4 on the larger tile).
 // A direct kernel pads K further than the staged one in 16 bit: where its spans do not fit, the staged one runs.
 static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, int64_t ldc) {
     const Variant *staged = pick_variant(v->scheme_id, v->dtype, M, N, K, 0, 0), *best = v;
@@ -102,7 +103,7 @@ static const Variant *pick_direct(const Variant *v, int64_t M, int64_t N, int64_
             us = 3.0 + rounds * (d.TM == 16 ? 0.0145 * (double)bk + 0.8 : 0.041 * (double)bk + 2.5);
         } else {
             const bool bf = v->dtype == LCMA_BF16;
-            const double few = d.TM == 16 ? (bf ? 0.68 : 0.62) : bf ? 0.83 : 0.70, all = d.TM == 16 ? (bf ? 0.82 : 0.75) : bf ? 0.98 : 0.92;
+            const double few = d.TM == 16 ? (bf ? 0.68 : 0.62) : bf ? 0.79 : 0.66, all = d.TM == 16 ? (bf ? 0.82 : 0.75) : bf ? 0.95 : 0.88;
             const double last = (double)(groups % 256) / 256.0; // (a whole last round: no partial one)
             const double step = (double)(groups / 256) * all + (last > 0.0 ? few + (all - few) * last : 0.0);
             us = 1.2 + rounds * (d.TM == 16 ? 2.9 : 3.8) + step * (double)(bk / d.TK);
