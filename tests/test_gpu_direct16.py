@@ -1,6 +1,6 @@
 """The direct kernels for 16-bit products with few tiles (csrc/lcma_direct16.hpp): the same bits for both layouts of B, at one
 element, a step that ends inside a lane's 32 bytes of K, fewer steps than waves, one more than a round of waves, edges of the
-16 x 64 tile, and where lcma_gemm chooses them (CHOSEN); alpha and beta applied once, at every shape.  (Exactness on integers, ragged edges and guard
+16 x 64 tile, and where lcma_gemm chooses them (CHOSEN); alpha and beta applied once, at every shape and with the 32 x 64 tile too.  (Exactness on integers, ragged edges and guard
 rows: every variant, tests/test_gpu_parity.py.)"""
 import pytest
 
@@ -38,19 +38,23 @@ def test_layouts_and_scaling(shape, dtype):
     if shape in CHOSEN:
         assert torch.equal(c, d)
     old = (torch.arange(M * N, device="cuda", dtype=torch.float32).view(M, N) / (M * N)).to(c.dtype)
-    y, z = old.clone(), old.clone()
-    for right, out, variant, nk in ((b, y, name, False), (w, z, name + "t", True)):
-        B.lcma_set_tuning("variant", variant)
-        try:
-            B.lcma_gemm_ex(0.5, -2.0, a, right, out, s, b_nk=nk)
-        finally:
-            B.lcma_set_tuning("variant", "")
-    torch.cuda.synchronize()
-    assert torch.equal(y, z)
-    # c rounded once (half an ulp of c, u = 2^-9 or 2^-12 of its magnitude, halved by alpha), then the sum rounded once
-    u = 2.0 ** (-9 if dtype == "bf16" else -12)
-    want = 0.5 * c.double() - 2.0 * old.double()
-    assert ((y.double() - want).abs() <= 2 * u * (c.double().abs() + want.abs()) + 1e-7).all().item()
+    for tile in (16, 32):
+        name = f"strassen_{dtype}_d{tile}x64k4"
+        print(f"{name} {M}x{N}x{K} alpha, beta", flush=True)
+        B.lcma_gemm_variant(name, a, b, c)
+        y, z = old.clone(), old.clone()
+        for right, out, variant, nk in ((b, y, name, False), (w, z, name + "t", True)):
+            B.lcma_set_tuning("variant", variant)
+            try:
+                B.lcma_gemm_ex(0.5, -2.0, a, right, out, s, b_nk=nk)
+            finally:
+                B.lcma_set_tuning("variant", "")
+        torch.cuda.synchronize()
+        assert torch.equal(y, z)
+        # c rounded once (half an ulp of c, u = 2^-9 or 2^-12 of its magnitude, halved by alpha), then the sum rounded once
+        u = 2.0 ** (-9 if dtype == "bf16" else -12)
+        want = 0.5 * c.double() - 2.0 * old.double()
+        assert ((y.double() - want).abs() <= 2 * u * (c.double().abs() + want.abs()) + 1e-7).all().item()
 
 
 # K of a step and less, of a step that ends inside a lane's 32 bytes, and more steps than waves
