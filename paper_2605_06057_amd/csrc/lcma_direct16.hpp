@@ -5,7 +5,9 @@
 // (or 16 x 64) of every block, a step is 64 k of all of them, and the eight waves of its work-group share the k of a step (and its
 // columns; see NW).  Raw blocks in LDS, conversions and sums on the fragments as in the fragment-combine kernels; the partial
 // tiles of C are added in LDS, in fp32, always in the same order, and rounded once.  Which k meets which lane is the same for both
-// layouts of B, so both give the same bits.
+// layouts of B, so both give the same bits.  K is padded to multiples of 128, by the staged kernels to 64: where that cuts it elsewhere (2056: 1088
+// instead of 1056) other elements of A and of B meet in the sums and are rounded to fp16, so the bits differ from theirs by more than an
+// order of sums would make them (8.5e-4 against 4e-5), the error against 64 bits does not (1.67e-3 both).
 // Fragments brought from memory straight into registers, as this kernel had them before, take a CU 26 to 64 clocks a load; a
 // load with eight lanes to the 128 bytes of a row takes 16.  So raw lines travel straight into LDS, two or three steps ahead
 // behind counted waits, and K x N operands are read from there with transposing reads.
