@@ -37,3 +37,13 @@ def test_partial_tiles_of_the_few_rows_kernels(tmp_path):
     lds = {m.group(1): int(m.group(2)) for m in re.finditer(r"_few_rows_(b?f16_\w+?)E4smem = .*?\[(\d+) x i8\]", text)}
     for t in ("bf16", "f16"):
         assert lds[f"{t}_16"] <= 32768 and lds[f"{t}_32"] <= 65536 and lds[f"{t}_16_deep"] <= 131072, lds
+
+
+def test_no_function_reaches_the_stages_by_both_ways():
+    """A function that is handed the stages as restrict pointers gets no pointer to all of LDS besides (csrc/lcma_pingpong_narrow.hpp writes its strips
+    where the stages were; its compiled form carries no alias scopes, so this is held in the source)."""
+    import glob
+    lists = [re.sub(r"\s+", " ", m.group(1)) for path in glob.glob(os.path.join(build.CSRC, "*.hpp")) for m in re.finditer(r"LCMA_DEV void \w+\(([^;{}]*?__restrict__[^;{}]*?)\) \{", open(path).read())]
+    assert len(lists) >= 3
+    for parameters in lists:
+        assert not re.search(r"LCMA_LDS char \*(?!__restrict__)", parameters), parameters
