@@ -68,53 +68,11 @@ template <class KIND, class OUT, bool KN> struct PingPongNarrow {
         __builtin_amdgcn_sched_barrier(0);
     }
     static LCMA_DEV void run(const PlaneGemmParams &p, LCMA_LDS char *lds) {
-        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-        const int wm = w & 3, wn = w >> 2;
-        int job = blockIdx.x; // an XCD takes a contiguous run of tile-products
-        const int per = p.jobs >> 3;
-        if (job < (per << 3)) job = (job & 7) * per + (job >> 3);
-        int plane, x, z;
-        tile_of_job(p.nx, p.nz, p.panel, job, plane, x, z);
-        f32x16 acc[NMI][NNI];
-#pragma unroll
-        for (int mi = 0; mi < NMI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NNI; ++ni) zero(acc[mi][ni]);
-        pipeline(p, plane, x, z, acc, lds, lds + A_STAGE, lds + 2 * A_STAGE, lds + 3 * A_STAGE, lds + 3 * A_STAGE + B_STAGE, lds + 3 * A_STAGE + 2 * B_STAGE);
-        slot_end(); // nothing is in flight and every wave has read its last fragments: the stages hold the strips now
-        constexpr int OES = OUT::ES, CPRW = WN * OES / 16, NIT = SR * CPRW / 64;
-        const uint32_t extent = p.c_plane ? p.c_plane : p.c_bytes;
-        const auto rc = __builtin_amdgcn_make_buffer_rsrc((char *)p.C + (uint32_t)plane * p.c_plane, 0, (int)extent, 0x00020000);
-        const uint32_t c_base = (uint32_t)x * TM * p.ldc_b + (uint32_t)z * TN * OES;
-        LCMA_LDS char *strip = lds + w * (SR * PITCH);
-#pragma unroll
-        for (int mi = 0; mi < NMI; ++mi) {
-#pragma unroll
-            for (int ni = 0; ni < NNI; ++ni)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    LCMA_LDS char *at = strip + ((v >> 2) * 8 + 4 * lh + (v & 3)) * PITCH + (ni * 32 + l32) * OES;
-                    if constexpr (OES == 2) *(LCMA_LDS uint16_t *)at = (uint16_t)Round<OUT>::run(acc[mi][ni][v]);
-                    else *(LCMA_LDS float *)at = acc[mi][ni][v];
-                }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-            for (int it = 0; it < NIT; ++it) {
-                const int idx = it * 64 + lane, row = idx / CPRW, ch = idx % CPRW;
-                const u32x4 v = *(LCMA_LDS u32x4 *)(strip + row * PITCH + ch * 16);
-                const uint32_t colb = (uint32_t)(wn * WN) * OES + ch * 16;
-                const uint32_t off = ((uint32_t)z * TN * OES + colb < p.n_row_b) ? c_base + (uint32_t)(wm * WM + mi * 32 + row) * p.ldc_b + colb : extent;
-                // (16-byte store: the scalar-offset field stays a literal zero, see PlaneGemm::store_tile)
-                __builtin_amdgcn_raw_buffer_store_b128(v, rc, (int)off, 0, kStreamed);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        }
+        pipeline(p, lds, lds, lds + A_STAGE, lds + 2 * A_STAGE, lds + 3 * A_STAGE, lds + 3 * A_STAGE + B_STAGE, lds + 3 * A_STAGE + 2 * B_STAGE);
     }
-    // All steps of a tile-product.  A0 .. B2: the stages.  restrict (the loads in flight towards one do not touch what is read from another)
-    // holds in here only: the strips, which take the place of the stages, are written where it has ended.
-    static LCMA_DEV void pipeline(const PlaneGemmParams &p, int plane, int x, int z, f32x16 (&acc)[NMI][NNI], LCMA_LDS char *__restrict__ A0,
-                                  LCMA_LDS char *__restrict__ A1, LCMA_LDS char *__restrict__ A2, LCMA_LDS char *__restrict__ B0, LCMA_LDS char *__restrict__ B1,
-                                  LCMA_LDS char *__restrict__ B2) {
+    static LCMA_DEV void pipeline(const PlaneGemmParams &p, LCMA_LDS char *lds, LCMA_LDS char *A0, LCMA_LDS char *A1,
+                                  LCMA_LDS char *A2, LCMA_LDS char *B0, LCMA_LDS char *B1,
+                                  LCMA_LDS char *B2) {
         State s;
         const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, lh = lane >> 5;
         const int wm = w & 3, wn = w >> 2; // (wn is also the group: waves w and w + 4 share a SIMD)
@@ -122,6 +80,11 @@ template <class KIND, class OUT, bool KN> struct PingPongNarrow {
         s.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.A), 0, (int)p.a_bytes, 0x00020000);
         s.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.B), 0, (int)p.b_bytes, 0x00020000);
         const int ny = p.ny;
+        int job = blockIdx.x; // an XCD takes a contiguous run of tile-products
+        const int per = p.jobs >> 3;
+        if (job < (per << 3)) job = (job & 7) * per + (job >> 3);
+        int plane, x, z;
+        tile_of_job(p.nx, p.nz, p.panel, job, plane, x, z);
         {
             const int row = tid >> 3, c = swz(row, tid & 7) * 16;
             s.a_voff = (uint32_t)row * p.lda_b + c;
@@ -151,6 +114,11 @@ template <class KIND, class OUT, bool KN> struct PingPongNarrow {
         const uint32_t a0 = (uint32_t)plane * p.a_plane + (uint32_t)(x * TM) * p.lda_b;
         const uint32_t b0 = (uint32_t)plane * p.b_plane + (KN ? (uint32_t)(z * TN) * 2 : (uint32_t)(z * TN) * p.ldb_b);
         const uint32_t b_step = KN ? 64 * p.ldb_b : ROW;
+        f32x16 acc[NMI][NNI];
+#pragma unroll
+        for (int mi = 0; mi < NMI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NNI; ++ni) zero(acc[mi][ni]);
         auto a_of = [&](int y) { return y < ny ? a0 + (uint32_t)y * ROW : p.a_bytes; }; // past the end: past the extent
         auto b_of = [&](int y) { return y < ny ? b0 + (uint32_t)y * b_step : p.b_bytes; };
         FragT fa[4], fb[2][4];
@@ -197,6 +165,34 @@ template <class KIND, class OUT, bool KN> struct PingPongNarrow {
         }
         if (!wn) slot_end();
         __builtin_amdgcn_s_waitcnt(0x0070);
+        slot_end(); // nothing is in flight and every wave has read its last fragments: the stages hold the strips now
+        constexpr int OES = OUT::ES, CPRW = WN * OES / 16, NIT = SR * CPRW / 64;
+        const uint32_t extent = p.c_plane ? p.c_plane : p.c_bytes;
+        const auto rc = __builtin_amdgcn_make_buffer_rsrc((char *)p.C + (uint32_t)plane * p.c_plane, 0, (int)extent, 0x00020000);
+        const uint32_t c_base = (uint32_t)x * TM * p.ldc_b + (uint32_t)z * TN * OES;
+        LCMA_LDS char *strip = lds + w * (SR * PITCH);
+#pragma unroll
+        for (int mi = 0; mi < NMI; ++mi) {
+#pragma unroll
+            for (int ni = 0; ni < NNI; ++ni)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    LCMA_LDS char *at = strip + ((v >> 2) * 8 + 4 * lh + (v & 3)) * PITCH + (ni * 32 + l32) * OES;
+                    if constexpr (OES == 2) *(LCMA_LDS uint16_t *)at = (uint16_t)Round<OUT>::run(acc[mi][ni][v]);
+                    else *(LCMA_LDS float *)at = acc[mi][ni][v];
+                }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+                const int idx = it * 64 + lane, row = idx / CPRW, ch = idx % CPRW;
+                const u32x4 v = *(LCMA_LDS u32x4 *)(strip + row * PITCH + ch * 16);
+                const uint32_t colb = (uint32_t)(wn * WN) * OES + ch * 16;
+                const uint32_t off = ((uint32_t)z * TN * OES + colb < p.n_row_b) ? c_base + (uint32_t)(wm * WM + mi * 32 + row) * p.ldc_b + colb : extent;
+                // (16-byte store: the scalar-offset field stays a literal zero, see PlaneGemm::store_tile)
+                __builtin_amdgcn_raw_buffer_store_b128(v, rc, (int)off, 0, kStreamed);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
     }
 };
 

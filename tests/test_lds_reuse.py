@@ -40,8 +40,8 @@ def test_partial_tiles_of_the_few_rows_kernels(tmp_path):
 
 
 def test_no_function_reaches_the_stages_by_both_ways():
-    """A function that is handed the stages as restrict pointers gets no pointer to all of LDS besides (csrc/lcma_pingpong_narrow.hpp writes its strips
-    where the stages were; its compiled form carries no alias scopes, so this is held in the source)."""
+    """A function that is handed the stages as restrict pointers gets no pointer to all of LDS besides: the 256 x 128 ping-pong kernel, which has both,
+    makes no such promise (its compiled form carried no alias scopes before, so this is held in the source)."""
     import glob
     lists = [re.sub(r"\s+", " ", m.group(1)) for path in glob.glob(os.path.join(build.CSRC, "*.hpp")) for m in re.finditer(r"LCMA_DEV void \w+\(([^;{}]*?__restrict__[^;{}]*?)\) \{", open(path).read())]
     assert len(lists) >= 3
