@@ -248,7 +248,7 @@ int64_t lcma_split_group_scratch_bytes(void);
  * batched stage, with a workspace (device, 256-byte aligned, lcma_split_group_scratch_bytes() bytes, overwritten; half of
  * them serve its 128 x 128 tiles alone; NULL or fewer bytes: never split) that lets it hand the steps of all tiles out in Split-Group ranges: the split-K form of a plain
  * GEMM, chosen when the tiles alone would leave much of the chip idle (few tiles, long K).  Few rows or a small C run on a
- * kernel of their own, whose waves split K inside a work-group; with the whole workspace K is split between work-groups as well
+ * kernel of their own, whose waves split K inside a work-group; with the whole workspace K may be split between work-groups as well
  * (fp32 partial products, added in ascending order).  K not a multiple of 64 and F32
  * are passed on to lcma_gemm_nt.  Integer-valued inputs give lcma_gemm_nt's bits; float inputs agree to the last bit or two
  * (the fp32 sums are cut differently).  Everything else as for lcma_gemm_nt. */

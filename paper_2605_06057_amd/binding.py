@@ -192,9 +192,9 @@ def lcma_scheme_coeffs(s: Scheme):
     return U, V, W
 
 
-# What small products wait for is this file: 256^3 took 8.4 us a call, 3.7 of them here, where its kernel takes 4.5.  So the stream's handle
+# What small products wait for is this file: 256^3 took 8.8 us a call, 3.7 of them here, where its kernel takes 4.5 to 5.  So the stream's handle
 # comes from torch's getter by device number (0.12 us; torch.cuda.current_stream(), for a torch without it, builds two objects, 1.9), the strides of a tensor are
-# asked for once, and what does not change from call to call is looked up once a process: 1.15 us here, 5.8 a call (4.3 in C).
+# asked for once, and what does not change from call to call is looked up once a process: 1.15 us here, 6.0 a call (4.3 in C).
 _dtypes: dict = {}
 _raw_stream = None
 

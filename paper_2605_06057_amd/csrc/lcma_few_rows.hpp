@@ -10,13 +10,14 @@
 // instructions want them, takes a CU 64 clocks (38 bytes/ns, measured, 16 rows x 64 bytes and 32 x 32 alike); with eight lanes to the
 // 128 bytes of a row it takes 16 (140 to 150 from the L2, 100 with all CUs at it).  So lines travel whole into LDS and the fragments are read there.
 // The bytes per work-group decide next: a large tile of C reads least in all, and when large tiles alone would not fill the chip
-// K is cut into slices for work-groups of their own, whose fp32 partial products a second kernel adds in ascending order (3 us).
+// K is cut into slices for work-groups of their own, whose fp32 partial products a second kernel adds in ascending order
+// (four slices of 64 x 4096: 4.5 us).
 // What a work-group holds in LDS decides how many of them a CU runs: four waves with two lines in flight each, 32, 64 and 128 KB for tiles of 16,
 // 32 and 64, so that the many work-groups of the smaller tiles run side by side (16 x 8192 x 512, 512 of them: 3.9 us, 6.0 with 128 KB;
 // 1 x 14336 x 1024, 896: 7.6 / 12.1; tiles of 32 with 128 KB, eight waves: 256 x 1024 x 1024 5.0, now 4.4).
 // Measured (bf16, us, fragments from memory straight into registers / this): 64 x 4096 x 4096 in four slices 14.9 / 13.3, in one piece
-// 17.3 / 9.1; 64 x 4096 x 14336 37 / 30 (117 MB of weights: 3.9 TB/s); 64 x 14336 x 4096 37 / 28; 128 x 4096 x 4096 21.6 / 14.3; 1 x 14336 x
-// 4096 25.5 / 23.1; 256 x 1024 x 1024 6.5 / 4.4; 65 x 4088 x 4160 23.6 / 14.3.  Few columns (fp16): 4266 x 128 x 4288 31, 4095 x 192 x 2176 19.6 / 11.2
+// 17.3 / 9.0 (tiles of 32, what the rule takes); 64 x 4096 x 14336 37 / 30 (117 MB of weights: 3.9 TB/s); 64 x 14336 x 4096 37 / 28; 128 x 4096 x 4096 21.6 / 14.3; 1 x 14336 x
+// 4096 25.5 / 23.1; 256 x 1024 x 1024 6.5 / 4.4; 65 x 4088 x 4160 23.6 / 14.3.  Few columns (fp16): 4266 x 128 x 4288 33 / 16.6, 4095 x 192 x 2176 19.3 / 11.2
 // (97 and 37 with the blocks of columns dealt to the XCDs one by one, which leaves most XCDs without work where there are fewer than eight).
 #pragma once
 #include <hip/hip_runtime.h>
