@@ -360,9 +360,11 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
         int t = 0, sc = 0;
         const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc);
         int err = 0;
-        // (the ranges of steps take up to a fifth less than their price, a quarter on the safe side: 512 x 4096 x 14336 92 us, priced 112, in few rows 109,
-        // priced 95; 512 x 4096 x 12288 87 / 98; but 512 x 4096 x 8192 57 / 50, 320 x 4096 x 4096 40 / 28)
-        const bool few = f.tile && f.us * (sc == 2 ? 1.25 : 1.0) < planes_us;
+        // (against the ranges of steps a quarter on the safe side with two tiles of 64 per CU: 512 x 4096 x 14336 92 us, priced 112, in few rows 109, priced 95;
+        // 512 x 4096 x 12288 87 / 98; but 512 x 4096 x 8192 57 / 50; with fewer or smaller tiles both prices hold, 3 x 12672 x 10432 74 / 50,
+        // 1 x 10440 x 13440 75 / 53)
+        const bool full = f.tile == 64 && f.row_blocks * f.col_blocks > kCUs;
+        const bool few = f.tile && f.us * (sc == 2 && full ? 1.25 : 1.0) < planes_us;
         // (1.5 us on the safe side: 840 x 5592 x 768 15.7 against 14.4, 4358 x 256 x 640 10.4 against 9.2)
         if (plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, (few ? f.us : planes_us) - 1.5, stream, &err))
             return err ? fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err) : LCMA_OK;
