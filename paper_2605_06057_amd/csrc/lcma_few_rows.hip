@@ -1,5 +1,6 @@
 // Instances of the plain product on few rows (csrc/lcma_few_rows.hpp) and of the kernel that adds the slices of K.
 #include "lcma_few_rows.hpp"
+#include "lcma_kpair.hpp"
 
 using namespace lcma;
 
@@ -15,6 +16,38 @@ using namespace lcma;
         lcma_k_few_rows_##NAME<<<dim3(grid), dim3(64 * WK), 0, (hipStream_t)stream>>>(*p);                             \
         return (int)hipGetLastError();                                                                                 \
     }
+// Tiles of 64 x 128 on csrc/lcma_kpair.hpp.
+static lcma::PlaneGemmParams wide_tiles(const lcma::FewRowsParams &p) {
+    lcma::PlaneGemmParams q{};
+    q.A = p.A;
+    q.B = p.W;
+    q.C = p.C;
+    q.a_bytes = p.a_bytes;
+    q.b_bytes = p.w_bytes;
+    q.c_bytes = p.c_bytes;
+    q.lda_b = p.lda_b;
+    q.ldb_b = p.ldw_b;
+    q.ldc_b = p.ldc_b;
+    q.n_row_b = p.n_row_b;
+    q.ny = p.steps / 2;
+    q.tail_b = 128;
+    q.nx = p.row_blocks;
+    q.nz = p.partial_ld / 128;
+    q.panel = q.nz < 8 ? q.nz : 8;
+    q.jobs = q.nx * q.nz;
+    return q;
+}
+#define LCMA_FEW_ROWS_WIDE(NAME, KIND)                                                                                 \
+    extern "C" __global__ __launch_bounds__(512, 2) void lcma_k_low_##NAME(const lcma::PlaneGemmParams p) { \
+        using G = KPair<KIND, KIND, 64>;                                                                               \
+        __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
+        G::run(p, (LCMA_LDS char *)smem);                                                                              \
+    }                                                                                                                  \
+    static int launch_wide_##NAME(const lcma::FewRowsParams *p, int grid, void *stream) {                              \
+        const lcma::PlaneGemmParams q = wide_tiles(*p);                                                                \
+        lcma_k_low_##NAME<<<dim3(grid), dim3(512), 0, (hipStream_t)stream>>>(q);                   \
+        return (int)hipGetLastError();                                                                                 \
+    }
 #define LCMA_FEW_ROWS_TYPE(NAME, KIND)                                                                                 \
     LCMA_FEW_ROWS_KERNEL(NAME##_16, KIND, 16, 4, 2)                                                                    \
     LCMA_FEW_ROWS_KERNEL(NAME##_16_deep, KIND, 16, 8, 4)                                                               \
@@ -24,7 +57,13 @@ using namespace lcma;
         return (int)hipGetLastError();                                                                                 \
     }                                                                                                                  \
     LCMA_FEW_ROWS(NAME##_32, KIND, 32, 4, 2)                                                                           \
-    LCMA_FEW_ROWS(NAME##_64, KIND, 64, 4, 2)                                                                           \
+    LCMA_FEW_ROWS_KERNEL(NAME##_64, KIND, 64, 4, 2)                                                                    \
+    LCMA_FEW_ROWS_WIDE(NAME, KIND)                                                                                     \
+    extern "C" int lcma_launch_few_rows_##NAME##_64(const lcma::FewRowsParams *p, int grid, void *stream) {            \
+        if (p->deep) return launch_wide_##NAME(p, grid, stream);                                                       \
+        lcma_k_few_rows_##NAME##_64<<<dim3(grid), dim3(256), 0, (hipStream_t)stream>>>(*p);                            \
+        return (int)hipGetLastError();                                                                                 \
+    }                                                                                                                  \
     extern "C" __global__ __launch_bounds__(256) void lcma_k_few_rows_sum_##NAME(const lcma::FewRowsParams p) {        \
         few_rows_sum<KIND>(p);                                                                                         \
     }                                                                                                                  \

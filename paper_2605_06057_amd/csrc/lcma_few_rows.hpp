@@ -19,6 +19,7 @@
 // 17.3 / 9.0 (tiles of 32, what the rule takes); 64 x 4096 x 14336 37 / 30 (117 MB of weights: 3.9 TB/s); 64 x 14336 x 4096 37 / 28; 128 x 4096 x 4096 21.6 / 14.3; 1 x 14336 x
 // 4096 25.5 / 23.1; 256 x 1024 x 1024 6.5 / 4.4; 65 x 4088 x 4160 23.6 / 14.3.  Few columns (fp16): 4266 x 128 x 4288 33 / 16.6, 4095 x 192 x 2176 19.3 / 11.2
 // (97 and 37 with the blocks of columns dealt to the XCDs one by one, which leaves most XCDs without work where there are fewer than eight).
+// Where there would be two tiles of 64 x 64 to a CU, 64 x 128 on csrc/lcma_kpair.hpp: 512 x 4096 x 4096 29.5 / 22.3, 320 x 4096 x 4096 28 / 19.3.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

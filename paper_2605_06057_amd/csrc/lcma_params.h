@@ -82,7 +82,9 @@ struct PlaneGemmParams {
     int32_t units;                                          // persistent work-groups launched
     int32_t interleave;                                     // persistent kernel: 0 = work-group u owns the steps [u * cap, (u + 1) * cap);
                                                             // whole tile-products in turn: 1 = u, u + units, ... (rounds of consecutive
-                                                            // ones), 2 = each XCD an eighth of them (units is a multiple of 8)
+                                                            // ones), 2 = each XCD an eighth of them (units is a multiple of 8); 128 x 128
+                                                            // tiles: 3 = slices of cap steps, 4 = two work-groups to a CU,
+                                                            // 5 = tiles of 64 x 128 instead
     int64_t cap;                                            // steps per work-group: ceil(jobs * ny / units)
     void *partial;                                          // fp32 scratch for pieces: 2 slots of TM * TN floats per work-group
                                                             // (never touched when cap is a multiple of ny)
@@ -100,7 +102,8 @@ struct FewRowsParams {
     int32_t slices, slice_steps;        // slices of K (1: C is written directly), steps of a slice
     int32_t partial_ld;                 // columns of C in whole blocks: the row pitch of the partial products in floats
     void *partial;                      // slices x (row_blocks * block_rows) x partial_ld fp32 partial products
-    int32_t deep;                       // blocks of 16 rows: eight waves with four lines in flight each instead of four with two
+    int32_t deep;                       // blocks of 16 rows: eight waves with four lines in flight each instead of four with two;
+                                        // of 64 rows: 128 columns wide
 };
 
 struct Fp8QuantParams {

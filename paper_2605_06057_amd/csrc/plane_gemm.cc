@@ -41,78 +41,98 @@ const int kCUs = 256;
 typedef int (*Launch)(const PlaneGemmParams *, void *);
 Launch launcher(int kind, int tile) {
     switch (kind * 2 + (tile == 256)) {
-    case PG_FP8_BF16 * 2 + 1: return lcma_launch_pg_fp8_t256_bf16;
-    case PG_FP8_BF16 * 2: return lcma_launch_pg_fp8_t128_bf16;
-    case PG_FP8_F16 * 2 + 1: return lcma_launch_pg_fp8_t256_f16;
-    case PG_FP8_F16 * 2: return lcma_launch_pg_fp8_t128_f16;
-    case PG_F16 * 2 + 1: return lcma_launch_pg_f16_t256_f16;
-    case PG_F16 * 2: return lcma_launch_pg_f16_t128_f16;
-    case PG_BF16 * 2 + 1: return lcma_launch_pg_bf16_t256_bf16;
-    case PG_BF16 * 2: return lcma_launch_pg_bf16_t128_bf16;
-    case PG_F16_OUT * 2 + 1: return lcma_launch_pg_f16_t256_f16;
-    case PG_F16_OUT * 2: return lcma_launch_pg_f16_t128_f16;
-    case PG_F16_F32 * 2 + 1: return lcma_launch_pg_f16_t256_f32;
-    case PG_F16_F32 * 2: return lcma_launch_pg_f16_t128_f32;
+#define LCMA_PG_TILES(KIND, TYPE, OUT)                                       \
+    case KIND * 2 + 1: return lcma_launch_pg_##TYPE##_t256_##OUT;            \
+    case KIND * 2: return lcma_launch_pg_##TYPE##_t128_##OUT;
+        LCMA_PG_TILES(PG_FP8_BF16, fp8, bf16)
+        LCMA_PG_TILES(PG_FP8_F16, fp8, f16)
+        LCMA_PG_TILES(PG_F16, f16, f16)
+        LCMA_PG_TILES(PG_BF16, bf16, bf16)
+        LCMA_PG_TILES(PG_F16_OUT, f16, f16)
+        LCMA_PG_TILES(PG_F16_F32, f16, f32)
     }
     return nullptr;
 }
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // work-groups that run at one time: one 256 x 256 tile (128 KB of LDS) or two 128 x 128 tiles (64 KB each) per CU
 int slots_of(int tile) { return tile == 256 ? kCUs : 2 * kCUs; }
+int64_t tile_cols(int tile) { return tile == 64 ? 128 : tile; }
 } // namespace
 
 int64_t plane_gemm_scratch_bytes(int tile) { return (int64_t)slots_of(tile) * 2 * tile * tile * 4; }
 
 namespace {
-// Tile and schedule together, by the time the slowest work-group takes.  All constants are measured (us; random operands;
-// f: share of the chip's work-group slots that a round fills: with fewer work-groups the memory side answers sooner and
-// the clock is higher).
-//   256 x 256, whole tile-products in turn (ping-pong kernel, csrc/lcma_pingpong.hpp): a step of 128 bytes of K takes 1.52
-//     with all 256 work-groups (8192 x 14336 x 4096: 712 us in 7 rounds of 64 steps; 7 planes of 4096 x 7168 x 2048: 724 us),
-//     1.16 with 128 (2048 x 4096 x 4096: 81 us), 0.98 with 64 (2048 x 2048 x 7168: 110 us); a tile-product 6 besides (12
-//     with fp32 output), and the start of the pipeline 1.5;
-//   256 x 256, one work-group per tile-product (PlaneGemm): 1.62 (FP8: 2.05) a step, but a shorter start: the faster one
-//     up to about eight steps (4096 x 4096 x 128: 11.0 against 11.8 us, x 256: 15.4 against 15.7, x 512: 22.4 both);
-//   128 x 128, two work-groups per CU: 1.06 a step of both (FP8: 1.16) with 512 work-groups, 0.72 to 0.9 with 256, 0.62
-//     with a few (2048 x 4096 x 4096: 68 us; 1024 x 4096 x 4096: 48 us; x 16384: 232 us; 64 x 4096 x 4096: 41 us): the one to take when the large
-//     tiles leave much of the chip idle;
-//   Split-Group ranges: 1.75 (1.6; FP8 2.0 and 1.1) a step, 6 (3) a tile-product and 65 (20, and 0.45 for every piece of a tile; FP8 40)
-//     for the pieces: nearly every work-group holds two, 134 (67) MB of fp32 partial sums in all, written at the end of the first
-//     kernel and read back by the second (1024 x 4096 x 16384: 161 us against 232 with 128 x 128 tiles; 512 x 4096 x 14336: 95 against 221): few
-//     tile-products and a long K only (2463 x 8344 x 6528: 334 against 248 with the ping-pong kernel; neighbouring tiles of the 128 x
-//     128 form start at different k and share little in L2: 857 x 3720 x 7040 112 against 91 with a work-group per tile).
-// tile, schedule: 0 = choose.  Returns microseconds (0 when nothing fits).
-double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, int64_t scratch_bytes, int *best_tile,
+// Tile and schedule together, by the time the slowest work-group takes.  Whole tile-products run in rounds of as many work-groups as fit;
+// a step of 128 bytes of K takes a + b f + c f^4 us when a share f of them has one (with few of them the memory side answers sooner, with
+// many the clock falls), a round `more` besides, the launch and the first loads `start`, and where rows do not start on 128-byte
+// lines a step `off` of itself more.  All measured on random operands, plain products by themselves (250 of 100 to 8192 rows, K 512 to 14336) and
+// batches where they run, between the passes over memory of Algorithm 1 (450; by themselves, one after the other, the ping-pong kernel is 10 % slower
+// against the others: the clock), fitted to 3 to 10 %.  What the prices choose takes 1.007 of the time of the fastest kernel on plain 16-bit products,
+// 1.003 in FP8, 1.001 to 1.007 on batches.  Without the 64 x 128 tile it is 1.09, 1.05 and 1.00, without both tiles of lcma_kpair.hpp 1.27, 1.25 and
+// 1.02, without the small tile's form with two work-groups to a CU (PlaneGemm: many tile-products of few steps, 384 x 384 x
+// 960 in 49 planes 17.9 us, 26.6 on KPair) 1.01 to 1.08.
+struct StepPrice {
+    double a, b, c, more, start, off;
+    double step(double f) const { return a + b * f + c * f * f * f * f; }
+};
+enum { WHOLE_256, KPAIR_128, TWO_128, KPAIR_64, STATIC_256 }; // 256 x 256 ping-pong, 128 x 128, the same twice to a CU, 64 x 128, 256 x 256 a work-group each
+const StepPrice kPlain[] = {{0.876, 0.202, 0.493, 6.93, 0.0, 0.055}, {0.301, 0.144, 0.0, 2.91, 0.97, 0.367}, {0.591, 0.320, 0.070, 1.53, 0.0, 0.187}, {0.245, 0.055, 0.0, 1.80, 1.28, 0.474}, {1.067, 0.171, 0.484, 4.70, 0.0, 0.11}};
+const StepPrice kBatch[] = {{0.775, 0.557, 0.150, 5.66, 3.0, 0.0}, {0.348, 0.008, 0.204, 2.26, 3.0, 0.0}, {0.601, 0.319, 0.126, 1.40, 3.0, 0.0}, {0.243, 0.0, 0.103, 1.69, 3.0, 0.0}, {1.087, 0.277, 0.455, 4.36, 3.0, 0.0}};
+const StepPrice kBatchF32[] = {{0.672, 0.692, 0.143, 8.87, 3.0, 0.0}, {0.487, 0.026, 0.028, 3.05, 3.0, 0.0}, {0.616, 0.420, 0.0, 2.24, 3.0, 0.0}, {0.346, 0.0, 0.0, 1.79, 3.0, 0.0}, {0.976, 0.008, 1.447, 4.10, 4.20, 0.0}};
+const StepPrice kBatchFp8[] = {{0.890, 0.273, 0.360, 4.97, 0.64, 0.0}, {0.239, 0.209, 0.095, 2.86, 0.0, 0.0}, {0.621, 0.424, 0.109, 0.91, 0.0, 0.0}, {0.160, 0.051, 0.148, 2.25, 0.0, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0, 0.0}};
+const StepPrice kFp8[] = {{0.924, 0.209, 0.304, 7.70, 0.0, 0.0}, {0.319, 0.129, 0.007, 3.27, 1.55, 0.0}, {0.682, 0.412, 0.0, 1.50, 0.0, 0.0}, {0.245, 0.077, 0.0, 2.18, 1.57, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0, 0.0}};
+double rounds_us(const StepPrice &q, int64_t jobs, int64_t slots, int64_t steps, bool off_line) {
+    const double line = off_line ? 1.0 + q.off : 1.0, f = (double)(jobs % slots) / (double)slots;
+    return q.start + (double)(jobs / slots) * ((double)steps * line * q.step(1.0) + q.more) + (f > 0.0 ? (double)steps * line * q.step(f) + q.more : 0.0);
+}
+// What else there is:
+//   slices of K for work-groups of their own (128 x 128, plain 16-bit products of few tiles): the fp32 products of the slices are written and
+//     added by a second kernel, 1.3 us, 0.25 a slice and 0.35 per MB (743 x 1400 x 7168, 66 tiles in three slices: 24.8 us, 43.8
+//     in one piece; 1024 x 1024 x 14336 36.7 / 85; 512 x 4096 x 14336 61.8 / 87.7);
+//   Split-Group ranges: 1.75 (FP8 2.0) a step on 256 x 256, 6 a tile-product and 65 for the pieces.  On 128 x 128 neighbouring tiles start at
+//     different k and share little in L2, 0.85 a step, unless the ranges divide a tile evenly; 12 and 2.3 a piece of a tile (512 x 4096 x
+//     14336 65.6 us, 255 x 8504 x 7296 71 against 44 without, 559 x 7184 x 9856 196 / 106).  Half of the workspace serves them alone.
+// tile, schedule: 0 = choose.  off_line: rows that do not start on 128-byte lines; low: tiles of 64 x 128 are offered.  Returns microseconds (0 when nothing fits).
+enum { STATIC = 1, RANGES = 2, PERSIST = 3, SLICES = 4, TWO_PER_CU = 5 };
+int64_t slice_steps(int64_t jobs, int ny) { return ceil_div(ny, std::max<int64_t>(1, std::min<int64_t>(kCUs / jobs, ny / 4))); }
+double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, bool off_line, bool low, int64_t scratch_bytes, int *best_tile,
               int *best_sched) {
     const bool fp8 = kind == PG_FP8_BF16 || kind == PG_FP8_F16;
-    const double out = kind == PG_F16_F32 ? 2.0 : 1.0; // a tile of fp32 takes twice as long to write
+    const StepPrice *const price = fp8 ? (planes > 1 ? kBatchFp8 : kFp8) : kind == PG_F16_F32 ? kBatchF32 : planes > 1 ? kBatch : kPlain;
     double best = 0.0;
     *best_tile = *best_sched = 0;
-    for (int t : {256, 128}) {
-        if (tile && t != tile) continue;
-        const int64_t jobs = (int64_t)planes * ceil_div(rows, t) * ceil_div(cols, t), slots = slots_of(t);
-        for (int sc : {1, 2, 3}) {
-            if (schedule && sc != schedule) continue;
-            const bool pingpong = t == 256 && sc == 3;
-            // (the 128 x 128 FP8 kernel loses with whole tile-products in turn: it does not fetch the next scales ahead)
-            if (!schedule && sc == 3 && fp8 && t == 128) continue;
+    for (int t : {256, 128, 64}) { // (64: 64 x 128)
+        if (tile ? t != tile : t == 64 && !low) continue;
+        const int64_t jobs = (int64_t)planes * ceil_div(rows, t) * ceil_div(cols, tile_cols(t));
+        const int64_t even = ny > 2 ? (ny + 1) & ~1 : ny; // (kernels of two groups of waves round an odd number of steps up)
+        for (int sc : {STATIC, RANGES, PERSIST, SLICES, TWO_PER_CU}) {
+            if (schedule && sc != schedule && !(sc == TWO_PER_CU && schedule == STATIC)) continue;
+            const bool pingpong = t == 256 && sc == PERSIST;
+            if (t == 64 && sc != STATIC) continue;
+            if (!schedule && sc == PERSIST && t == 128) continue; // (the same kernel as STATIC)
             // planes lie back to back: only the ping-pong kernel lets a tile hang over the end of one
-            if (planes > 1 && !pingpong && (rows % t || cols % t)) continue;
-            if (sc == 2 && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
+            if (planes > 1 && !pingpong && (rows % t || cols % tile_cols(t))) continue;
+            if (sc == RANGES && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
             double cost;
-            if (sc == 2) {
-                const double cap = (double)ceil_div(jobs * ny, slots), pieces = t == 256 ? 65.0 : fp8 ? 40.0 : 20.0 + 0.45 * (double)ny / cap;
-                cost = cap * (t == 256 ? fp8 ? 2.0 : 1.75 : fp8 ? 1.1 : 1.6) + (t == 256 ? 6.0 : 3.0) * out * (double)jobs / (double)slots + pieces;
+            if (sc == RANGES) {
+                const int64_t cap = ceil_div(jobs * ny, slots_of(t));
+                cost = t == 256 ? (double)cap * (fp8 ? 2.0 : 1.75) + 6.0 * (double)jobs / kCUs + 65.0
+                                : (double)(2 * cap) * (ny % (2 * cap) ? 0.85 : price[KPAIR_128].step(1.0)) + 12.0 + 2.3 * (double)kCUs / (double)jobs;
+            } else if (sc == SLICES) {
+                if (t != 128 || planes > 1 || fp8 || kind == PG_F16_F32 || 2 * jobs > kCUs || ny < 8 || scratch_bytes < plane_gemm_scratch_bytes(256)) continue;
+                const int64_t cap = slice_steps(jobs, ny), slices = ceil_div(ny, cap);
+                cost = rounds_us(price[KPAIR_128], jobs * slices, kCUs, (cap + 1) & ~(int64_t)1, off_line) + 1.3 + 0.25 * (double)slices + 0.35 * 65536e-6 * (double)(jobs * slices);
+            } else if (sc == TWO_PER_CU) {
+                if (t != 128) continue;
+                cost = rounds_us(price[TWO_128], jobs, 2 * kCUs, ny, off_line);
+            } else if (t < 256) {
+                cost = rounds_us(price[t == 128 ? KPAIR_128 : KPAIR_64], jobs, kCUs, even, off_line);
+            } else if (pingpong) {
+                cost = rounds_us(price[WHOLE_256], jobs, kCUs, (ny + 1) & ~1, off_line);
             } else {
-                const int64_t full = jobs / slots, rest = jobs % slots;
-                auto round = [&](double f) {
-                    if (pingpong) return (double)((ny + 1) & ~1) * (0.80 + 0.72 * f) + 6.0 * out;
-                    if (t == 256) return (double)ny * (fp8 ? 1.0 + 1.05 * f : 0.85 + 0.77 * f) + 6.0 * out;
-                    const double alone = 0.62 + 0.5 * (f < 0.5 ? f : 0.5); // one work-group per CU up to f = 0.5
-                    return (double)ny * (alone + (f > 0.5 ? 0.5 * (f - 0.5) : 0.0)) + (sc == 3 && full ? 2.5 : 3.0) * out;
-                };
-                cost = (double)full * round(1.0) + (rest ? round((double)rest / (double)slots) : 0.0) + (pingpong ? 1.5 : 0.0);
+                cost = rounds_us(price[STATIC_256], jobs, kCUs, ny, off_line);
             }
+            if (t < 256) cost = std::max(cost, 5.0 + (double)planes * (double)(rows + cols) * ny * 128.0 / 6e6); // (operands from memory)
             if (!*best_tile || cost < best) {
                 best = cost;
                 *best_tile = t;
@@ -125,11 +145,16 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
 } // namespace
 
 // Seconds of the batched stage of Algorithm 1 in 16 bit as plane_gemm runs it by now (fp32_out: products kept in fp32), for
-// lcma_select_dataflow: measured 54.6 us at 53 predicted (7 planes, 2048 x 4096 x 4096), 318 / 315 (6144^3), 695 / 695 (FFN).
+// lcma_select_dataflow: measured 54.6 us at 53 predicted (7 planes, 2048 x 4096 x 4096), 318 / 315 (6144^3), 695 / 695 (FFN).  On many large
+// tiles the ping-pong kernel at the price that the plain product is compared at there: a batch of its own, timed back to back, runs 10 %
+// slower than as a stage between passes over memory.
 double batched_plane_gemm_seconds(bool fp32_out, int planes, int64_t rows, int64_t cols, int ny) {
     int t = 0, sc = 0;
-    const double us = choose(fp32_out ? PG_F16_F32 : PG_F16, planes, rows, cols, ny, 0, tuning_schedule(), 0, &t, &sc);
-    return t ? 1e-6 * us : -1.0;
+    const double us = choose(fp32_out ? PG_F16_F32 : PG_F16, planes, rows, cols, ny, 0, tuning_schedule(), false, true, 0, &t, &sc);
+    if (!t) return -1.0;
+    const double out = fp32_out ? 12.0 : 6.0;
+    const double stage = rounds_us(StepPrice{0.80, 0.72, 0.0, out, 1.5, 0.0}, planes * ceil_div(rows, 256) * ceil_div(cols, 256), kCUs, (ny + 1) & ~1, false);
+    return 1e-6 * (t == 256 && stage < us ? stage : us);
 }
 
 // The same as lcma_predict_unfused_seconds was published with, and as lcma_gemm_ws, whose contract names that function, compares it:
@@ -169,13 +194,13 @@ static int panel_of(int nz, int wide) {
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
 // (padded sizes; when batched only the ping-pong kernel takes planes that are no whole tiles).  tile: 256 or 128, 0 = choose.
 // schedule: 0 = choose, 1 = one tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of
-// plane_gemm_scratch_bytes(tile) bytes), 3 = persistent work-groups that each take every units-th whole tile-product.
+// plane_gemm_scratch_bytes(tile) bytes), 4 = slices of K (plain 16-bit products), 3 = persistent work-groups that each take every units-th whole tile-product.
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,
                        int schedule, void *scratch, int64_t scratch_bytes, void *stream) {
     const int forced = tuning_schedule();
     if (forced) schedule = forced;
     int best_tile = 0, best_sched = 0;
-    choose(kind, planes, rows, cols, p.ny, tile, schedule, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
+    choose(kind, planes, rows, cols, p.ny, tile, schedule, planes == 1 && ((p.lda_b | p.ldb_b) & 127), true, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
     if (!best_tile) {
         if (schedule == 2)
             return fail(LCMA_ERR_ARG, "%s: the Split-Group schedule needs %lld bytes of scratch", who,
@@ -188,21 +213,26 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     if (!launch) return fail(LCMA_ERR_NOKERNEL, "%s: no plane GEMM kernel of kind %d", who, kind);
     if (!p.tail_b) p.tail_b = 128; // whole steps
     p.nx = (int32_t)ceil_div(rows, tile);
-    p.nz = (int32_t)ceil_div(cols, tile);
+    p.nz = (int32_t)ceil_div(cols, tile_cols(tile));
     const int64_t jobs = (int64_t)planes * p.nx * p.nz, total = jobs * p.ny;
     if (total >= ((int64_t)1 << 31)) return fail(LCMA_ERR_SHAPE, "%s: too many tile steps", who);
     p.jobs = (int32_t)jobs;
     p.panel = panel_of(p.nz, 8);
     const int slots = slots_of(tile);
     p.interleave = 0;
-    if (schedule == 3) { // persistent work-groups, whole tile-products u, u + units, ...
+    if (schedule == SLICES) {
+        p.cap = slice_steps(jobs, p.ny);
+        p.units = (int32_t)(2 * jobs * ceil_div(p.ny, p.cap)); // (groups of four waves, two to a work-group)
+        p.interleave = 3;
+        p.partial = scratch;
+    } else if (schedule == PERSIST) { // persistent work-groups, whole tile-products u, u + units, ...
         p.units = (int32_t)(jobs < slots ? jobs : slots);
         p.cap = p.ny;
         // batches of planes: rounds of consecutive tile-products; one product: an eighth of them per XCD (see
         // PlaneGemm::run), which needs the same number of work-groups on every XCD
         p.interleave = planes > 1 || (p.units & 7) ? 1 : 2;
         p.partial = nullptr;
-    } else if (schedule == 2) {
+    } else if (schedule == RANGES) {
         p.units = (int32_t)(total < slots ? total : slots);
         p.cap = ceil_div(total, p.units);
         p.units = (int32_t)ceil_div(total, p.cap); // no idle work-group at the end
@@ -211,15 +241,31 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
         p.units = (int32_t)jobs;
         p.cap = p.ny;
         p.partial = nullptr;
+        p.interleave = schedule == TWO_PER_CU ? 4 : tile == 64 ? 5 : 0;
     }
-    if (const int err = launch(&p, stream)) return fail(LCMA_ERR_HIP, "%s: plane GEMM launch failed with HIP error %d", who, err);
+    int err = launch(&p, stream);
+    if (!err && schedule == SLICES) { // the fp32 products of the slices lie one after the other, in whole tiles
+        FewRowsParams q;
+        std::memset(&q, 0, sizeof q);
+        q.C = p.C;
+        q.ldc_b = p.ldc_b;
+        q.n_row_b = p.n_row_b;
+        q.row_blocks = p.nx;
+        q.block_rows = tile;
+        q.slices = p.units / (2 * p.jobs);
+        q.partial_ld = p.nz * tile;
+        q.partial = p.partial;
+        err = (kind == PG_BF16 ? lcma_launch_few_rows_sum_bf16 : lcma_launch_few_rows_sum_f16)(&q, (int)rows, stream);
+    }
+    if (err) return fail(LCMA_ERR_HIP, "%s: plane GEMM launch failed with HIP error %d", who, err);
     return LCMA_OK;
 }
 
-// Microseconds of the plain product on the ping-pong kernel with tiles of 256 x tn (f as in choose()).  256 x 128: 0.52 + 0.38 f a
+// Microseconds of the plain product on the ping-pong kernel with tiles of 256 x tn (f: share of the CUs that a round fills), as
+// the choice between it and the generated kernels was measured.  256 x 128: 0.52 + 0.38 f a
 // step (K x N: 0.60 + 0.32 f, its fragments wait for their own reads) and 4 a round (K x N: 2048 x 4096 x 4096 62 against 87 for
-// the generated kernel, 1024 x 4096 x 4096 50 / 56, 2048 x 4096 x 14336 210 / 284, 704 x 704 x 8000 80 / 98); 256 x 256: as in
-// choose() for either layout (K x N: 6144^3 394 / 495, 8192 x 14336 x 4096 704 / 863); 15 % more when rows do not start on
+// the generated kernel, 1024 x 4096 x 4096 50 / 56, 2048 x 4096 x 14336 210 / 284, 704 x 704 x 8000 80 / 98); 256 x 256: 0.80 + 0.72 f
+// and 6 (K x N: 6144^3 394 / 495, 8192 x 14336 x 4096 704 / 863); 15 % more when rows do not start on
 // 128-byte lines (5000 x 3000 x 1000 43 / 42), 30 % with N x K weights on the 256 x 128 tile (1178 x 2592 x 9952 130 / 104).
 double plain_product_us(bool b_kn, int tn, int64_t M, int64_t N, int64_t K, bool off_line) {
     const int64_t ny = ceil_div(K, 64), jobs = ceil_div(M, 256) * ceil_div(N, tn), full = jobs / kCUs, rest = jobs % kCUs;
@@ -234,13 +280,15 @@ double plain_product_us(bool b_kn, int tn, int64_t M, int64_t N, int64_t K, bool
 // The plain 16-bit product C = A B (b_kn: B is K x N) or A W^T on the ping-pong kernels, for lcma_gemm, lcma_gemm_nt and lcma_gemm_ex
 // (the same bits as the generated kernels: every element of C is one chain of 32x32x16 instructions over ascending k).
 // Arguments are checked by the caller; K a multiple of 8.  Returns false, with nothing launched, when the generated kernel is
-// predicted to take less than the `limit_us` given, or when padded offsets do not fit; else *err is the launch's HIP error.
+// predicted to take less than the `limit_us` given (tn, 256 or 128: this tile, whatever is predicted), or when padded offsets do not fit; else *err is the launch's HIP error.
 bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc,
-                   int dtype, double limit_us, void *stream, int *err) {
+                   int dtype, double limit_us, void *stream, int *err, int tn) {
     const int ny = (int)ceil_div(K, 64);
     auto cost = [&](int tn) { return plain_product_us(b_kn, tn, M, N, K, lda % 64 || ldb % 64); };
-    const int tn = cost(256) < cost(128) ? 256 : 128;
-    if (cost(tn) >= limit_us) return false;
+    if (!tn) {
+        tn = cost(256) < cost(128) ? 256 : 128;
+        if (cost(tn) >= limit_us) return false;
+    }
     const int64_t lim = (int64_t)1 << 31, Mp = ceil_div(M, 256) * 256, Np = ceil_div(N, 256) * 256, Kp = (int64_t)(ny + 1) * 64;
     if (((Mp - 1) * lda + Kp) * 2 >= lim || (b_kn ? (Kp - 1) * ldb + Np : (Np - 1) * ldb + Kp) * 2 >= lim || ((Mp - 1) * ldc + Np) * 2 >= lim) return false;
     PlaneGemmParams p;
@@ -274,40 +322,48 @@ bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, in
 
 namespace {
 // Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): form and slices of K with the smallest time, all constants measured (us;
-// bf16, three sets of operands in turn).  A CU takes in the lines of its work-groups at `rate` bytes/ns; `first` besides for the launch, the
-// first lines and the sum over the waves, `next` for every further work-group of a CU; and what the operands themselves take from
-// beyond the L2, as far as it does not lie behind the lines, 8 TB/s.  Slices of K: 1.3 for the second kernel, 0.25 a slice and 0.35 per MB of
-// partial products.  At 190 shapes, M 1 to 8872, N 8 to 14336, K 128 to 14400, with the workspace and without, the choice takes 1.009 of the time of
-// the fastest form (the plane GEMM among them), at the worst 1.23; the rates of the kernel before, 36 bytes/ns for all tiles: 1.27 and 2.1.
+// bf16).  A CU takes in the lines of its work-groups at `rate` bytes/ns, the slower by `crowd` the more CUs are at it and by `off` where rows do
+// not start on lines; `first` besides for the launch, the first lines and the sum over the waves, `next` for every further work-group of a
+// CU; and the operands come from beyond the L2 at `memory` TB/s.  Slices of K: 1.3 for the second kernel, 0.25 a slice and 0.35 per MB of
+// partial products.  Fitted to 260 shapes, M 16 to 6000, N 64 to 14336, K 512 to 14336, to 5 to 12 %; the choice between the forms takes 1.005 of the
+// time of the fastest.  (The rates before, 90 to 115 for all of them and 8 TB/s besides, were for the smallest form; they had 32 x 32 tiles a third
+// too slow.)
 struct FewRowsForm {
-    int tile, waves, deep, most; // most: work-groups per CU
-    double first, next, alone, rate;    // alone: rate with one work-group per CU
+    int tile, cols, waves, deep, most, sliced; // most: work-groups per CU; sliced: K in slices
+    double first, next, alone, rate, crowd, off, memory; // alone: rate with one work-group per CU
 };
-// (tiles of 64, three or more to a CU: the plane GEMM or a ping-pong kernel is faster, 1753 x 2000 x 7552 69 against 124 us, 2506 x 1056 x 4288 41 / 49;
-// tiles of 16 with eight waves and four lines in flight each fill the LDS of a CU: no second work-group beside the first, and slower
-// where there is one: 1 x 14336 x 1024 12.1 us, 7.6 with the smaller form, 16 x 8192 x 512 6.0 / 3.9; with few of them and a long K
-// the faster ones, 1 x 4096 x 14336 22.5 / 25.6, with a short one not, 1 x 1000 x 2048 4.3 / 3.7)
-const FewRowsForm kFewRowsForms[] = {{16, 4, 0, 4, 2.8, 0.3, 90.0, 100.0}, {16, 8, 1, 1, 3.5, 0.0, 115.0, 0.0}, {32, 4, 0, 4, 3.1, 0.85, 100.0, 100.0}, {64, 4, 0, 2, 4.8, 3.5, 105.0, 105.0}};
+// (tiles of 64, three or more to a CU: the plane GEMM or a ping-pong kernel is faster, 1753 x 2000 x 7552 69 against 124 us, 2506 x 1056 x 4288 41 / 49; two
+// to a CU: 64 x 128, 512 x 4096 x 4096 22.3 / 29.5, 320 x 4096 x 4096 19.3 / 28; tiles of 16 with eight waves and four lines in flight each fill the LDS of a CU: no
+// second work-group beside the first, and slower where there is one: 1 x 14336 x 1024 12.1 us, 7.6 with the smaller form, 16 x 8192 x 512 6.0
+// / 3.9; with few of them and a long K, from memory, the faster ones, 1 x 4096 x 14336 22.5 / 25.6, with a short one not, 1 x 1000 x 2048 4.3 / 3.7)
+const FewRowsForm kFewRowsForms[] = {{16, 16, 4, 0, 4, 0, 2.55, 0.02, 155.0, 172.0, 0.17, 0.24, 22.8}, {16, 16, 8, 1, 1, 0, 3.6, 0.0, 197.0, 0.0, 0.20, 0.13, 22.2},
+                                       {32, 32, 4, 0, 4, 0, 2.8, 0.09, 170.0, 163.0, 0.53, 0.27, 25.7}, {64, 64, 4, 0, 1, 0, 4.07, 0.0, 138.0, 0.0, 0.55, 0.26, 49.8},
+                                       {64, 64, 4, 0, 1, 1, 4.0, 0.0, 122.0, 0.0, 0.0, 0.35, 23.0}, {64, 128, 2, 1, 1, 0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0}};
+const int64_t kFewRows = 1024; // (with more the 64 x 128 tiles are the plane GEMM's)
 struct FewRowsPlan {
-    int tile, deep;
+    int tile, cols, deep;
     int64_t row_blocks, col_blocks, slices, slice_steps;
     double us;
 };
-FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, int64_t scratch_bytes) {
+FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, bool off_line, int64_t scratch_bytes) {
     FewRowsPlan best{};
     for (const FewRowsForm &f : kFewRowsForms) {
-        const int64_t rb = ceil_div(M, f.tile), cb = ceil_div(N, f.tile), steps = K / 32, batch = 2 * f.waves; // (steps of 32; a line of every wave)
-        if (rb * cb > (int64_t)f.most * kCUs) continue;
-        for (int64_t want : {(int64_t)1, kCUs / (rb * cb)}) {
-            if (want < 1 || (want > 1 && f.tile != 64)) continue;
-            const int64_t slice_steps = ceil_div(ceil_div(steps, want), batch) * batch, slices = ceil_div(steps, slice_steps);
-            const int64_t scratch = slices > 1 ? slices * rb * f.tile * cb * f.tile * 4 : 0;
-            if (scratch > scratch_bytes) continue;
-            const int64_t per_cu = ceil_div(rb * cb * slices, kCUs), lines = std::min(slice_steps, steps) / 2;
-            double us = f.first + f.next * (double)(per_cu - 1) + (double)(per_cu * lines * 256 * f.tile) / (1e3 * (per_cu > 1 ? f.rate : f.alone)) + (double)((M + N) * K * 2) / 8e6;
-            if (slices > 1) us += 1.3 + 0.25 * (double)slices + 0.35e-6 * (double)scratch;
-            if (!best.tile || us < best.us) best = FewRowsPlan{f.tile, f.deep, rb, cb, slices, slice_steps, us};
+        const int64_t rb = ceil_div(M, f.tile), cb = ceil_div(N, f.cols), steps = K / 32, batch = 2 * f.waves; // (steps of 32; a line of every wave)
+        if (rb * cb > (int64_t)f.most * kCUs || (f.cols == 128 && M > kFewRows)) continue;
+        const int64_t want = f.sliced ? kCUs / (rb * cb) : 1, slice_steps = ceil_div(ceil_div(steps, want), batch) * batch, slices = ceil_div(steps, slice_steps);
+        if (f.sliced && slices < 2) continue;
+        const int64_t scratch = slices > 1 ? slices * rb * f.tile * cb * f.cols * 4 : 0;
+        if (scratch > scratch_bytes) continue;
+        const int64_t groups = rb * cb * slices, per_cu = ceil_div(groups, kCUs), lines = std::min(slice_steps, steps) / 2;
+        double us;
+        if (f.cols == 128) {
+            us = rounds_us(kPlain[KPAIR_64], groups, kCUs, (lines + 1) & ~(int64_t)1, off_line);
+        } else {
+            const double share = std::min(1.0, (double)groups / kCUs), line = (off_line ? 1.0 + f.off : 1.0) * (1.0 + f.crowd * share);
+            us = f.first + f.next * (double)(per_cu - 1) + line * (double)(per_cu * lines * 128 * (f.tile + f.cols)) / (1e3 * (per_cu > 1 ? f.rate : f.alone)) + (double)((M + N) * K * 2) / (1e6 * f.memory);
         }
+        if (slices > 1) us += 1.3 + 0.25 * (double)slices + 0.35e-6 * (double)scratch;
+        if (!best.tile || us < best.us) best = FewRowsPlan{f.tile, f.cols, f.deep, rb, cb, slices, slice_steps, us};
     }
     return best;
 }
@@ -354,19 +410,18 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
     if (workspace && ((uintptr_t)workspace & 255)) return fail(LCMA_ERR_ARG, "%s: the workspace must be 256-byte aligned", who);
     const int kind = dtype == LCMA_BF16 ? PG_BF16 : PG_F16_OUT;
     const int64_t scratch = workspace ? workspace_bytes : 0;
+    int t = 0, sc = 0;
     if (!tuning_schedule()) { // (a forced schedule is one of the plane GEMM's)
         // (slices only with the bytes that the interface names: half of them serve the ranges on 128 x 128 tiles, fewer are left alone)
-        const FewRowsPlan f = few_rows_plan(M, N, K, scratch >= plane_gemm_scratch_bytes(256) ? scratch : 0);
-        int t = 0, sc = 0;
-        const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, scratch, &t, &sc);
+        const FewRowsPlan f = few_rows_plan(M, N, K, lda % 64 || ldw % 64, scratch >= plane_gemm_scratch_bytes(256) ? scratch : 0);
+        const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, lda % 64 || ldw % 64, M > kFewRows, scratch, &t, &sc);
         int err = 0;
-        // (against the ranges of steps a quarter on the safe side with two tiles of 64 per CU: 512 x 4096 x 14336 92 us, priced 112, in few rows 109, priced 95;
-        // 512 x 4096 x 12288 87 / 98; but 512 x 4096 x 8192 57 / 50; with fewer or smaller tiles both prices hold, 3 x 12672 x 10432 74 / 50,
-        // 1 x 10440 x 13440 75 / 53)
-        const bool full = f.tile == 64 && f.row_blocks * f.col_blocks > kCUs;
-        const bool few = f.tile && f.us * (sc == 2 && full ? 1.25 : 1.0) < planes_us;
-        // (1.5 us on the safe side: 840 x 5592 x 768 15.7 against 14.4, 4358 x 256 x 640 10.4 against 9.2)
-        if (plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, (few ? f.us : planes_us) - 1.5, stream, &err))
+        const bool few = f.tile && f.us < planes_us + (sc == SLICES && f.cols == 64 ? 2.0 : 0.0);
+        // the 256 x 128 ping-pong kernel, with some room: where the prices are that close 840 x 5592 x 768 runs in 14.2 us against 14.4
+        static const StepPrice narrow{0.51, 0.178, 0.21, 4.26, 0.0, 0.226};
+        const double narrow_us = rounds_us(narrow, ceil_div(M, 256) * ceil_div(N, 128), kCUs, p.ny, lda % 64 || ldw % 64);
+        if (narrow_us < 0.97 * (few ? f.us : planes_us) &&
+            plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, 0.0, stream, &err, 128))
             return err ? fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err) : LCMA_OK;
         if (few) {
             FewRowsParams q;
@@ -386,7 +441,7 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
             q.block_rows = f.tile;
             q.slices = (int32_t)f.slices;
             q.slice_steps = (int32_t)f.slice_steps;
-            q.partial_ld = (int32_t)(f.col_blocks * f.tile);
+            q.partial_ld = (int32_t)(f.col_blocks * f.cols);
             q.partial = workspace;
             q.deep = f.deep;
             const bool bf = dtype == LCMA_BF16;
@@ -399,5 +454,5 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
             return LCMA_OK;
         }
     }
-    return plane_gemm(who, kind, p, 1, M, N, 0, 0, workspace, scratch, stream);
+    return plane_gemm(who, kind, p, 1, M, N, t, sc, workspace, scratch, stream);
 }
