@@ -177,9 +177,11 @@ lcma_status empty_product(int64_t M, int64_t N, void *C, int64_t ldc, int dtype,
 
 // B and ldb describe the K x N matrix; for a variant that takes the weight layout, the N x K matrix W;
 // for a prepared-B variant, the planes written by lcma_prepare_b (ldb is then ignored).
-// plain_us > 0: the plain product may run on the ping-pong kernels instead if they take less than that.
+// plain_us > 0: the plain product may run on the ping-pong kernels instead if they take less than that.  small: the plain product, which may run on
+// the kernels for few tiles.
 static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
-                       int64_t ldb, void *C, int64_t ldc, void *stream, float alpha = 1.f, float beta = 0.f, double plain_us = 0.0) {
+                       int64_t ldb, void *C, int64_t ldc, void *stream, float alpha = 1.f, float beta = 0.f, double plain_us = 0.0,
+                       bool small = false) {
     const int es = dtype_size(v.dtype);
     if (v.left_planes || v.batch)
         return fail(LCMA_ERR_ARG, "lcma_gemm: %s is a stage kernel of lcma_gemm_unfused and takes no matrices", v.name);
@@ -208,6 +210,11 @@ static lcma_status run(const Variant &v, int64_t M, int64_t N, int64_t K, const 
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: a matrix spans 2 GiB or more");
     if (overlap(C, c_bytes, A, a_bytes) || overlap(C, c_bytes, B, b_bytes))
         return fail(LCMA_ERR_ARG, "lcma_gemm: C overlaps A or B");
+    if (small) {
+        int err = 0;
+        if (small_plain(!v.b_nk, M, N, K, A, lda, B, ldb, C, ldc, v.dtype, stream, &err))
+            return err ? fail(LCMA_ERR_HIP, "lcma_gemm: launch failed with HIP error %d", err) : LCMA_OK;
+    }
     if (plain_us > 0.0) {
         int err = 0;
         if (plain_product(!v.b_nk, M, N, K, A, lda, B, ldb, C, ldc, v.dtype, plain_us, stream, &err))
@@ -281,6 +288,7 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
     const Variant *v = forced_variant(); // ablation override
     if (v && (v->scheme_id != id || v->dtype != (int)dtype || v->prepared || v->b_nk != b_nk)) v = nullptr;
     double plain_us = 0.0;
+    const bool small = !v && id == LCMA_PLAIN && alpha == 1.f && beta == 0.f;
     if (!v) {
         v = pick_variant(id, dtype, M, N, K, 0, b_nk);
         // the plain 16-bit product without scaling: the ping-pong kernels where they are faster (the same bits)
@@ -306,7 +314,7 @@ static lcma_status gemm(int b_nk, int64_t M, int64_t N, int64_t K, const void *A
         return fail(LCMA_ERR_SHAPE, "lcma_gemm: no kernel of scheme id %d takes N = %lld (whole 16-byte vectors) and K = %lld (whole tiles)",
                     id, (long long)N, (long long)K);
     }
-    return run(*v, M, N, K, A, lda, B, ldb, C, ldc, stream, alpha, beta, plain_us);
+    return run(*v, M, N, K, A, lda, B, ldb, C, ldc, stream, alpha, beta, plain_us, small);
 }
 
 extern "C" lcma_status lcma_gemm_ex(float alpha, float beta, int b_layout, int64_t M, int64_t N, int64_t K, const void *A,

@@ -40,6 +40,15 @@ template <> struct Mma16<BF16> {
     static LCMA_DEV f32x4 run(frag a, frag b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 
+template <> struct Mma16<F32> { // (the same four k of a lane in both operands)
+    using frag = f32x4;
+    static LCMA_DEV f32x4 run(frag a, frag b, f32x4 c) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], c, 0, 0, 0);
+        return c;
+    }
+};
+
 // s_waitcnt for all but the N youngest vector memory instructions; nothing moves across it
 template <int N> LCMA_DEV void wait_loads() {
     __builtin_amdgcn_sched_barrier(0);
@@ -48,9 +57,13 @@ template <int N> LCMA_DEV void wait_loads() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// T: rows and columns of the tile of C; WK waves, all along K; S lines of 64 k of a wave in flight.
-template <class KIND, int T, int WK, int S> struct FewRows {
+// T: rows and columns of the tile of C; WK waves, all along K; S lines of 128 bytes of every row (64 k, fp32: 32) of a wave in flight.
+// KN: the right operand is B, K x N: a line of it is its rows (k) of T columns, and the fragments of 16-bit types are read with the transposing
+// LDS read.  TAIL: K may end inside a line.  Either layout adds the same terms in the same order.
+template <class KIND, int T, int WK, int S, bool KN = false, bool TAIL = KN> struct FewRows {
     static constexpr int F = T == 16 ? 16 : 32, NF = T / F, KF = 64 / (512 / F); // 16x16x32 or 32x32x16 instructions; fragments of a line along K
+    static constexpr int ES = KIND::ES, LINE_K = 128 / ES;
+    static_assert(T >= 32 || (!KN && ES == 2), "tiles of 16: rows of 16-bit weights");
     static constexpr int LOADS = T / 8, HALF = T * 128, STAGE = 2 * HALF;         // direct loads of 1 KB and bytes of a line of either operand
     static constexpr int PITCH = T + 4;                                           // (floats; 4: the row groups of a write meet different banks)
     static constexpr int SUMS = WK * T * PITCH * 4, STAGES = WK * S * STAGE, LDS_BYTES = SUMS > STAGES ? SUMS : STAGES;
@@ -99,12 +112,40 @@ template <class KIND, int T, int WK, int S> struct FewRows {
             if (p.slices > 1) { // (the second kernel adds the slices)
                 *(f32x4 *)((float *)p.partial + ((int64_t)slice * p.row_blocks * T + m) * p.partial_ld + cb * T + col) = sum;
             } else {
-                const uint32_t colb = (uint32_t)(cb * T + col) * 2;
+                const uint32_t colb = (uint32_t)(cb * T + col) * ES;
                 const uint32_t off = colb < p.n_row_b ? (uint32_t)m * p.ldc_b + colb : p.c_bytes; // rows past M: past the extent
-                const u32x2 v = {Round<KIND>::run(sum[0]) | (Round<KIND>::run(sum[1]) << 16), Round<KIND>::run(sum[2]) | (Round<KIND>::run(sum[3]) << 16)};
-                __builtin_amdgcn_raw_buffer_store_b64(v, rc, (int)off, 0, 0);
+                if constexpr (ES == 4) {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, sum), rc, (int)off, 0, 0);
+                } else {
+                    const u32x2 v = {Round<KIND>::run(sum[0]) | (Round<KIND>::run(sum[1]) << 16), Round<KIND>::run(sum[2]) | (Round<KIND>::run(sum[3]) << 16)};
+                    __builtin_amdgcn_raw_buffer_store_b64(v, rc, (int)off, 0, 0);
+                }
             }
         }
+    }
+    // KN, 16-bit: chunk c of row k of a line sits at position c ^ column_swizzle(k), so that the four rows of a transposing read meet different
+    // banks (rows of 64 bytes do so by themselves).
+    static LCMA_DEV constexpr int column_swizzle(int k) { return KN && ES == 2 && T == 64 ? (k >> 1 & 1) * 4 : 0; }
+    // Fragments of 32 columns, 32 block and on, of a line (64 rows of T columns); as read_columns of lcma_pingpong.hpp, whose rows are 256 bytes.
+    static LCMA_DEV void read_columns(const LCMA_LDS char *line, int block, Frag (&f)[KF]) {
+        constexpr int P = T * 2;
+        const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4, k = i >> 2, c = block * 4 + (g & 1) * 2 + ((i & 3) >> 1);
+        const uint32_t at = (uint32_t)(uintptr_t)line + ((g >> 1) * 8 + k) * P + (c ^ column_swizzle(k)) * 16 + (i & 1) * 8;
+        u32x2 r[4][2];
+        asm volatile("ds_read_b64_tr_b16 %0, %8\n"
+                     "ds_read_b64_tr_b16 %1, %8 offset:%9\n"
+                     "ds_read_b64_tr_b16 %2, %8 offset:%10\n"
+                     "ds_read_b64_tr_b16 %3, %8 offset:%11\n"
+                     "ds_read_b64_tr_b16 %4, %8 offset:%12\n"
+                     "ds_read_b64_tr_b16 %5, %8 offset:%13\n"
+                     "ds_read_b64_tr_b16 %6, %8 offset:%14\n"
+                     "ds_read_b64_tr_b16 %7, %8 offset:%15\n"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(r[0][0]), "=&v"(r[0][1]), "=&v"(r[1][0]), "=&v"(r[1][1]), "=&v"(r[2][0]), "=&v"(r[2][1]), "=&v"(r[3][0]), "=&v"(r[3][1])
+                     : "v"(at), "n"(4 * P), "n"(16 * P), "n"(20 * P), "n"(32 * P), "n"(36 * P), "n"(48 * P), "n"(52 * P)
+                     : "memory");
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = __builtin_bit_cast(Frag, u32x4{r[j][0][0], r[j][0][1], r[j][1][0], r[j][1][1]});
     }
     // Lines `line`, line + WK, ... below `end` of tile (mb, cb).  s0 .. s3: the stages of the wave.  restrict: the loads in flight towards
     // one do not touch what is read from another (the compiler would otherwise wait for all of them in front of every read).  It holds
@@ -116,21 +157,27 @@ template <class KIND, int T, int WK, int S> struct FewRows {
         const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.W), 0, (int)p.w_bytes, 0x00020000);
         // A load brings 8 rows of 128 bytes, lanes 8 i to 8 i + 7 one row.  Rows past M or N lie past the extents and read as zero; 16-byte
         // chunk c of row i sits at position c ^ (i / 2 % 8), so that 16 rows at one chunk column meet all banks once.
-        uint32_t av[2], bv[2]; // even and odd loads of a line
+        uint32_t av[2], bv[2], at[2], bt[2]; // even and odd loads of a line (at, bt: of the last one, what is past K from past the extents)
+        const int lines = p.steps / 2;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const uint32_t c = ((lane & 7) ^ (lane >> 4) ^ (4 * i)) * 16;
             av[i] = (uint32_t)(mb * T + (lane >> 3)) * p.lda_b + c;
             bv[i] = (uint32_t)(cb * T + (lane >> 3)) * p.ldw_b + c;
+            at[i] = TAIL && c >= p.tail_b ? p.a_bytes : av[i];
+            bt[i] = TAIL && c >= p.tail_b ? p.w_bytes : bv[i];
         }
+        constexpr int CPR = T * ES / 16, RPL = 64 / CPR; // KN: 16-byte chunks of a row (k) of the line, rows of a load
+        if constexpr (KN) bv[0] = (uint32_t)(lane / CPR) * p.ldw_b + (uint32_t)(cb * T) * ES + ((lane % CPR) ^ column_swizzle(lane / CPR)) * 16; // (rows past K: past the extent)
         auto load = [&](LCMA_LDS char *st, int line) { // a line past the end is read from the end of the extents: zeros
-            const uint32_t ka = line < end ? (uint32_t)line * 128 : p.a_bytes, kb = line < end ? (uint32_t)line * 128 : p.w_bytes;
+            const bool in = line < end, last = TAIL && line + 1 == lines;
+            const uint32_t ka = in ? (uint32_t)line * 128 : p.a_bytes, kb = in ? (uint32_t)line * (KN ? LINE_K * p.ldw_b : 128) : p.w_bytes;
 #pragma unroll
             for (int i = 0; i < LOADS; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LCMA_LDS void *)(st + i * 1024), 16, (int)av[i & 1], (int)(ka + i * 8 * p.lda_b), 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (LCMA_LDS void *)(st + i * 1024), 16, (int)(last ? at[i & 1] : av[i & 1]), (int)(ka + i * 8 * p.lda_b), 0, 0);
 #pragma unroll
             for (int i = 0; i < LOADS; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (LCMA_LDS void *)(st + HALF + i * 1024), 16, (int)bv[i & 1], (int)(kb + i * 8 * p.ldw_b), 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (LCMA_LDS void *)(st + HALF + i * 1024), 16, (int)(KN ? bv[0] : last ? bt[i & 1] : bv[i & 1]), (int)(kb + i * (KN ? RPL : 8) * p.ldw_b), 0, 0);
         };
         uint32_t frag[KF]; // of this lane's 16 bytes in either operand's rows
 #pragma unroll
@@ -143,7 +190,18 @@ template <class KIND, int T, int WK, int S> struct FewRows {
 #pragma unroll
                 for (int i = 0; i < NF; ++i) {
                     a[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + frag[k] + i * F * 128));
-                    b[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + HALF + frag[k] + i * F * 128));
+                    if constexpr (!KN) b[k][i] = __builtin_bit_cast(Frag, *(const LCMA_LDS u32x4 *)(st + HALF + frag[k] + i * F * 128));
+                    else if constexpr (ES == 4)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) b[k][i][t] = *(const LCMA_LDS float *)(st + HALF + ((k * 2 + fk) * 4 + t) * (T * ES) + (i * F + fr) * 4);
+                }
+            if constexpr (KN && ES == 2)
+#pragma unroll
+                for (int i = 0; i < NF; ++i) {
+                    Frag col[KF];
+                    read_columns(st + HALF, i, col);
+#pragma unroll
+                    for (int k = 0; k < KF; ++k) b[k][i] = col[k];
                 }
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_s_waitcnt(0xC07F); // lgkmcnt(0): what was read has left LDS, so its place may be loaded anew

@@ -34,6 +34,24 @@ LCMA_FR_DECL(bf16_16)
 LCMA_FR_DECL(bf16_32)
 LCMA_FR_DECL(bf16_64)
 
+#define LCMA_SP_DECL(NAME) extern "C" int lcma_launch_plain_##NAME(const lcma::FewRowsParams *p, int grid, void *stream);
+#define LCMA_SP_DECL2(NAME) extern "C" int lcma_launch_plain_##NAME(const lcma::PlaneGemmParams *p, void *stream);
+LCMA_SP_DECL(f32_t32x32x32_k4)
+LCMA_SP_DECL(f32_t32x32x32_k4t)
+#define LCMA_SP_TYPE(TYPE)                                                                          \
+    LCMA_SP_DECL(TYPE##_t32x32x64_k4)                                                               \
+    LCMA_SP_DECL(TYPE##_t32x32x64_k4t)                                                              \
+    LCMA_SP_DECL(TYPE##_t64x64x64_k4)                                                               \
+    LCMA_SP_DECL(TYPE##_t64x64x64_k4t)                                                              \
+    LCMA_SP_PAIRS(TYPE)
+#define LCMA_SP_PAIRS(TYPE)                                                                         \
+    LCMA_SP_DECL2(TYPE##_t64x128x64_k2)                                                             \
+    LCMA_SP_DECL2(TYPE##_t64x128x64_k2t)                                                            \
+    LCMA_SP_DECL2(TYPE##_t128x128x64_k2)                                                            \
+    LCMA_SP_DECL2(TYPE##_t128x128x64_k2t)
+LCMA_SP_TYPE(bf16)
+LCMA_SP_TYPE(f16)
+
 namespace lcma {
 
 namespace {
@@ -368,6 +386,113 @@ FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, bool off_line, int64_
     return best;
 }
 } // namespace
+
+namespace {
+// The plain product on few tiles (csrc/lcma_small_plain.hip): microseconds of a form that splits K between waves, and of the fastest of the generated and
+// the ping-pong kernels with N x K weights.  Both from sizes and the alignment of A's rows alone, so that either layout of B makes the
+// same choice (they add the same terms in the same order: the same bits).  All measured: 470 products of 192 to 8192 rows and columns, K 192 to 14336,
+// rows on lines and off, fitted to 4 to 14 % (the forms) and 14 to 20 % (what they are compared with, hence the margin).  With it the choice
+// takes, K x N, 16 bit, 0.61 of the time of before in the geometric mean (every time the faster form: 0.59), fp32 0.71 (0.70), none slower; N x K
+// 0.72 (0.70) and 0.75 (0.74), the worst 1.07 (920 x 632 x 616: 6.3 us).  K x N, us: 335 x 1328 x 4344 bf16 55 / 17, 448 x 312 x 3416 fp16 32 / 8, 1117
+// x 608 x 7448 92 / 32, 1767 x 1216 x 10968 142 / 79, fp32 205 x 328 x 4256 96 / 23, 883 x 800 x 13800 316 / 192.
+struct SmallForm {
+    int tm, tn, slots;
+    double start, step, crowd, off, more; // a step of 128 bytes of K, `crowd` times the share of the work-groups that fit more; `more`: a round
+};
+const SmallForm kSmall16[] = {{32, 32, 256, 2.56, 0.110, 0.0045, 0.104, 0.48}, {64, 64, 256, 4.07, 0.193, 0.021, 0.167, 2.97}, {64, 128, 256, 1.09, 0.264, 0.073, 0.227, 2.05}, {128, 128, 256, 0.93, 0.335, 0.134, 0.249, 2.93}};
+const SmallForm kSmall32[] = {{32, 32, 256, 3.30, 0.136, 0.0, 0.035, 0.79}}; // (64 x 64, matrix instructions of one wave after the other: never ahead)
+const SmallForm kOther16[] = {{64, 64, 1024, 1.62, 0.41, 0.29, 0.19, 1.14}, {128, 128, 512, 4.28, 0.90, 0.08, 0.19, 3.84}, {256, 128, 256, 3.84, 0.39, 0.59, 0.19, 3.59}, {256, 256, 256, 2.96, 0.60, 0.85, 0.19, 6.86}};
+const SmallForm kOther32[] = {{64, 64, 1024, 0.65, 0.45, 1.60, 0.03, 1.60}, {128, 128, 512, 0.04, 0.71, 3.11, 0.03, 2.52}};
+double small_us(const SmallForm &f, int64_t M, int64_t N, int64_t lines, bool off_line, bool in_rounds) {
+    const int64_t groups = ceil_div(M, f.tm) * ceil_div(N, f.tn), full = groups / f.slots, rest = groups % f.slots;
+    const double line = off_line ? 1.0 + f.off : 1.0, share = (double)rest / f.slots;
+    auto step = [&](double s) { return (double)lines * line * (f.step + f.crowd * s); };
+    if (in_rounds) return f.start + (double)full * (step(1.0) + f.more) + (rest ? step(share) + f.more : 0.0);
+    const int64_t turns = full + (rest != 0); // (four waves to a work-group, several work-groups to a CU)
+    return f.start + (double)turns * step(full ? 1.0 : share) + f.more * (double)(turns - 1);
+}
+} // namespace
+
+// Returns false, with nothing launched, when another kernel is predicted to be as fast or padded offsets do not fit; else *err is the launch's
+// HIP error.  Arguments are checked by the caller; rows are whole 16-byte vectors.
+bool small_plain(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc, int dtype,
+                 void *stream, int *err) {
+    const int es = dtype_size(dtype);
+    const bool wide = es == 4, off_line = (lda * es & 127) != 0;
+    const int64_t lines = ceil_div(K * es, 128);
+    double limit = 0.0;
+    for (int i = 0; i < (wide ? 2 : 4); ++i) {
+        const double other = small_us(wide ? kOther32[i] : kOther16[i], M, N, lines, off_line, true);
+        if (!i || other < limit) limit = other;
+    }
+    limit *= wide ? 0.82 : 0.85;
+    const SmallForm *form = nullptr;
+    for (int i = 0; i < (wide ? 1 : 4); ++i) {
+        const SmallForm &f = wide ? kSmall32[i] : kSmall16[i];
+        if (i < 2 && ceil_div(M, f.tm) * ceil_div(N, f.tn) > 8 * kCUs) continue;
+        const double t = small_us(f, M, N, i > 1 && lines > 2 ? (lines + 1) & ~(int64_t)1 : lines, off_line, i > 1);
+        if (t < limit) {
+            form = &f;
+            limit = t;
+        }
+    }
+    if (!form) return false;
+    const int64_t lim = (int64_t)1 << 31, Mp = ceil_div(M, 128) * 128, Np = ceil_div(N, 128) * 128, Kp = lines * 128 / es;
+    if (((Mp - 1) * lda + Kp) * es >= lim || (b_kn ? (Kp - 1) * ldb + Np : (Np - 1) * ldb + Kp) * es >= lim || ((Mp - 1) * ldc + Np) * es >= lim) return false;
+    const int64_t rb = ceil_div(M, form->tm), cb = ceil_div(N, form->tn);
+    const uint32_t a_bytes = (uint32_t)(((M - 1) * lda + K) * es), b_bytes = (uint32_t)((b_kn ? (K - 1) * ldb + N : (N - 1) * ldb + K) * es);
+    const uint32_t c_bytes = (uint32_t)(((M - 1) * ldc + N) * es), tail_b = (uint32_t)(K * es - (lines - 1) * 128);
+    const int type = dtype == LCMA_BF16 ? 0 : dtype == LCMA_F16 ? 1 : 2;
+    if (form->tn == 128) {
+        PlaneGemmParams p;
+        std::memset(&p, 0, sizeof p);
+        p.A = A;
+        p.B = B;
+        p.C = C;
+        p.a_bytes = a_bytes;
+        p.b_bytes = b_bytes;
+        p.c_bytes = c_bytes;
+        p.lda_b = (uint32_t)(lda * es);
+        p.ldb_b = (uint32_t)(ldb * es);
+        p.ldc_b = (uint32_t)(ldc * es);
+        p.ny = (int32_t)lines;
+        p.cap = lines;
+        p.tail_b = tail_b;
+        p.n_row_b = (uint32_t)(N * es);
+        p.nx = (int32_t)rb;
+        p.nz = (int32_t)cb;
+        p.jobs = p.units = (int32_t)(rb * cb);
+        p.panel = panel_of(p.nz, 8);
+        static const Launch launch[2][2][2] = {{{lcma_launch_plain_bf16_t64x128x64_k2t, lcma_launch_plain_bf16_t64x128x64_k2}, {lcma_launch_plain_bf16_t128x128x64_k2t, lcma_launch_plain_bf16_t128x128x64_k2}},
+                                               {{lcma_launch_plain_f16_t64x128x64_k2t, lcma_launch_plain_f16_t64x128x64_k2}, {lcma_launch_plain_f16_t128x128x64_k2t, lcma_launch_plain_f16_t128x128x64_k2}}};
+        *err = launch[type][form->tm == 128][b_kn](&p, stream);
+        return true;
+    }
+    FewRowsParams q;
+    std::memset(&q, 0, sizeof q);
+    q.A = A;
+    q.W = B;
+    q.C = C;
+    q.a_bytes = a_bytes;
+    q.w_bytes = b_bytes;
+    q.c_bytes = c_bytes;
+    q.lda_b = (uint32_t)(lda * es);
+    q.ldw_b = (uint32_t)(ldb * es);
+    q.ldc_b = (uint32_t)(ldc * es);
+    q.n_row_b = (uint32_t)(N * es);
+    q.steps = (int32_t)(2 * lines);
+    q.row_blocks = (int32_t)rb;
+    q.block_rows = form->tm;
+    q.slices = 1;
+    q.slice_steps = (int32_t)(2 * lines);
+    q.partial_ld = (int32_t)(cb * form->tn);
+    q.tail_b = tail_b;
+    typedef int (*FewLaunch)(const FewRowsParams *, int, void *);
+#define LCMA_SP_ROW(TYPE) {{lcma_launch_plain_##TYPE##_t32x32x64_k4t, lcma_launch_plain_##TYPE##_t32x32x64_k4}, {lcma_launch_plain_##TYPE##_t64x64x64_k4t, lcma_launch_plain_##TYPE##_t64x64x64_k4}}
+    static const FewLaunch launch[3][2][2] = {LCMA_SP_ROW(bf16), LCMA_SP_ROW(f16), {{lcma_launch_plain_f32_t32x32x32_k4t, lcma_launch_plain_f32_t32x32x32_k4}, {nullptr, nullptr}}};
+    *err = launch[type][form->tm == 64][b_kn](&q, (int)(rb * cb), stream);
+    return true;
+}
 
 } // namespace lcma
 
