@@ -105,7 +105,7 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
     }
 
     struct State {
-        __amdgpu_buffer_rsrc_t ra, rb, rsa, rsb, rc;
+        __amdgpu_buffer_rsrc_t ra, rb, rsa, rsb;
         uint32_t a_voff, b_voff; // of the first direct load of a step; load q is NT / 8 rows further down
         uint32_t a_step, b_step; // byte step between the rows of consecutive loads
         uint32_t a_lds, b_lds;   // register staging: LDS position of this thread's chunk (load q: q * NT / 8 rows further down)
@@ -266,7 +266,6 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
         s.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.B), 0, (int)p.b_bytes, 0x00020000);
         s.rsa = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.SA), 0, (int)p.sa_bytes, 0x00020000);
         s.rsb = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.SB), 0, (int)p.sb_bytes, 0x00020000);
-        s.rc = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)p.c_bytes, 0x00020000);
         // direct loads: LDS position (row, cs) of a stage is filled from memory chunk swz(row, cs) of that row (the XOR
         // is its own inverse); a wave instruction fills 64 consecutive positions
         // (load q of a thread covers row q * NT / 8 + tid / 8 at position tid % 8; NT / 8 is a multiple of 16, so the
@@ -502,7 +501,10 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
         constexpr int OES = OUT::ES; // 2: C rounded to fp16 / bf16; 4: the fp32 sums as they are
         constexpr int SR = STRIP_ROWS, PITCH = WN * OES + 16, CPRW = WN * OES / 16, NIT = SR * CPRW / 64;
         static_assert(NT / 64 * SR * PITCH <= (XTILE ? STAGE : LDS_BYTES), "the strips of all waves fit the stage buffers");
-        const uint32_t c_base = (uint32_t)plane * p.c_plane + (uint32_t)x * TM * p.ldc_b + (uint32_t)z * TN * OES;
+        // batched: the extent is that of the plane, so a tile may hang over the end of it
+        const uint32_t extent = p.c_plane ? p.c_plane : p.c_bytes;
+        const auto rc = __builtin_amdgcn_make_buffer_rsrc((char *)p.C + (uint32_t)plane * p.c_plane, 0, (int)extent, 0x00020000);
+        const uint32_t c_base = (uint32_t)x * TM * p.ldc_b + (uint32_t)z * TN * OES;
         LCMA_LDS char *strip = lds + s.w * (SR * PITCH);
 #pragma unroll
         for (int mi = 0; mi < NMI; ++mi) {
@@ -526,8 +528,8 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
                     // past M fall outside the extent by themselves
                     const uint32_t off = ((uint32_t)z * TN * OES + colb < p.n_row_b)
                                              ? c_base + (uint32_t)(s.wm * WM + mi * 32 + h * SR + row) * p.ldc_b + colb
-                                             : p.c_bytes;
-                    __builtin_amdgcn_raw_buffer_store_b128(v, s.rc, (int)off, 0, kStreamed);
+                                             : extent;
+                    __builtin_amdgcn_raw_buffer_store_b128(v, rc, (int)off, 0, kStreamed);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             }
@@ -567,7 +569,6 @@ template <class KIND, int TM, int TN, int WGM, int WGN, class OUT, bool SPLIT = 
         s.wn = s.w % WGN;
         s.l32 = s.lane & 31;
         s.lh = s.lane >> 5;
-        s.rc = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)p.c_bytes, 0x00020000);
         f32x16 acc[NMI][NNI];
         auto add_piece = [&](int slot, bool first) {
             const float *src = (const float *)p.partial + (int64_t)slot * TILE_FLOATS;

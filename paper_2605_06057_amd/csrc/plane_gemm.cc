@@ -127,9 +127,7 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             if (schedule && sc != schedule && !(sc == TWO_PER_CU && schedule == STATIC)) continue;
             const bool pingpong = t == 256 && sc == PERSIST;
             if (t == 64 && sc != STATIC) continue;
-            if (!schedule && sc == PERSIST && t == 128) continue; // (the same kernel as STATIC)
-            // planes lie back to back: only the ping-pong kernel lets a tile hang over the end of one
-            if (planes > 1 && !pingpong && (rows % t || cols % tile_cols(t))) continue;
+            if (!schedule && (t == 128 ? sc == PERSIST : t == 256 && sc == STATIC)) continue; // (128: the same kernel as STATIC; 256 x 256: never ahead by more than 1 %)
             if (sc == RANGES && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
             double cost;
             if (sc == RANGES) {
@@ -143,6 +141,7 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             } else if (sc == TWO_PER_CU) {
                 if (t != 128) continue;
                 cost = rounds_us(price[TWO_128], jobs, 2 * kCUs, ny, off_line);
+                if (planes > 1 && jobs >= 20 * kCUs) cost *= 1.05; // (ten rounds and more, measured: the planes lie far beyond the caches; 4838 x 12672 x 1656 346 us, 328 on the large tile)
             } else if (t < 256) {
                 cost = rounds_us(price[t == 128 ? KPAIR_128 : KPAIR_64], jobs, kCUs, even, off_line);
             } else if (pingpong) {
@@ -210,7 +209,7 @@ static int panel_of(int nz, int wide) {
 }
 
 // p: operands, extents, pitches, plane strides, ny, n_row_b filled in by the caller for `planes` planes of rows x cols
-// (padded sizes; when batched only the ping-pong kernel takes planes that are no whole tiles).  tile: 256 or 128, 0 = choose.
+// (padded sizes; a tile may hang over the end of a plane).  tile: 256 or 128, 0 = choose.
 // schedule: 0 = choose, 1 = one tile-product per work-group, 2 = Split-Group ranges (needs `scratch` of
 // plane_gemm_scratch_bytes(tile) bytes), 4 = slices of K (plain 16-bit products), 3 = persistent work-groups that each take every units-th whole tile-product.
 lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes, int64_t rows, int64_t cols, int tile,
@@ -223,7 +222,7 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
         if (schedule == 2)
             return fail(LCMA_ERR_ARG, "%s: the Split-Group schedule needs %lld bytes of scratch", who,
                         (long long)plane_gemm_scratch_bytes(tile ? tile : 256));
-        return fail(LCMA_ERR_SHAPE, "%s: planes must be whole tiles", who);
+        return fail(LCMA_ERR_SHAPE, "%s: no tile and schedule fit", who);
     }
     tile = best_tile;
     schedule = best_sched;

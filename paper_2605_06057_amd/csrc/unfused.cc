@@ -247,7 +247,7 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
     if (N % vec || K % vec)
         return fail(LCMA_ERR_SHAPE, "%s: N = %lld and K = %lld must be multiples of %d (16 bytes of elements)", who,
                     (long long)N, (long long)K, vec);
-    const Geometry g = geometry(*scheme, M, N, K, dtype);
+    Geometry g = geometry(*scheme, M, N, K, dtype);
     if (workspace_bytes < g.total())
         return fail(LCMA_ERR_ARG, "%s: the workspace holds %lld bytes, %lld are needed", who, (long long)workspace_bytes,
                     (long long)g.total());
@@ -266,6 +266,13 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
     const Variant *gemm = level == 1 ? find_gemm(true, LCMA_PLAIN, ct, R, g) : find_gemm(false, id, dtype, scheme->R, g);
     if (!gemm) return fail(LCMA_ERR_NOKERNEL, "%s: no GEMM stage kernel for level %d fits the planes", who, level);
 
+    // Level 1 in 16 bit: the blocks of rows are cut at whole 16 rows (what Combine A and Combine H give to a work-group) and not at whole
+    // tiles, which the plane GEMM does not need: 545 rows in four are 144 each instead of 256.  Planes stay where whole tiles would have
+    // put them.  Only where an eighth of the rows or more, and 4 MB or more (about 1 us), would be nothing but padding: with less nothing is
+    // gained (4838 x 12672 x 1656 in four 330 -> 340 us), and the cut stays that of the generated kernels.
+    const bool on_planes = level == 1 && es == 2 && !forced_unfused_variant() && !tuning_batch_order();
+    const int64_t fine = round_up((M + scheme->m - 1) / scheme->m, 16);
+    if (on_planes && fine * 8 <= g.bm * 7 && (int64_t)R * (g.bm - fine) * (g.bk * es + g.bn * g.h_es) >= (4 << 20)) g.bm = fine;
     // (the rows of the planes are the y dimension of the grids of Combine A and Combine H)
     if (g.bm / 16 > 65535) return fail(LCMA_ERR_SHAPE, "%s: M is too large", who);
     const int stages = tuning_unfused_stages(); // measurement aid: stages switched off keep the output of an earlier call
@@ -319,14 +326,13 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
         // 16-bit: the plane GEMM, which can hand the tile-products out in Split-Group ranges (Sec. 3.2) when the
         // workspace has room for the pieces beyond the planes; it writes the products in fp32 for fp16 storage.  The
         // generated batched kernel (ablations) writes them in fp16 for both 16-bit types.
-        const bool planes = es == 2 && !forced_unfused_variant() && !p.batch_order;
-        const int h_es = planes ? (int)g.h_es : es;
+        const int h_es = on_planes ? (int)g.h_es : es;
         p.c_bytes = (uint32_t)((int64_t)R * g.bm * g.bn * h_es);
         p.ldc_b = (uint32_t)(g.bn * h_es);
         p.c_brow = (uint32_t)(g.bm * g.bn * h_es);
         p.n_row_b = (uint32_t)(g.bn * h_es);
         if (!(stages & 4)) {
-        } else if (planes) {
+        } else if (on_planes) {
             PlaneGemmParams q;
             std::memset(&q, 0, sizeof q);
             q.A = At;
