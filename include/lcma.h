@@ -247,7 +247,8 @@ int64_t lcma_split_group_scratch_bytes(void);
 /* Plain GEMM C = A x W^T for weights stored N x K (as lcma_gemm_nt with scheme == NULL; BF16 and F16) on the kernel of the
  * batched stage, with a workspace (device, 256-byte aligned, lcma_split_group_scratch_bytes() bytes, overwritten; half of
  * them serve its 128 x 128 tiles alone; NULL or fewer bytes: never split) that lets it hand the steps of all tiles out in Split-Group ranges: the split-K form of a plain
- * GEMM, chosen when the tiles alone would leave much of the chip idle (few tiles, long K).  Few rows or a small C run on a
+ * GEMM, chosen when the tiles alone would leave much of the chip idle (few tiles, long K); with the whole workspace K is cut into slices for
+ * work-groups of their own instead where that is faster (fp32 partial products, added in ascending order).  Few rows or a small C run on a
  * kernel of their own, whose waves split K inside a work-group; with the whole workspace K may be split between work-groups as well
  * (fp32 partial products, added in ascending order).  K not a multiple of 64 and F32
  * are passed on to lcma_gemm_nt.  Integer-valued inputs give lcma_gemm_nt's bits; float inputs agree to the last bit or two
@@ -387,10 +388,11 @@ double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int64_t K, lcma
  *                                                   5 (15, 14, 13) where that divides the columns of tiles and 8 (16) does not)
  *   "batch_order"      LCMA_BATCH_ORDER=1           batched GEMM of lcma_gemm_unfused level 1 in group-major instead of
  *                                                   product-major order
- *   "schedule"         LCMA_SCHEDULE=static|split|persist   batched GEMM stages: one tile-product per work-group, contiguous
+ *   "schedule"         LCMA_SCHEDULE=static|split|persist|slices   batched GEMM stages: one tile-product per work-group, contiguous
  *                                                   ranges of steps per persistent work-group (Sec. 3.2, Split-Group
- *                                                   Parallelism), or persistent work-groups that take whole tile-products in
- *                                                   turn; default: whichever the time model prefers
+ *                                                   Parallelism), persistent work-groups that take whole tile-products in
+ *                                                   turn, or slices of K (plain 16-bit products of few tiles with the whole
+ *                                                   workspace; SHAPE elsewhere); default: whichever the time model prefers
  *   "unfused_stages"   LCMA_UNFUSED_STAGES=<mask>   for timing one stage of lcma_gemm_unfused alone: bit 0 Combine A, bit 1
  *                                                   Combine B, bit 2 the GEMM stage, bit 3 Combine H (default 15, all).  The one
  *                                                   setting that is not result-neutral: a stage switched off leaves its output

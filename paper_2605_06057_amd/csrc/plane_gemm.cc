@@ -94,7 +94,7 @@ struct StepPrice {
     double step(double f) const { return a + b * f + c * f * f * f * f; }
 };
 enum { WHOLE_256, KPAIR_128, TWO_128, KPAIR_64, STATIC_256 }; // 256 x 256 ping-pong, 128 x 128, the same twice to a CU, 64 x 128, 256 x 256 a work-group each
-const StepPrice kPlain[] = {{0.876, 0.202, 0.493, 6.93, 0.0, 0.055}, {0.301, 0.144, 0.0, 2.91, 0.97, 0.367}, {0.591, 0.320, 0.070, 1.53, 0.0, 0.187}, {0.245, 0.055, 0.0, 1.80, 1.28, 0.474}, {1.067, 0.171, 0.484, 4.70, 0.0, 0.11}};
+const StepPrice kPlain[] = {{0.876, 0.202, 0.493, 6.93, 0.0, 0.055}, {0.301, 0.144, 0.0, 2.91, 0.97, 0.367}, {0.620, 0.450, 0.0, 1.53, 0.0, 0.187}, {0.245, 0.055, 0.0, 1.80, 1.28, 0.474}, {1.067, 0.171, 0.484, 4.70, 0.0, 0.11}};
 const StepPrice kBatch[] = {{0.775, 0.557, 0.150, 5.66, 3.0, 0.0}, {0.348, 0.008, 0.204, 2.26, 3.0, 0.0}, {0.601, 0.319, 0.126, 1.40, 3.0, 0.0}, {0.243, 0.0, 0.103, 1.69, 3.0, 0.0}, {1.087, 0.277, 0.455, 4.36, 3.0, 0.0}};
 const StepPrice kBatchF32[] = {{0.672, 0.692, 0.143, 8.87, 3.0, 0.0}, {0.487, 0.026, 0.028, 3.05, 3.0, 0.0}, {0.616, 0.420, 0.0, 2.24, 3.0, 0.0}, {0.346, 0.0, 0.0, 1.79, 3.0, 0.0}, {0.976, 0.008, 1.447, 4.10, 4.20, 0.0}};
 const StepPrice kBatchFp8[] = {{0.890, 0.273, 0.360, 4.97, 0.64, 0.0}, {0.239, 0.209, 0.130, 2.86, 0.0, 0.0}, {0.621, 0.424, 0.109, 0.91, 0.0, 0.0}, {0.160, 0.051, 0.148, 2.25, 0.0, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0, 0.0}};
