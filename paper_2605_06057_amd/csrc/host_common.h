@@ -138,6 +138,7 @@ double plain_seconds(int64_t M, int64_t N, int64_t K, int dtype); // csrc/model.
 double plain_product_us(bool b_kn, int tn, int64_t M, int64_t N, int64_t K, bool off_line);
 bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc,
                    int dtype, double limit_us, void *stream, int *err, int tn = 0);
+double small_plain_us(int64_t M, int64_t N, int64_t K, int dtype);
 bool small_plain(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc, int dtype,
                  void *stream, int *err);
 int tuning_schedule(); // 0 = choose, 1 = one tile-product per work-group, 2 = Split-Group ranges

@@ -129,11 +129,14 @@ extern "C" double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int6
     return t;
 }
 
-// The plain product as lcma_select_dataflow prices it: with the 256 x 128 ping-pong kernel too, which stands in where tiles are few
-// (2048 x 4096 x 4096 62 us; the published prediction, without it, 86).
+// The plain product as lcma_select_dataflow prices it: by the kernel that runs it.  Few tiles: the forms that split K between waves
+// (448 x 312 x 3416 fp16 7.7 us; priced by the kernels they replaced 20.6 of Algorithm 1 were chosen).  Else with the 256 x 128 ping-pong kernel too, which stands in
+// where tiles are few (2048 x 4096 x 4096 62 us; the published prediction, without it, 86).
 double lcma::plain_seconds(int64_t M, int64_t N, int64_t K, int dtype) {
     const double t = lcma_predict_seconds(LCMA_PLAIN, M, N, K, (lcma_dtype)dtype);
-    if (t <= 0.0 || dtype == LCMA_F32) return t;
+    if (t <= 0.0) return t;
+    if (const double us = small_plain_us(M, N, K, dtype)) return 1e-6 * us;
+    if (dtype == LCMA_F32) return t;
     return std::min(t, 1e-6 * plain_product_us(true, 128, M, N, K, K % 64 || N % 64) + kLaunch);
 }
 

@@ -412,12 +412,10 @@ double small_us(const SmallForm &f, int64_t M, int64_t N, int64_t lines, bool of
 }
 } // namespace
 
-// Returns false, with nothing launched, when another kernel is predicted to be as fast or padded offsets do not fit; else *err is the launch's
-// HIP error.  Arguments are checked by the caller; rows are whole 16-byte vectors.
-bool small_plain(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc, int dtype,
-                 void *stream, int *err) {
-    const int es = dtype_size(dtype);
-    const bool wide = es == 4, off_line = (lda * es & 127) != 0;
+namespace {
+// The form of few tiles that the plain product takes, or null where another kernel is predicted to be as fast; *us: what it takes.
+const SmallForm *small_form(int64_t M, int64_t N, int64_t K, int es, bool off_line, double *us) {
+    const bool wide = es == 4;
     const int64_t lines = ceil_div(K * es, 128);
     double limit = 0.0;
     for (int i = 0; i < (wide ? 2 : 4); ++i) {
@@ -435,6 +433,26 @@ bool small_plain(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int6
             limit = t;
         }
     }
+    *us = limit;
+    return form;
+}
+} // namespace
+
+// Microseconds of the plain product of dense matrices on the kernels for few tiles, 0 where it does not take them.
+double small_plain_us(int64_t M, int64_t N, int64_t K, int dtype) {
+    const int es = dtype_size(dtype);
+    double us;
+    return small_form(M, N, K, es, (K * es & 127) != 0, &us) ? us : 0.0;
+}
+
+// Returns false, with nothing launched, when another kernel is predicted to be as fast or padded offsets do not fit; else *err is the launch's
+// HIP error.  Arguments are checked by the caller; rows are whole 16-byte vectors.
+bool small_plain(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb, void *C, int64_t ldc, int dtype,
+                 void *stream, int *err) {
+    const int es = dtype_size(dtype);
+    const int64_t lines = ceil_div(K * es, 128);
+    double us;
+    const SmallForm *form = small_form(M, N, K, es, (lda * es & 127) != 0, &us);
     if (!form) return false;
     const int64_t lim = (int64_t)1 << 31, Mp = ceil_div(M, 128) * 128, Np = ceil_div(N, 128) * 128, Kp = lines * 128 / es;
     if (((Mp - 1) * lda + Kp) * es >= lim || (b_kn ? (Kp - 1) * ldb + Np : (Np - 1) * ldb + Kp) * es >= lim || ((Mp - 1) * ldc + Np) * es >= lim) return false;

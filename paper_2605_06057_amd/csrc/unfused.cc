@@ -45,6 +45,15 @@ Geometry geometry(const lcma_scheme &s, int64_t M, int64_t N, int64_t K, int dty
     return g;
 }
 
+// Rows of a block in Algorithm 1 in 16 bit: the blocks are cut at whole 16 rows (what Combine A and Combine H give to a work-group) and not at
+// whole tiles, which the plane GEMM does not need: 545 rows in four are 144 each instead of 256.  Planes stay where whole tiles would have
+// put them.  Only where an eighth of the rows or more, and 4 MB or more (about 1 us), would be nothing but padding: with less nothing is
+// gained (4838 x 12672 x 1656 in four 330 -> 340 us), and the cut stays that of the generated kernels.
+int64_t block_rows(const Geometry &g, const lcma_scheme &s, int R, int64_t M) {
+    const int64_t fine = round_up((M + s.m - 1) / s.m, 16);
+    return fine * 8 <= g.bm * 7 && (int64_t)R * (g.bm - fine) * (g.bk * g.es + g.bn * g.h_es) >= (4 << 20) ? fine : g.bm;
+}
+
 const StageKernel *find_stage(int scheme_id, int dtype) {
     for (int i = 0; i < kStageKernelCount; ++i)
         if (kStageKernels[i].launch_comb_a && kStageKernels[i].scheme_id == scheme_id && kStageKernels[i].dtype == dtype)
@@ -112,9 +121,10 @@ static double algorithm1_seconds(int scheme_id, int64_t M, int64_t N, int64_t K,
     const lcma_scheme *s = builtin_scheme(scheme_id);
     const StageKernel *sk = find_stage(scheme_id, dtype);
     if (!es || !s || M <= 0 || N <= 0 || K <= 0 || !sk) return -1.0;
-    const Geometry g = geometry(*s, M, N, K, dtype);
+    Geometry g = geometry(*s, M, N, K, dtype);
     const Variant *gemm = find_gemm(true, LCMA_PLAIN, dtype == LCMA_F32 ? LCMA_F32 : LCMA_F16, sk->planes, g);
     if (!gemm) return -1.0;
+    if (present && es == 2) g.bm = block_rows(g, *s, sk->planes, M);
     const double R = sk->planes, dM = (double)M, dN = (double)N, dK = (double)K;
     const double at = R * g.bm * g.bk, bt = R * g.bn * g.bk, h = R * g.bm * g.bn; // elements of the planes
     double t = (dM * dK + at) * es / sk->rate_a + kLaunch;
@@ -266,13 +276,8 @@ lcma_status lcma::gemm_unfused(const char *who, int level, int64_t M, int64_t N,
     const Variant *gemm = level == 1 ? find_gemm(true, LCMA_PLAIN, ct, R, g) : find_gemm(false, id, dtype, scheme->R, g);
     if (!gemm) return fail(LCMA_ERR_NOKERNEL, "%s: no GEMM stage kernel for level %d fits the planes", who, level);
 
-    // Level 1 in 16 bit: the blocks of rows are cut at whole 16 rows (what Combine A and Combine H give to a work-group) and not at whole
-    // tiles, which the plane GEMM does not need: 545 rows in four are 144 each instead of 256.  Planes stay where whole tiles would have
-    // put them.  Only where an eighth of the rows or more, and 4 MB or more (about 1 us), would be nothing but padding: with less nothing is
-    // gained (4838 x 12672 x 1656 in four 330 -> 340 us), and the cut stays that of the generated kernels.
     const bool on_planes = level == 1 && es == 2 && !forced_unfused_variant() && !tuning_batch_order();
-    const int64_t fine = round_up((M + scheme->m - 1) / scheme->m, 16);
-    if (on_planes && fine * 8 <= g.bm * 7 && (int64_t)R * (g.bm - fine) * (g.bk * es + g.bn * g.h_es) >= (4 << 20)) g.bm = fine;
+    if (on_planes) g.bm = block_rows(g, *scheme, R, M);
     // (the rows of the planes are the y dimension of the grids of Combine A and Combine H)
     if (g.bm / 16 > 65535) return fail(LCMA_ERR_SHAPE, "%s: M is too large", who);
     const int stages = tuning_unfused_stages(); // measurement aid: stages switched off keep the output of an earlier call
