@@ -82,38 +82,50 @@ int64_t plane_gemm_scratch_bytes(int tile) { return (int64_t)slots_of(tile) * 2 
 namespace {
 // Tile and schedule together, by the time the slowest work-group takes.  Whole tile-products run in rounds of as many work-groups as fit;
 // a step of 128 bytes of K takes a + b f + c f^4 us when a share f of them has one (with few of them the memory side answers sooner, with
-// many the clock falls), a round `more` besides, the launch and the first loads `start`, and where rows do not start on 128-byte
-// lines a step `off` of itself more.  All measured on random operands, plain products by themselves (250 of 100 to 8192 rows, K 512 to 14336) and
-// batches where they run, between the passes over memory of Algorithm 1 (450; by themselves, one after the other, the ping-pong kernel is 10 % slower
-// against the others: the clock), fitted to 3 to 10 %.  What the prices choose takes 1.007 of the time of the fastest kernel on plain 16-bit products,
-// 1.003 in FP8, 1.001 to 1.007 on batches.  Without the 64 x 128 tile it is 1.09, 1.05 and 1.00, without both tiles of lcma_kpair.hpp 1.27, 1.25 and
-// 1.02, without the small tile's form with two work-groups to a CU (PlaneGemm: many tile-products of few steps, 384 x 384 x
-// 960 in 49 planes 17.9 us, 26.6 on KPair) 1.01 to 1.08.
+// many the clock falls), and longer by `off_a` and `off_w` of itself for every 128 lines of K where rows of A or of W do not start on 128-byte lines
+// (each piece of such a row lies in two; the longer the rows, the less of the other half is still there), a round `more` besides, the launch and the first loads
+// `start`, 100 MB of operands `memory`, and beyond 80 MB `far` more.
+// Plain products: all forms of 5880 products, 1 to 16384 rows, N and K 256 to 16384, three sets of operands in turn (with one set the operands
+// of small products come from the L2, and what waits longest looks best: 1 x 1096 x 11840 11.1 us instead of 8.2).  The prices are those with which
+// the choice loses least, not the nearest to each time (7 to 13 % off): it takes 1.007 of the time of the fastest form at the sizes of linear layers, 1.009 over all, without the
+// workspace 1.007 and 1.008; priced with one set and one penalty for either operand, ranges without any, 1.014 and 1.024 (658 x 8696 x 4736, rows of A off
+// lines, 96 us on 256 x 256 instead of 72; 5506 x 3616 x 15744, both off, 1026 in ranges instead of 744).  Batches of Algorithm 1 where they
+// run, between the passes over memory (450; by themselves, one after the other, the ping-pong kernel is 10 % slower against the others: the clock).
+// Without the 64 x 128 tile plain products take 1.09, without both tiles of lcma_kpair.hpp 1.27; without the small tile's form with two work-groups to a CU
+// (PlaneGemm: many tile-products of few steps, 384 x 384 x 960 in 49 planes 17.9 us, 26.6 on KPair) 1.01 to 1.08.
 struct StepPrice {
-    double a, b, c, more, start, off;
+    double a, b, c, more, start, off_a, off_w, memory, far;
     double step(double f) const { return a + b * f + c * f * f * f * f; }
 };
-enum { WHOLE_256, KPAIR_128, TWO_128, KPAIR_64, STATIC_256 }; // 256 x 256 ping-pong, 128 x 128, the same twice to a CU, 64 x 128, 256 x 256 a work-group each
-const StepPrice kPlain[] = {{0.876, 0.202, 0.493, 6.93, 0.0, 0.055}, {0.301, 0.144, 0.0, 2.91, 0.97, 0.367}, {0.620, 0.450, 0.0, 1.53, 0.0, 0.187}, {0.245, 0.055, 0.0, 1.80, 1.28, 0.474}, {1.067, 0.171, 0.484, 4.70, 0.0, 0.11}};
-const StepPrice kBatch[] = {{0.775, 0.557, 0.150, 5.66, 3.0, 0.0}, {0.348, 0.008, 0.204, 2.26, 3.0, 0.0}, {0.601, 0.319, 0.126, 1.40, 3.0, 0.0}, {0.243, 0.0, 0.103, 1.69, 3.0, 0.0}, {1.087, 0.277, 0.455, 4.36, 3.0, 0.0}};
-const StepPrice kBatchF32[] = {{0.672, 0.692, 0.143, 8.87, 3.0, 0.0}, {0.487, 0.026, 0.028, 3.05, 3.0, 0.0}, {0.616, 0.420, 0.0, 2.24, 3.0, 0.0}, {0.346, 0.0, 0.0, 1.79, 3.0, 0.0}, {0.976, 0.008, 1.447, 4.10, 4.20, 0.0}};
-const StepPrice kBatchFp8[] = {{0.890, 0.273, 0.360, 4.97, 0.64, 0.0}, {0.239, 0.209, 0.130, 2.86, 0.0, 0.0}, {0.621, 0.424, 0.109, 0.91, 0.0, 0.0}, {0.160, 0.051, 0.148, 2.25, 0.0, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0, 0.0}};
-const StepPrice kFp8[] = {{0.924, 0.209, 0.304, 7.70, 0.0, 0.0}, {0.319, 0.129, 0.007, 3.27, 1.55, 0.0}, {0.682, 0.412, 0.0, 1.50, 0.0, 0.0}, {0.245, 0.077, 0.0, 2.18, 1.57, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0, 0.0}};
-double rounds_us(const StepPrice &q, int64_t jobs, int64_t slots, int64_t steps, bool off_line) {
-    const double line = off_line ? 1.0 + q.off : 1.0, f = (double)(jobs % slots) / (double)slots;
-    return q.start + (double)(jobs / slots) * ((double)steps * line * q.step(1.0) + q.more) + (f > 0.0 ? (double)steps * line * q.step(f) + q.more : 0.0);
+enum { WHOLE_256, KPAIR_128, TWO_128, KPAIR_64, STATIC_256, NARROW }; // 256 x 256 ping-pong, 128 x 128, the same twice to a CU, 64 x 128, 256 x 256 a work-group each, 256 x 128 ping-pong
+const StepPrice kPlain[] = {{0.807, 0.447, 0.0, 7.43, 0.0, 0.0, 0.113, 8.24, 0.0}, {0.339, 0.0559, 0.0735, 3.92, 1.4, 0.13, 0.0683, 0.167, 19.2}, {0.758, 0.212, 0.0, 2.14, 0.15, 0.0739, 0.089, 0.0, 0.0}, {0.241, 0.0685, 0.0, 2.64, 1.42, 0.19, 0.167, 0.362, 21.5}, {1.067, 0.171, 0.484, 4.70, 0.0, 0.11, 0.11, 0.0, 0.0}, {0.466, 0.265, 0.0, 6.22, 0.0, 0.432, 0.0, 0.0, 11.6}};
+const StepPrice kBatch[] = {{0.775, 0.557, 0.150, 5.66, 3.0}, {0.348, 0.008, 0.204, 2.26, 3.0}, {0.601, 0.319, 0.126, 1.40, 3.0}, {0.243, 0.0, 0.103, 1.69, 3.0}, {1.087, 0.277, 0.455, 4.36, 3.0}};
+const StepPrice kBatchF32[] = {{0.672, 0.692, 0.143, 8.87, 3.0}, {0.487, 0.026, 0.028, 3.05, 3.0}, {0.616, 0.420, 0.0, 2.24, 3.0}, {0.346, 0.0, 0.0, 1.79, 3.0}, {0.976, 0.008, 1.447, 4.10, 4.20}};
+const StepPrice kBatchFp8[] = {{0.890, 0.273, 0.360, 4.97, 0.64}, {0.239, 0.209, 0.130, 2.86, 0.0}, {0.621, 0.424, 0.109, 0.91, 0.0}, {0.160, 0.051, 0.148, 2.25, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0}};
+const StepPrice kFp8[] = {{0.924, 0.209, 0.304, 7.70, 0.0}, {0.319, 0.129, 0.007, 3.27, 1.55}, {0.682, 0.412, 0.0, 1.50, 0.0}, {0.245, 0.077, 0.0, 2.18, 1.57}, {1.277, 0.169, 0.237, 4.16, 0.0}};
+struct Operands {
+    bool off_a, off_w; // rows that do not start on 128-byte lines
+    double mbytes, lines; // lines: of 128 bytes along K
+    double far() const { return std::max(0.0, mbytes - 80.0); } // (three sets of them in turn no longer fit the last-level cache)
+};
+Operands plain_operands(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldw) { return Operands{lda % 64 != 0, ldw % 64 != 0, (double)(M + N) * (double)K * 2e-6, (double)K / 64.0}; }
+double off_lines(const Operands &o, double off_a, double off_w) { return 1.0 + (o.off_a ? off_a : 0.0) + (o.off_w ? off_w : 0.0); }
+double rounds_us(const StepPrice &q, int64_t jobs, int64_t slots, int64_t steps, const Operands &o) {
+    const double line = 1.0 + (off_lines(o, q.off_a, q.off_w) - 1.0) * o.lines / 128.0, f = (double)(jobs % slots) / (double)slots;
+    return q.start + 0.01 * (q.memory * o.mbytes + q.far * o.far()) + (double)(jobs / slots) * ((double)steps * line * q.step(1.0) + q.more) + (f > 0.0 ? (double)steps * line * q.step(f) + q.more : 0.0);
 }
-// What else there is:
+// What else there is (measured as above):
 //   slices of K for work-groups of their own (128 x 128, plain 16-bit products of few tiles): the fp32 products of the slices are written and
-//     added by a second kernel, 1.3 us, 0.25 a slice and 0.35 per MB (743 x 1400 x 7168, 66 tiles in three slices: 24.8 us, 43.8
+//     added by a second kernel, 1.4 us, 0.64 a slice and 0.2 per MB (743 x 1400 x 7168, 66 tiles in three slices: 24.8 us, 43.8
 //     in one piece; 1024 x 1024 x 14336 36.7 / 85; 512 x 4096 x 14336 61.8 / 87.7);
-//   Split-Group ranges: 1.75 (FP8 2.0) a step on 256 x 256, 6 a tile-product and 65 for the pieces.  On 128 x 128 neighbouring tiles start at
-//     different k and share little in L2, 0.85 a step, unless the ranges divide a tile evenly; 12 and 2.3 a piece of a tile (512 x 4096 x
-//     14336 65.6 us, 255 x 8504 x 7296 71 against 44 without, 559 x 7184 x 9856 196 / 106).  Half of the workspace serves them alone.
-// tile, schedule: 0 = choose.  off_line: rows that do not start on 128-byte lines; low: tiles of 64 x 128 are offered.  Returns microseconds (0 when nothing fits).
+//   Split-Group ranges: 1.75 (FP8 2.0) a step on 256 x 256, 6 a tile-product and 65 for the pieces (882 x 5224 x 10368 126 us, 179 on 256 x 128).  On
+//     128 x 128 neighbouring tiles start at different k and share little in L2, 0.95 a step, unless the ranges divide a tile evenly, 0.68; 2.9 and 1.5 a piece
+//     of a tile (512 x 4096 x 14336 65.6 us, 255 x 8504 x 7296 71 against 44 without, 559 x 7184 x 9856 196 / 106).  Half of the workspace serves
+//     them alone.  Batches and FP8, which have ranges only where a workspace is larger than asked for, at the older prices.
+// tile, schedule: 0 = choose.  low: tiles of 64 x 128 are offered.  Returns microseconds (0 when nothing fits).
 enum { STATIC = 1, RANGES = 2, PERSIST = 3, SLICES = 4, TWO_PER_CU = 5 };
 int64_t slice_steps(int64_t jobs, int ny) { return ceil_div(ny, std::max<int64_t>(1, std::min<int64_t>(kCUs / jobs, ny / 4))); }
-double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, bool off_line, bool low, int64_t scratch_bytes, int *best_tile,
+double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile, int schedule, const Operands &o, bool low, int64_t scratch_bytes, int *best_tile,
               int *best_sched) {
     const bool fp8 = kind == PG_FP8_BF16 || kind == PG_FP8_F16;
     const StepPrice *const price = fp8 ? (planes > 1 ? kBatchFp8 : kFp8) : kind == PG_F16_F32 ? kBatchF32 : planes > 1 ? kBatch : kPlain;
@@ -132,24 +144,32 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             double cost;
             if (sc == RANGES) {
                 const int64_t cap = ceil_div(jobs * ny, slots_of(t));
-                cost = t == 256 ? (double)cap * (fp8 ? 2.0 : 1.75) + 6.0 * (double)jobs / kCUs + 65.0
-                                : (double)(2 * cap) * (ny % (2 * cap) ? 0.85 : price[KPAIR_128].step(1.0)) + 12.0 + 2.3 * (double)kCUs / (double)jobs;
+                const bool even_ranges = ny % (2 * cap) == 0;
+                if (price == kPlain)
+                    cost = t == 256 ? (double)cap * 1.75 * off_lines(o, 0.05, 0.175) + 6.0 * (double)jobs / kCUs + 65.0
+                                    : (double)(2 * cap) * (even_ranges ? 0.682 : 0.946) * off_lines(o, 0.0, 0.123) + 2.9 + 1.46 * (double)kCUs / (double)jobs + 2.44 * 0.01 * o.far();
+                else
+                    cost = t == 256 ? (double)cap * (fp8 ? 2.0 : 1.75) + 6.0 * (double)jobs / kCUs + 65.0
+                                    : (double)(2 * cap) * (even_ranges ? price[KPAIR_128].step(1.0) : 0.85) + 12.0 + 2.3 * (double)kCUs / (double)jobs;
             } else if (sc == SLICES) {
                 if (t != 128 || planes > 1 || fp8 || kind == PG_F16_F32 || 2 * jobs > kCUs || ny < 8 || scratch_bytes < plane_gemm_scratch_bytes(256)) continue;
                 const int64_t cap = slice_steps(jobs, ny), slices = ceil_div(ny, cap);
-                cost = rounds_us(price[KPAIR_128], jobs * slices, kCUs, (cap + 1) & ~(int64_t)1, off_line) + 1.3 + 0.25 * (double)slices + 0.35 * 65536e-6 * (double)(jobs * slices);
+                StepPrice q = price[KPAIR_128];
+                q.far = 4.62; // (more CUs at it)
+                cost = rounds_us(q, jobs * slices, kCUs, (cap + 1) & ~(int64_t)1, o) + 1.35 + 0.641 * (double)slices + 0.2 * 65536e-6 * (double)(jobs * slices);
             } else if (sc == TWO_PER_CU) {
-                if (t != 128) continue;
-                cost = rounds_us(price[TWO_128], jobs, 2 * kCUs, ny, off_line);
+                // (one or two steps and one round of tiles stay on KPair, where they are one chain: 6.0 us, 4.7 here, both below a call's 6 on the host)
+                if (t != 128 || (price == kPlain && ny <= 2 && jobs <= kCUs)) continue;
+                cost = rounds_us(price[TWO_128], jobs, 2 * kCUs, ny, o);
                 if (planes > 1 && jobs >= 20 * kCUs) cost *= kind == PG_F16_F32 ? 1.05 : 1.12; // (ten rounds and more, measured: planes far beyond the caches)
             } else if (t < 256) {
-                cost = rounds_us(price[t == 128 ? KPAIR_128 : KPAIR_64], jobs, kCUs, even, off_line);
+                cost = rounds_us(price[t == 128 ? KPAIR_128 : KPAIR_64], jobs, kCUs, even, o);
             } else if (pingpong) {
-                cost = rounds_us(price[WHOLE_256], jobs, kCUs, (ny + 1) & ~1, off_line);
+                cost = rounds_us(price[WHOLE_256], jobs, kCUs, (ny + 1) & ~1, o);
             } else {
-                cost = rounds_us(price[STATIC_256], jobs, kCUs, ny, off_line);
+                cost = rounds_us(price[STATIC_256], jobs, kCUs, ny, o);
             }
-            if (t < 256) cost = std::max(cost, 5.0 + (double)planes * (double)(rows + cols) * ny * 128.0 / 6e6); // (operands from memory)
+            if (t < 256 && price != kPlain) cost = std::max(cost, 5.0 + (double)planes * (double)(rows + cols) * ny * 128.0 / 6e6); // (operands from memory)
             if (!*best_tile || cost < best) {
                 best = cost;
                 *best_tile = t;
@@ -167,10 +187,10 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
 // slower than as a stage between passes over memory.
 double batched_plane_gemm_seconds(bool fp32_out, int planes, int64_t rows, int64_t cols, int ny) {
     int t = 0, sc = 0;
-    const double us = choose(fp32_out ? PG_F16_F32 : PG_F16, planes, rows, cols, ny, 0, tuning_schedule(), false, true, 0, &t, &sc);
+    const double us = choose(fp32_out ? PG_F16_F32 : PG_F16, planes, rows, cols, ny, 0, tuning_schedule(), Operands{}, true, 0, &t, &sc);
     if (!t) return -1.0;
     const double out = fp32_out ? 12.0 : 6.0;
-    const double stage = rounds_us(StepPrice{0.80, 0.72, 0.0, out, 1.5, 0.0}, planes * ceil_div(rows, 256) * ceil_div(cols, 256), kCUs, (ny + 1) & ~1, false);
+    const double stage = rounds_us(StepPrice{0.80, 0.72, 0.0, out, 1.5}, planes * ceil_div(rows, 256) * ceil_div(cols, 256), kCUs, (ny + 1) & ~1, Operands{});
     return 1e-6 * (t == 256 && stage < us ? stage : us);
 }
 
@@ -217,7 +237,7 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     const int forced = tuning_schedule();
     if (forced) schedule = forced;
     int best_tile = 0, best_sched = 0;
-    choose(kind, planes, rows, cols, p.ny, tile, schedule, planes == 1 && ((p.lda_b | p.ldb_b) & 127), true, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
+    choose(kind, planes, rows, cols, p.ny, tile, schedule, planes == 1 ? plain_operands(rows, cols, (int64_t)p.ny * 64, p.lda_b / 2, p.ldb_b / 2) : Operands{}, true, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
     if (!best_tile) {
         if (schedule == 2)
             return fail(LCMA_ERR_ARG, "%s: the Split-Group schedule needs %lld bytes of scratch", who,
@@ -338,31 +358,29 @@ bool plain_product(bool b_kn, int64_t M, int64_t N, int64_t K, const void *A, in
 }
 
 namespace {
-// Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): form and slices of K with the smallest time, all constants measured (us;
-// bf16).  A CU takes in the lines of its work-groups at `rate` bytes/ns, the slower by `crowd` the more CUs are at it and by `off` where rows do
-// not start on lines; `first` besides for the launch, the first lines and the sum over the waves, `next` for every further work-group of a
-// CU; and the operands come from beyond the L2 at `memory` TB/s.  Slices of K: 1.3 for the second kernel, 0.25 a slice and 0.35 per MB of
-// partial products.  Fitted to 260 shapes, M 16 to 6000, N 64 to 14336, K 512 to 14336, to 5 to 12 %; the choice between the forms takes 1.005 of the
-// time of the fastest.  (The rates before, 90 to 115 for all of them and 8 TB/s besides, were for the smallest form; they had 32 x 32 tiles a third
-// too slow.)
+// Plain product on few rows or a small C (csrc/lcma_few_rows.hpp): form and slices of K with the smallest time, priced on the same 5880 products as
+// the tiles above and together with them (us; bf16).  A CU takes in the lines of its work-groups at `rate` bytes/ns, the slower by `crowd` the more CUs are
+// at it and by `off_a`, `off_w` where rows do not start on lines; `first` besides for the launch, the first lines and the sum over the waves, `next` for every
+// further work-group of a CU; and the operands come from beyond the L2 at `memory` TB/s, beyond 80 MB of them 100 MB take `far` more.  Slices of K: 1.3 for the second kernel, 0.47 a
+// slice and 0.35 per MB of partial products.
 struct FewRowsForm {
     int tile, cols, waves, deep, most, sliced; // most: work-groups per CU; sliced: K in slices
-    double first, next, alone, rate, crowd, off, memory; // alone: rate with one work-group per CU
+    double first, next, alone, rate, crowd, off_a, off_w, memory, far; // alone: rate with one work-group per CU
 };
 // (tiles of 64, three or more to a CU: the plane GEMM or a ping-pong kernel is faster, 1753 x 2000 x 7552 69 against 124 us, 2506 x 1056 x 4288 41 / 49; two
 // to a CU: 64 x 128, 512 x 4096 x 4096 22.3 / 29.5, 320 x 4096 x 4096 19.3 / 28; tiles of 16 with eight waves and four lines in flight each fill the LDS of a CU: no
 // second work-group beside the first, and slower where there is one: 1 x 14336 x 1024 12.1 us, 7.6 with the smaller form, 16 x 8192 x 512 6.0
 // / 3.9; with few of them and a long K, from memory, the faster ones, 1 x 4096 x 14336 22.5 / 25.6, with a short one not, 1 x 1000 x 2048 4.3 / 3.7)
-const FewRowsForm kFewRowsForms[] = {{16, 16, 4, 0, 4, 0, 2.55, 0.02, 155.0, 172.0, 0.17, 0.24, 22.8}, {16, 16, 8, 1, 1, 0, 3.6, 0.0, 197.0, 0.0, 0.20, 0.13, 22.2},
-                                       {32, 32, 4, 0, 4, 0, 2.8, 0.09, 170.0, 163.0, 0.53, 0.27, 25.7}, {64, 64, 4, 0, 1, 0, 4.07, 0.0, 138.0, 0.0, 0.55, 0.26, 49.8},
-                                       {64, 64, 4, 0, 1, 1, 4.0, 0.0, 122.0, 0.0, 0.0, 0.35, 23.0}, {64, 128, 2, 1, 1, 0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0}};
+const FewRowsForm kFewRowsForms[] = {{16, 16, 4, 0, 4, 0, 1.91, 0.0, 114.0, 167.0, 0.418, 0.228, 0.139, 22.2, 7.83}, {16, 16, 8, 1, 1, 0, 3.29, 0.0, 221.0, 0.0, 1.57, 0.608, 0.304, 87.7, 3.17},
+                                       {32, 32, 4, 0, 4, 0, 1.98, 0.631, 114.0, 139.0, 0.408, 0.21, 0.239, 44.9, 15.1}, {64, 64, 4, 0, 1, 0, 4.31, 0.0, 110.0, 0.0, 0.136, 0.22, 0.137, 90.0, 8.68},
+                                       {64, 64, 4, 0, 1, 1, 2.96, 0.0, 121.0, 0.0, 0.298, 0.333, 0.167, 40.5, 11.3}, {64, 128, 2, 1, 1, 0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0}};
 const int64_t kFewRows = 1024; // (with more the 64 x 128 tiles are the plane GEMM's)
 struct FewRowsPlan {
     int tile, cols, deep;
     int64_t row_blocks, col_blocks, slices, slice_steps;
     double us;
 };
-FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, bool off_line, int64_t scratch_bytes) {
+FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, const Operands &o, int64_t scratch_bytes) {
     FewRowsPlan best{};
     for (const FewRowsForm &f : kFewRowsForms) {
         const int64_t rb = ceil_div(M, f.tile), cb = ceil_div(N, f.cols), steps = K / 32, batch = 2 * f.waves; // (steps of 32; a line of every wave)
@@ -374,12 +392,12 @@ FewRowsPlan few_rows_plan(int64_t M, int64_t N, int64_t K, bool off_line, int64_
         const int64_t groups = rb * cb * slices, per_cu = ceil_div(groups, kCUs), lines = std::min(slice_steps, steps) / 2;
         double us;
         if (f.cols == 128) {
-            us = rounds_us(kPlain[KPAIR_64], groups, kCUs, (lines + 1) & ~(int64_t)1, off_line);
+            us = rounds_us(kPlain[KPAIR_64], groups, kCUs, (lines + 1) & ~(int64_t)1, o);
         } else {
-            const double share = std::min(1.0, (double)groups / kCUs), line = (off_line ? 1.0 + f.off : 1.0) * (1.0 + f.crowd * share);
-            us = f.first + f.next * (double)(per_cu - 1) + line * (double)(per_cu * lines * 128 * (f.tile + f.cols)) / (1e3 * (per_cu > 1 ? f.rate : f.alone)) + (double)((M + N) * K * 2) / (1e6 * f.memory);
+            const double share = std::min(1.0, (double)groups / kCUs), line = off_lines(o, f.off_a, f.off_w) * (1.0 + f.crowd * share * share);
+            us = f.first + f.next * (double)(per_cu - 1) + line * (double)(per_cu * lines * 128 * (f.tile + f.cols)) / (1e3 * (per_cu > 1 ? f.rate : f.alone)) + o.mbytes / f.memory + f.far * 0.01 * o.far();
         }
-        if (slices > 1) us += 1.3 + 0.25 * (double)slices + 0.35e-6 * (double)scratch;
+        if (slices > 1) us += 1.3 + 0.469 * (double)slices + 0.35e-6 * (double)scratch;
         if (!best.tile || us < best.us) best = FewRowsPlan{f.tile, f.cols, f.deep, rb, cb, slices, slice_steps, us};
     }
     return best;
@@ -555,15 +573,12 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
     int t = 0, sc = 0;
     if (!tuning_schedule()) { // (a forced schedule is one of the plane GEMM's)
         // (slices only with the bytes that the interface names: half of them serve the ranges on 128 x 128 tiles, fewer are left alone)
-        const FewRowsPlan f = few_rows_plan(M, N, K, lda % 64 || ldw % 64, scratch >= plane_gemm_scratch_bytes(256) ? scratch : 0);
-        const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, lda % 64 || ldw % 64, M > kFewRows, scratch, &t, &sc);
+        const Operands o = plain_operands(M, N, K, lda, ldw);
+        const FewRowsPlan f = few_rows_plan(M, N, K, o, scratch >= plane_gemm_scratch_bytes(256) ? scratch : 0);
+        const double planes_us = choose(kind, 1, M, N, p.ny, 0, 0, o, M > kFewRows, scratch, &t, &sc);
         int err = 0;
-        const bool few = f.tile && f.us < planes_us + (sc == SLICES && f.cols == 64 ? 2.0 : 0.0);
-        // the 256 x 128 ping-pong kernel, with some room: where the prices are that close 840 x 5592 x 768 runs in 14.2 us against 14.4; rows off lines cost it
-        // most where K is long, 3848 x 1424 x 13568 237 us, ranges of steps on the large tile 204
-        static const StepPrice narrow{0.51, 0.178, 0.21, 4.26, 0.0, 0.45};
-        const double narrow_us = rounds_us(narrow, ceil_div(M, 256) * ceil_div(N, 128), kCUs, p.ny, lda % 64 || ldw % 64);
-        if (narrow_us < 0.97 * (few ? f.us : planes_us) &&
+        const bool few = f.tile && f.us < planes_us;
+        if (rounds_us(kPlain[NARROW], ceil_div(M, 256) * ceil_div(N, 128), kCUs, (p.ny + 1) & ~1, o) < (few ? f.us : planes_us) &&
             plain_product(false, M, N, K, A, lda, W, ldw, C, ldc, dtype, 0.0, stream, &err, 128))
             return err ? fail(LCMA_ERR_HIP, "%s: launch failed with HIP error %d", who, err) : LCMA_OK;
         if (few) {
