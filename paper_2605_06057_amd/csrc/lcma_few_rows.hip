@@ -1,6 +1,5 @@
 // Instances of the plain product on few rows (csrc/lcma_few_rows.hpp) and of the kernel that adds the slices of K.
 #include "lcma_few_rows.hpp"
-#include "lcma_kpair.hpp"
 
 using namespace lcma;
 
@@ -16,7 +15,9 @@ using namespace lcma;
         lcma_k_few_rows_##NAME<<<dim3(grid), dim3(64 * WK), 0, (hipStream_t)stream>>>(*p);                             \
         return (int)hipGetLastError();                                                                                 \
     }
-// Tiles of 64 x 128 on csrc/lcma_kpair.hpp.
+// Tiles of 64 x 128: those of the plane GEMM (csrc/lcma_plane_gemm.hip).
+extern "C" int lcma_launch_pg_f16_t128_f16(const lcma::PlaneGemmParams *p, void *stream);
+extern "C" int lcma_launch_pg_bf16_t128_bf16(const lcma::PlaneGemmParams *p, void *stream);
 static lcma::PlaneGemmParams wide_tiles(const lcma::FewRowsParams &p) {
     lcma::PlaneGemmParams q{};
     q.A = p.A;
@@ -33,21 +34,11 @@ static lcma::PlaneGemmParams wide_tiles(const lcma::FewRowsParams &p) {
     q.tail_b = 128;
     q.nx = p.row_blocks;
     q.nz = p.partial_ld / 128;
-    q.panel = q.nz < 8 ? q.nz : 8;
+    q.panel = p.panel;
     q.jobs = q.nx * q.nz;
+    q.interleave = 5;
     return q;
 }
-#define LCMA_FEW_ROWS_WIDE(NAME, KIND)                                                                                 \
-    extern "C" __global__ __launch_bounds__(512, 2) void lcma_k_low_##NAME(const lcma::PlaneGemmParams p) { \
-        using G = KPair<KIND, KIND, 64>;                                                                               \
-        __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
-        G::run(p, (LCMA_LDS char *)smem);                                                                              \
-    }                                                                                                                  \
-    static int launch_wide_##NAME(const lcma::FewRowsParams *p, int grid, void *stream) {                              \
-        const lcma::PlaneGemmParams q = wide_tiles(*p);                                                                \
-        lcma_k_low_##NAME<<<dim3(grid), dim3(512), 0, (hipStream_t)stream>>>(q);                   \
-        return (int)hipGetLastError();                                                                                 \
-    }
 #define LCMA_FEW_ROWS_TYPE(NAME, KIND)                                                                                 \
     LCMA_FEW_ROWS_KERNEL(NAME##_16, KIND, 16, 4, 2)                                                                    \
     LCMA_FEW_ROWS_KERNEL(NAME##_16_deep, KIND, 16, 8, 4)                                                               \
@@ -58,9 +49,11 @@ static lcma::PlaneGemmParams wide_tiles(const lcma::FewRowsParams &p) {
     }                                                                                                                  \
     LCMA_FEW_ROWS(NAME##_32, KIND, 32, 4, 2)                                                                           \
     LCMA_FEW_ROWS_KERNEL(NAME##_64, KIND, 64, 4, 2)                                                                    \
-    LCMA_FEW_ROWS_WIDE(NAME, KIND)                                                                                     \
     extern "C" int lcma_launch_few_rows_##NAME##_64(const lcma::FewRowsParams *p, int grid, void *stream) {            \
-        if (p->deep) return launch_wide_##NAME(p, grid, stream);                                                       \
+        if (p->deep) {                                                                                                 \
+            const lcma::PlaneGemmParams q = wide_tiles(*p);                                                            \
+            return lcma_launch_pg_##NAME##_t128_##NAME(&q, stream);                                                    \
+        }                                                                                                              \
         lcma_k_few_rows_##NAME##_64<<<dim3(grid), dim3(256), 0, (hipStream_t)stream>>>(*p);                            \
         return (int)hipGetLastError();                                                                                 \
     }                                                                                                                  \

@@ -40,13 +40,8 @@ template <> struct Mma16<BF16> {
     static LCMA_DEV f32x4 run(frag a, frag b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 
-template <> struct Mma16<F32> { // (the same four k of a lane in both operands)
+template <> struct Mma16<F32> { // (no tiles of 16 in fp32: the fragment alone)
     using frag = f32x4;
-    static LCMA_DEV f32x4 run(frag a, frag b, f32x4 c) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], b[t], c, 0, 0, 0);
-        return c;
-    }
 };
 
 // s_waitcnt for all but the N youngest vector memory instructions; nothing moves across it

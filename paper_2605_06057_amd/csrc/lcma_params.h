@@ -96,7 +96,7 @@ struct FewRowsParams {
     void *C;
     uint32_t a_bytes, w_bytes, c_bytes; // byte extents (< 2 GiB each)
     uint32_t lda_b, ldw_b, ldc_b;       // row pitches in bytes
-    uint32_t n_row_b;                   // N * 2: columns of C at or beyond it are never written
+    uint32_t n_row_b;                   // N elements in bytes: columns of C at or beyond it are never written
     int32_t steps;                      // halves of the lines of 128 bytes of K: K / 32 in 16 bit
     int32_t row_blocks, block_rows;     // blocks of rows of C, and the rows of a block
     int32_t slices, slice_steps;        // slices of K (1: C is written directly), steps of a slice
@@ -105,6 +105,7 @@ struct FewRowsParams {
     void *partial;                      // slices x (row_blocks * block_rows) x partial_ld fp32 partial products
     int32_t deep;                       // blocks of 16 rows: eight waves with four lines in flight each instead of four with two;
                                         // of 64 rows: 128 columns wide
+    int32_t panel;                      // ... and the width, in tiles, of its column panels
 };
 
 struct Fp8QuantParams {

@@ -26,9 +26,9 @@ LCMA_SMALL_PLAIN(plain_f16_t64x64x64_k4t, F16, 64, false)
 LCMA_SMALL_PLAIN(plain_f32_t32x32x32_k4, F32, 32, true)
 LCMA_SMALL_PLAIN(plain_f32_t32x32x32_k4t, F32, 32, false)
 
-#define LCMA_KPAIR_PLAIN(NAME, KIND, TM, KN)                                                                           \
+#define LCMA_KPAIR_PLAIN(NAME, KIND, TM)                                                                               \
     extern "C" __global__ __launch_bounds__(512, 2) void lcma_k_##NAME(const lcma::PlaneGemmParams p) {                \
-        using G = KPair<KIND, KIND, TM, KN>;                                                                           \
+        using G = KPair<KIND, KIND, TM, true>;                                                                         \
         __shared__ __attribute__((aligned(16))) char smem[G::LDS_BYTES];                                               \
         G::run(p, (LCMA_LDS char *)smem);                                                                              \
     }                                                                                                                  \
@@ -36,11 +36,19 @@ LCMA_SMALL_PLAIN(plain_f32_t32x32x32_k4t, F32, 32, false)
         lcma_k_##NAME<<<dim3(p->jobs), dim3(512), 0, (hipStream_t)stream>>>(*p);                                       \
         return (int)hipGetLastError();                                                                                 \
     }
-LCMA_KPAIR_PLAIN(plain_bf16_t128x128x64_k2, BF16, 128, true)
-LCMA_KPAIR_PLAIN(plain_bf16_t128x128x64_k2t, BF16, 128, false)
-LCMA_KPAIR_PLAIN(plain_bf16_t64x128x64_k2, BF16, 64, true)
-LCMA_KPAIR_PLAIN(plain_bf16_t64x128x64_k2t, BF16, 64, false)
-LCMA_KPAIR_PLAIN(plain_f16_t128x128x64_k2, F16, 128, true)
-LCMA_KPAIR_PLAIN(plain_f16_t128x128x64_k2t, F16, 128, false)
-LCMA_KPAIR_PLAIN(plain_f16_t64x128x64_k2, F16, 64, true)
-LCMA_KPAIR_PLAIN(plain_f16_t64x128x64_k2t, F16, 64, false)
+// N x K weights: the tiles of the plane GEMM (csrc/lcma_plane_gemm.hip), dealt 0 (128 x 128) or 5 (64 x 128)
+#define LCMA_KPAIR_PLAIN_T(NAME, TYPE, DEALT)                                                                          \
+    extern "C" int lcma_launch_pg_##TYPE##_t128_##TYPE(const lcma::PlaneGemmParams *p, void *stream);                  \
+    extern "C" int lcma_launch_##NAME(const lcma::PlaneGemmParams *p, void *stream) {                                  \
+        lcma::PlaneGemmParams q = *p;                                                                                  \
+        q.interleave = DEALT;                                                                                          \
+        return lcma_launch_pg_##TYPE##_t128_##TYPE(&q, stream);                                                        \
+    }
+LCMA_KPAIR_PLAIN(plain_bf16_t128x128x64_k2, BF16, 128)
+LCMA_KPAIR_PLAIN_T(plain_bf16_t128x128x64_k2t, bf16, 0)
+LCMA_KPAIR_PLAIN(plain_bf16_t64x128x64_k2, BF16, 64)
+LCMA_KPAIR_PLAIN_T(plain_bf16_t64x128x64_k2t, bf16, 5)
+LCMA_KPAIR_PLAIN(plain_f16_t128x128x64_k2, F16, 128)
+LCMA_KPAIR_PLAIN_T(plain_f16_t128x128x64_k2t, f16, 0)
+LCMA_KPAIR_PLAIN(plain_f16_t64x128x64_k2, F16, 64)
+LCMA_KPAIR_PLAIN_T(plain_f16_t64x128x64_k2t, f16, 5)

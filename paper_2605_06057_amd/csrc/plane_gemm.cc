@@ -602,6 +602,7 @@ extern "C" lcma_status lcma_gemm_nt_ws(int64_t M, int64_t N, int64_t K, const vo
             q.partial_ld = (int32_t)(f.col_blocks * f.cols);
             q.partial = workspace;
             q.deep = f.deep;
+            q.panel = panel_of((int)f.col_blocks, 8);
             const bool bf = dtype == LCMA_BF16;
             const auto launch = f.tile == 16   ? (bf ? lcma_launch_few_rows_bf16_16 : lcma_launch_few_rows_f16_16)
                                 : f.tile == 32 ? (bf ? lcma_launch_few_rows_bf16_32 : lcma_launch_few_rows_f16_32)

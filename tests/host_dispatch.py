@@ -20,10 +20,16 @@ extern "C" void dispatch_clear() { g_log.clear(); }
 extern "C" const char *dispatch_log() { return g_log.c_str(); }
 static int note(const char *name, const std::string &args = "") { g_log += std::string(name) + args + "\\n"; return 0; }
 static std::string num(const char *k, long long v) { return std::string(" ") + k + "=" + std::to_string(v); }
+static thread_local long long g_panel, g_rows; // of the last launch: column panels in tiles; rows of a plane (0: no batch)
+extern "C" long long dispatch_panel() { return g_panel; }
+extern "C" long long dispatch_plane_rows() { return g_rows; }
 static std::string args(const lcma::PlaneGemmParams *p) {
+    g_panel = p->panel;
+    g_rows = p->c_plane / p->ldc_b;
     return num("jobs", p->jobs) + num("units", p->units) + num("ny", p->ny) + num("tail", p->tail_b) + num("panel", p->panel) + num("dealt", p->interleave);
 }
 static std::string args(const lcma::FewRowsParams *p) {
+    g_panel = p->panel;
     return num("tile", p->block_rows) + num("steps", p->steps) + num("slices", p->slices) + num("slice_steps", p->slice_steps) + num("deep", p->deep);
 }
 static std::string args(const lcma::CombHParams *p) { return num("lanes", 1 << p->lane_shift) + num("streamed", p->streamed); }
@@ -65,7 +71,7 @@ def lib():
         os.unlink(p)
     os.rmdir(out)
     L.dispatch_log.restype = L.lcma_last_error.restype = ctypes.c_char_p
-    L.lcma_split_group_scratch_bytes.restype = ctypes.c_int64
+    L.lcma_split_group_scratch_bytes.restype = L.dispatch_panel.restype = L.dispatch_plane_rows.restype = ctypes.c_int64
     _lib = L
     return L
 
