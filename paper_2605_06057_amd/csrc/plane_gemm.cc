@@ -84,35 +84,42 @@ namespace {
 // a step of 128 bytes of K takes a + b f + c f^4 us when a share f of them has one (with few of them the memory side answers sooner, with
 // many the clock falls), and longer by `off_a` and `off_w` of itself for every 128 lines of K where rows of A or of W do not start on 128-byte lines
 // (each piece of such a row lies in two; the longer the rows, the less of the other half is still there), a round `more` besides, the launch and the first loads
-// `start`, 100 MB of operands `memory`, and beyond 80 MB `far` more.
+// `start`, 100 MB of operands `memory`, and beyond 80 MB `far` more, 100 MB of products `products`.
 // Plain products: all forms of 5880 products, 1 to 16384 rows, N and K 256 to 16384, three sets of operands in turn (with one set the operands
 // of small products come from the L2, and what waits longest looks best: 1 x 1096 x 11840 11.1 us instead of 8.2).  The prices are those with which
 // the choice loses least, not the nearest to each time (7 to 13 % off): it takes 1.007 of the time of the fastest form at the sizes of linear layers, 1.009 over all, without the
 // workspace 1.007 and 1.008; priced with one set and one penalty for either operand, ranges without any, 1.014 and 1.024 (658 x 8696 x 4736, rows of A off
-// lines, 96 us on 256 x 256 instead of 72; 5506 x 3616 x 15744, both off, 1026 in ranges instead of 744).  Batches of Algorithm 1 where they
-// run, between the passes over memory (450; by themselves, one after the other, the ping-pong kernel is 10 % slower against the others: the clock).
+// lines, 96 us on 256 x 256 instead of 72; 5506 x 3616 x 15744, both off, 1026 in ranges instead of 744).  Batches of Algorithm 1 (2050,
+// planes of 128 to 8192 rows) where they run, between the passes over memory (by themselves, one after the other, the ping-pong kernel is 10 % slower against the
+// others: the clock), again with three sets in turn; FP8 products (700) behind the quantisation of A.  The choice takes 1.004 of the time of the whole call with the fastest
+// kernel in 16 bit, 1.002 and 1.001 in FP8; with the prices before, which had a step of 5 or 12 % at 5120 tile-products, 1.007 (fp32 products 1.015),
+// 1.007 and 1.002 (9536 x 4592 x 1584 <3,3,3;23> fp16 360 us with the small tile twice to a CU, 329 with the large one).  256 x 256 with a work-group each, which has a step less
+// where their number is odd, was not among them: 4582 x 3688 x 3624 <3,3,3;23> fp16, 19 steps, 231 us in turn, 215.
 // Without the 64 x 128 tile plain products take 1.09, without both tiles of lcma_kpair.hpp 1.27; without the small tile's form with two work-groups to a CU
 // (PlaneGemm: many tile-products of few steps, 384 x 384 x 960 in 49 planes 17.9 us, 26.6 on KPair) 1.01 to 1.08.
 struct StepPrice {
-    double a, b, c, more, start, off_a, off_w, memory, far;
+    double a, b, c, more, start, off_a, off_w, memory, far, products;
     double step(double f) const { return a + b * f + c * f * f * f * f; }
 };
 enum { WHOLE_256, KPAIR_128, TWO_128, KPAIR_64, STATIC_256, NARROW }; // 256 x 256 ping-pong, 128 x 128, the same twice to a CU, 64 x 128, 256 x 256 a work-group each, 256 x 128 ping-pong
 const StepPrice kPlain[] = {{0.807, 0.447, 0.0, 7.43, 0.0, 0.0, 0.113, 8.24, 0.0}, {0.339, 0.0559, 0.0735, 3.92, 1.4, 0.13, 0.0683, 0.167, 19.2}, {0.758, 0.212, 0.0, 2.14, 0.15, 0.0739, 0.089, 0.0, 0.0}, {0.241, 0.0685, 0.0, 2.64, 1.42, 0.19, 0.167, 0.362, 21.5}, {1.067, 0.171, 0.484, 4.70, 0.0, 0.11, 0.11, 0.0, 0.0}, {0.466, 0.265, 0.0, 6.22, 0.0, 0.432, 0.0, 0.0, 11.6}};
-const StepPrice kBatch[] = {{0.775, 0.557, 0.150, 5.66, 3.0}, {0.348, 0.008, 0.204, 2.26, 3.0}, {0.601, 0.319, 0.126, 1.40, 3.0}, {0.243, 0.0, 0.103, 1.69, 3.0}, {1.087, 0.277, 0.455, 4.36, 3.0}};
-const StepPrice kBatchF32[] = {{0.672, 0.692, 0.143, 8.87, 3.0}, {0.487, 0.026, 0.028, 3.05, 3.0}, {0.616, 0.420, 0.0, 2.24, 3.0}, {0.346, 0.0, 0.0, 1.79, 3.0}, {0.976, 0.008, 1.447, 4.10, 4.20}};
-const StepPrice kBatchFp8[] = {{0.890, 0.273, 0.360, 4.97, 0.64}, {0.239, 0.209, 0.130, 2.86, 0.0}, {0.621, 0.424, 0.109, 0.91, 0.0}, {0.160, 0.051, 0.148, 2.25, 0.0}, {1.277, 0.169, 0.237, 4.16, 0.0}};
-const StepPrice kFp8[] = {{0.924, 0.209, 0.304, 7.70, 0.0}, {0.319, 0.129, 0.007, 3.27, 1.55}, {0.682, 0.412, 0.0, 1.50, 0.0}, {0.245, 0.077, 0.0, 2.18, 1.57}, {1.277, 0.169, 0.237, 4.16, 0.0}};
+const StepPrice kBatch[] = {{0.99, 0.0, 0.416, 3.54, 8.0, 0.0, 0.0, 0.0, 0.0, 4.21}, {0.296, 0.0, 0.181, 1.47, 0.0, 0.0, 0.0, 14.3, 0.0, 14.8}, {0.651, 0.0, 0.311, 0.0, 0.0, 0.0, 0.0, 10.5, 0.0, 10.9}, {0.161, 0.0, 0.149, 1.53, 0.0, 0.0, 0.0, 12.3, 0.0, 6.3}, {1.29, 0.0, 0.318, 0.0, 0.0, 0.0, 0.0, 9.08, 0.0, 15.1}};
+const StepPrice kBatchF32[] = {{1.02, 0.0, 0.34, 5.42, 8.0, 0.0, 0.0, 0.0, 0.0, 3.6}, {0.239, 0.0, 0.255, 3.17, 1.62, 0.0, 0.0, 14.2, 0.0, 0.0}, {0.575, 0.101, 0.339, 2.43, 0.293, 0.0, 0.0, 8.63, 0.0, 0.0}, {0.145, 0.0, 0.164, 1.84, 2.09, 0.0, 0.0, 11.1, 0.0, 2.38}, {1.18, 0.167, 0.354, 2.43, 0.0, 0.0, 0.0, 5.43, 0.0, 8.29}};
+const StepPrice kBatchFp8[] = {{1.12, 0.0118, 0.28, 1.11, 4.08, 0.0, 0.0, 6.91, 0.0, 12.7}, {0.353, 0.00691, 0.238, 0.563, 0.000211, 0.0, 0.0, 9.92, 0.0, 30.1}, {0.744, 0.0, 0.332, 0.0, 0.0, 0.0, 0.0, 12.5, 0.0, 13.2}, {0.211, 0.0, 0.231, 1.29, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, {1.32, 0.179, 0.24, 0.0, 0.0, 0.0, 0.0, 11.4, 0.0, 15.0}};
+const StepPrice kFp8[] = {{1.07, 0.0, 0.309, 5.5, 0.0, 0.0, 0.0, 0.0, 0.0, 5.42}, {0.3, 0.162, 0.0286, 2.08, 0.0, 0.0, 0.0, 0.0, 0.0, 17.3}, {0.667, 0.45, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 8.92}, {0.241, 0.102, 0.000282, 0.99, 0.0, 0.0, 0.0, 0.0, 0.0, 30.0}, {1.32, 0.217, 0.238, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 17.3}};
 struct Operands {
     bool off_a, off_w; // rows that do not start on 128-byte lines
-    double mbytes, lines; // lines: of 128 bytes along K
+    double mbytes, lines, products; // lines: of 128 bytes along K; products: MB of them
     double far() const { return std::max(0.0, mbytes - 80.0); } // (three sets of them in turn no longer fit the last-level cache)
 };
-Operands plain_operands(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldw) { return Operands{lda % 64 != 0, ldw % 64 != 0, (double)(M + N) * (double)K * 2e-6, (double)K / 64.0}; }
+Operands plain_operands(int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldw) { return Operands{lda % 64 != 0, ldw % 64 != 0, (double)(M + N) * (double)K * 2e-6, (double)K / 64.0, 0.0}; }
+Operands planes_operands(int kind, int planes, int64_t rows, int64_t cols, int ny) {
+    return Operands{false, false, (double)planes * (double)(rows + cols) * ny * 128e-6, (double)ny, (double)planes * (double)rows * (double)cols * (kind == PG_F16_F32 ? 4e-6 : 2e-6)};
+}
 double off_lines(const Operands &o, double off_a, double off_w) { return 1.0 + (o.off_a ? off_a : 0.0) + (o.off_w ? off_w : 0.0); }
 double rounds_us(const StepPrice &q, int64_t jobs, int64_t slots, int64_t steps, const Operands &o) {
     const double line = 1.0 + (off_lines(o, q.off_a, q.off_w) - 1.0) * o.lines / 128.0, f = (double)(jobs % slots) / (double)slots;
-    return q.start + 0.01 * (q.memory * o.mbytes + q.far * o.far()) + (double)(jobs / slots) * ((double)steps * line * q.step(1.0) + q.more) + (f > 0.0 ? (double)steps * line * q.step(f) + q.more : 0.0);
+    return q.start + 0.01 * (q.memory * o.mbytes + q.far * o.far() + q.products * o.products) + (double)(jobs / slots) * ((double)steps * line * q.step(1.0) + q.more) + (f > 0.0 ? (double)steps * line * q.step(f) + q.more : 0.0);
 }
 // What else there is (measured as above):
 //   slices of K for work-groups of their own (128 x 128, plain 16-bit products of few tiles): the fp32 products of the slices are written and
@@ -121,7 +128,7 @@ double rounds_us(const StepPrice &q, int64_t jobs, int64_t slots, int64_t steps,
 //   Split-Group ranges: 1.75 (FP8 2.0) a step on 256 x 256, 6 a tile-product and 65 for the pieces (882 x 5224 x 10368 126 us, 179 on 256 x 128).  On
 //     128 x 128 neighbouring tiles start at different k and share little in L2, 0.95 a step, unless the ranges divide a tile evenly, 0.68; 2.9 and 1.5 a piece
 //     of a tile (512 x 4096 x 14336 65.6 us, 255 x 8504 x 7296 71 against 44 without, 559 x 7184 x 9856 196 / 106).  Half of the workspace serves
-//     them alone.  Batches and FP8, which have ranges only where a workspace is larger than asked for, at the older prices.
+//     them alone.  Batches at the older prices: in 16 bit they have ranges only where a workspace is larger than asked for; of 420 FP8 calls none took them.
 // tile, schedule: 0 = choose.  low: tiles of 64 x 128 are offered.  Returns microseconds (0 when nothing fits).
 enum { STATIC = 1, RANGES = 2, PERSIST = 3, SLICES = 4, TWO_PER_CU = 5 };
 int64_t slice_steps(int64_t jobs, int ny) { return ceil_div(ny, std::max<int64_t>(1, std::min<int64_t>(kCUs / jobs, ny / 4))); }
@@ -139,7 +146,7 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             if (schedule && sc != schedule && !(sc == TWO_PER_CU && schedule == STATIC)) continue;
             const bool pingpong = t == 256 && sc == PERSIST;
             if (t == 64 && sc != STATIC) continue;
-            if (!schedule && (t == 128 ? sc == PERSIST : t == 256 && sc == STATIC)) continue; // (128: the same kernel as STATIC; 256 x 256: never ahead by more than 1 %)
+            if (!schedule && (t == 128 ? sc == PERSIST : price == kPlain && t == 256 && sc == STATIC)) continue; // (128: the same kernel as STATIC; plain 256 x 256: never ahead by more than 1 %)
             if (sc == RANGES && scratch_bytes < plane_gemm_scratch_bytes(t)) continue;
             double cost;
             if (sc == RANGES) {
@@ -161,7 +168,6 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
                 // (one or two steps and one round of tiles stay on KPair, where they are one chain: 6.0 us, 4.7 here, both below a call's 6 on the host)
                 if (t != 128 || (price == kPlain && ny <= 2 && jobs <= kCUs)) continue;
                 cost = rounds_us(price[TWO_128], jobs, 2 * kCUs, ny, o);
-                if (planes > 1 && jobs >= 20 * kCUs) cost *= kind == PG_F16_F32 ? 1.05 : 1.12; // (ten rounds and more, measured: planes far beyond the caches)
             } else if (t < 256) {
                 cost = rounds_us(price[t == 128 ? KPAIR_128 : KPAIR_64], jobs, kCUs, even, o);
             } else if (pingpong) {
@@ -169,7 +175,6 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
             } else {
                 cost = rounds_us(price[STATIC_256], jobs, kCUs, ny, o);
             }
-            if (t < 256 && price != kPlain) cost = std::max(cost, 5.0 + (double)planes * (double)(rows + cols) * ny * 128.0 / 6e6); // (operands from memory)
             if (!*best_tile || cost < best) {
                 best = cost;
                 *best_tile = t;
@@ -182,16 +187,12 @@ double choose(int kind, int planes, int64_t rows, int64_t cols, int ny, int tile
 } // namespace
 
 // Seconds of the batched stage of Algorithm 1 in 16 bit as plane_gemm runs it by now (fp32_out: products kept in fp32), for
-// lcma_select_dataflow: measured 54.6 us at 53 predicted (7 planes, 2048 x 4096 x 4096), 318 / 315 (6144^3), 695 / 695 (FFN).  On many large
-// tiles the ping-pong kernel at the price that the plain product is compared at there: a batch of its own, timed back to back, runs 10 %
-// slower than as a stage between passes over memory.
+// lcma_select_dataflow.
 double batched_plane_gemm_seconds(bool fp32_out, int planes, int64_t rows, int64_t cols, int ny) {
+    const int kind = fp32_out ? PG_F16_F32 : PG_F16;
     int t = 0, sc = 0;
-    const double us = choose(fp32_out ? PG_F16_F32 : PG_F16, planes, rows, cols, ny, 0, tuning_schedule(), Operands{}, true, 0, &t, &sc);
-    if (!t) return -1.0;
-    const double out = fp32_out ? 12.0 : 6.0;
-    const double stage = rounds_us(StepPrice{0.80, 0.72, 0.0, out, 1.5}, planes * ceil_div(rows, 256) * ceil_div(cols, 256), kCUs, (ny + 1) & ~1, Operands{});
-    return 1e-6 * (t == 256 && stage < us ? stage : us);
+    const double us = choose(kind, planes, rows, cols, ny, 0, tuning_schedule(), planes_operands(kind, planes, rows, cols, ny), true, 0, &t, &sc);
+    return t ? 1e-6 * us : -1.0;
 }
 
 // The same as lcma_predict_unfused_seconds was published with, and as lcma_gemm_ws, whose contract names that function, compares it:
@@ -237,7 +238,7 @@ lcma_status plane_gemm(const char *who, int kind, PlaneGemmParams p, int planes,
     const int forced = tuning_schedule();
     if (forced) schedule = forced;
     int best_tile = 0, best_sched = 0;
-    choose(kind, planes, rows, cols, p.ny, tile, schedule, planes == 1 ? plain_operands(rows, cols, (int64_t)p.ny * 64, p.lda_b / 2, p.ldb_b / 2) : Operands{}, true, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
+    choose(kind, planes, rows, cols, p.ny, tile, schedule, kind == PG_BF16 || kind == PG_F16_OUT ? plain_operands(rows, cols, (int64_t)p.ny * 64, p.lda_b / 2, p.ldb_b / 2) : planes_operands(kind, planes, rows, cols, p.ny), true, scratch ? scratch_bytes : 0, &best_tile, &best_sched);
     if (!best_tile) {
         if (schedule == 2)
             return fail(LCMA_ERR_ARG, "%s: the Split-Group schedule needs %lld bytes of scratch", who,
