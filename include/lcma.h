@@ -377,9 +377,12 @@ lcma_status lcma_model_intensity(const lcma_scheme *s, int64_t M, int64_t N, int
 double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int64_t K, lcma_dtype dtype);
 
 /* ------------------------------------------------------------------ measurement aids
- * Process-wide settings; none but the last changes a result.  lcma_set_tuning(key, value) sets one (value "" or NULL restores the
- * default); the initial values come from the environment variables named below, which are read ONCE, at the first
- * call that needs them.  Errors: ARG for an unknown key.
+ * Process-wide settings.  Where all sums are exact (small integers) none but the last changes a result.  Elsewhere "panel" changes nothing;
+ * "variant" and "schedule" group fp32 sums differently (K split between waves or work-groups, or one chain: 1e-4 of the result's norm and less);
+ * "unfused_variant" and "batch_order" do so too, and Algorithm 1 in 16 bit then cuts its blocks of rows at whole tiles and not at 16 rows,
+ * so that other elements are combined and rounded (2e-3 in bf16, the error of the dataflow itself), and keeps the products in fp16 for
+ * fp16 storage too.  lcma_set_tuning(key, value) sets one (value "" or NULL restores the default); the initial values come from the
+ * environment variables named below, which are read ONCE, at the first call that needs them.  Errors: ARG for an unknown key.
  *   "variant"          LCMA_VARIANT=<name>          lcma_gemm / lcma_gemm_prepared run this generated kernel when it belongs
  *                                                   to the requested scheme, dtype and layout (otherwise ignored)
  *   "unfused_variant"  LCMA_UNFUSED_VARIANT=<name>  the same for the GEMM stage of lcma_gemm_unfused
@@ -394,9 +397,9 @@ double lcma_predict_seconds(int scheme_id, int64_t M, int64_t N, int64_t K, lcma
  *                                                   turn, or slices of K (plain 16-bit products of few tiles with the whole
  *                                                   workspace; SHAPE elsewhere); default: whichever the time model prefers
  *   "unfused_stages"   LCMA_UNFUSED_STAGES=<mask>   for timing one stage of lcma_gemm_unfused alone: bit 0 Combine A, bit 1
- *                                                   Combine B, bit 2 the GEMM stage, bit 3 Combine H (default 15, all).  The one
- *                                                   setting that is not result-neutral: a stage switched off leaves its output
- *                                                   as an earlier call wrote it, so C is only valid with all four on.
+ *                                                   Combine B, bit 2 the GEMM stage, bit 3 Combine H (default 15, all).  A stage
+ *                                                   switched off leaves its output as an earlier call wrote it, so C is only
+ *                                                   valid with all four on.
  */
 lcma_status lcma_set_tuning(const char *key, const char *value);
 
