@@ -94,7 +94,7 @@ namespace {
 // others: the clock), again with three sets in turn; FP8 products (700) behind the quantisation of A.  The choice takes 1.004 of the time of the whole call with the fastest
 // kernel in 16 bit, 1.002 and 1.001 in FP8; with the prices before, which had a step of 5 or 12 % at 5120 tile-products, 1.007 (fp32 products 1.015),
 // 1.007 and 1.002 (9536 x 4592 x 1584 <3,3,3;23> fp16 360 us with the small tile twice to a CU, 329 with the large one).  256 x 256 with a work-group each, which has a step less
-// where their number is odd, was not among them: 4582 x 3688 x 3624 <3,3,3;23> fp16, 19 steps, 231 us in turn, 215.
+// where their number is odd, was not among them: 2841 x 2576 x 1264 <4,4,4;49> bf16, 5 steps, 94 us twice to a CU, 97 in turn, 88.
 // Without the 64 x 128 tile plain products take 1.09, without both tiles of lcma_kpair.hpp 1.27; without the small tile's form with two work-groups to a CU
 // (PlaneGemm: many tile-products of few steps, 384 x 384 x 960 in 49 planes 17.9 us, 26.6 on KPair) 1.01 to 1.08.
 struct StepPrice {

@@ -35,6 +35,15 @@ def test_batches_on_large_tiles(scheme, dtype, shape):
     assert len(ran) == 1 and ran[0].startswith(f"pg_f16_t256_{'f32' if dtype == 'f16' else 'f16'} "), ran
 
 
+# An odd number of steps, which the ping-pong kernel rounds up; whole calls, us: 256 x 256 a work-group each / in turn / 128 x 128 twice to a CU
+@pytest.mark.parametrize("scheme,dtype,shape", [("strassen2", "bf16", (2841, 2576, 1264)),   # 88 / 97 / 94
+                                                ("laderman", "f16", (592, 6040, 1688))],     # 59.2 / 62.7 / 68.5
+                         ids=str)
+def test_odd_steps_a_work_group_each(scheme, dtype, shape):
+    ran = gemm_stage(scheme, dtype, *shape)
+    assert ran[0].startswith("pg_f16_t256_") and ran[0].endswith(" dealt=0"), ran
+
+
 # us: 128 x 128 twice to a CU / 256 x 256: many tile-products of few steps keep it
 def test_batches_on_small_tiles():
     ran = gemm_stage("strassen2", "bf16", 1536, 1536, 3840)     # 384 x 384 x 960 in 49 planes: 17.9 / 27.8 (the stage)
